@@ -72,6 +72,35 @@ def test_pack_zero_is_plus_and_strided_input(gpu):
     np.testing.assert_array_equal(back, orc.sign_pm1(big[:, 10:210]))
 
 
+@pytest.mark.parametrize("rows,cols,pad", [(16, 512, 0), (63, 513, 3), (65, 1023, 5), (1041, 519, 1), (33, 1536, 7), (3, 7, 2)])
+def test_packed_words_are_where_the_layout_says(gpu, rows, cols, pad):
+    """Every word of the packed blob, from the layout's formula, at the edges of the packing kernel's blocks of
+    512 columns, of its 8-column groups and of a group of 64 tiles, with rows at any byte alignment."""
+    torch, mb = gpu
+    rng = np.random.default_rng(rows + cols)
+    big = torch.from_numpy(rng.integers(-2, 2, size=(rows, cols + 2 * pad)).astype(np.int8)).to("cuda:0")
+    view = big[:, pad:pad + cols]
+    neg = view.cpu().numpy() < 0
+    nt, nb = (rows + 15) // 16, (cols + 127) // 128
+    full = np.zeros((nt * 16, nb * 128), dtype=bool)
+    full[:rows, :cols] = neg
+    want = np.zeros(nt * nb * 64, dtype=np.uint32)
+    kl = np.arange(128)
+    f, e = kl // 32, kl % 8
+    bit = (8 * (f // 2) + 4 * (f % 2) + e // 2 + 16 * (e % 2)).astype(np.uint32)
+    for t in range(nt):
+        g0 = t // 64 * 64
+        gt = min(64, nt - g0)
+        for q in range(nb):
+            blk = full[t * 16:t * 16 + 16, q * 128:q * 128 + 128].astype(np.uint32) << bit
+            for kg in range(4):
+                base = (g0 * nb + q * gt + (t - g0)) * 64 + kg * 16
+                want[base:base + 16] = np.bitwise_or.reduce(blk[:, (kl % 32) // 8 == kg], axis=1)
+    packed = mb.mdbf_pack(view)
+    np.testing.assert_array_equal(packed.cpu().numpy().view(np.uint32), want)
+    np.testing.assert_array_equal(mb.mdbf_unpack(packed, rows, cols).cpu().numpy() < 0, neg)
+
+
 # ---------------------------------------------------------------- forward: small and ragged
 SMALL = [
     # m, n, k, l, T
