@@ -125,7 +125,9 @@ int mdbf_pad_envelope(const void* env_dev, int rows, int l, int dtype, void* out
 /* ---- forward product ------------------------------------------------------------------
  * Workspace bytes needed by mdbf_forward for T tokens (room for the inner vector z in fp32, for the
  * scaled activations of few-token calls, and for the partial sums of a one-token call).  Host arithmetic
- * only: the same value on every machine. */
+ * only: the same value on every machine.  (mdbf_forward also takes what a call without partial sums needs where
+ * the rank is not 8 or 16 or the envelopes are not fp16: MDBF_FLAG_FP16_STAGED in the descriptor gives that
+ * size; such a call runs the slower general kernel.) */
 int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
 
 /* Y[b,:] = What X[b,:] for b < T.
@@ -136,8 +138,8 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * Default arithmetic: fp32 accumulation on the matrix cores.  One token: z kept in fp32; the l-way
  * scaled activations (b^(s) o x and q^(t) o z) are quantised once -- to three fp6 limbs under a shared
  * power-of-two scale per 32 values (about 13 bits; the block-scaled variant, taken by single calls and large
- * plans of rank 8 or 16 with fp16 envelopes), or to fp16 (small plans, MDBF_FLAG_FP16_STAGED) -- and
- * contracted with the sign words.  A single one-token call of the block-scaled variant is two launches: each
+ * plans of rank 8 or 16 with fp16 envelopes), to four such limbs (about 17 bits; single calls of other ranks and
+ * envelope types), or to fp16 (small plans, MDBF_FLAG_FP16_STAGED) -- and contracted with the sign words.  A single one-token call of the block-scaled variant is two launches: each
  * factor's contraction is split across workgroups (a layer by itself cannot fill the device otherwise) and
  * the fp32 partial sums are added in a fixed order, so repeated calls return the same bits; they differ in
  * the last bits from what a plan returns for the same layer (another fixed order).  Two tokens or more: the factors
@@ -146,7 +148,8 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * 65504 in those fp16 quantities overflow.
  * Range: the one-token variants carry their own power-of-two exponents (the block-scaled one per 32 values,
  * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32: they hold their accuracy
- * wherever the inputs and results are representable.  The general kernel (other ranks and envelope types) stages
+ * wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope
+ * types, and single calls of those with MDBF_FLAG_FP16_STAGED) stages
  * b^(s) o x and q^(t) o z in plain fp16, divided by up to 8: magnitudes below about 5e-4 lose accuracy.  The
  * many-token variant needs the entries of A Q^T and
  * G B^T, the activations and z inside fp16's normal range (6e-5 .. 65504); What is unchanged when A is divided
@@ -164,7 +167,7 @@ int mdbf_forward(const mdbf_desc_t* desc,
  * workspace to pass.  Same arguments, kernels, arithmetic and results as mdbf_forward; the scratch memory
  * (the inner vector z and the scaled activations) lives in a static device array of
  * MDBF_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds until the process
- * ends.  The call allocates and frees nothing.  A request whose mdbf_workspace_bytes() exceeds
+ * ends.  The call allocates and frees nothing.  A request for which the least workspace mdbf_forward takes exceeds
  * MDBF_STATIC_SCRATCH_BYTES returns MDBF_EWORKSPACE (checked on the host, before any HIP call): every layer
  * shape up to 11008 x 11008 with k <= 8192 fits with T <= 16; the 2048-token prefill does not.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different streams,

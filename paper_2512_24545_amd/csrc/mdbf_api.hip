@@ -68,8 +68,12 @@ size_t plan_layer_ws_bytes(const mdbf_desc_t* d, int T) { return z_bytes(d, T) +
 // A single call with one token splits the contraction of each factor across workgroups (split_geom); its
 // partial sums and the completion counters of the second factor lie behind the plan-style workspace.
 bool wants_split(const mdbf_desc_t* d, int T) {
-  return T == 1 && (d->l == 16 || d->l == 8) && d->env_dtype == MDBF_F16 &&
-         !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED));
+  return T == 1 && !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED));
+}
+// ... and does without them where the caller's workspace has no room (ranks and envelope types that the general
+// kernel serves too: a one-token call of those never needed more than z before it was split)
+bool must_split(const mdbf_desc_t* d, int T) {
+  return wants_split(d, T) && (d->l == 16 || d->l == 8) && d->env_dtype == MDBF_F16;
 }
 struct SplitLayout {
   SplitGeom g[2];
@@ -90,6 +94,10 @@ SplitLayout split_layout(const mdbf_desc_t* d) {
 }
 size_t layer_ws_bytes(const mdbf_desc_t* d, int T) {
   return plan_layer_ws_bytes(d, T) + (wants_split(d, T) ? split_layout(d).bytes : 0);
+}
+// the least a call is accepted with
+size_t least_ws_bytes(const mdbf_desc_t* d, int T) {
+  return plan_layer_ws_bytes(d, T) + (must_split(d, T) ? split_layout(d).bytes : 0);
 }
 
 int check_layer(const mdbf_desc_t* d, const void* SA, const void* SB, const mdbf_env_t* env, const void* X,
@@ -251,11 +259,11 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
   if (st) return st;
   if (!workspace_dev) return MDBF_EINVAL;
   if (!aligned16(workspace_dev)) return MDBF_EALIGN;
-  if (workspace_bytes < layer_ws_bytes(desc, T)) return MDBF_EWORKSPACE;
+  if (workspace_bytes < least_ws_bytes(desc, T)) return MDBF_EWORKSPACE;
   StageProb sp[2];
   make_stages(desc, SA_packed_dev, SB_packed_dev, env, X_dev, ldx, Y_dev, ldy, T, workspace_dev, sp);
   hipStream_t s = (hipStream_t)stream;
-  if (wants_split(desc, T) && stage_is_split(sp[0]) && stage_is_split(sp[1])) {
+  if (wants_split(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
     // two launches, no scale-in launch: the second factor's workgroups add up the first factor's partial sums
     const SplitLayout L = split_layout(desc);
     unsigned char* base = (unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T);
@@ -343,7 +351,7 @@ int mdbf_forward_static(const mdbf_desc_t* desc, const void* SA_packed_dev, cons
                         void* stream) {
   int st = check_layer(desc, SA_packed_dev, SB_packed_dev, env, X_dev, ldx, Y_dev, ldy, T);
   if (st) return st;
-  if (layer_ws_bytes(desc, T) > kStaticScratchBytes) return MDBF_EWORKSPACE;
+  if (least_ws_bytes(desc, T) > kStaticScratchBytes) return MDBF_EWORKSPACE;
   void* ws = nullptr;
   int e = static_scratch(&ws);
   if (e) return hip_fail(e);

@@ -173,7 +173,7 @@ int launch_scale_in_mx(const StageProb* probs_dev, int count, int max_units, con
 // for it) and does not store its own results.  Needs that factor to be served by this variant too.
 int launch_stage_mx(const WorkItem* items_dev, int nitems, const StageProb* single, const StageProb* next_probs_dev,
                     hipStream_t s);
-// Split variant of the block-scaled kernel for one small problem with one token: workgroup (g, s) takes row
+// Split variant of the block-scaled kernel for one small problem with one token, any rank and types: workgroup (g, s) takes row
 // tiles 8g .. 8g + 7 and `bs` blocks of the contraction dimension and builds its activation records itself;
 // the partial sums of the nsplit workgroups of a tile group are added in a fixed order, by the reader
 // (part_in of the next launch) or by the last workgroup of the group to finish (counters).
@@ -181,7 +181,6 @@ struct SplitGeom {
   int bs, nsplit, ngroup;
 };
 SplitGeom split_geom(int ntiles, int KB);    // host arithmetic only: the same on every machine
-bool stage_is_split(const StageProb& p);     // l == 16 or 8, fp16 envelopes, one token
 // part_in (or null: p->vin): nsplit_in vectors part_in_ld apart whose sum is the activation vector.
 // part_out: g.nsplit vectors part_out_ld apart (unused when g.nsplit == 1: the result goes to p->out).
 // counters (or null): g.ngroup zeroed words; with them the launch itself stores the sums to p->out.

@@ -28,6 +28,8 @@
 // loads beyond the stage that is due) and run two stages ahead; the contraction waves read everything
 // from LDS and issue no global loads in their loop, so a saturated memory pipeline stalls only the
 // loaders.  One barrier per stage hands a filled stage to the contraction waves and a drained one back.
+#include <type_traits>
+
 #include "mdbf_internal.h"
 
 namespace mdbf {
@@ -178,8 +180,11 @@ __device__ __forceinline__ void record_store(unsigned char* base, int index, V v
 
 // A lane's 32 values of a block in operand order (val, divided by their nibble values; m = their largest
 // magnitude) -> block exponent, three fp6 limbs, the record's slots, scales and column sums at `blk`.
-template <bool RANK8, bool TO_LDS>
-__device__ __forceinline__ void quantise_store(const float (&val)[32], float m, int lane, unsigned char* blk) {
+// FOUR: a fourth limb, 2^-4 of the third's scale: rank 8 in the half of slot 1 that is zero otherwise, rank 16 at
+// `limb4` (its scale is byte 3 of the scale words).
+template <bool RANK8, bool TO_LDS, bool FOUR = false>
+__device__ __forceinline__ void quantise_store(const float (&val)[32], float m, int lane, unsigned char* blk,
+                                               float part = 0.f, unsigned char* limb4 = nullptr) {
   constexpr bool rank8 = RANK8;   // the launch's rank: every problem of it has l = 8, or every one l = 16
   const int n = lane & 15;
   int E = -100;
@@ -204,26 +209,35 @@ __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, 
   for (int j = 0; j < 32; ++j) r[j] -= b2[j];
   const v6u l3 = fp6_encode32(r, sc3);
   const v32f b3 = fp6_decode32(l3, sc3);
-  // quantised value = val - (last residual); back at the scale of xs, summed over the lane's columns
-  float part = 0.f;
+  v6u l4 = {0, 0, 0, 0, 0, 0};
+  v32f b4;
+  if constexpr (FOUR) {
+    const float sc4 = __builtin_bit_cast(float, (uint32_t)(E + 115) << 23);
+#pragma unroll
+    for (int j = 0; j < 32; ++j) r[j] -= b3[j];
+    l4 = fp6_encode32(r, sc4);
+    b4 = fp6_decode32(l4, sc4);
+  }
+  // quantised value = val - (last residual); back at the scale of xs, summed over the lane's columns (on top of
+  // what the caller starts the sum with: 0 or NaN)
 #pragma unroll
   for (int j = 0; j < 32; ++j) {
     const float inv = (j < 8) ? 0.5f : (j < 16 ? 1.f : 2.f);
-    if (j < 24) part += (val[j] - (r[j] - b3[j])) * inv;   // the fourth register's columns need no fix-up
+    if (j < 24) part += (val[j] - (r[j] - (FOUR ? b4[j] : b3[j]))) * inv;   // the fourth register's columns need no fix-up
   }
   // record slots: rank 16: limbs 1, 2, 3 of mode n.  Rank 8: slot 0 = limb 1 (n < 8) or limb 2 (n >= 8) of
-  // mode n & 7, slot 1 = limb 3 (n < 8) or zeros, slot 2 unused and not written; each lane's scale bytes
+  // mode n & 7, slot 1 = limb 3 (n < 8) or zeros (FOUR: limb 4), slot 2 unused and not written; each lane's scale bytes
   // follow its slots.
   const bool upper = rank8 && n >= 8;
   v6u slot[3];
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     slot[0][c] = upper ? l2[c] : l1[c];
-    slot[1][c] = rank8 ? (upper ? 0u : l3[c]) : l2[c];
+    slot[1][c] = rank8 ? (upper ? l4[c] : l3[c]) : l2[c];
     slot[2][c] = l3[c];
   }
   const uint32_t e0 = (uint32_t)(upper ? E + 123 : E + 127);
-  const uint32_t e1 = (uint32_t)(rank8 ? E + 119 : E + 123);
+  const uint32_t e1 = (uint32_t)(FOUR && upper ? E + 115 : rank8 ? E + 119 : E + 123);
 #pragma unroll
   for (int L = 0; L < 3; ++L) {
     if (L < 2 || !rank8) {
@@ -235,7 +249,13 @@ __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, 
       record_store<TO_LDS>(blk + L * kLimbBytes + 64 * 16, lane, bpart);
     }
   }
-  record_store<TO_LDS>(blk + kScaleOff, lane, e0 | (e1 << 8) | ((uint32_t)(E + 119) << 16));
+  uint32_t scales = e0 | (e1 << 8) | ((uint32_t)(E + 119) << 16);
+  if constexpr (FOUR && !RANK8) {
+    scales |= (uint32_t)(E + 115) << 24;
+    record_store<TO_LDS>(limb4, lane, u32x4{l4[0], l4[1], l4[2], l4[3]});
+    record_store<TO_LDS>(limb4 + 64 * 16, lane, u32x2{l4[4], l4[5]});
+  }
+  record_store<TO_LDS>(blk + kScaleOff, lane, scales);
   if (upper) part = 0.f;   // the column sum of a mode is stored once
 
   // ---- 3. column sums of the block
@@ -245,11 +265,40 @@ __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, 
 }
 
 
+// step 2 of a record, from the products in LDS: a lane's values in operand order, quantised and stored.  Rank 8:
+// lanes n and n + 8 both take mode n; the first keeps limbs 1 and 3, the second limb 2, so that two matrix-core
+// instructions cover three limbs.  ANY: any rank; modes from l on are zero (pr need not hold them); with a
+// fourth limb, so that the path is nowhere less accurate than the fp16-staged kernel it took over from (three
+// limbs leave about the error of fp16 staging; up to rank 8 the fourth costs no instruction of the contraction).
+template <bool RANK8, bool TO_LDS, bool ANY>
+__device__ __forceinline__ void gather_quantise(float* pr, int l, int lane, unsigned char* blk) {
+  const int kg = lane >> 4, n = lane & 15;
+  const int nsrc = RANK8 ? (n & 7) : n;
+  float val[32];
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const float presc = (j < 8) ? 2.f : (j < 16 ? 1.f : (j < 24 ? 0.5f : -0.5f));   // undo the nibble values 0.5, 1, 2, -2
+    const float v = pr[(local_col_of_element(j, 0) + 8 * kg) * kProdStride + nsrc];
+    val[j] = !ANY || nsrc < l ? v * presc : 0.f;
+    m = fmaxf(m, fabsf(val[j]));
+  }
+  wave_lds_sync();   // the next record's products may overwrite the buffer
+  // The limbs saturate.  An infinity or NaN among the first three registers' columns reaches the result through
+  // the column sum; the fourth register's columns are not in it.
+  float poison = 0.f;
+  if (ANY) {
+#pragma unroll
+    for (int j = 24; j < 32; ++j) poison += val[j] * 0.f;
+  }
+  // (ANY: a fourth limb; of rank 16 it takes the place of the products, which have been read)
+  quantise_store<RANK8, TO_LDS, ANY>(val, m, lane, blk, poison, (unsigned char*)pr);
+}
+
 // the record of block q of the problem's contraction dimension, from the inputs `in`, written to `blk`
 template <bool RANK8, bool TO_LDS>
 __device__ __forceinline__ void prep_record_to(const StageProb& p, int q, int lane, const PrepInput& in, float* pr,
                                                unsigned char* blk) {
-  const int kg = lane >> 4, n = lane & 15;
   const bool has_modes = (lane & 1) < (p.l >> 3);
 
   // ---- 1. products
@@ -270,20 +319,7 @@ __device__ __forceinline__ void prep_record_to(const StageProb& p, int q, int la
     }
   }
   wave_lds_sync();
-
-  // ---- 2. gather in operand order, quantise.  Rank 8: lanes n and n + 8 both take mode n; the first
-  //         keeps limbs 1 and 3, the second limb 2, so that two matrix-core instructions cover three limbs
-  const int nsrc = RANK8 ? (n & 7) : n;
-  float val[32];
-  float m = 0.f;
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const float presc = (j < 8) ? 2.f : (j < 16 ? 1.f : (j < 24 ? 0.5f : -0.5f));   // undo the nibble values 0.5, 1, 2, -2
-    val[j] = pr[(local_col_of_element(j, 0) + 8 * kg) * kProdStride + nsrc] * presc;
-    m = fmaxf(m, fabsf(val[j]));
-  }
-  wave_lds_sync();   // the next record's products may overwrite the buffer
-  quantise_store<RANK8, TO_LDS>(val, m, lane, blk);
+  gather_quantise<RANK8, TO_LDS, false>(pr, RANK8 ? 8 : 16, lane, blk);
 }
 
 // record of unit (token, block) of the problem's activation stream in global memory
@@ -347,7 +383,8 @@ __device__ __forceinline__ floatx4 mx_mfma(v8i a, v8i b, floatx4 c, int L, uint3
   // A: fp4 (format 4), scale 2^0; B: fp6 e2m3 (format 2), scale byte L of sc
   if (L == 0) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 0, (int)sc);
   if (L == 1) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 1, (int)sc);
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 2, (int)sc);
+  if (L == 2) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 2, (int)sc);
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 3, (int)sc);
 }
 
 __device__ __forceinline__ float row16_sum(float v) {
@@ -786,6 +823,46 @@ __device__ __forceinline__ float ordered_sum(const MDBF_GLOBAL float* first, int
   return sum;
 }
 
+// The record of block q for any rank and type of the envelope factor (one token).  A block's 128 rows of the
+// factor are 128 l consecutive elements: lane i takes elements i, i + 64, ... (coalesced whatever the rank), the
+// activations, x0 and x1 = columns lane and lane + 64 of the block, meet them through LDS.
+template <bool RANK8>
+__device__ __forceinline__ void prep_record_any(const StageProb& p, int q, int lane, float x0, float x1, float* xbuf,
+                                                float* pr, unsigned char* blk) {
+  constexpr int kMaxT = RANK8 ? 16 : 32;        // elements per lane at most
+  const int l = p.l;
+  const int64_t e0 = (int64_t)q * kBlockCols * l;
+  const int last = (int)min((int64_t)p.K * l - 1 - e0, (int64_t)kBlockCols * l - 1);   // of the block's elements
+  float ev[kMaxT];
+  if (p.env_dt == MDBF_F32) {
+#pragma unroll
+    for (int t = 0; t < kMaxT; ++t)
+      if (t < 2 * l) ev[t] = ((g_f32_ptr)p.Ein)[e0 + min(lane + 64 * t, last)];
+  } else {
+    uint32_t bits[kMaxT];
+#pragma unroll
+    for (int t = 0; t < kMaxT; ++t)
+      if (t < 2 * l) bits[t] = ((g_u16_ptr)p.Ein)[e0 + min(lane + 64 * t, last)];
+#pragma unroll
+    for (int t = 0; t < kMaxT; ++t)
+      ev[t] = p.env_dt == MDBF_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits[t]) : __builtin_bit_cast(float, bits[t] << 16);
+  }
+  xbuf[lane] = q * kBlockCols + lane < p.K ? x0 : 0.f;
+  xbuf[64 + lane] = q * kBlockCols + 64 + lane < p.K ? x1 : 0.f;
+  wave_lds_sync();
+  const float rl = 1.f / (float)l;
+#pragma unroll
+  for (int t = 0; t < kMaxT; ++t) {
+    if (t < 2 * l) {
+      const int e = lane + 64 * t;
+      const int col = (int)(((float)e + 0.5f) * rl);       // e / l: e < 2048, half a unit away from every edge
+      pr[col * kProdStride + (e - col * l)] = q * kBlockCols + col < p.K ? ev[t] * xbuf[col] : 0.f;
+    }
+  }
+  wave_lds_sync();
+  gather_quantise<RANK8, true, true>(pr, l, lane, blk);
+}
+
 struct SplitArgs {
   StageProb p;
   int32_t bs, nsplit;               // blocks per workgroup; workgroups per tile group
@@ -798,13 +875,19 @@ struct SplitArgs {
   int32_t nsplit_in, nclear;
 };
 
-template <bool RANK8>
+// VEC: fp16 envelope factors of rank 8 or 16, read as 16-byte vectors; otherwise any rank up to 8 (RANK8) or 16 and
+// any type, element by element.  The fp16-staged general kernel that ranks other than 8 and 16 used to take by
+// themselves rebuilt all scaled activations in every workgroup: two 4096 x 4096 calls, k = 1601, l = 1: 114 -> 27 us;
+// 256 x 256, k = 128, l = 4 in fp32: 21.9 -> 12.0 us, errors
+// against 64 bits 1e-4 .. 4e-4 -> 1e-5 .. 2e-5.
+template <bool RANK8, bool VEC>
 __global__ __launch_bounds__(64 * kSplitWaves) void stage_mx_split_kernel(SplitArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char recs[kSplitMaxBs * kBlockBytes];
   __shared__ __attribute__((aligned(16))) float prod[kSplitMaxBs][128 * kProdStride];
+  __shared__ float xbuf[VEC ? 1 : kSplitMaxBs][kBlockCols];
   __shared__ uint32_t is_last;
   constexpr int RANK = RANK8 ? 8 : 16;
-  constexpr int NL = RANK8 ? 2 : 3;
+  constexpr int NL = RANK8 ? 2 : VEC ? 3 : 4;
   const StageProb& p = a.p;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -823,28 +906,41 @@ __global__ __launch_bounds__(64 * kSplitWaves) void stage_mx_split_kernel(SplitA
 #pragma unroll
   for (int i = 0; i < kSplitMaxBs; ++i)
     w[i] = ((g_u32_ptr)p.S)[word_offset(tile_c, min(q0 + i, p.KB - 1), lane, p.KB, p.ntiles)];
-  _Float16 ev[4];
+  const int mode = n & (RANK - 1);
+  typename std::conditional<VEC, _Float16, float>::type ev[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = min(tile_c * kTileRows + 4 * kg + i, p.rows - 1);
-    ev[i] = ((const MDBF_GLOBAL _Float16*)p.Eout)[(size_t)row * RANK + (n & (RANK - 1))];
+    if constexpr (VEC) ev[i] = ((const MDBF_GLOBAL _Float16*)p.Eout)[(size_t)row * RANK + mode];
+    else ev[i] = load_as_float(p.Eout, (int64_t)row * p.l + min(mode, p.l - 1), p.env_dt);
   }
 
   // ---- records of the workgroup's blocks: wave i builds block q0 + i
   if (wave < nb) {
     const int q = q0 + wave;
-    PrepInput in = prep_load(p, q, lane);              // (token 0; with part_in the activations read here are not used)
-    StageProb pp = p;
-    if (a.part_in) {
-      pp.vin_dt = MDBF_F32;
+    if constexpr (VEC) {
+      PrepInput in = prep_load(p, q, lane);            // (token 0; with part_in the activations read here are not used)
+      StageProb pp = p;
+      if (a.part_in) {
+        pp.vin_dt = MDBF_F32;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int kc = min(q * kBlockCols + (lane >> 1) + 32 * i, p.K - 1);
-        const float sum = ordered_sum<false>((g_f32_ptr)a.part_in + kc, a.nsplit_in, a.part_in_ld);
-        in.xbits[i] = __builtin_bit_cast(uint32_t, sum);
+        for (int i = 0; i < 4; ++i) {
+          const int kc = min(q * kBlockCols + (lane >> 1) + 32 * i, p.K - 1);
+          const float sum = ordered_sum<false>((g_f32_ptr)a.part_in + kc, a.nsplit_in, a.part_in_ld);
+          in.xbits[i] = __builtin_bit_cast(uint32_t, sum);
+        }
       }
+      prep_record_to<RANK8, true>(pp, q, lane, in, prod[wave], recs + wave * kBlockBytes);
+    } else {
+      float x[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int kc = min(q * kBlockCols + lane + 64 * i, p.K - 1);
+        x[i] = a.part_in ? ordered_sum<false>((g_f32_ptr)a.part_in + kc, a.nsplit_in, a.part_in_ld)
+                         : load_as_float(p.vin, kc, p.vin_dt);
+      }
+      prep_record_any<RANK8>(p, q, lane, x[0], x[1], xbuf[wave], prod[wave], recs + wave * kBlockBytes);
     }
-    prep_record_to<RANK8, true>(pp, q, lane, in, prod[wave], recs + wave * kBlockBytes);
   }
   __syncthreads();
 
@@ -861,8 +957,9 @@ __global__ __launch_bounds__(64 * kSplitWaves) void stage_mx_split_kernel(SplitA
       const v8i sa = sign_operand(w[i], sconst);
 #pragma unroll
       for (int L = 0; L < NL; ++L) {
-        const u32x4 x = reinterpret_cast<const u32x4*>(rec + L * kLimbBytes)[lane];
-        const u32x2 y = reinterpret_cast<const u32x2*>(rec + L * kLimbBytes + 64 * 16)[lane];
+        const unsigned char* limbs = L < 3 ? rec + L * kLimbBytes : (const unsigned char*)prod[i];
+        const u32x4 x = reinterpret_cast<const u32x4*>(limbs)[lane];
+        const u32x2 y = reinterpret_cast<const u32x2*>(limbs + 64 * 16)[lane];
         v8i limb;
         limb[0] = (int)x.x; limb[1] = (int)x.y; limb[2] = (int)x.z; limb[3] = (int)x.w;
         limb[4] = (int)y.x; limb[5] = (int)y.y; limb[6] = 0; limb[7] = 0;
@@ -874,7 +971,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void stage_mx_split_kernel(SplitA
   // ---- envelope rows: fix-up, accumulate over the modes; one partial sum per row
   float v[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = row16_sum((float)ev[i] * (colsum - 2.f * acc[i]));
+  for (int i = 0; i < 4; ++i) {
+    const float e = VEC || mode < p.l ? (float)ev[i] : 0.f;
+    v[i] = row16_sum(e * (colsum - 2.f * acc[i]));
+  }
   const int sel = n & 3;
   const float res = sel == 0 ? v[0] : sel == 1 ? v[1] : sel == 2 ? v[2] : v[3];
   const int row = tile * kTileRows + 4 * kg + n;
@@ -1032,10 +1132,6 @@ SplitGeom split_geom(int ntiles, int KB) {
   return g;
 }
 
-bool stage_is_split(const StageProb& p) {
-  return (p.l == 16 || p.l == 8) && p.env_dt == MDBF_F16 && p.T == 1 && p.KB >= 1 && p.ntiles >= 1;
-}
-
 int launch_stage_mx_split(const StageProb* p, const SplitGeom& g, const float* part_in, int nsplit_in,
                           int64_t part_in_ld, float* part_out, int64_t part_out_ld, uint32_t* counters,
                           uint32_t* clear, int nclear, hipStream_t s) {
@@ -1052,8 +1148,11 @@ int launch_stage_mx_split(const StageProb* p, const SplitGeom& g, const float* p
   a.nsplit_in = nsplit_in;
   a.nclear = nclear;
   const dim3 grid((unsigned)(g.ngroup * g.nsplit)), block(64 * mx::kSplitWaves);
-  if (p->l == 8) hipLaunchKernelGGL(mx::stage_mx_split_kernel<true>, grid, block, 0, s, a);
-  else hipLaunchKernelGGL(mx::stage_mx_split_kernel<false>, grid, block, 0, s, a);
+  const bool vec = (p->l == 16 || p->l == 8) && p->env_dt == MDBF_F16;
+  if (vec && p->l == 8) hipLaunchKernelGGL((mx::stage_mx_split_kernel<true, true>), grid, block, 0, s, a);
+  else if (vec) hipLaunchKernelGGL((mx::stage_mx_split_kernel<false, true>), grid, block, 0, s, a);
+  else if (p->l <= 8) hipLaunchKernelGGL((mx::stage_mx_split_kernel<true, false>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((mx::stage_mx_split_kernel<false, false>), grid, block, 0, s, a);
   return (int)hipGetLastError();
 }
 

@@ -309,6 +309,42 @@ def test_determinism_of_the_split_contraction(gpu):
         assert orc.max_rel_error(first.cpu().numpy(), ref) <= TOL
 
 
+ANY_RANK = [
+    # m, n, k, l, env, x: edges of the 16-row tiles, of the 128-column blocks, of the 8-tile groups and of a split of
+    # four blocks; the smallest and largest rank of both record forms
+    (1, 1, 1, 1, "f32", "f32"), (16, 127, 128, 8, "bf16", "f16"), (17, 129, 127, 9, "f16", "bf16"),
+    (129, 513, 385, 1, "f16", "f16"), (128, 512, 1024, 16, "f32", "f32"), (2049, 4097, 1601, 3, "bf16", "bf16"),
+    (300, 5000, 2049, 15, "f32", "f16"),
+]
+
+
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", ANY_RANK)
+def test_one_token_calls_of_any_rank_and_type(gpu, m, n, k, l, env_dtype, x_dtype):
+    """Four fp6 limbs hold a scaled activation to 2^-16 of the largest of its 32 (a limb's step is an eighth of
+    its scale, the scales fall by 16): relative to the largest output some 1e-5 at these sizes, 1e-4 allowed.  A
+    workspace without room for partial sums takes the fp16-staged general kernel instead; an infinity or NaN
+    anywhere in the input reaches every output."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="llama", signed_env=True)
+    X = synth.make_activations(n, 1, seed=9 + m, x_dtype=x_dtype)
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, x_dtype)
+    got = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    assert orc.max_rel_error(got.cpu().numpy(), ref) <= 1e-4
+    assert torch.equal(got, mb.mdbf_forward(dl, Xd, y_dtype="f32"))
+    twice = mb.mdbf_forward(dl, Xd, y_dtype="f32", Y=got.clone(), accumulate=True)
+    assert torch.equal(twice, got + got)
+    small = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32", fp16_staged=True), 1), dtype=torch.uint8, device="cuda:0")
+    if l not in (8, 16) or env_dtype != "f16":
+        staged = mb.mdbf_forward(dl, Xd, y_dtype="f32", workspace=small)
+        assert torch.equal(staged, mb.mdbf_forward(dl, Xd, y_dtype="f32", fp16_staged=True))
+    for where in {0, n // 2, n - 1}:
+        for bad in (float("inf"), float("nan")):
+            Xb = Xd.clone()
+            Xb[0, where] = bad
+            assert not torch.isfinite(mb.mdbf_forward(dl, Xb, y_dtype="f32")).any()
+
+
 # ---------------------------------------------------------------- many layers in one launch pair
 def _batch_case(gpu, specs, tokens=lambda i: 1 + (i % 2)):
     torch, mb = gpu
