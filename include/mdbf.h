@@ -124,10 +124,10 @@ int mdbf_pad_envelope(const void* env_dev, int rows, int l, int dtype, void* out
 
 /* ---- forward product ------------------------------------------------------------------
  * Workspace bytes needed by mdbf_forward for T tokens (room for the inner vector z in fp32, for the
- * scaled activations of few-token calls, and for the partial sums of a one-token call).  Host arithmetic
- * only: the same value on every machine.  (mdbf_forward also takes what a call without partial sums needs where
- * the rank is not 8 or 16 or the envelopes are not fp16: MDBF_FLAG_FP16_STAGED in the descriptor gives that
- * size; such a call runs the slower general kernel.) */
+ * scaled activations and for the partial sums of few-token calls).  Host arithmetic
+ * only: the same value on every machine.  (mdbf_forward also takes less where it can do without the partial sums:
+ * with one token if the rank is not 8 or 16 or the envelopes are not fp16, and with more tokens always.  Such a
+ * call runs slower kernels; its results differ in the last bits.) */
 int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
 
 /* Y[b,:] = What X[b,:] for b < T.

@@ -92,8 +92,44 @@ SplitLayout split_layout(const mdbf_desc_t* d) {
   L.bytes = L.ctr_off + align_up((size_t)L.g[1].ngroup * 4u, 256);
   return L;
 }
+// A single call with few tokens splits both contractions as well; the two factors' partial sums take turns in one
+// buffer (the first factor's are added up before the second one starts).  Up to 16 tokens always.  From 17 to
+// kFewMaxTokens only where the many-token kernel would load its operands element by element (172 against 25 us
+// at 5000 x 3001, k = 2003, l = 3, 37 tokens); the shapes it loads as vectors keep one run over the contraction from
+// 17 tokens on: a token's result is the same bits in a call of 40 and of 2048 tokens.
+bool forced_mx(const mdbf_desc_t* d, int T, int rows, int K) {
+  StageProb p;
+  memset(&p, 0, sizeof(p));
+  p.rows = rows;
+  p.K = K;
+  p.KB = num_blocks(K);
+  p.l = d->l;
+  p.T = T;
+  p.env_dt = d->env_dtype;
+  p.xs = wants_xs(d, T) ? (void*)(uintptr_t)256 : nullptr;      // (only the predicate is wanted)
+  return (d->flags & MDBF_FLAG_BLOCK_SCALED) && use_mx(p, d->flags);
+}
+bool vector_shape(const mdbf_desc_t* d) {
+  return d->env_dtype == MDBF_F16 && (d->l == 16 || d->l == 8) && (d->n & 7) == 0 && (d->k & 7) == 0;
+}
+bool wants_few(const mdbf_desc_t* d, int T) {
+  return T >= kGemmMinTokensSingle && T <= (vector_shape(d) ? 16 : kFewMaxTokens) && !(d->flags & MDBF_FLAG_PRECISE) && !forced_mx(d, T, d->k, d->n) &&
+         !forced_mx(d, T, d->m, d->k);
+}
+SplitLayout few_layout(const mdbf_desc_t* d, int T) {
+  SplitLayout L;
+  L.g[0] = few_geom(num_tiles(d->k), num_blocks(d->n), T, vector_shape(d));
+  L.g[1] = few_geom(num_tiles(d->m), num_blocks(d->k), T, vector_shape(d));
+  L.ld[0] = (int64_t)align_up((size_t)d->k, 64);
+  L.ld[1] = (int64_t)align_up((size_t)d->m, 64);
+  L.part_off[0] = L.part_off[1] = L.ctr_off = 0;
+  L.bytes = 0;
+  for (int i = 0; i < 2; ++i)
+    if (L.g[i].nsplit > 1) L.bytes = std::max(L.bytes, (size_t)L.g[i].nsplit * (size_t)T * (size_t)L.ld[i] * 4u);
+  return L;
+}
 size_t layer_ws_bytes(const mdbf_desc_t* d, int T) {
-  return plan_layer_ws_bytes(d, T) + (wants_split(d, T) ? split_layout(d).bytes : 0);
+  return plan_layer_ws_bytes(d, T) + (wants_split(d, T) ? split_layout(d).bytes : wants_few(d, T) ? few_layout(d, T).bytes : 0);
 }
 // the least a call is accepted with
 size_t least_ws_bytes(const mdbf_desc_t* d, int T) {
@@ -280,17 +316,25 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
   {
     bool both_gemm = !(desc->flags & MDBF_FLAG_PRECISE) && T >= kGemmMinTokensSingle;
     for (int i = 0; i < 2; ++i)
-      both_gemm = both_gemm && stage_is_gemm(sp[i]) && !((desc->flags & MDBF_FLAG_BLOCK_SCALED) && use_mx(sp[i], desc->flags));
+      both_gemm = both_gemm && !((desc->flags & MDBF_FLAG_BLOCK_SCALED) && use_mx(sp[i], desc->flags));
     if (both_gemm) half_intermediate(sp);
+  }
+  if (wants_few(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
+    const SplitLayout L = few_layout(desc, T);
+    unsigned char* base = (unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T);
+    float* part = (float*)(base + L.part_off[0]);
+    int e = launch_stage_gemm_few(&sp[0], L.g[0], part, L.ld[0], s);
+    if (!e) e = launch_stage_gemm_few(&sp[1], L.g[1], part, L.ld[1], s);
+    return hip_fail(e);
   }
   for (int i = 0; i < 2; ++i) {
     int e;
-    const bool forced_mx = (desc->flags & MDBF_FLAG_BLOCK_SCALED) && use_mx(sp[i], desc->flags);
+    const bool forced = (desc->flags & MDBF_FLAG_BLOCK_SCALED) && use_mx(sp[i], desc->flags);
     if (desc->flags & MDBF_FLAG_PRECISE)
       e = launch_stage_precise(nullptr, nullptr, 0, &sp[i], s);
-    else if (!forced_mx && T >= kGemmMinTokensSingle && stage_is_gemm(sp[i]))
+    else if (!forced && T >= kGemmMinTokensSingle)
       e = launch_stage_gemm(nullptr, 0, 0, &sp[i], s);
-    else if (forced_mx || (use_mx(sp[i], desc->flags) && (mx_worthwhile(sp[i].ntiles) || !stage_is_fast(sp[i])))) {
+    else if (forced || (use_mx(sp[i], desc->flags) && (mx_worthwhile(sp[i].ntiles) || !stage_is_fast(sp[i])))) {
       // (a small launch the fp16 variant cannot take -- rank 8 -- is still better off here than in the
       // element-wise kernel)
       e = launch_scale_in_mx(nullptr, 1, T * sp[i].KB, &sp[i], s);

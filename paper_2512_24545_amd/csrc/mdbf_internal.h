@@ -203,7 +203,6 @@ int mfma_tiles_per_item(long total_tiles);
 // kernels read the signs once per token; the rebuild pays off from a few tokens on).
 constexpr int kGemmMinTokensSingle = 2;
 constexpr int kGemmMinTokensPlan = 4;
-bool stage_is_gemm(const StageProb& p);
 // how the kernel may load the problem's operands: a dtype code (vector loads of that activation type, fp16
 // rank-16 envelopes, aligned rows) or 3 (element by element); a plan takes 3 unless all problems agree
 int gemm_load_mode(const StageProb& p);
@@ -214,6 +213,14 @@ int gemm_plan_max_tokens();
 // items_dev null: the single problem *p (mode ignored).  Else the work items of a plan (at most
 // gemm_plan_max_tokens() tokens per problem); p->T = the longest token count among its problems, mode as above.
 int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s);
+
+// Few-token single problem (at most kFewMaxTokens tokens): contraction split across workgroups, as split_geom's
+// kernel does for one token, and the partial sums added by a second launch.  part: g.nsplit x T vectors part_ld
+// apart (unused when g.nsplit == 1: the result goes to p->out).
+constexpr int kFewMaxTokens = 64;
+// host arithmetic only; vectors: the shape qualifies for the vector-load modes (gemm_load_mode)
+SplitGeom few_geom(int ntiles, int KB, int T, bool vectors);
+int launch_stage_gemm_few(const StageProb* p, const SplitGeom& g, float* part, int64_t part_ld, hipStream_t s);
 
 // MSVID_l (sign mask + truncated SVD of |Z| by block subspace iteration), csrc/mdbf_msvid.hip
 int msvid_block(int l);                                  // columns of the iteration's block: l plus oversampling

@@ -341,7 +341,8 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// One short problem by itself (at most 16 tokens, the vector-load modes): the launch above would give each
+// One short problem by itself (at most 16 tokens, the vector-load modes) with few row tiles or blocks, or without
+// room for partial sums (the kernel further down splits the others): the launch above would give each
 // wave one row tile and the whole contraction dimension, a chain of KB dependent steps on a quarter of the
 // device.  Here a workgroup owns ONE row tile and its four waves split the column blocks (wave w takes blocks
 // 4 i + w); an iteration stages four blocks, two iterations ahead; the four partial results meet in LDS and
@@ -514,6 +515,301 @@ static int launch_split(const StageProb* p, hipStream_t s) {
   return launch_split_r<MODE, 1>(p, s);
 }
 
+// ---------------------------------------------------------------------------------------------------
+// One short problem by itself (at most 64 tokens).  A workgroup owns 8 row tiles (one per wave) and `bs` column
+// blocks: its eight tiles share one staging of the activations and envelope rows, and the contraction is split
+// over workgroups until the launch fills the device.  Partial sums go to the workspace and a small launch adds
+// them in the order of the splits (3 to 4 us; letting the last workgroup of a row group add them took 5 us with
+// 16 tokens and 13 us with 37).
+// What bounds it: a launch is a few microseconds of dependent trips (stage, rebuild, partial sums), not traffic
+// or arithmetic.  One row tile per workgroup and the blocks split over its waves, as before, made every tile
+// stage all activations again (176 MB through the L2s for 16 tokens x 11008 columns x 256 tiles: 28 us of the
+// call's 38).  4096 x 11008, k = 4096, l = 16, 16 tokens: 38.0 -> 23.2 us per call; 5000 x 3001, k = 2003, l = 3,
+// 37 tokens in bf16 (element-wise loads before, vector loads of any alignment now): 172 -> 25.1 us.
+//   MODE: type of the activations; rows may start at any element (the target's vector loads need no alignment).
+//   EVEC: fp16 envelope rows of rank 8 or 16, one or two vectors each; otherwise any type and rank: the chunk's
+//   rows are consecutive elements, loaded as vectors and spread over the LDS rows.
+//   TB: slabs of 16 tokens.
+// ---------------------------------------------------------------------------------------------------
+constexpr int kFewWaves = 8;
+constexpr int kFewThreads = 64 * kFewWaves;
+constexpr int kFewSplits = 16;                                  // partial sums per output at most
+__host__ __device__ constexpr int few_chunk(int TB) { return TB == 1 ? 4 : 2; }   // blocks staged at a time
+__host__ __device__ constexpr int few_vin_bytes(int TB) { return few_chunk(TB) * TB * 16 * 256; }
+__host__ __device__ constexpr int few_smem(int TB) { return 2 * (few_vin_bytes(TB) + few_chunk(TB) * kEinBufBytes); }
+
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // a vector at any element's address
+
+struct FewArgs {
+  StageProb p;
+  int32_t bs, nsplit;          // blocks per workgroup, workgroups per row group
+  float* part;                 // [nsplit][T][part_ld] (unused when nsplit == 1)
+  int64_t part_ld;
+};
+
+template <int MODE, bool EVEC, int TB>
+__global__ __launch_bounds__(kFewThreads, 4)
+void stage_gemm_few_kernel(FewArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr int CK = few_chunk(TB);
+  constexpr int kVinBytes = few_vin_bytes(TB);
+  constexpr int kVinSlots = CK * TB * 256 / kFewThreads;        // 16-byte LDS slots per thread and chunk
+  constexpr int kRaw = MODE == MDBF_F32 ? 2 : 1;                // vectors a slot is loaded as
+  constexpr int kEinSlots = EVEC ? CK * 256 / kFewThreads : CK; // EVEC false: up to 128 CK rows of 64 bytes
+  const StageProb& p = a.p;
+  unsigned char* vin_buf = smem;                                // [2][CK blocks][16 TB tokens][16 slots], swizzled
+  unsigned char* ein_buf = smem + 2 * kVinBytes;                // [2][CK blocks][128 columns][16 modes]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int group = (int)blockIdx.x / a.nsplit, split = (int)blockIdx.x - group * a.nsplit;
+  const int q_lo = split * a.bs, q_hi = min(q_lo + a.bs, p.KB);
+  const int chunks = (q_hi - q_lo + CK - 1) / CK;
+  const int tile = group * kFewWaves + wave;                    // (a tile past the end repeats the last, unstored)
+  const int tile_c = min(tile, p.ntiles - 1);
+  const MDBF_GLOBAL uint32_t* sbase = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(tile_c, p.KB) + lane;
+  const size_t sstride = (size_t)group_tiles(tile_c, p.ntiles) * 64u;
+
+  u32x4 vin_reg[kVinSlots][kRaw], ein_reg[kEinSlots];
+  uint32_t sw[CK], sw_next[CK];
+  const int es = dtype_size(p.env_dt);
+  const int hl = p.l >> 3;
+  const int row_bytes = p.l * es;
+  const int64_t ein_bytes = (int64_t)p.K * row_bytes;
+  auto fetch = [&](int chunk) {
+    const int q0 = q_lo + chunk * CK;
+#pragma unroll
+    for (int i = 0; i < kVinSlots; ++i) {
+      const int id = tid + kFewThreads * i;
+      const int c = id & 15, tok = (id >> 4) & (16 * TB - 1), j = id / (256 * TB);
+      const int64_t e = (int64_t)min(tok, p.T - 1) * p.vin_ld + max(0, min((q0 + j) * kBlockCols + c * 8, p.K - 8));
+      if (p.K >= 8) {                                           // (shorter rows are read when they are parked)
+#pragma unroll
+        for (int v = 0; v < kRaw; ++v)
+          vin_reg[i][v] = *(const MDBF_GLOBAL u32x4_any*)((const MDBF_GLOBAL unsigned char*)p.vin +
+                                                          (e + 4 * v) * dtype_size(MODE));
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kEinSlots; ++i) {
+      const int id = tid + kFewThreads * i;
+      if (EVEC) {
+        const int col = q0 * kBlockCols + (id >> 1);
+        ein_reg[i] = ((const MDBF_GLOBAL u32x4*)p.Ein)[(size_t)min(col, p.K - 1) * hl + ((id & 1) < hl ? (id & 1) : 0)];
+      } else {
+        // 16-byte pieces of the chunk's rows; pieces past the factor's end repeat the last one, which never
+        // leaves the 16-byte granule of the factor's last element
+        const int64_t off = (int64_t)q0 * kBlockCols * row_bytes + id * 16;
+        if (kFewThreads * i < CK * 8 * row_bytes)
+          ein_reg[i] = *(const MDBF_GLOBAL u32x4*)((const MDBF_GLOBAL unsigned char*)p.Ein + min(off, (ein_bytes - 1) & ~(int64_t)15));
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < CK; ++j) sw_next[j] = sbase[(size_t)min(q0 + j, p.KB - 1) * sstride];
+  };
+  auto stash = [&](int chunk, int buf) {
+    const int q0 = q_lo + chunk * CK;
+#pragma unroll
+    for (int i = 0; i < kVinSlots; ++i) {
+      const int id = tid + kFewThreads * i;
+      const int c = id & 15, tok = (id >> 4) & (16 * TB - 1), j = id / (256 * TB);
+      const int col = (q0 + j) * kBlockCols + c * 8;
+      u32x4 v;
+      if (p.K < 8) {
+        v = load8_as_half(p.vin, (int64_t)min(tok, p.T - 1) * p.vin_ld + col, p.K - col, MODE);
+      } else {
+        if (MODE == MDBF_F16) {
+          v = vin_reg[i][0];
+        } else if (MODE == MDBF_BF16) {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            v[t] = pack_half2(__builtin_bit_cast(float, vin_reg[i][0][t] << 16),
+                              __builtin_bit_cast(float, vin_reg[i][0][t] & 0xFFFF0000u));
+        } else {
+          const floatx4 f0 = __builtin_bit_cast(floatx4, vin_reg[i][0]), f1 = __builtin_bit_cast(floatx4, vin_reg[i][kRaw - 1]);
+          v = u32x4{pack_half2(f0.x, f0.y), pack_half2(f0.z, f0.w), pack_half2(f1.x, f1.y), pack_half2(f1.z, f1.w)};
+        }
+        if ((p.K & 7) != 0 && q0 + j == p.KB - 1 && col < p.K && col + 8 > p.K) {
+          // the row's last, partial octet was loaded as its last eight elements: move it down, zeros behind
+          const int sh = 16 * (col + 8 - p.K);
+          uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+          if (sh >= 64) {
+            lo = hi >> (sh - 64);
+            hi = 0;
+          } else {
+            lo = (lo >> sh) | (hi << (64 - sh));
+            hi >>= sh;
+          }
+          v = u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+        }
+        const bool ok = col < p.K;
+        v = u32x4{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+      }
+      *reinterpret_cast<u32x4*>(vin_buf + buf * kVinBytes + (j * 16 * TB + tok) * 256 + ((c ^ (tok & 15)) << 4)) = v;
+    }
+    unsigned char* eb = ein_buf + buf * (CK * kEinBufBytes);
+#pragma unroll
+    for (int i = 0; i < kEinSlots; ++i) {
+      const int id = tid + kFewThreads * i;
+      if (EVEC) {
+        const int col = id >> 1;                                // inside the chunk
+        const bool ok = (q0 * kBlockCols + col < p.K) && (id & 1) < hl;
+        const u32x4 v = ein_reg[i];
+        *reinterpret_cast<u32x4*>(eb + (col >> 7) * kEinBufBytes + ein_row(col & 127) * 32 + (((id & 1) ^ ((col >> 4) & 1)) << 4)) =
+            u32x4{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+      } else if (kFewThreads * i < CK * 8 * row_bytes && id * 16 < CK * kBlockCols * row_bytes) {
+        const float rl = 1.f / (float)p.l;
+        const int per = 16 / es;
+        int first = id * per;                                   // element of the chunk: below 8192
+        asm volatile("" : "+v"(first));                         // (its LDS offsets are not worth 32 registers)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          if (t < per) {
+            const int e = first + t;
+            const int col = (int)(((float)e + 0.5f) * rl), mode = e - col * p.l;
+            uint32_t bits = es == 4 ? ein_reg[i][t & 3] : (t & 1) ? ein_reg[i][t >> 1] >> 16 : ein_reg[i][t >> 1] & 0xFFFFu;
+            if (p.env_dt != MDBF_F16) {
+              const float f = __builtin_bit_cast(float, es == 4 ? bits : bits << 16);
+              bits = pack_half2(f, 0.f) & 0xFFFFu;
+            }
+            if (q0 * kBlockCols + col >= p.K) bits = 0;
+            *reinterpret_cast<uint16_t*>(eb + (col >> 7) * kEinBufBytes + ein_row(col & 127) * 32 +
+                                         (((mode >> 3) ^ ((col >> 4) & 1)) << 4) + (mode & 7) * 2) = (uint16_t)bits;
+          }
+        }
+      }
+    }
+  };
+
+  fetch(0);
+  // Eout row of this lane's tile row, 4 modes per lane (B operand of the reconstruction)
+  half4 eo_op;
+  {
+    const int row = min(tile_c * kTileRows + r16, p.rows - 1);
+    float v[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int mode = 4 * g + t;
+      v[t] = load_as_float(p.Eout, (int64_t)row * p.l + min(mode, p.l - 1), p.env_dt);
+      if (mode >= p.l) v[t] = 0.f;
+    }
+    eo_op = half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+  }
+  if (!EVEC) {                                                  // the modes past the rank stay zero
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (int i = tid; i < 2 * CK * kEinBufBytes / 16; i += kFewThreads) reinterpret_cast<u32x4*>(ein_buf)[i] = zero;
+    __syncthreads();
+  }
+  stash(0, 0);
+#pragma unroll
+  for (int j = 0; j < CK; ++j) sw[j] = sw_next[j];
+  fetch(min(1, chunks - 1));
+
+  floatx4 acc[TB];
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb) acc[tb] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int ch = 0; ch < chunks; ++ch) {
+    const int cur = ch & 1;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < CK; ++j) {
+      if (q_lo + ch * CK + j < q_hi) {
+        const unsigned char* ein = ein_buf + (cur * CK + j) * kEinBufBytes;
+        const unsigned char* vin = vin_buf + cur * kVinBytes + j * (16 * TB * 256);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          const int col0 = 32 * f + 8 * (r16 >> 2) + (r16 & 3);
+          const int eoff = ein_row(col0) * 32 + ((g ^ ((r16 >> 2) & 2)) << 3);
+          const half4 ea0 = *reinterpret_cast<const half4*>(ein + eoff);
+          const half4 ea1 = *reinterpret_cast<const half4*>(ein + eoff + (ein_row(4) - ein_row(0)) * 32);
+          const floatx4 z4 = {0.f, 0.f, 0.f, 0.f};
+          const floatx4 e0 = __builtin_amdgcn_mfma_f32_16x16x16f16(ea0, eo_op, z4, 0, 0, 0);
+          const floatx4 e1 = __builtin_amdgcn_mfma_f32_16x16x16f16(ea1, eo_op, z4, 0, 0, 0);
+          const int pbase = 8 * (f >> 1) + 4 * (f & 1);
+          u32x4 w4;
+          w4.x = pack_half2(e0[0], e0[1]) ^ ((sw[j] << (15 - (pbase + 0))) & 0x80008000u);
+          w4.y = pack_half2(e0[2], e0[3]) ^ ((sw[j] << (15 - (pbase + 1))) & 0x80008000u);
+          w4.z = pack_half2(e1[0], e1[1]) ^ ((sw[j] << (15 - (pbase + 2))) & 0x80008000u);
+          w4.w = pack_half2(e1[2], e1[3]) ^ ((sw[j] << (15 - (pbase + 3))) & 0x80008000u);
+          const half8 wop = __builtin_bit_cast(half8, w4);
+          const int c = f * 4 + g;
+#pragma unroll
+          for (int tb = 0; tb < TB; ++tb) {
+            const half8 x = *reinterpret_cast<const half8*>(vin + (tb * 16 + r16) * 256 + ((c ^ r16) << 4));
+            acc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, wop, acc[tb], 0, 0, 0);
+          }
+        }
+      }
+    }
+    if (ch + 1 < chunks) {
+      stash(ch + 1, cur ^ 1);
+#pragma unroll
+      for (int j = 0; j < CK; ++j) sw[j] = sw_next[j];
+      fetch(min(ch + 2, chunks - 1));
+    }
+  }
+
+  // ---- lane (r16, g) holds token 16 tb + 4 g + i of row r16 of the tile
+  const int row = tile * kTileRows + r16;
+  const bool mine = tile < p.ntiles && row < p.rows;
+#pragma unroll
+  for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int b = tb * 16 + 4 * g + i;
+      if (mine && b < p.T) {
+        if (a.nsplit == 1) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, acc[tb][i], p.flags);
+        else ((MDBF_GLOBAL float*)a.part)[((size_t)split * p.T + b) * a.part_ld + row] = acc[tb][i];
+      }
+    }
+}
+
+// the partial sums of the launch before, added in the order of the splits, eight loads in flight
+__global__ __launch_bounds__(256) void few_reduce_kernel(FewArgs a) {
+  const int row = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y;
+  if (row >= a.p.rows) return;
+  const MDBF_GLOBAL float* first = (const MDBF_GLOBAL float*)a.part + (size_t)b * a.part_ld + row;
+  const size_t step = (size_t)a.p.T * a.part_ld;
+  float sum = 0.f;
+  for (int t0 = 0; t0 < a.nsplit; t0 += 8) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = first[min(t0 + j, a.nsplit - 1) * step];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (t0 + j < a.nsplit) sum += v[j];
+  }
+  emit_result(a.p.out, (int64_t)b * a.p.out_ld + row, a.p.out_dt, sum, a.p.flags);
+}
+
+template <int MODE, bool EVEC, int TB>
+static int launch_few_met(const FewArgs& a, hipStream_t s) {
+  static KernelSetup setup;
+  if (int e = kernel_setup(setup, [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&stage_gemm_few_kernel<MODE, EVEC, TB>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, few_smem(TB));
+      }))
+    return e;
+  const int groups = (a.p.ntiles + kFewWaves - 1) / kFewWaves;
+  hipLaunchKernelGGL((stage_gemm_few_kernel<MODE, EVEC, TB>), dim3((unsigned)(groups * a.nsplit)),
+                     dim3(kFewThreads), few_smem(TB), s, a);
+  return (int)hipGetLastError();
+}
+
+template <int MODE, bool EVEC>
+static int launch_few_me(const FewArgs& a, hipStream_t s) {
+  if (a.p.T > 32) return launch_few_met<MODE, EVEC, 4>(a, s);
+  if (a.p.T > 16) return launch_few_met<MODE, EVEC, 2>(a, s);
+  return launch_few_met<MODE, EVEC, 1>(a, s);
+}
+
+template <int MODE>
+static int launch_few_m(const FewArgs& a, hipStream_t s) {
+  const bool evec = a.p.env_dt == MDBF_F16 && (a.p.l == 16 || a.p.l == 8);
+  return evec ? launch_few_me<MODE, true>(a, s) : launch_few_me<MODE, false>(a, s);
+}
+
 // items_dev null: the single problem *p.  Else nitems work items of a plan, `p` describing the launch:
 // p->T = the longest token count among the problems.
 template <int R, int TB, int MODE, bool BATCH>
@@ -544,7 +840,7 @@ static int launch_rtm(const WorkItem* items_dev, int nitems, const StageProb* p,
     if constexpr (R == kPlanR && TB <= 4) return launch_rtmb<R, TB, MODE, true>(items_dev, nitems, p, s);
     return (int)hipErrorInvalidValue;
   } else {
-    if constexpr (R == 1 || TB >= 6) return launch_rtmb<R, TB, MODE, false>(nullptr, 0, p, s);
+    if constexpr (TB >= 6 || (R == 1 && MODE != kGeneric)) return launch_rtmb<R, TB, MODE, false>(nullptr, 0, p, s);
     return (int)hipErrorInvalidValue;
   }
 }
@@ -576,7 +872,6 @@ static int long_problem_slabs(const StageProb& p) {
   }
   return best;
 }
-bool stage_is_gemm(const StageProb& p) { return p.l >= 1 && p.l <= 16; }
 
 int gemm_load_mode(const StageProb& p) {
   const int es = dtype_size(p.vin_dt);
@@ -602,12 +897,66 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const Sta
       default: return gemm::launch_rt<2, 8>(nullptr, 0, mode, p, s);
     }
   }
-  if (p->T > 32) return gemm::launch_rt<1, 4>(nullptr, 0, mode, p, s);
-  if (p->T > 16) return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
-  if (mode == MDBF_F16) return gemm::launch_split<MDBF_F16>(p, s);
-  if (mode == MDBF_BF16) return gemm::launch_split<MDBF_BF16>(p, s);
-  if (mode == MDBF_F32) return gemm::launch_split<MDBF_F32>(p, s);
-  return gemm::launch_rt<1, 1>(nullptr, 0, mode, p, s);
+  if (p->T > 16 && mode != gemm::kGeneric) {
+    if (p->T > 32) return gemm::launch_rt<1, 4>(nullptr, 0, mode, p, s);
+    return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
+  }
+  const SplitGeom one = {p->KB, 1, 0};                          // (no room for partial sums)
+  return launch_stage_gemm_few(p, one, nullptr, 0, s);
+}
+
+SplitGeom few_geom(int ntiles, int KB, int T, bool vectors) {
+  // Host arithmetic only (the workspace layout follows from it), for a device of 256 compute units that hold two
+  // workgroups each.  In tenths of the time of a chunk, 0.3 us: a workgroup by itself on a unit takes 10 per
+  // chunk, two that share one 17 each, further ones queue; partial sums cost 22 for their launch and 4 TB/s.  Measured
+  // with 16 tokens: 86 blocks on 32 row groups, 7 or 8 splits of 12 blocks against 11 of 8, 23.8 and 25.6 us per
+  // call; 32 blocks on 86 groups, 4 splits of 8 against 3 of 12 (258 workgroups), 24.7 and 27.3 us.
+  // Few row tiles or blocks: the kernel with one tile per workgroup needs no partial sums; 4 per iteration of
+  // four blocks and 8 KB of staging per tile and block at 10 TB/s (1856 x 2848, k = 128, 11 tokens: 13.8 us
+  // against 16.1 split).
+  const int64_t ck = gemm::few_chunk(T > 32 ? 4 : T > 16 ? 2 : 1);
+  SplitGeom best = {KB, 1, (ntiles + gemm::kFewWaves - 1) / gemm::kFewWaves};
+  int64_t least = -1;
+  for (int64_t bs = ck;; bs += ck) {
+    const int64_t nsplit = (KB + bs - 1) / bs, wgs = nsplit * best.ngroup;
+    if (nsplit <= gemm::kFewSplits) {
+      int64_t cost = (bs < KB ? bs / ck : (KB + ck - 1) / ck) * (wgs <= 256 ? 10 : 17 * ((wgs + 511) / 512));
+      if (nsplit > 1) cost += 22 + nsplit * T * ntiles * kTileRows * 8 / 1200000;
+      if (least < 0 || cost < least) {
+        least = cost;
+        best.bs = (int)(bs < KB ? bs : KB);
+        best.nsplit = (int)nsplit;
+      }
+    }
+    if (nsplit == 1) break;
+  }
+  if (vectors && T <= 16) {
+    const int64_t rounds = ntiles > 512 ? 2 : 1;                // (two tiles per workgroup then)
+    if ((KB + 3) / 4 * 4 * rounds + (int64_t)ntiles * KB / 366 < least) best = SplitGeom{KB, 1, ntiles};
+  }
+  return best;
+}
+
+int launch_stage_gemm_few(const StageProb* p, const SplitGeom& g, float* part, int64_t part_ld, hipStream_t s) {
+  if (g.nsplit == 1 && p->T <= 16) {
+    const int mode = gemm_load_mode(*p);
+    if (mode == MDBF_F16) return gemm::launch_split<MDBF_F16>(p, s);
+    if (mode == MDBF_BF16) return gemm::launch_split<MDBF_BF16>(p, s);
+    if (mode == MDBF_F32) return gemm::launch_split<MDBF_F32>(p, s);
+  }
+  gemm::FewArgs a;
+  a.p = *p;
+  a.bs = g.bs;
+  a.nsplit = g.nsplit;
+  a.part = part;
+  a.part_ld = part_ld;
+  int e;
+  if (p->vin_dt == MDBF_F16) e = gemm::launch_few_m<MDBF_F16>(a, s);
+  else if (p->vin_dt == MDBF_BF16) e = gemm::launch_few_m<MDBF_BF16>(a, s);
+  else e = gemm::launch_few_m<MDBF_F32>(a, s);
+  if (e || g.nsplit == 1) return e;
+  hipLaunchKernelGGL(gemm::few_reduce_kernel, dim3((unsigned)((p->rows + 255) / 256), (unsigned)p->T), dim3(256), 0, s, a);
+  return (int)hipGetLastError();
 }
 
 }  // namespace mdbf

@@ -309,6 +309,41 @@ def test_determinism_of_the_split_contraction(gpu):
         assert orc.max_rel_error(first.cpu().numpy(), ref) <= TOL
 
 
+FEW_TOKENS = [
+    # m, n, k, l, T, env, x, columns of X behind each row: rows shorter than a vector, last octets of 1 and 7 columns,
+    # chunk and split edges, the largest token count of each slab count, rows at odd addresses
+    (5, 3, 7, 1, 2, "f32", "f32", 0), (16, 129, 127, 16, 16, "f16", "bf16", 3), (130, 513, 1031, 8, 7, "f16", "f32", 1),
+    (1041, 4097, 2049, 3, 17, "bf16", "f16", 5), (300, 1025, 4100, 15, 32, "f32", "bf16", 0),
+    (2064, 2055, 515, 5, 33, "f16", "f32", 2), (4096, 11008, 4096, 16, 16, "f16", "f16", 8), (520, 640, 3000, 16, 64, "f32", "f16", 1),
+]
+
+
+@pytest.mark.parametrize("m,n,k,l,T,env_dtype,x_dtype,pad", FEW_TOKENS)
+def test_few_token_calls(gpu, m, n, k, l, T, env_dtype, x_dtype, pad):
+    """Single calls with 2 to 64 tokens, the contraction split across workgroups and (with a workspace that has no
+    room for partial sums) in one run: both against the oracle at the fp16 gate, and against each other: z is
+    rounded to fp16 between the factors, so a sum that rounds the other way moves it by 2^-11."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l + T, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, T, seed=19 + m, x_dtype=x_dtype)
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    dl = mb.DeviceLayer.from_host(L)
+    wide = torch.full((T, n + pad), float("nan"), dtype=_to_dev(torch, X[:1], x_dtype).dtype, device="cuda:0")
+    wide[:, :n] = _to_dev(torch, X, x_dtype)
+    Xd = wide[:, :n]
+    got = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    assert orc.max_rel_error(got.cpu().numpy(), ref) <= TOL
+    assert torch.equal(got, mb.mdbf_forward(dl, Xd, y_dtype="f32"))
+    assert torch.equal(mb.mdbf_forward(dl, Xd, y_dtype="f32", Y=got.clone(), accumulate=True), got + got)
+    z = (T * ((k + 7) // 8 * 8) * 4 + 255) // 256 * 256
+    small = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32", precise=True), T), dtype=torch.uint8, device="cuda:0")
+    assert small.numel() == z
+    if T > 16 or l not in (8, 16) or env_dtype != "f16":
+        run = mb.mdbf_forward(dl, Xd, y_dtype="f32", workspace=small)
+        assert orc.max_rel_error(run.cpu().numpy(), ref) <= TOL
+        assert orc.max_rel_error(run.cpu().numpy(), got.cpu().numpy().astype(np.float64)) <= 2.0 ** -11
+
+
 ANY_RANK = [
     # m, n, k, l, env, x: edges of the 16-row tiles, of the 128-column blocks, of the 8-tile groups and of a split of
     # four blocks; the smallest and largest rank of both record forms
