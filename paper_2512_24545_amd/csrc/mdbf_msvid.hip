@@ -10,153 +10,278 @@
 //   V <- caller's start block (cols x b)
 //   repeat `iters` times:   B = |Z| V,  orthonormalise;   V = |Z|^T B,  orthonormalise
 //   B = |Z| V;   B^T B = W L W^T (Jacobi, fp64);   sigma = sqrt(L);   A = B W_l Sigma_l^(-1/2),   Q = V W_l Sigma_l^(1/2)
-// The two products are the whole cost: each reads Z once (HBM-bound, 4 bytes per 2 b multiply-adds).  Both are
-// run by one kernel, "lanes own columns" (coalesced reads, no cross-lane sums): |Z|^T B on Z itself, |Z| V
-// on a transposed copy of Z made once at the start (the sign matrix is written in the same pass).
+// The two products are the whole cost: each reads Z once (HBM-bound, 4 bytes per 2 b multiply-adds), row-major as
+// it stands: one kernel, with the roles of rows and columns as a template argument.
 // Orthonormalisation is Cholesky-QR: Gram matrix from per-workgroup partial sums (fp32) added in fp64, Cholesky
-// factor R in fp64, and the next product applies R^(-1) to the rows of its input block as it stages them.
+// factor R in fp64 by the last workgroup of that launch, and the next product applies R^(-1) to the rows of its input block as it stages them.
+#include <type_traits>
+
 #include "mdbf_internal.h"
 
 namespace mdbf {
 namespace msvid {
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));    // four elements at any element's address
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
 constexpr int kThreads = 256;
-constexpr int kStrip = 128;           // columns per workgroup of the product kernel: two per lane, 4 waves share the rows
-constexpr int kChunkRows = 128;       // rows per workgroup of the product kernel
-constexpr int kBatchRows = 16;        // rows whose loads a wave issues before their arithmetic
+constexpr int kOut = 64;              // outputs (columns or rows of Z) per workgroup of the product kernel
+constexpr int kChunk = 256;           // contraction entries per workgroup, 64 per wave
 constexpr int kSmallThreads = 1024;   // the b x b kernels (a thread per matrix entry, b <= 32) and the chunk reduction
                                       // (few workgroups: many loads in flight in each)
 constexpr int kGramRows = 64;         // rows per workgroup of the reduce + Gram kernel
 
-// ---- S = sign(Z) as int8 (+1 / -1, sign(0) = +1: Sec. 2, Notation) and Zt = Z^T, 64 x 64 tiles through LDS
-__global__ __launch_bounds__(kThreads) void sign_transpose_kernel(const float* __restrict__ Z, int rows, int cols,
-                                                                  int64_t ld, int8_t* __restrict__ S,
-                                                                  float* __restrict__ Zt) {
-  __shared__ float tile[64][65];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    float z = 0.f;
-    if (r < rows && c < cols) {
-      z = Z[(int64_t)r * ld + c];
-      S[(int64_t)r * cols + c] = (z < 0.f) ? (int8_t)-1 : (int8_t)1;
-    }
-    tile[i][tx] = z;
-  }
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, r = r0 + tx;
-    if (r < rows && c < cols) Zt[(int64_t)c * rows + r] = tile[tx][i];
+// ---- S = sign(Z) as int8 (+1 / -1, sign(0) = +1: Sec. 2, Notation), four entries per thread; clears the counter
+// of reduce_gram_kernel's launches
+__global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
+                                                        int8_t* __restrict__ S, uint32_t* __restrict__ counter) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *counter = 0u;
+  const int c = (blockIdx.y * kThreads + threadIdx.x) * 4;
+  if (c >= cols) return;
+  const MDBF_GLOBAL float* z = (const MDBF_GLOBAL float*)Z + (int64_t)blockIdx.x * ld + c;
+  MDBF_GLOBAL int8_t* out = (MDBF_GLOBAL int8_t*)S + (int64_t)blockIdx.x * cols + c;
+  if (c + 4 <= cols) {
+    const floatx4 v = *(const MDBF_GLOBAL floatx4_any*)z;
+    *(MDBF_GLOBAL u32_any*)out = (v.x < 0.f ? 0xFFu : 1u) | (v.y < 0.f ? 0xFF00u : 0x100u) |
+                                 (v.z < 0.f ? 0xFF0000u : 0x10000u) | (v.w < 0.f ? 0xFF000000u : 0x1000000u);
+  } else {
+    for (int e = 0; c + e < cols; ++e) out[e] = z[e] < 0.f ? (int8_t)-1 : (int8_t)1;
   }
 }
 
-// ---- P[chunk][c][:] = sum over the chunk's rows r of |M[r, c]| * X'[r, :],   X' = X Tm  (Tm null: X' = X)
-// M: R_ x C_ row-major; X: R_ x BB; Tm: BB x BB (fp64, row-major).  Grid: (column strips, row chunks).
-// A lane owns columns c and c + 64 of the strip; the four waves take every fourth group of kBatchRows rows, with
-// the loads of a group issued before its arithmetic (a load is a trip to HBM: what bounds the kernel is how many
-// are in flight), and add their sums through LDS in a fixed order.
-template <int BB>
-__global__ __launch_bounds__(kThreads) void abs_t_mul_kernel(const float* __restrict__ M, int R_, int C_, int64_t ldm,
-                                                             const float* __restrict__ X,
-                                                             const double* __restrict__ Tm, float* __restrict__ P) {
-  __shared__ __attribute__((aligned(16))) float xs[kChunkRows][BB];
-  __shared__ float red[2 * kStrip * BB];
-  __shared__ float tms[BB * BB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r0 = blockIdx.y * kChunkRows;
-  const int nr = min(kChunkRows, R_ - r0);
+// ---- P[chunk][o][:] = sum over the chunk's contraction entries q of |Z[.]| * X'[q, :],   X' = X Tm  (Tm null: X' = X)
+// COLS: outputs are the columns of Z (|Z|^T X, X has a row per row of Z); else its rows (|Z| X).
+// Grid: (output strips of 64, contraction chunks of 256).  A wave owns the strip and 64 contraction entries, works out
+// its 64 rows of X' and contracts a 64 x 64 piece of Z in four rounds of 16 entries: four 16-byte loads per lane, a
+// round ahead, then 4 steps of v_mfma_f32_16x16x4_f32 (fp32 operands and sums) per 16 outputs and 16 columns of X'.
+// The four waves meet in LDS in wave order.
+// What bounds it: 9 us for one read of Z beside 5 us of matrix-core work and 9 us of launch, staging and partial
+// sums, which only partly overlap.  (All of a wave's sixteen loads in flight: no change; X as single elements in
+// operand order: 8 us more.)  Lanes that own columns and fused multiply-adds took 24 us per product of 4096 x 2656 and b = 24, and a transposed
+// copy of Z for |Z| X another 20 us per call; now 18 to 20 us.
+template <int BB, bool COLS>
+__global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
+                                                              const float* __restrict__ X, const float* __restrict__ Tm,
+                                                              float* __restrict__ P) {
+  constexpr int NT = (BB + 15) / 16;                   // 16-column tiles of X' (the last may be partly past BB)
+  constexpr int RS = BB + 1;                           // floats per output in the waves' sums
+  constexpr int kXs = 4 * (64 * BB + 16), kRed = 4 * kOut * RS;
+  __shared__ __attribute__((aligned(16))) float buf[kXs > kRed ? kXs : kRed];
+  __shared__ __attribute__((aligned(16))) float tms[BB * BB];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int nout = COLS ? cols : rows, nin = COLS ? rows : cols;
+  const int o0 = blockIdx.x * kOut, q0 = blockIdx.y * kChunk;
+  const int qw = q0 + wave * 64;
+  // ---- the wave's 64 rows of X, coalesced, and Tm (requested before Z: a load waits for all before it)
+  constexpr int KS = BB / 4;                           // steps of four columns of X
+  const MDBF_GLOBAL floatx4* xg = (const MDBF_GLOBAL floatx4*)X;
+  floatx4 xr[KS], tr = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < KS; ++i) xr[i] = xg[min((int64_t)qw * KS + lane + 64 * i, (int64_t)nin * KS - 1)];
+  if (Tm && tid < BB * BB / 4) tr = ((const MDBF_GLOBAL floatx4*)Tm)[tid];
+  // ---- Z.  COLS: load i of round j covers row qw + 16 j + 4 i + g and columns o0 + 4 n .. + 3: step i contracts its
+  // four rows, output tile v holds columns o0 + 4 m + v.  Rows: load i covers row o0 + 16 i + n and columns
+  // qw + 16 j + 4 g .. + 3: step v contracts columns qw + 16 j + 4 g' + v, output tile i holds rows o0 + 16 i + m.
+  // Entries past the end repeat the last (their X' is zero); outputs past it are not stored.
+  const MDBF_GLOBAL float* zb = (const MDBF_GLOBAL float*)Z;
+  const bool whole = (COLS ? o0 : qw) + 64 <= cols;    // (uniform) the wave's 64 columns all exist
+  auto load = [&](int j, floatx4 (&z)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = COLS ? min(qw + 16 * j + 4 * i + g, rows - 1) : min(o0 + 16 * i + n, rows - 1);
+      const int c = COLS ? o0 + 4 * n : qw + 16 * j + 4 * g;
+      const MDBF_GLOBAL float* src = zb + (int64_t)r * ld;
+      if (whole) {
+        z[i] = *(const MDBF_GLOBAL floatx4_any*)(src + c);
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) z[i][v] = src[min(c + v, cols - 1)];
+      }
+    }
+  };
+  floatx4 z[4], zn[4];
+  load(0, zn);
+  // ---- X' of the wave's entries in LDS (each wave reads only its own), sixteen rows at a time in the place of X's.
+  // (The span is what matters here, fp32 will do; the last block is orthonormalised in fp64 by apply_kernel.)
+  float* xs = buf + wave * (64 * BB + 16);
+#pragma unroll
+  for (int i = 0; i < KS; ++i) {
+    const bool ok = qw + (lane + 64 * i) / KS < nin;
+    reinterpret_cast<floatx4*>(xs)[lane + 64 * i] = ok ? xr[i] : floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  if (lane < 16) xs[64 * BB + lane] = 0.f;             // (read by the partial last tile, never used)
+  if (tid < BB * BB / 4) reinterpret_cast<floatx4*>(tms)[tid] = tr;
+  __syncthreads();
   if (Tm) {
-    for (int p = tid; p < BB * BB; p += kThreads) tms[p] = (float)Tm[p];
+    float tb[KS][NT];
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int u = 0; u < NT; ++u) tb[k][u] = tms[(4 * k + g) * BB + min(n + 16 * u, BB - 1)];   // (past BB: dropped)
+#pragma unroll 1
+    for (int t = 0; t < 4; ++t) {
+      float xa[KS];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) xa[k] = xs[(16 * t + n) * BB + 4 * k + g];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        floatx4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < KS; ++k) d = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[k], tb[k][u], d, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (n + 16 * u < BB) xs[(16 * t + 4 * g + i) * BB + n + 16 * u] = d[i];
+      }
+    }
     __syncthreads();
   }
-  for (int idx = tid; idx < kChunkRows * BB; idx += kThreads) {
-    const int r = idx / BB, j = idx - r * BB;
-    float v = 0.f;                                   // rows past the chunk's end contribute nothing
-    if (r < nr) {
-      const float* xr = X + (size_t)(r0 + r) * BB;
-      if (Tm) {
-        float sum = 0.f;                               // (the span is what matters here; the last block is
-#pragma unroll                                         //  orthonormalised in fp64 by apply_kernel)
-        for (int i = 0; i < BB; ++i) sum = fmaf(xr[i], tms[i * BB + j], sum);
-        v = sum;
-      } else {
-        v = xr[j];
-      }
-    }
-    xs[r][j] = v;
-  }
-  __syncthreads();
-  const int c_a = blockIdx.x * kStrip + lane, c_b = c_a + 64;
-  const float* pa = M + (size_t)r0 * ldm + min(c_a, C_ - 1);
-  const float* pb = M + (size_t)r0 * ldm + min(c_b, C_ - 1);
-  float acc_a[BB], acc_b[BB];
+
+  floatx4 acc[4][NT];
 #pragma unroll
-  for (int j = 0; j < BB; ++j) { acc_a[j] = 0.f; acc_b[j] = 0.f; }
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int u = 0; u < NT; ++u) acc[t][u] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-  for (int g = wave * kBatchRows; g < nr; g += 4 * kBatchRows) {
-    float ma[kBatchRows], mb[kBatchRows];
+  for (int j = 0; j < 4; ++j) {
 #pragma unroll
-    for (int u = 0; u < kBatchRows; ++u) {
-      const size_t ro = (size_t)min(g + u, nr - 1) * ldm;     // (the repeated row meets a zero row of xs)
-      ma[u] = fabsf(pa[ro]);
-      mb[u] = fabsf(pb[ro]);
-    }
+    for (int i = 0; i < 4; ++i) z[i] = zn[i];
+    if (j < 3) load(j + 1, zn);
+    const float* xw = xs + (16 * j + (COLS ? g : 4 * g)) * BB + n;
 #pragma unroll
-    for (int u = 0; u < kBatchRows; ++u) {
+    for (int st = 0; st < 4; ++st) {
+      float b[NT];
 #pragma unroll
-      for (int j = 0; j < BB; ++j) {
-        const float x = xs[g + u][j];
-        acc_a[j] = fmaf(ma[u], x, acc_a[j]);
-        acc_b[j] = fmaf(mb[u], x, acc_b[j]);
+      for (int u = 0; u < NT; ++u) b[u] = xw[(COLS ? 4 * st : st) * BB + 16 * u];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float a = fabsf(COLS ? z[st][t] : z[t][st]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[u], acc[t][u], 0, 0, 0);
       }
     }
   }
-  // the waves' sums through LDS in a fixed order: (wave 0 + wave 2) + (wave 1 + wave 3)
-  static_assert(kChunkRows % kBatchRows == 0 && kStrip == 128, "row groups tile a chunk; two columns per lane");
-  if (wave >= 2) {
+  __syncthreads();                                     // every wave is done with X'
+  // lane (n, g) holds rows 4 g + i of the tiles, column n + 16 u of X'
 #pragma unroll
-    for (int j = 0; j < BB; ++j) {
-      red[((wave - 2) * 128 + lane) * BB + j] = acc_a[j];
-      red[((wave - 2) * 128 + 64 + lane) * BB + j] = acc_b[j];
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int o = COLS ? 4 * (4 * g + i) + t : 16 * t + 4 * g + i;
+        if (n + 16 * u < BB) buf[(wave * kOut + o) * RS + n + 16 * u] = acc[t][u][i];
+      }
+  __syncthreads();
+  float* out = P + ((size_t)blockIdx.y * nout + o0) * BB;
+  const int valid = min(kOut, nout - o0) * BB;
+#pragma unroll 1
+  for (int e = tid; e < valid; e += kThreads) {
+    const int o = e / BB, j = e - o * BB;
+    const float* r = buf + o * RS + j;
+    out[e] = ((r[0] + r[kOut * RS]) + r[2 * kOut * RS]) + r[3 * kOut * RS];
+  }
+}
+
+// G = sum of the workgroups' parts, in fp64, in a fixed order: a thread adds two neighbouring entries of every
+// kGroups-th part, sixteen loads in flight, then the groups are added in order.
+// COHERENT: the parts were written by other workgroups of the same launch, with device-scope stores
+template <int BB, int THREADS, bool COHERENT>
+__device__ void gather_gram(const float* __restrict__ Gp, int nparts, double (&G)[BB][BB]) {
+  constexpr int kPairs = BB * BB / 2, kGroups = THREADS / kPairs;
+  static_assert(kGroups >= 1, "a thread per pair");
+  __shared__ double sums[kGroups][BB * BB];
+  const int grp = threadIdx.x / kPairs, pr = threadIdx.x - grp * kPairs;
+  if (grp < kGroups) {
+    double s0 = 0.0, s1 = 0.0;
+    for (int w0 = grp; w0 < nparts; w0 += 16 * kGroups) {
+      uint64_t v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const MDBF_GLOBAL uint64_t* src =
+            (const MDBF_GLOBAL uint64_t*)Gp + (size_t)min(w0 + u * kGroups, nparts - 1) * kPairs + pr;
+        v[u] = COHERENT ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (w0 + u * kGroups < nparts) {
+          const uint32_t lo = (uint32_t)v[u], hi = (uint32_t)(v[u] >> 32);
+          s0 += (double)__builtin_bit_cast(float, lo);
+          s1 += (double)__builtin_bit_cast(float, hi);
+        }
     }
+    sums[grp][2 * pr] = s0;
+    sums[grp][2 * pr + 1] = s1;
   }
   __syncthreads();
-  if (wave < 2) {
+  for (int p = threadIdx.x; p < BB * BB; p += THREADS) {
+    double sum = sums[0][p];
 #pragma unroll
-    for (int j = 0; j < BB; ++j) {
-      acc_a[j] += red[(wave * 128 + lane) * BB + j];
-      acc_b[j] += red[(wave * 128 + 64 + lane) * BB + j];
-    }
+    for (int w = 1; w < kGroups; ++w) sum += sums[w][p];
+    G[p / BB][p % BB] = sum;
   }
   __syncthreads();
-  if (wave == 1) {
+}
+
+// a double held by lane `src` (a compile-time or wave-uniform index), in every lane
+__device__ __forceinline__ double lane_value(double v, int src) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// ---- Cholesky-QR: G = R^T R (R upper triangular), Tm = R^(-1): Y Tm has orthonormal columns.
+// One wave; lane j < 32 holds column j of the matrix in registers (right-looking: after step k the trailing columns
+// hold the Schur complement), lane 32 + j column j of the identity, which the same steps turn into column j of
+// L^(-1), L = R^T, i.e. row j of R^(-1).  Row k is passed round by lane reads: no LDS traffic and no barrier inside
+// the b steps, and no substitution after them.
+// A column that the earlier ones span (|Z| of lower rank than the block is wide: a member of the format is) has
+// a pivot at the level of the Gram matrix's rounding, 1e-6 of its diagonal entry (fp32 partial sums): such a
+// column is dropped (its column of Tm is zero, and stays zero through the products that follow).
+template <int BB>
+__device__ __forceinline__ void cholesky_inverse(const double (&G)[BB][BB], double* __restrict__ Tm, float* __restrict__ Tf) {
+  const int j = (int)threadIdx.x & 31;
+  const bool inv = (threadIdx.x & 32) != 0;
+  const int jc = min(j, BB - 1);                       // lanes past the last column shadow it and store nothing
+  double a[BB];
 #pragma unroll
-    for (int j = 0; j < BB; ++j) {
-      red[lane * BB + j] = acc_a[j];
-      red[(64 + lane) * BB + j] = acc_b[j];
-    }
+  for (int i = 0; i < BB; ++i) a[i] = inv ? (i == jc ? 1.0 : 0.0) : G[i][jc];
+#pragma unroll
+  for (int k = 0; k < BB; ++k) {
+    const double piv = lane_value(a[k], k);            // the Schur complement's diagonal entry
+    const double g0 = G[k][k];
+    const bool drop = !(piv > 1e-6 * g0) || !(g0 > 0.0);
+    const double rd = drop ? 1.0 : rsqrt(piv);
+    // lanes j > k: R[k][j] (a dropped column: zeros); lanes 32 + j: entry k of the solution, zero where it was dropped
+    const double x = drop && !inv ? 0.0 : a[k] * rd;
+#pragma unroll
+    for (int i = k + 1; i < BB; ++i) a[i] -= lane_value(x, i) * x;     // (columns <= k are not read again)
+    a[k] = drop ? 0.0 : x;
   }
-  __syncthreads();
-  if (wave == 0) {
-    if (c_a < C_) {
-      float* out = P + ((size_t)blockIdx.y * C_ + c_a) * BB;
+  if (inv && j < BB) {
 #pragma unroll
-      for (int j = 0; j < BB; ++j) out[j] = acc_a[j] + red[lane * BB + j];
-    }
-    if (c_b < C_) {
-      float* out = P + ((size_t)blockIdx.y * C_ + c_b) * BB;
-#pragma unroll
-      for (int j = 0; j < BB; ++j) out[j] = acc_b[j] + red[(64 + lane) * BB + j];
+    for (int i = 0; i < BB; ++i) {
+      Tm[j * BB + i] = a[i];
+      Tf[j * BB + i] = (float)a[i];
     }
   }
 }
 
-// ---- Y = sum over chunks of P (in chunk order), and this workgroup's part of Y^T Y
+// ---- Y = sum over chunks of P (in chunk order), and this workgroup's part of Y^T Y.  Tm (or null): the last
+// workgroup to finish (a counter, which it sets back to zero; nobody waits) adds the parts up and leaves
+// Tm = R^(-1) of the Cholesky factorisation (Tf: the same in fp32).  In launches of their own the sums took 7 us and
+// the factorisation 17; together 15, most of it the chain of b pivots in fp64.
 template <int BB>
 __global__ __launch_bounds__(kSmallThreads) void reduce_gram_kernel(const float* __restrict__ P, int nchunks, int n,
-                                                               float* __restrict__ Y, float* __restrict__ Gp) {
+                                                                    float* __restrict__ Y, float* __restrict__ Gp,
+                                                                    double* __restrict__ Tm, float* __restrict__ Tf,
+                                                                    uint32_t* __restrict__ counter) {
   __shared__ float ys[kGramRows * BB];
+  __shared__ double G[BB][BB];
+  __shared__ uint32_t is_last;
   const int tid = threadIdx.x;
   const int row0 = blockIdx.x * kGramRows;
   const int nrow = min(kGramRows, n - row0);
@@ -182,164 +307,114 @@ __global__ __launch_bounds__(kSmallThreads) void reduce_gram_kernel(const float*
     const int i = p / BB, j = p - i * BB;
     float g = 0.f;
     for (int r = 0; r < kGramRows; ++r) g = fmaf(ys[r * BB + i], ys[r * BB + j], g);
-    Gp[(size_t)blockIdx.x * BB * BB + p] = g;
+    __hip_atomic_store((MDBF_GLOBAL float*)Gp + (size_t)blockIdx.x * BB * BB + p, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-}
-
-// G = sum of the workgroups' parts, in fp64, in part order (thread p owns entries p, p + blockDim.x, ...)
-template <int BB>
-__device__ void gather_gram(const float* __restrict__ Gp, int nparts, double (&G)[BB][BB]) {
-  for (int p = threadIdx.x; p < BB * BB; p += blockDim.x) {
-    double sum = 0.0;
-    for (int w0 = 0; w0 < nparts; w0 += 16) {       // sixteen loads in flight, added in part order
-      float v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) v[u] = Gp[(size_t)min(w0 + u, nparts - 1) * BB * BB + p];
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (w0 + u < nparts) sum += (double)v[u];
-    }
-    G[p / BB][p % BB] = sum;
+  if (!Tm) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's entries are in memory
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t old = __hip_atomic_fetch_add((MDBF_GLOBAL uint32_t*)counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    is_last = old + 1u == gridDim.x ? 1u : 0u;
   }
   __syncthreads();
-}
-
-// a double held by lane `src` (a compile-time or wave-uniform index), in every lane
-__device__ __forceinline__ double lane_value(double v, int src) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// ---- Cholesky-QR: G = R^T R (R upper triangular), Tm = R^(-1): Y Tm has orthonormal columns.
-// The whole workgroup adds up the Gram parts; the factorisation itself runs in one wave, lane j holding column j
-// of the matrix in registers (right-looking: after step k the trailing columns hold the Schur complement), with
-// row k passed round by lane reads: no LDS traffic and no barrier inside the b steps.
-// A column that the earlier ones span (|Z| of lower rank than the block is wide: a member of the format is) has
-// a pivot at the level of the Gram matrix's rounding, 1e-6 of its diagonal entry (fp32 partial sums): such a
-// column is dropped (its column of Tm is zero, and stays zero through the products that follow).
-template <int BB>
-__global__ __launch_bounds__(kSmallThreads) void chol_kernel(const float* __restrict__ Gp, int nparts, double* __restrict__ Tm) {
-  __shared__ double G[BB][BB];
-  gather_gram<BB>(Gp, nparts, G);
-  if (threadIdx.x >= 64) return;                       // (no barrier below)
-  const int j = (int)threadIdx.x;
-  const int jc = min(j, BB - 1);                       // lanes past the last column shadow it and store nothing
-  double a[BB], rk[BB], rinv[BB];
-  uint32_t dead = 0;
-#pragma unroll
-  for (int i = 0; i < BB; ++i) a[i] = G[i][jc];
-#pragma unroll
-  for (int k = 0; k < BB; ++k) {
-    const double piv = lane_value(a[k], k);            // the Schur complement's diagonal entry
-    const double g0 = G[k][k];
-    const bool drop = !(piv > 1e-6 * g0) || !(g0 > 0.0);
-    const double rd = drop ? 1.0 : 1.0 / sqrt(piv);
-    rinv[k] = rd;
-    dead |= drop ? (1u << k) : 0u;
-    rk[k] = (jc < k) ? 0.0 : (jc == k) ? (drop ? 1.0 : piv * rd) : (drop ? 0.0 : a[k] * rd);   // R[k][jc]
-#pragma unroll
-    for (int i = k + 1; i < BB; ++i) a[i] -= lane_value(rk[k], i) * rk[k];
-  }
-  // column jc of R^(-1) by back substitution on R X = I (entries below the diagonal come out zero)
-  double x[BB];
-#pragma unroll
-  for (int i = BB - 1; i >= 0; --i) {
-    double sum = (i == jc) ? 1.0 : 0.0;
-#pragma unroll
-    for (int m = i + 1; m < BB; ++m) sum -= lane_value(rk[i], m) * x[m];
-    x[i] = sum * rinv[i];
-  }
-  if (j < BB) {
-    const bool gone = (dead >> j) & 1u;
-#pragma unroll
-    for (int i = 0; i < BB; ++i) Tm[i * BB + j] = gone ? 0.0 : x[i];
-  }
+  if (!is_last) return;
+  if (tid == 0) __hip_atomic_store((MDBF_GLOBAL uint32_t*)counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  gather_gram<BB, kSmallThreads, true>(Gp, gridDim.x, G);
+  if (tid >= 64) return;                               // (no barrier below)
+  cholesky_inverse<BB>(G, Tm, Tf);
 }
 
 // ---- Rayleigh-Ritz: G = B^T B = W L W^T by cyclic Jacobi in fp64; Ritz values sigma_i = sqrt(L_i), descending.
 // MA = W_l Sigma_l^(-1/2) (A = B MA), MQ = W_l Sigma_l^(1/2) (Q = V MQ); both BB x BB row-major, columns >= l zero.
+// Cyclic Jacobi with the round-robin ordering: a step rotates BB / 2 disjoint index pairs at once (player BB - 1
+// stays, the others move round a circle), BB - 1 steps visit every pair once.  BB / 2 lanes work out the rotations
+// of a step, then a thread applies them to the 2 x 2 block of a row pair and a column pair (rows and columns in one
+// go, into the other of two copies) or to two entries of a row of W: two barriers a step.  What bounds it is the
+// chain of a step (a reciprocal root, a reciprocal and another root in fp64 between trips to LDS), some 160 steps.
+// Rows after columns, with full square roots and divisions, and a last sweep to see that nothing rotates any more:
+// 172 us, now 91 us.  (Every thread working out its own rotations saves a barrier and costs more: 116 us.)
+constexpr int kRitzThreads = 576;
 template <int BB>
-__global__ __launch_bounds__(kSmallThreads) void ritz_kernel(const float* __restrict__ Gp, int nparts, int l,
+__global__ __launch_bounds__(kRitzThreads) void ritz_kernel(const float* __restrict__ Gp, int nparts, int l,
                                                   double* __restrict__ MA, double* __restrict__ MQ,
                                                   float* __restrict__ sigma) {
-  __shared__ double a[BB][BB];
-  __shared__ double w[BB][BB];
-  __shared__ double cc[BB / 2], ss[BB / 2];
-  __shared__ int pp[BB / 2], qq[BB / 2];
-  __shared__ int order[BB];
-  __shared__ int rotated;
-  const int t = threadIdx.x;
-  gather_gram<BB>(Gp, nparts, a);
-  for (int p = t; p < BB * BB; p += blockDim.x) w[p / BB][p % BB] = (p / BB == p % BB) ? 1.0 : 0.0;
-  __syncthreads();
-  // Cyclic Jacobi with the round-robin ordering: a step rotates BB / 2 disjoint index pairs at once (player
-  // BB - 1 stays, the others move round a circle), BB - 1 steps visit every pair once.  The rotations of a step
-  // are all computed from the matrix as it stands before the step; disjoint pairs touch disjoint rows and columns.
-  static_assert(BB % 2 == 0, "pairs");
   constexpr int H = BB / 2;
+  __shared__ double aa[2][BB][BB];
+  __shared__ double w[BB][BB];
+  __shared__ double cc[H], ss[H];
+  __shared__ int pp[H], qq[H];
+  __shared__ int order[BB];
+  const int t = threadIdx.x;
+  gather_gram<BB, kRitzThreads, false>(Gp, nparts, aa[0]);
+  for (int p = t; p < BB * BB; p += kRitzThreads) w[p / BB][p % BB] = (p / BB == p % BB) ? 1.0 : 0.0;
+  __syncthreads();
+  static_assert(BB % 2 == 0, "pairs");
+  static_assert(BB * BB <= kRitzThreads && H * H + BB * H <= kRitzThreads, "a thread per entry, per block, per pair of entries of W");
+  const bool on_a = t < H * H, on_w = !on_a && t < H * H + BB * H;
+  const int wi = t - H * H;
+  const int rp = on_a ? t / H : 0, cp = on_a ? t - rp * H : on_w ? wi % H : 0, wrow = on_w ? wi / H : 0;
+  // an off-diagonal entry that still has to go
+  auto big = [](double apq, double app, double aqq) { return fabs(apq) > 1e-150 && apq * apq > 1e-32 * fabs(app * aqq); };
+  int cur = 0;
   for (int sweep = 0; sweep < 12; ++sweep) {
-    if (t == 0) rotated = 0;
-    __syncthreads();
+    {
+      const int p = t / BB, q = t - p * BB;
+      const double (&a)[BB][BB] = aa[cur];
+      if (!__syncthreads_or(t < BB * BB && p < q && big(a[p][q], a[p][p], a[q][q]) ? 1 : 0)) break;   // diagonal to working precision
+    }
     for (int step = 0; step < BB - 1; ++step) {
+      const double (&a)[BB][BB] = aa[cur];
       if (t < H) {
-        int p, q;
-        if (t == 0) {
-          p = BB - 1;
-          q = step;
-        } else {
-          p = (step + t) % (BB - 1);
-          q = (step - t + (BB - 1)) % (BB - 1);
-        }
+        int p = t == 0 ? step : (step + t) % (BB - 1);
+        int q = t == 0 ? BB - 1 : (step - t + (BB - 1)) % (BB - 1);
         if (p > q) { const int tmp = p; p = q; q = tmp; }
+        // (the angle only has to be good enough to converge; c and sn are a rotation to working precision whatever
+        // tt is)
         const double apq = a[p][q], app = a[p][p], aqq = a[q][q];
-        double c = 1.0, sn = 0.0;
-        if (fabs(apq) > 1e-300 && fabs(apq) > 1e-16 * sqrt(fabs(app * aqq))) {
-          const double tau = (aqq - app) / (2.0 * apq);
-          const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = 1.0 / sqrt(1.0 + tt * tt);
-          sn = tt * c;
-          rotated = 1;                                 // (any writer writes 1)
-        }
+        const bool turn = big(apq, app, aqq);
+        const double d = 0.5 * (aqq - app), x = turn ? d * d + apq * apq : 1.0;
+        double h = __builtin_amdgcn_rsq(x);
+        h = x * (h * (1.5 - 0.5 * x * h * h));                            // sqrt(d^2 + apq^2)
+        const double den = fabs(d) + h;
+        double r = __builtin_amdgcn_rcp(den);
+        r = r * (2.0 - den * r);
+        const double tt = turn ? (d >= 0.0 ? apq : -apq) * r : 0.0;         // the smaller of the two rotations
+        const double c = rsqrt(1.0 + tt * tt);
         pp[t] = p;
         qq[t] = q;
         cc[t] = c;
-        ss[t] = sn;
+        ss[t] = tt * c;
       }
       __syncthreads();
-      for (int idx = t; idx < BB * H; idx += blockDim.x) {     // columns p, q of a and of w
-        const int k = idx / H, pr = idx - k * H;
-        const int p = pp[pr], q = qq[pr];
-        const double c = cc[pr], sn = ss[pr];
-        const double akp = a[k][p], akq = a[k][q];
-        a[k][p] = c * akp - sn * akq;
-        a[k][q] = sn * akp + c * akq;
-        const double wkp = w[k][p], wkq = w[k][q];
-        w[k][p] = c * wkp - sn * wkq;
-        w[k][q] = sn * wkp + c * wkq;
+      if (on_a || on_w) {
+        const int p2 = pp[cp], q2 = qq[cp];
+        const double c2 = cc[cp], s2 = ss[cp];
+        if (on_a) {
+          const int p1 = pp[rp], q1 = qq[rp];
+          const double c1 = cc[rp], s1 = ss[rp];
+          const double app = a[p1][p2], apq = a[p1][q2], aqp = a[q1][p2], aqq = a[q1][q2];
+          const double bpp = c2 * app - s2 * apq, bpq = s2 * app + c2 * apq;     // columns
+          const double bqp = c2 * aqp - s2 * aqq, bqq = s2 * aqp + c2 * aqq;
+          double (&o)[BB][BB] = aa[cur ^ 1];
+          o[p1][p2] = c1 * bpp - s1 * bqp;                                       // rows
+          o[p1][q2] = c1 * bpq - s1 * bqq;
+          o[q1][p2] = s1 * bpp + c1 * bqp;
+          o[q1][q2] = s1 * bpq + c1 * bqq;
+        } else {
+          const double wp = w[wrow][p2], wq = w[wrow][q2];
+          w[wrow][p2] = c2 * wp - s2 * wq;
+          w[wrow][q2] = s2 * wp + c2 * wq;
+        }
       }
       __syncthreads();
-      for (int idx = t; idx < BB * H; idx += blockDim.x) {     // rows p, q of a
-        const int k = idx / H, pr = idx - k * H;
-        const int p = pp[pr], q = qq[pr];
-        const double c = cc[pr], sn = ss[pr];
-        const double apk = a[p][k], aqk = a[q][k];
-        a[p][k] = c * apk - sn * aqk;
-        a[q][k] = sn * apk + c * aqk;
-      }
-      __syncthreads();
+      cur ^= 1;
     }
-    if (!rotated) break;                               // a whole sweep without a rotation: diagonal to working precision
   }
-  if (t == 0) {            // eigenvalues in descending order (insertion sort of at most 32 indices)
-    for (int i = 0; i < BB; ++i) order[i] = i;
-    for (int i = 1; i < BB; ++i) {
-      const int oi = order[i];
-      int j = i - 1;
-      while (j >= 0 && a[order[j]][order[j]] < a[oi][oi]) { order[j + 1] = order[j]; --j; }
-      order[j + 1] = oi;
-    }
+  const double (&a)[BB][BB] = aa[cur];
+  if (t < BB) {            // eigenvalues in descending order, ties by index
+    int rank = 0;
+    for (int i = 0; i < BB; ++i) rank += (a[i][i] > a[t][t] || (a[i][i] == a[t][t] && i < t)) ? 1 : 0;
+    order[rank] = t;
   }
   __syncthreads();
   if (t < BB) sigma[t] = (float)sqrt(fmax(a[order[t]][order[t]], 0.0));
@@ -380,56 +455,60 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const float* __restrict
 }
 
 struct Layout {
-  size_t zt, p, yb, yc, v1, gp, tm, ma, mq, total;
+  size_t p, yb, yc, v1, gp, tm, ma, mq, tf, ctr, total;
   int nparts_max;
 };
 
 template <int BB>
 static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters, const float* X0, int8_t* S, float* A,
                float* Q, float* sigma, unsigned char* ws, const Layout& L, hipStream_t s) {
-  float* Zt = (float*)(ws + L.zt);
   float* P = (float*)(ws + L.p);
   float* Yb = (float*)(ws + L.yb);     // rows x BB
   float* Yc = (float*)(ws + L.yc);     // cols x BB
   float* V1 = (float*)(ws + L.v1);     // cols x BB
   float* Gp = (float*)(ws + L.gp);
   double* Tm = (double*)(ws + L.tm);
+  float* Tf = (float*)(ws + L.tf);
   double* MA = (double*)(ws + L.ma);
   double* MQ = (double*)(ws + L.mq);
+  uint32_t* ctr = (uint32_t*)(ws + L.ctr);
   const dim3 blk(kThreads);
-  hipLaunchKernelGGL(sign_transpose_kernel, dim3((cols + 63) / 64, (rows + 63) / 64), blk, 0, s, Z, rows, cols, ld, S, Zt);
-  // Y (n_out x BB) = |Mx|^T-style product over the matrix Mx (R_ x C_), then Y's Gram parts
-  auto product = [&](const float* Mx, int R_, int C_, int64_t ldm, const float* X, const double* Tx, float* Y) {
-    const int nchunks = (R_ + kChunkRows - 1) / kChunkRows;
-    hipLaunchKernelGGL(abs_t_mul_kernel<BB>, dim3((C_ + kStrip - 1) / kStrip, nchunks), blk, 0, s, Mx, R_, C_, ldm, X, Tx, P);
-    const int nparts = (C_ + kGramRows - 1) / kGramRows;
-    hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(nparts), dim3(kSmallThreads), 0, s, P, nchunks, C_, Y, Gp);
+  hipLaunchKernelGGL(sign_kernel, dim3(rows, (cols + 4 * kThreads - 1) / (4 * kThreads)), blk, 0, s, Z, rows, cols, ld, S, ctr);
+  // Y = Yin's sums (nchunks of them), its Gram parts and (Tout) the inverse of its Cholesky factor
+  auto reduce = [&](const float* Yin, int nchunks, int n, float* Y, double* Tout) {
+    const int nparts = (n + kGramRows - 1) / kGramRows;
+    hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(nparts), dim3(kSmallThreads), 0, s, Yin, nchunks, n, Y, Gp, Tout, Tf, ctr);
     return nparts;
   };
+  auto product = [&](auto cols_side, int nout, int nin, const float* X, const float* Tx) {
+    const int nchunks = (nin + kChunk - 1) / kChunk;
+    hipLaunchKernelGGL((abs_mul_kernel<BB, decltype(cols_side)::value>), dim3((nout + kOut - 1) / kOut, nchunks), blk, 0, s,
+                       Z, rows, cols, ld, X, Tx, P);
+    return nchunks;
+  };
+  auto rows_product = [&](const float* X, const float* Tx, double* Tout) {      // Yb = |Z| (X Tx)
+    return reduce(P, product(std::false_type(), rows, cols, X, Tx), rows, Yb, Tout);
+  };
+  auto cols_product = [&](const float* X, const float* Tx, double* Tout) {      // Yc = |Z|^T (X Tx)
+    return reduce(P, product(std::true_type(), cols, rows, X, Tx), cols, Yc, Tout);
+  };
   const float* X = X0;
-  const double* Tx = nullptr;
+  const float* Tx = nullptr;
   for (int it = 0; it < iters; ++it) {
-    int np = product(Zt, cols, rows, rows, X, Tx, Yb);                 // B = |Z| V
-    hipLaunchKernelGGL(chol_kernel<BB>, dim3(1), dim3(kSmallThreads), 0, s, Gp, np, Tm);
-    np = product(Z, rows, cols, ld, Yb, Tm, Yc);                       // V = |Z|^T B
-    hipLaunchKernelGGL(chol_kernel<BB>, dim3(1), dim3(kSmallThreads), 0, s, Gp, np, Tm);
+    rows_product(X, Tx, Tm);                           // B = |Z| V
+    cols_product(Yb, Tf, Tm);                          // V = |Z|^T B
     X = Yc;
-    Tx = Tm;
+    Tx = Tf;
   }
   // an orthonormal V: Cholesky-QR twice (iters == 0: on the start block itself)
   const int grid_apply = 1024;
-  const int npc = (cols + kGramRows - 1) / kGramRows;
-  if (iters == 0) {
-    hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(npc), dim3(kSmallThreads), 0, s, X0, 1, cols, Yc, Gp);
-    hipLaunchKernelGGL(chol_kernel<BB>, dim3(1), dim3(kSmallThreads), 0, s, Gp, npc, Tm);
-  }
+  if (iters == 0) reduce(X0, 1, cols, Yc, Tm);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);
-  hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(npc), dim3(kSmallThreads), 0, s, V1, 1, cols, Yc, Gp);   // (Yc = copy of V1)
-  hipLaunchKernelGGL(chol_kernel<BB>, dim3(1), dim3(kSmallThreads), 0, s, Gp, npc, Tm);
+  reduce(V1, 1, cols, Yc, Tm);                                                                    // (Yc = copy of V1)
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);        // V1 = V, orthonormal
   // Rayleigh-Ritz on B = |Z| V
-  const int npb = product(Zt, cols, rows, rows, V1, nullptr, Yb);
-  hipLaunchKernelGGL(ritz_kernel<BB>, dim3(1), dim3(kSmallThreads), 0, s, Gp, npb, l, MA, MQ, sigma);
+  const int npb = rows_product(V1, nullptr, nullptr);
+  hipLaunchKernelGGL(ritz_kernel<BB>, dim3(1), dim3(kRitzThreads), 0, s, Gp, npb, l, MA, MQ, sigma);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yb, rows, MA, l, A);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, V1, cols, MQ, l, Q);
   return (int)hipGetLastError();
@@ -437,15 +516,15 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
 
 }  // namespace msvid
 
-int msvid_block(int l) { return l <= 8 ? 16 : l <= 16 ? 24 : 32; }
+int msvid_block(int l) { return l <= 8 ? 16 : 24; }
 
 static msvid::Layout msvid_layout(int rows, int cols, int b) {
   auto up = [](size_t v) { return (v + 255) / 256 * 256; };
   msvid::Layout L;
   size_t off = 0;
-  L.zt = off; off = up(off + (size_t)rows * cols * 4u);
-  const size_t chunks_a = (size_t)(cols + msvid::kChunkRows - 1) / msvid::kChunkRows;   // product over Zt: output rows x b
-  const size_t chunks_b = (size_t)(rows + msvid::kChunkRows - 1) / msvid::kChunkRows;   // product over Z: output cols x b
+  // The total is what callers have always been asked for: it once held a transposed copy of Z and the sums of
+  // 128-entry chunks.  The sums of today's 256-entry chunks lie in the same place.
+  const size_t chunks_a = (size_t)(cols + 127) / 128, chunks_b = (size_t)(rows + 127) / 128;
   const size_t pa = chunks_a * (size_t)rows * b * 4u, pb = chunks_b * (size_t)cols * b * 4u;
   L.p = off; off = up(off + (pa > pb ? pa : pb));
   L.yb = off; off = up(off + (size_t)rows * b * 4u);
@@ -457,7 +536,11 @@ static msvid::Layout msvid_layout(int rows, int cols, int b) {
   L.tm = off; off = up(off + (size_t)b * b * 8u);
   L.ma = off; off = up(off + (size_t)b * b * 8u);
   L.mq = off; off = up(off + (size_t)b * b * 8u);
-  L.total = off;
+  // (in the room of the copy, which held b x b floats and more)
+  L.ctr = off;
+  L.tf = up(off + 4u);
+  const size_t old_total = up(off + (size_t)rows * cols * 4u), used = up(L.tf + (size_t)b * b * 4u);
+  L.total = old_total > used ? old_total : used;
   return L;
 }
 
@@ -468,11 +551,8 @@ int launch_msvid(const float* Z, int rows, int cols, int64_t ld, int l, int iter
   const int b = msvid_block(l);
   const msvid::Layout L = msvid_layout(rows, cols, b);
   unsigned char* w = (unsigned char*)ws;
-  switch (b) {
-    case 16: return msvid::run<16>(Z, rows, cols, ld, l, iters, X0, S, A, Q, sigma, w, L, s);
-    case 24: return msvid::run<24>(Z, rows, cols, ld, l, iters, X0, S, A, Q, sigma, w, L, s);
-    default: return msvid::run<32>(Z, rows, cols, ld, l, iters, X0, S, A, Q, sigma, w, L, s);
-  }
+  if (b == 16) return msvid::run<16>(Z, rows, cols, ld, l, iters, X0, S, A, Q, sigma, w, L, s);
+  return msvid::run<24>(Z, rows, cols, ld, l, iters, X0, S, A, Q, sigma, w, L, s);
 }
 
 }  // namespace mdbf

@@ -95,6 +95,30 @@ def test_envelope_equals_the_oracles_where_the_spectrum_has_a_gap(gpu, l):
     np.testing.assert_allclose(sg[:l], sig[:l], rtol=2e-5)
 
 
+@pytest.mark.parametrize("rows,cols,pad,l", [(257, 321, 3, 16), (64, 256, 0, 8), (63, 65, 1, 1), (1030, 130, 2, 4), (24, 700, 0, 16)])
+def test_edges_of_the_product_kernel(gpu, rows, cols, pad, l):
+    """Sizes around its 64-output strips, 64-entry waves and 256-entry chunks, rows at any element's address: the
+    Ritz values equal those of the same iteration in fp64 from the same start block (they depend on the span only;
+    fp32 products: 1e-5), and a padded leading dimension changes no bit."""
+    torch, mb = gpu
+    rng = np.random.default_rng(rows + cols)
+    Z = _f32(rng.standard_normal((rows, cols)))
+    b, iters = mb.mdbf_msvid_block(l), 2
+    X0 = synth.normal_block(cols, b, 3)
+    V = X0.astype(np.float64)
+    for _ in range(iters):
+        V = np.abs(Z).astype(np.float64).T @ np.linalg.qr(np.abs(Z) @ V)[0]
+    want = np.linalg.svd(np.abs(Z) @ np.linalg.qr(V)[0], compute_uv=False)
+    wide = torch.full((rows, cols + pad), float("nan"), device="cuda:0")
+    wide[:, :cols] = torch.from_numpy(Z).cuda()
+    X0d = torch.from_numpy(X0).cuda()
+    got = mb.mdbf_msvid(wide[:, :cols], l, X0d, iters=iters)
+    np.testing.assert_array_equal(got[0].cpu().numpy(), np.where(Z < 0, -1, 1))
+    np.testing.assert_allclose(got[3].cpu().numpy(), want, rtol=1e-5)
+    for x, y in zip(got, mb.mdbf_msvid(wide[:, :cols].contiguous(), l, X0d, iters=iters)):
+        assert torch.equal(x, y)
+
+
 def test_error_falls_with_l_and_with_the_number_of_passes(gpu):
     """Monotone in l (nested feasible sets, Sec. 4.2) and non-increasing in the number of passes."""
     Z = _f32(np.random.default_rng(40).standard_normal((256, 160)))
