@@ -128,8 +128,32 @@ SplitLayout few_layout(const mdbf_desc_t* d, int T) {
     if (L.g[i].nsplit > 1) L.bytes = std::max(L.bytes, (size_t)L.g[i].nsplit * (size_t)T * (size_t)L.ld[i] * 4u);
   return L;
 }
+// A long call whose shapes or types the many-token kernel would load element by element works on fp16 copies of its
+// operands (what it rounds them to anyway) behind the plan-style workspace: X (T x n8), then A, G, Q, B with `modes`
+// columns, n8 and k8 = n and k rounded up to eight.
+struct HalfLayout {
+  int n8, k8, modes;
+  size_t x, a, g, q, b, bytes;
+};
+bool wants_half(const mdbf_desc_t* d, int T) {
+  return T > kFewMaxTokens && !(d->flags & MDBF_FLAG_PRECISE) && !(vector_shape(d) && d->x_dtype == MDBF_F16);
+}
+HalfLayout half_layout(const mdbf_desc_t* d, int T) {
+  HalfLayout L;
+  L.n8 = (d->n + 7) & ~7;
+  L.k8 = (d->k + 7) & ~7;
+  L.modes = d->l <= 8 ? 8 : 16;
+  const size_t row = (size_t)L.modes * 2u;
+  L.x = 0;
+  L.a = align_up((size_t)T * (size_t)L.n8 * 2u, 256);
+  L.g = L.a + align_up((size_t)d->m * row, 256);
+  L.q = L.g + align_up((size_t)d->k * row, 256);
+  L.b = L.q + align_up((size_t)L.k8 * row, 256);
+  L.bytes = L.b + align_up((size_t)L.n8 * row, 256);
+  return L;
+}
 size_t layer_ws_bytes(const mdbf_desc_t* d, int T) {
-  return plan_layer_ws_bytes(d, T) + (wants_split(d, T) ? split_layout(d).bytes : wants_few(d, T) ? few_layout(d, T).bytes : 0);
+  return plan_layer_ws_bytes(d, T) + (wants_split(d, T) ? split_layout(d).bytes : wants_few(d, T) ? few_layout(d, T).bytes : wants_half(d, T) ? half_layout(d, T).bytes : 0);
 }
 // the least a call is accepted with
 size_t least_ws_bytes(const mdbf_desc_t* d, int T) {
@@ -318,6 +342,32 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
     for (int i = 0; i < 2; ++i)
       both_gemm = both_gemm && !((desc->flags & MDBF_FLAG_BLOCK_SCALED) && use_mx(sp[i], desc->flags));
     if (both_gemm) half_intermediate(sp);
+  }
+  if (wants_half(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
+    const HalfLayout L = half_layout(desc, T);
+    unsigned char* base = (unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T);
+    const int l = desc->l, et = desc->env_dtype;
+    const HalfMatrix copies[6] = {
+        {X_dev, ldx, T, desc->n, desc->x_dtype, base + L.x, L.n8, T, L.n8},
+        {env->A_dev, l, desc->m, l, et, base + L.a, L.modes, desc->m, L.modes},
+        {env->G_dev, l, desc->k, l, et, base + L.g, L.modes, desc->k, L.modes},
+        {env->Q_dev, l, desc->k, l, et, base + L.q, L.modes, L.k8, L.modes},
+        {env->B_dev, l, desc->n, l, et, base + L.b, L.modes, L.n8, L.modes},
+        // the last columns of z: those past k meet zero envelope rows and have to be finite (the first factor's
+        // launch writes those below k afterwards)
+        {nullptr, 0, 0, 0, MDBF_F16, (uint16_t*)workspace_dev + (L.k8 - 8), L.k8, T, 8}};
+    int e = launch_half_copies(copies, 6, s);
+    sp[0].vin = base + L.x;
+    sp[0].vin_ld = sp[0].K = L.n8;
+    sp[0].Eout = base + L.g;
+    sp[0].Ein = base + L.b;
+    sp[1].K = L.k8;
+    sp[1].Eout = base + L.a;
+    sp[1].Ein = base + L.q;
+    sp[0].vin_dt = sp[0].env_dt = sp[1].env_dt = MDBF_F16;
+    sp[0].l = sp[1].l = L.modes;
+    for (int i = 0; i < 2 && !e; ++i) e = launch_stage_gemm(nullptr, 0, 0, &sp[i], s);
+    return hip_fail(e);
   }
   if (wants_few(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
     const SplitLayout L = few_layout(desc, T);

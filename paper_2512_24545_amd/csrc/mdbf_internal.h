@@ -222,6 +222,18 @@ constexpr int kFewMaxTokens = 64;
 SplitGeom few_geom(int ntiles, int KB, int T, bool vectors);
 int launch_stage_gemm_few(const StageProb* p, const SplitGeom& g, float* part, int64_t part_ld, hipStream_t s);
 
+// Copies in fp16 with padded rows (one launch, at most six): dst (rows x dst_cols, dst_ld apart; both multiples of
+// eight) receives src (src_rows x cols of type dt, ld apart) and zeros in the rest; src null: zeros only.
+struct HalfMatrix {
+  const void* src;
+  int64_t ld;
+  int32_t src_rows, cols, dt;
+  void* dst;
+  int64_t dst_ld;
+  int32_t rows, dst_cols;
+};
+int launch_half_copies(const HalfMatrix* m, int count, hipStream_t s);
+
 // MSVID_l (sign mask + truncated SVD of |Z| by block subspace iteration), csrc/mdbf_msvid.hip
 int msvid_block(int l);                                  // columns of the iteration's block: l plus oversampling
 size_t msvid_ws_bytes(int rows, int cols, int l);

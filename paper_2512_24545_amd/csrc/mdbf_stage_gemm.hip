@@ -35,7 +35,6 @@ constexpr int kDies = 8;                    // accelerator dies (XCDs); workgrou
 constexpr int kEinBufBytes = 128 * 32;      // 128 columns x 16 modes fp16
 // LDS of a workgroup with TB slabs of 16 tokens: two buffers of (16 TB tokens x 128 columns fp16) + envelope rows
 __host__ __device__ constexpr int vin_buf_bytes(int TB) { return 16 * TB * 256; }
-__host__ __device__ constexpr int smem_bytes(int TB) { return 2 * (vin_buf_bytes(TB) + kEinBufBytes); }
 // waves per SIMD the register budget is cut for: the small shapes live on occupancy (their blocks are short
 // dependent chains), the big one on registers
 __host__ __device__ constexpr int min_waves(int TB) { return TB >= 4 ? 2 : (TB == 2 ? 3 : 4); }
@@ -99,6 +98,28 @@ __device__ __forceinline__ u32x4 load8_vec(const void* p, int64_t idx0) {
   return u32x4{pack_half2(a.x, a.y), pack_half2(a.z, a.w), pack_half2(b.x, b.y), pack_half2(b.z, b.w)};
 }
 
+// Four consecutive modes of an envelope row (zeros past the rank), any type, rounded to fp16: the four loads go out
+// together.  (One by one, each behind a test and its own wait, they were up to eight trips to memory in front of
+// every workgroup's loop.)
+__device__ __forceinline__ half4 load4_modes(const StageProb& p, const void* env, int row, int mode0) {
+  const int64_t base = (int64_t)row * p.l;
+  float v[4];
+  if (p.env_dt == MDBF_F32) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) v[t] = ((const MDBF_GLOBAL float*)env)[base + min(mode0 + t, p.l - 1)];
+  } else {
+    uint32_t b[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) b[t] = ((const MDBF_GLOBAL uint16_t*)env)[base + min(mode0 + t, p.l - 1)];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      v[t] = p.env_dt == MDBF_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)b[t]) : __builtin_bit_cast(float, b[t] << 16);
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = mode0 + t < p.l ? v[t] : 0.f;
+  return half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+}
+
 // R row tiles per wave, TB slabs of 16 tokens per workgroup.  MODE 0..2: the common case -- fp16 envelopes of
 // rank 16 or 8, activations of type MODE with 16-byte aligned rows and K a multiple of 8: every load is a full
 // vector, issued without a branch (addresses are clamped, values past the end replaced by zero).  MODE 3:
@@ -109,7 +130,16 @@ constexpr int kPlanR = 2;   // row tiles per wave in a plan's work items
 template <int R, int TB, int MODE, bool BATCH>
 __global__ __launch_bounds__(64 * kWaves, min_waves(TB))
 void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  // Two buffers each, as objects of their own and chosen at compile time (the loop is written out twice).  With one
+  // array and a run-time offset no LDS read could move across the direct-to-LDS loads of the next block: they were
+  // all issued first, and the first read then waited for them to land, in every block.  Now the reads of a block
+  // go ahead and the loads follow between its products (2048 tokens on 4096 x 4096, k = 2656: 139 -> 124 us; 40
+  // tokens: 61 -> 42 us).
+  constexpr int kVinBufBytes = vin_buf_bytes(TB);
+  __shared__ __attribute__((aligned(1024))) unsigned char vin_a[kVinBufBytes];   // [16*TB tokens][16 chunks of 16 B], swizzled
+  __shared__ __attribute__((aligned(1024))) unsigned char vin_b[kVinBufBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char ein_a[kEinBufBytes];   // [128 columns][16 modes]
+  __shared__ __attribute__((aligned(1024))) unsigned char ein_b[kEinBufBytes];
   // the rows of this workgroup: a work item of a plan (at most kWaves * R row tiles of one problem), or
   // the blockIdx.x-th run of kWaves * R tiles of the single problem
   StageProb p;
@@ -135,9 +165,6 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     item_tile0 = (unit - slab_group * row_groups) * (kWaves * R);
     item_end = min(item_tile0 + kWaves * R, p.ntiles);
   }
-  unsigned char* vin_buf = smem;                               // [2][16*TB tokens][16 chunks of 16 B], swizzled
-  constexpr int kVinBufBytes = vin_buf_bytes(TB);
-  unsigned char* ein_buf = smem + 2 * kVinBufBytes;            // [2][128 columns][16 modes]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
@@ -150,14 +177,8 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   half4 eo_op[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int row = (tile0 + r) * kTileRows + r16;
-    float v[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int mode = 4 * g + t;
-      v[t] = (row < p.rows && mode < p.l) ? load_as_float(p.Eout, (int64_t)row * p.l + mode, p.env_dt) : 0.f;
-    }
-    eo_op[r] = half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+    const int row = min((tile0 + r) * kTileRows + r16, p.rows - 1);      // (rows past the end are not stored)
+    eo_op[r] = load4_modes(p, p.Eout, row, 4 * g);
   }
   // sign words: tiles past the end read the last tile (their rows are never stored)
   const MDBF_GLOBAL uint32_t* sbase[R];
@@ -184,8 +205,9 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   constexpr int kVinChunks = (16 * TB * 16) / (64 * kWaves);   // 16-byte chunks per thread: TB
   u32x4 vin_reg[kDma ? 1 : kVinChunks];
   u32x4 ein_reg;
+  bool ein_ok = true;
   uint32_t sw_next[R];
-  auto dma_block = [&](int q, int buf) {
+  auto dma_block = [&](int q, unsigned char* vin_buf) {
 #pragma unroll
     for (int i = 0; i < kVinChunks; ++i) {
       const int id = tid + 64 * kWaves * i;
@@ -193,11 +215,11 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
       const int col = min(q * kBlockCols + c * 8, p.K - 8);
       const int b = min(tok0 + tok, p.T - 1);
       const MDBF_GLOBAL _Float16* src = (const MDBF_GLOBAL _Float16*)p.vin + ((int64_t)b * p.vin_ld + col);
-      unsigned char* dst = vin_buf + buf * kVinBufBytes + (wave * 64 + 64 * kWaves * i) * 16;   // wave-uniform
+      unsigned char* dst = vin_buf + (wave * 64 + 64 * kWaves * i) * 16;   // wave-uniform
       __builtin_amdgcn_global_load_lds((const MDBF_GLOBAL void*)src, (MDBF_LDS void*)dst, 16, 0, 0);
     }
   };
-  auto fetch_block = [&](int q) {
+  auto fetch_block = [&](int q) __attribute__((always_inline)) {
     if (!kDma) {
 #pragma unroll
       for (int i = 0; i < kVinChunks; ++i) {
@@ -220,9 +242,9 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
       // rank 8: a row is one 16-byte vector; the half that would hold modes 8..15 becomes zero
       const int hl = p.l >> 3;
       const bool has_modes = (tid & 1) < hl;
-      const u32x4 v = ((const MDBF_GLOBAL u32x4*)p.Ein)[(size_t)min(col, p.K - 1) * hl + (has_modes ? (tid & 1) : 0)];
-      const bool ok = (col < p.K) && has_modes;
-      ein_reg = u32x4{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+      ein_reg = ((const MDBF_GLOBAL u32x4*)p.Ein)[(size_t)min(col, p.K - 1) * hl + (has_modes ? (tid & 1) : 0)];
+      ein_ok = (col < p.K) && has_modes;               // (the zeros go in when the row is parked: a select here
+                                                       //  would make the wave wait for the load here)
     } else {
       const int colr = tid >> 1, half = tid & 1;
       const int col = q * kBlockCols + colr;
@@ -237,17 +259,18 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 #pragma unroll
     for (int r = 0; r < R; ++r) sw_next[r] = sbase[r][(size_t)min(q, KB - 1) * sstride[r]];
   };
-  auto stash_block = [&](int buf) {
+  auto stash_block = [&](unsigned char* vin_buf, unsigned char* ein_buf) __attribute__((always_inline)) {
     if (!kDma) {
 #pragma unroll
       for (int i = 0; i < kVinChunks; ++i) {
         const int id = tid + 64 * kWaves * i;
         const int tok = id >> 4, c = id & 15;
-        *reinterpret_cast<u32x4*>(vin_buf + buf * kVinBufBytes + tok * 256 + ((c ^ (tok & 15)) << 4)) = vin_reg[i];
+        *reinterpret_cast<u32x4*>(vin_buf + tok * 256 + ((c ^ (tok & 15)) << 4)) = vin_reg[i];
       }
     }
-    *reinterpret_cast<u32x4*>(ein_buf + buf * kEinBufBytes + ein_row(tid >> 1) * 32 +
-                              (((tid & 1) ^ ((tid >> 5) & 1)) << 4)) = ein_reg;
+    *reinterpret_cast<u32x4*>(ein_buf + ein_row(tid >> 1) * 32 +
+                              (((tid & 1) ^ ((tid >> 5) & 1)) << 4)) =
+        u32x4{ein_ok ? ein_reg.x : 0u, ein_ok ? ein_reg.y : 0u, ein_ok ? ein_reg.z : 0u, ein_ok ? ein_reg.w : 0u};
   };
 
   // Register staging runs two blocks ahead (a block is requested at the end of one iteration and parked at
@@ -255,28 +278,25 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   // barrier that opens iteration q, into the buffer iteration q - 1 has just released, and every wave waits
   // for its own requests before it reaches the next barrier.
   uint32_t sw[R];
-  if (kDma) dma_block(0, 0);
+  if (kDma) dma_block(0, vin_a);
   fetch_block(0);
-  stash_block(0);
+  stash_block(vin_a, ein_a);
 #pragma unroll
   for (int r = 0; r < R; ++r) sw[r] = sw_next[r];
   if (kDma) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   else fetch_block(min(1, KB - 1));
 
-#pragma unroll 1
-  for (int q = 0; q < KB; ++q) {
-    const int cur = q & 1;
+  auto block = [&](int q, const unsigned char* vin, const unsigned char* ein, unsigned char* vin_next,
+                   unsigned char* ein_next) __attribute__((always_inline)) {
     __syncthreads();
     if (kDma) {
-      dma_block(min(q + 1, KB - 1), cur ^ 1);
+      dma_block(min(q + 1, KB - 1), vin_next);
       fetch_block(min(q + 1, KB - 1));
     }
 
     // ---- per contraction step f (32 columns): rebuild the wave's pieces of W, wop[r] = B operand of the
     //      token product, then run the step over all token slabs.  The steps are independent of each other,
     //      which lets the rebuild of one step overlap the matrix-core work of the previous one.
-    const unsigned char* ein = ein_buf + cur * kEinBufBytes;
-    const unsigned char* vin = vin_buf + cur * kVinBufBytes;
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
       // A operands of the two reconstruction products: rows mi -> columns 32f + 8(mi/4) + mi%4 (+4)
@@ -317,11 +337,16 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 
     // park the next block's register-staged parts and (register staging) request the one after
     // (past the end the last block is requested again: no branch around the loads)
-    stash_block(cur ^ 1);
+    stash_block(vin_next, ein_next);
 #pragma unroll
     for (int r = 0; r < R; ++r) sw[r] = sw_next[r];
     if (kDma) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else fetch_block(min(q + 2, KB - 1));
+  };
+#pragma unroll 1
+  for (int q = 0; q < KB; q += 2) {
+    block(q, vin_a, ein_a, vin_b, ein_b);
+    if (q + 1 < KB) block(q + 1, vin_b, ein_b, vin_a, ein_a);
   }
 
   // ---- store: lane (r16, g) holds out[token 16 tb + 4g + i][row r16 of tile r]
@@ -371,14 +396,7 @@ void stage_gemm_split_kernel(StageProb p) {
   size_t sstride[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int row = (tile0 + r) * kTileRows + r16;
-    float v[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int mode = 4 * g + t;
-      v[t] = (row < p.rows && mode < p.l) ? load_as_float(p.Eout, (int64_t)row * p.l + mode, p.env_dt) : 0.f;
-    }
-    eo_op[r] = half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+    eo_op[r] = load4_modes(p, p.Eout, min((tile0 + r) * kTileRows + r16, p.rows - 1), 4 * g);
     const int t = min(tile0 + r, p.ntiles - 1);               // a tile past the end repeats the last (never stored)
     sbase[r] = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(t, KB) + lane;
     sstride[r] = (size_t)group_tiles(t, p.ntiles) * 64u;
@@ -683,18 +701,7 @@ void stage_gemm_few_kernel(FewArgs a) {
 
   fetch(0);
   // Eout row of this lane's tile row, 4 modes per lane (B operand of the reconstruction)
-  half4 eo_op;
-  {
-    const int row = min(tile_c * kTileRows + r16, p.rows - 1);
-    float v[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int mode = 4 * g + t;
-      v[t] = load_as_float(p.Eout, (int64_t)row * p.l + min(mode, p.l - 1), p.env_dt);
-      if (mode >= p.l) v[t] = 0.f;
-    }
-    eo_op = half4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
-  }
+  const half4 eo_op = load4_modes(p, p.Eout, min(tile_c * kTileRows + r16, p.rows - 1), 4 * g);
   if (!EVEC) {                                                  // the modes past the rank stay zero
     const u32x4 zero = {0u, 0u, 0u, 0u};
     for (int i = tid; i < 2 * CK * kEinBufBytes / 16; i += kFewThreads) reinterpret_cast<u32x4*>(ein_buf)[i] = zero;
@@ -814,12 +821,6 @@ static int launch_few_m(const FewArgs& a, hipStream_t s) {
 // p->T = the longest token count among the problems.
 template <int R, int TB, int MODE, bool BATCH>
 static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
-  static KernelSetup setup;
-  if (int e = kernel_setup(setup, [] {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&stage_gemm_kernel<R, TB, MODE, BATCH>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes(TB));
-      }))
-    return e;
   const int rows_per_wg = kWaves * R;   // tiles
   unsigned gx = BATCH ? (unsigned)nitems : (unsigned)((p->ntiles + rows_per_wg - 1) / rows_per_wg);
   unsigned gy = (unsigned)((p->T + 16 * TB - 1) / (16 * TB));
@@ -828,7 +829,7 @@ static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p
     gx = kDies * ((total + kDies - 1) / kDies);
     gy = 1;
   }
-  hipLaunchKernelGGL((stage_gemm_kernel<R, TB, MODE, BATCH>), dim3(gx, gy), dim3(64 * kWaves), smem_bytes(TB), s,
+  hipLaunchKernelGGL((stage_gemm_kernel<R, TB, MODE, BATCH>), dim3(gx, gy), dim3(64 * kWaves), 0, s,
                      items_dev, *p);
   return (int)hipGetLastError();
 }
@@ -853,22 +854,93 @@ static int launch_rt(const WorkItem* items_dev, int nitems, int mode, const Stag
   return launch_rtm<R, TB, MDBF_F32>(items_dev, nitems, p, s);
 }
 
+// ---------------------------------------------------------------------------------------------------
+// Operands of a long call whose rows or types the vector-load mode cannot take as they are: copies in fp16, rows
+// of the activations padded with zeros to a multiple of eight columns, envelope rows to 8 or 16 modes (rows past the
+// end: zeros).  The values are the ones the element-wise mode rounds to on every load, so the results are the same
+// bits; what it cost was one element per load and its conversion again in every workgroup.  5000 x 3001, k = 2003,
+// l = 3, 2048 tokens in fp32: 444 -> 149 us per call.
+// One launch for up to six copies; a thread makes eight consecutive elements of one.
+// ---------------------------------------------------------------------------------------------------
+struct HalfCopy {
+  const void* src;             // src_rows x cols of type dt, rows ld apart; null: only zeros are written
+  void* dst;                   // rows x dst_cols fp16, dst_ld apart (multiples of eight)
+  int64_t ld, dst_ld, first;   // first: index of the copy's first thread
+  int32_t src_rows, cols, dst_cols, dt;
+};
+struct HalfCopies {
+  HalfCopy c[6];
+  int64_t threads;
+};
+__global__ __launch_bounds__(256) void half_copy_kernel(HalfCopies a) {
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= a.threads) return;
+  int k = 0;
+#pragma unroll
+  for (int i = 1; i < 6; ++i) k = t >= a.c[i].first ? i : k;
+  HalfCopy c = a.c[0];
+#pragma unroll
+  for (int i = 1; i < 6; ++i)
+    if (i == k) c = a.c[i];
+  const int64_t v = t - c.first;
+  const int per = c.dst_cols >> 3;
+  const int64_t row = v / per;
+  const int col = (int)(v - row * per) * 8;
+  const int nvalid = c.src && row < c.src_rows ? c.cols - col : 0;
+  u32x4 out = {0u, 0u, 0u, 0u};
+  if (nvalid >= 8) {                                            // (vector loads of any alignment)
+    const MDBF_GLOBAL unsigned char* p = (const MDBF_GLOBAL unsigned char*)c.src + (row * c.ld + col) * dtype_size(c.dt);
+    const u32x4 r0 = *(const MDBF_GLOBAL u32x4_any*)p;
+    if (c.dt == MDBF_F16) {
+      out = r0;
+    } else if (c.dt == MDBF_BF16) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t w = r0[i];
+        out[i] = pack_half2(__builtin_bit_cast(float, w << 16), __builtin_bit_cast(float, w & 0xFFFF0000u));
+      }
+    } else {
+      const floatx4 f0 = __builtin_bit_cast(floatx4, r0);
+      const u32x4 r1 = *(const MDBF_GLOBAL u32x4_any*)(p + 16);
+      const floatx4 f1 = __builtin_bit_cast(floatx4, r1);
+      out = u32x4{pack_half2(f0.x, f0.y), pack_half2(f0.z, f0.w), pack_half2(f1.x, f1.y), pack_half2(f1.z, f1.w)};
+    }
+  } else if (nvalid > 0) {
+    out = load8_as_half(c.src, row * c.ld + col, nvalid, c.dt);
+  }
+  *(MDBF_GLOBAL u32x4*)((MDBF_GLOBAL uint16_t*)c.dst + row * c.dst_ld + col) = out;
+}
+
 }  // namespace gemm
 
-// Token slabs per workgroup for a long single problem (two row tiles per wave).  A workgroup's cost per
-// column block is a fixed part (rebuilding its piece of the factor) plus a part per slab; the launch takes as
-// long as the busiest compute unit, which holds ceil(workgroups / units) of them.  Fewer slabs per workgroup
-// make more, lighter workgroups: worth it when that evens out the last round (166 row tiles x 2048 tokens:
-// 336 workgroups of 8 slabs leave most units with one workgroup and some with two; 462 of 6 slabs fill them).
-static int long_problem_slabs(const StageProb& p) {
+// Row tiles per wave and token slabs per workgroup for a single problem of more than 32 tokens.  A column block takes
+// a workgroup that has a compute unit to itself about 600 + 110 TB ns with two tiles per wave (rebuilding its piece
+// of the factor, then the slabs), 800 and 700 ns with one tile and four or two slabs (mostly the wait for the next
+// block's activations); every further workgroup on the unit adds two thirds of that.  Fewer slabs make more,
+// lighter workgroups: worth it when that evens out the last round (166 row tiles x 2048 tokens: 336 workgroups of 8
+// slabs leave most units with one workgroup and some with two; 462 of 6 slabs fill them) or fills the device at all
+// (300 tokens on 4096 x 4096, k = 2656: 63 workgroups of 2 x 8 take 79 us, 210 of 1 x 4 61 us).  Each output is
+// the same sum in the same order whatever the choice.  The element-wise mode has the two-tile forms only.
+struct LongShape {
+  int R, TB;
+};
+static LongShape long_problem_shape(const StageProb& p, bool vectors) {
+  static const struct {
+    LongShape shape;
+    int ns;
+  } forms[] = {{{2, 8}, 1480}, {{2, 7}, 1370}, {{2, 6}, 1260}, {{1, 4}, 800}, {{1, 2}, 700}};
   const int cus = compute_units();
-  const int row_groups = (p.ntiles + 2 * gemm::kWaves - 1) / (2 * gemm::kWaves);
-  int best = 8;
-  double best_cost = 0.0;
-  for (int tb = 8; tb >= 6; --tb) {
-    const int64_t wgs = (int64_t)row_groups * ((p.T + 16 * tb - 1) / (16 * tb));
-    const double cost = (double)((wgs + cus - 1) / cus) * (4.8 + tb);   // fixed part ~ 4.8 slabs' worth
-    if (tb == 8 || cost < best_cost) { best = tb; best_cost = cost; }
+  LongShape best = {2, 8};
+  double least = -1.0;
+  for (const auto& f : forms) {
+    if (f.shape.R == 1 && !vectors) continue;
+    const int tiles = f.shape.R * gemm::kWaves;
+    const int64_t wgs = (int64_t)((p.ntiles + tiles - 1) / tiles) * ((p.T + 16 * f.shape.TB - 1) / (16 * f.shape.TB));
+    const double cost = f.ns * (1.0 + (double)((wgs + cus - 1) / cus - 1) * (2.0 / 3.0));
+    if (least < 0.0 || cost < least) {
+      least = cost;
+      best = f.shape;
+    }
   }
   return best;
 }
@@ -878,6 +950,28 @@ int gemm_load_mode(const StageProb& p) {
   const bool fast = p.env_dt == MDBF_F16 && (p.l == 16 || p.l == 8) && (p.K & 7) == 0 && p.K >= 8 &&
                     (((uintptr_t)p.vin | (uintptr_t)p.Ein) & 15u) == 0 && ((p.vin_ld * es) & 15) == 0;
   return fast ? p.vin_dt : gemm::kGeneric;
+}
+
+int launch_half_copies(const HalfMatrix* m, int count, hipStream_t s) {
+  gemm::HalfCopies a;
+  a.threads = 0;
+  for (int i = 0; i < 6; ++i) {
+    gemm::HalfCopy& c = a.c[i];
+    c = gemm::HalfCopy{nullptr, nullptr, 0, 0, INT64_MAX, 0, 0, 8, MDBF_F16};
+    if (i >= count) continue;
+    c.src = m[i].src;
+    c.dst = m[i].dst;
+    c.ld = m[i].ld;
+    c.dst_ld = m[i].dst_ld;
+    c.first = a.threads;
+    c.src_rows = m[i].src_rows;
+    c.cols = m[i].cols;
+    c.dst_cols = m[i].dst_cols;
+    c.dt = m[i].dt;
+    a.threads += (int64_t)m[i].rows * (m[i].dst_cols / 8);
+  }
+  hipLaunchKernelGGL(gemm::half_copy_kernel, dim3((unsigned)((a.threads + 255) / 256)), dim3(256), 0, s, a);
+  return (int)hipGetLastError();
 }
 
 int gemm_tiles_per_item() { return gemm::kWaves * gemm::kPlanR; }
@@ -890,17 +984,16 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const Sta
     return gemm::launch_rt<gemm::kPlanR, 1>(items_dev, nitems, mode, p, s);
   }
   mode = gemm_load_mode(*p);
-  if (p->T > 64) {
-    switch (long_problem_slabs(*p)) {
-      case 6: return gemm::launch_rt<2, 6>(nullptr, 0, mode, p, s);
-      case 7: return gemm::launch_rt<2, 7>(nullptr, 0, mode, p, s);
-      default: return gemm::launch_rt<2, 8>(nullptr, 0, mode, p, s);
-    }
+  const bool vectors = mode != gemm::kGeneric;
+  if (p->T > kFewMaxTokens || (p->T > 32 && vectors)) {
+    const LongShape f = long_problem_shape(*p, vectors);
+    if (f.R == 1 && f.TB == 2) return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
+    if (f.R == 1) return gemm::launch_rt<1, 4>(nullptr, 0, mode, p, s);
+    if (f.TB == 6) return gemm::launch_rt<2, 6>(nullptr, 0, mode, p, s);
+    if (f.TB == 7) return gemm::launch_rt<2, 7>(nullptr, 0, mode, p, s);
+    return gemm::launch_rt<2, 8>(nullptr, 0, mode, p, s);
   }
-  if (p->T > 16 && mode != gemm::kGeneric) {
-    if (p->T > 32) return gemm::launch_rt<1, 4>(nullptr, 0, mode, p, s);
-    return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
-  }
+  if (p->T > 16 && vectors) return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
   const SplitGeom one = {p->KB, 1, 0};                          // (no room for partial sums)
   return launch_stage_gemm_few(p, one, nullptr, 0, s);
 }

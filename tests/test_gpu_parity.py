@@ -344,6 +344,30 @@ def test_few_token_calls(gpu, m, n, k, l, T, env_dtype, x_dtype, pad):
         assert orc.max_rel_error(run.cpu().numpy(), got.cpu().numpy().astype(np.float64)) <= 2.0 ** -11
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype,pad", [
+    (530, 1032, 1000, 16, "f16", "f16", 8), (2064, 520, 1160, 8, "f16", "bf16", 1), (300, 649, 515, 3, "bf16", "bf16", 0),
+    (130, 1025, 2049, 16, "f32", "f32", 3), (17, 5, 9, 1, "f32", "f16", 1)])
+def test_a_token_of_a_long_call_does_not_depend_on_its_length(gpu, m, n, k, l, env_dtype, x_dtype, pad):
+    """From 65 tokens on every token is the same sum in the same order, whatever tile shape the call's length
+    picks and whether the operands are loaded as they are or copied to fp16 first (without room for the copies:
+    element by element): the same bits.  The longest call against the oracle at the fp16 gate."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 2100, seed=29 + m, x_dtype=x_dtype)
+    dl = mb.DeviceLayer.from_host(L)
+    wide = torch.full((2100, n + pad), float("nan"), dtype=_to_dev(torch, X[:1], x_dtype).dtype, device="cuda:0")
+    wide[:, :n] = _to_dev(torch, X, x_dtype)
+    Xd = wide[:, :n]
+    full = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    rows = list(range(0, 2100, 171))
+    assert orc.max_rel_error(full[rows].cpu().numpy(), orc.forward_factored(*_oracle_args(L), X[rows])) <= TOL
+    for T in (65, 97, 128, 300, 777, 1500):
+        assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32"), full[:T]), T
+    ws = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32", precise=True), 777), dtype=torch.uint8, device="cuda:0")
+    assert torch.equal(mb.mdbf_forward(dl, Xd[:777], y_dtype="f32", workspace=ws), full[:777])
+    assert torch.equal(mb.mdbf_forward(dl, Xd[:777], y_dtype="f32", Y=full[:777].clone(), accumulate=True), full[:777] * 2)
+
+
 ANY_RANK = [
     # m, n, k, l, env, x: edges of the 16-row tiles, of the 128-column blocks, of the 8-tile groups and of a split of
     # four blocks; the smallest and largest rank of both record forms
