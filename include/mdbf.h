@@ -258,6 +258,8 @@ int mdbf_stream_read(const void* src_dev, size_t bytes, uint32_t* sink_dev, int 
  *              are the singular values of A Q^T)
  *   workspace_dev  caller-owned, >= mdbf_msvid_workspace_bytes (a transposed copy of Z and the iteration's blocks)
  * Needs b <= min(rows, cols) (else MDBF_EUNSUPPORTED), 1 <= l <= MDBF_MAX_L, pointers 16-byte aligned.
+ * A Z with a NaN or an infinity in it has no projection: S is still its mask (a NaN counts as +1), the entries of A
+ * and Q are zeros or NaNs and those of sigma zeros or infinities, the same ones in every call.
  * Asynchronous on `stream`; no host synchronisation, no allocation; deterministic (fixed summation orders). */
 int mdbf_msvid_block(int l);
 int mdbf_msvid_workspace_bytes(int rows, int cols, int l, size_t* bytes_out);

@@ -412,8 +412,14 @@ __global__ __launch_bounds__(kRitzThreads) void ritz_kernel(const float* __restr
   }
   const double (&a)[BB][BB] = aa[cur];
   if (t < BB) {            // eigenvalues in descending order, ties by index
+    // (a NaN, from a NaN or infinity in Z, ranks below everything: `order` is a permutation whatever the entries are)
+    const double none = -__builtin_huge_val();
+    const double own = a[t][t] == a[t][t] ? a[t][t] : none;
     int rank = 0;
-    for (int i = 0; i < BB; ++i) rank += (a[i][i] > a[t][t] || (a[i][i] == a[t][t] && i < t)) ? 1 : 0;
+    for (int i = 0; i < BB; ++i) {
+      const double e = a[i][i] == a[i][i] ? a[i][i] : none;
+      rank += (e > own || (e == own && i < t)) ? 1 : 0;
+    }
     order[rank] = t;
   }
   __syncthreads();

@@ -119,6 +119,33 @@ def test_edges_of_the_product_kernel(gpu, rows, cols, pad, l):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+@pytest.mark.parametrize("l,iters", [(4, 0), (4, 2), (16, 0), (16, 3)])
+def test_non_finite_input_gives_the_same_defined_result_every_time(gpu, bad, l, iters):
+    """One NaN or infinity in Z spoils the whole Gram matrix: no eigenvalue compares with another, and the Ritz step
+    still has to order them.  The mask is right, nothing finite but zeros comes out, and a call whose workspace held
+    other bytes, after calls on other matrices, returns the same."""
+    torch, mb = gpu
+    rows, cols = 130, 77
+    good = torch.from_numpy(_f32(np.random.default_rng(l).standard_normal((rows, cols))).astype(np.float32)).cuda()
+    start = {k: torch.from_numpy(synth.normal_block(cols, mb.mdbf_msvid_block(k), 3)).cuda() for k in (4, 16)}
+    Z = good.clone()
+    Z[71, 40] = bad
+    got = []
+    for fill in (0, 255, 63):
+        ws = torch.full((8 << 20,), fill, dtype=torch.uint8, device="cuda:0")
+        got.append([x.cpu() for x in mb.mdbf_msvid(Z, l, start[l], iters=iters, workspace=ws)])
+        mb.mdbf_msvid(good, 20 - l, start[20 - l], iters=1)
+    S, A, Q, sg = got[0]
+    np.testing.assert_array_equal(S.numpy(), np.where(Z.cpu().numpy() < 0, -1, 1))
+    for E in (A, Q):
+        assert not (torch.isinf(E) | (torch.isfinite(E) & (E != 0))).any()
+    assert ((sg == 0) | torch.isinf(sg)).all()
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            np.testing.assert_array_equal(x.numpy(), y.numpy())         # (NaNs at the same places count as equal)
+
+
 def test_error_falls_with_l_and_with_the_number_of_passes(gpu):
     """Monotone in l (nested feasible sets, Sec. 4.2) and non-increasing in the number of passes."""
     Z = _f32(np.random.default_rng(40).standard_normal((256, 160)))
