@@ -180,11 +180,14 @@ __device__ __forceinline__ void record_store(unsigned char* base, int index, V v
 
 // A lane's 32 values of a block in operand order (val, divided by their nibble values; m = their largest
 // magnitude) -> block exponent, three fp6 limbs, the record's slots, scales and column sums at `blk`.
+// The limbs saturate.  An infinity or NaN among the first three registers' columns reaches the result through the
+// column sum; the fourth register's columns are not in it, so that their products with zero start it (without them
+// a quarter of the columns could hold one and every output stayed finite).
 // FOUR: a fourth limb, 2^-4 of the third's scale: rank 8 in the half of slot 1 that is zero otherwise, rank 16 at
 // `limb4` (its scale is byte 3 of the scale words).
 template <bool RANK8, bool TO_LDS, bool FOUR = false>
 __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, int lane, unsigned char* blk,
-                                               float part = 0.f, unsigned char* limb4 = nullptr) {
+                                               unsigned char* limb4 = nullptr) {
   constexpr bool rank8 = RANK8;   // the launch's rank: every problem of it has l = 8, or every one l = 16
   const int n = lane & 15;
   int E = -100;
@@ -218,8 +221,10 @@ __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, 
     l4 = fp6_encode32(r, sc4);
     b4 = fp6_decode32(l4, sc4);
   }
-  // quantised value = val - (last residual); back at the scale of xs, summed over the lane's columns (on top of
-  // what the caller starts the sum with: 0 or NaN)
+  // quantised value = val - (last residual); back at the scale of xs, summed over the lane's columns, from 0 or NaN
+  float part = 0.f;
+#pragma unroll
+  for (int j = 24; j < 32; ++j) part += val[j] * 0.f;
 #pragma unroll
   for (int j = 0; j < 32; ++j) {
     const float inv = (j < 8) ? 0.5f : (j < 16 ? 1.f : 2.f);
@@ -284,15 +289,8 @@ __device__ __forceinline__ void gather_quantise(float* pr, int l, int lane, unsi
     m = fmaxf(m, fabsf(val[j]));
   }
   wave_lds_sync();   // the next record's products may overwrite the buffer
-  // The limbs saturate.  An infinity or NaN among the first three registers' columns reaches the result through
-  // the column sum; the fourth register's columns are not in it.
-  float poison = 0.f;
-  if (ANY) {
-#pragma unroll
-    for (int j = 24; j < 32; ++j) poison += val[j] * 0.f;
-  }
   // (ANY: a fourth limb; of rank 16 it takes the place of the products, which have been read)
-  quantise_store<RANK8, TO_LDS, ANY>(val, m, lane, blk, poison, (unsigned char*)pr);
+  quantise_store<RANK8, TO_LDS, ANY>(val, m, lane, blk, (unsigned char*)pr);
 }
 
 // the record of block q of the problem's contraction dimension, from the inputs `in`, written to `blk`

@@ -404,6 +404,41 @@ def test_one_token_calls_of_any_rank_and_type(gpu, m, n, k, l, env_dtype, x_dtyp
             assert not torch.isfinite(mb.mdbf_forward(dl, Xb, y_dtype="f32")).any()
 
 
+@pytest.mark.parametrize("where", ["single", "forced", "plan"])
+@pytest.mark.parametrize("l,T", [(8, 1), (16, 1), (16, 3)])
+def test_non_finite_input_reaches_every_output_of_the_block_scaled_kernels(gpu, l, T, where):
+    """The fp6 limbs saturate, the column sums carry infinities and NaNs: a bad value in any column of a block (each of
+    the four operand registers of a lane holds other columns), in the input or in either factor's input-side envelope,
+    leaves no output of its token finite, and the other tokens' alone."""
+    torch, mb = gpu
+    m, n, k = 150, 300, 260
+    L = synth.make_layer(m, n, k, l, seed=l, env_dtype="f16", env_kind="llama", signed_env=True)
+    dl = mb.DeviceLayer.from_host(L)
+    X = torch.from_numpy(synth.make_activations(n, T, seed=7, x_dtype="f16")).half().cuda()
+    Y = torch.zeros((T, m), dtype=torch.float32, device="cuda:0")
+    plan = mb.BatchPlan([dl], [X], [Y], block_scaled=True)
+    assert plan.kernel(1) == plan.kernel(2) == "stage_mx_kernel"
+
+    def out():
+        if where == "plan":
+            plan.run()
+            return Y
+        return mb.mdbf_forward(dl, X, y_dtype="f32", block_scaled=where == "forced")
+    ref = out().clone()
+    assert torch.isfinite(ref).all()
+    for t, rows in ((X[T - 1], n), (dl.B[:, l - 1], n), (dl.Q[:, 0], k)):
+        for c in list(range(128)) + [rows - 1]:
+            for bad in (float("inf"), float("nan")):
+                keep = t[c].clone()
+                t[c] = bad
+                got = out()
+                assert not torch.isfinite(got[T - 1]).any(), (rows, c, bad)
+                if rows == n and t.data_ptr() == X[T - 1].data_ptr():
+                    assert torch.equal(got[:T - 1], ref[:T - 1])
+                t[c] = keep
+    assert torch.equal(out(), ref)
+
+
 # ---------------------------------------------------------------- many layers in one launch pair
 def _batch_case(gpu, specs, tokens=lambda i: 1 + (i % 2)):
     torch, mb = gpu
