@@ -200,7 +200,8 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   //      (kDma) go from global memory straight into LDS, 16 bytes per lane and 1 KB (four token rows) per
   //      instruction; the row swizzle is applied on the global side (a lane fetches the chunk that belongs at
   //      its LDS slot).  Other types are converted in registers on the way.  Values past the end: tokens past
-  //      T are never stored; columns past K meet zeroed envelope rows (kDma) or are zeroed themselves.
+  //      T are never stored; columns past K meet zeroed envelope rows and are zeroed themselves (an infinity in the
+  //      row's last columns, which a partial block's loads repeat, would turn into a NaN there).
   constexpr bool kDma = (MODE == MDBF_F16);
   constexpr int kVinChunks = (16 * TB * 16) / (64 * kWaves);   // 16-byte chunks per thread: TB
   u32x4 vin_reg[kDma ? 1 : kVinChunks];
@@ -217,6 +218,16 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
       const MDBF_GLOBAL _Float16* src = (const MDBF_GLOBAL _Float16*)p.vin + ((int64_t)b * p.vin_ld + col);
       unsigned char* dst = vin_buf + (wave * 64 + 64 * kWaves * i) * 16;   // wave-uniform
       __builtin_amdgcn_global_load_lds((const MDBF_GLOBAL void*)src, (MDBF_LDS void*)dst, 16, 0, 0);
+    }
+  };
+  // (kDma) zeros over the columns past K of a partial block: each thread over what it has loaded, once that landed
+  auto clear_tail = [&](int q, unsigned char* vin_buf) __attribute__((always_inline)) {
+    if ((q + 1) * kBlockCols <= p.K) return;                   // (uniform)
+#pragma unroll
+    for (int i = 0; i < kVinChunks; ++i) {
+      const int id = tid + 64 * kWaves * i;
+      const int c = (id & 15) ^ ((id >> 4) & 15);
+      if (q * kBlockCols + c * 8 >= p.K) *reinterpret_cast<u32x4*>(vin_buf + id * 16) = u32x4{0u, 0u, 0u, 0u};
     }
   };
   auto fetch_block = [&](int q) __attribute__((always_inline)) {
@@ -283,8 +294,12 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   stash_block(vin_a, ein_a);
 #pragma unroll
   for (int r = 0; r < R; ++r) sw[r] = sw_next[r];
-  if (kDma) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  else fetch_block(min(1, KB - 1));
+  if (kDma) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    clear_tail(0, vin_a);
+  } else {
+    fetch_block(min(1, KB - 1));
+  }
 
   auto block = [&](int q, const unsigned char* vin, const unsigned char* ein, unsigned char* vin_next,
                    unsigned char* ein_next) __attribute__((always_inline)) {
@@ -340,8 +355,12 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     stash_block(vin_next, ein_next);
 #pragma unroll
     for (int r = 0; r < R; ++r) sw[r] = sw_next[r];
-    if (kDma) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    else fetch_block(min(q + 2, KB - 1));
+    if (kDma) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      clear_tail(min(q + 1, KB - 1), vin_next);
+    } else {
+      fetch_block(min(q + 2, KB - 1));
+    }
   };
 #pragma unroll 1
   for (int q = 0; q < KB; q += 2) {

@@ -368,6 +368,30 @@ def test_a_token_of_a_long_call_does_not_depend_on_its_length(gpu, m, n, k, l, e
     assert torch.equal(mb.mdbf_forward(dl, Xd[:777], y_dtype="f32", Y=full[:777].clone(), accumulate=True), full[:777] * 2)
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", [
+    (90, 300, 203, 3, "bf16", "bf16"), (90, 256, 40, 16, "f16", "f32"), (17, 5, 9, 1, "f32", "f16"), (40, 130, 128, 8, "f32", "f32")])
+def test_overflows_of_a_long_call_do_not_depend_on_the_copies(gpu, m, n, k, l, env_dtype, x_dtype):
+    """One entry of the first token's z overflows fp16 (its row of G is 2^12 times the others): its outputs are
+    infinities with the fp16 copies as without room for them, element by element, and the other tokens are the same
+    bits.  Entries in the last, partial block and octet of z above all."""
+    torch, mb = gpu
+    T = 70
+    L = synth.make_layer(m, n, k, l, seed=m + k, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, T, seed=4, x_dtype=x_dtype)
+    for j in sorted({0, k // 2, k - 1, k - 2, max(0, k - 9)}):
+        H = dict(L, G=L["G"] * 2.0 ** -6)
+        H["G"][j] = L["G"][j] * 2.0 ** 6
+        z = H["G"][j] @ ((L["SB"][j][:, None] * L["B"]).T @ X[0])
+        Xj = X.copy()
+        Xj[0] *= 2.0 ** np.ceil(np.log2(4 * 65504 / abs(z)))
+        dl, Xd = mb.DeviceLayer.from_host(H), _to_dev(torch, Xj, x_dtype)
+        small = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32", precise=True), T), dtype=torch.uint8, device="cuda:0")
+        got = mb.mdbf_forward(dl, Xd, y_dtype="f32").cpu().numpy()
+        want = mb.mdbf_forward(dl, Xd, y_dtype="f32", workspace=small).cpu().numpy()
+        assert np.isinf(want[0]).all() and np.isfinite(want[1:]).all(), j
+        np.testing.assert_array_equal(got, want)
+
+
 ANY_RANK = [
     # m, n, k, l, env, x: edges of the 16-row tiles, of the 128-column blocks, of the 8-tile groups and of a split of
     # four blocks; the smallest and largest rank of both record forms
