@@ -145,7 +145,10 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * the last bits from what a plan returns for the same layer (another fixed order).  Two tokens or more: the factors
  * S_A o (A Q^T), S_B o (G B^T) are rebuilt piece by piece in fp16 and applied as dense products to the
  * fp16-rounded activations (x and z; z is stored in fp16 between the two products).  Magnitudes above
- * 65504 in those fp16 quantities overflow.
+ * 65504 in those fp16 quantities overflow.  A token's result is the same bits in every single call of 2 to 16 tokens
+ * with the same layer and types, in every one of 17 to 64 and in every one of 65 and more (of 17 and more with fp16
+ * envelopes of rank 8 or 16, n and k multiples of eight and 16-byte aligned rows of X); between these ranges it
+ * differs in the last bits.
  * Range: the one-token variants carry their own power-of-two exponents (the block-scaled one per 32 values,
  * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32: they hold their accuracy
  * wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope

@@ -1026,14 +1026,19 @@ SplitGeom few_geom(int ntiles, int KB, int T, bool vectors) {
   // Few row tiles or blocks: the kernel with one tile per workgroup needs no partial sums; 4 per iteration of
   // four blocks and 8 KB of staging per tile and block at 10 TB/s (1856 x 2848, k = 128, 11 tokens: 13.8 us
   // against 16.1 split).
-  const int64_t ck = gemm::few_chunk(T > 32 ? 4 : T > 16 ? 2 : 1);
+  // The partial sums are priced for 4 or 32 tokens whatever T is: one split for 2 to 16 tokens and one for 17 to 64,
+  // so that a token's result is the same bits in every call of such a range.  Against pricing them for T: 9920 x 640,
+  // k = 1790, l = 3, 16 tokens 21.1 -> 19.4 us; 9920 x 896, k = 1792, l = 16, 16 tokens 16.2 -> 16.6 us; 5000 x 3001,
+  // k = 2003, l = 3, 17 tokens 20.3 -> 19.8 us; 11008 x 11008, k = 8191, l = 3, 40 tokens 71.8 -> 69.0 us.
+  const int64_t tokens = T > 16 ? 32 : 4;
+  const int64_t ck = gemm::few_chunk(T > 16 ? 2 : 1);
   SplitGeom best = {KB, 1, (ntiles + gemm::kFewWaves - 1) / gemm::kFewWaves};
   int64_t least = -1;
   for (int64_t bs = ck;; bs += ck) {
     const int64_t nsplit = (KB + bs - 1) / bs, wgs = nsplit * best.ngroup;
     if (nsplit <= gemm::kFewSplits) {
       int64_t cost = (bs < KB ? bs / ck : (KB + ck - 1) / ck) * (wgs <= 256 ? 10 : 17 * ((wgs + 511) / 512));
-      if (nsplit > 1) cost += 22 + nsplit * T * ntiles * kTileRows * 8 / 1200000;
+      if (nsplit > 1) cost += 22 + nsplit * tokens * ntiles * kTileRows * 8 / 1200000;
       if (least < 0 || cost < least) {
         least = cost;
         best.bs = (int)(bs < KB ? bs : KB);

@@ -344,6 +344,21 @@ def test_few_token_calls(gpu, m, n, k, l, T, env_dtype, x_dtype, pad):
         assert orc.max_rel_error(run.cpu().numpy(), got.cpu().numpy().astype(np.float64)) <= 2.0 ** -11
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", [
+    (5000, 3001, 2003, 3, "bf16", "bf16"), (9920, 640, 1790, 3, "f16", "f16"), (9920, 896, 1792, 16, "f16", "f16")])
+def test_a_token_of_a_short_call_does_not_depend_on_its_length(gpu, m, n, k, l, env_dtype, x_dtype):
+    """The split of the contraction is one for 2 to 16 tokens and one for 17 to 64: the same bits in every call of a
+    range.  Shapes whose best split, priced by the token count, would change inside of one."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    dl = mb.DeviceLayer.from_host(L)
+    X = _to_dev(torch, synth.make_activations(n, 64, seed=5, x_dtype=x_dtype), x_dtype)
+    for lo, hi in ((2, 16), (17, 64)):
+        full = mb.mdbf_forward(dl, X[:hi], y_dtype="f32")
+        for T in sorted({lo, lo + 1, (lo + hi) // 2, 32, 33, hi - 1} & set(range(lo, hi))):
+            assert torch.equal(mb.mdbf_forward(dl, X[:T], y_dtype="f32"), full[:T]), T
+
+
 @pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype,pad", [
     (530, 1032, 1000, 16, "f16", "f16", 8), (2064, 520, 1160, 8, "f16", "bf16", 1), (300, 649, 515, 3, "bf16", "bf16", 0),
     (130, 1025, 2049, 16, "f32", "f32", 3), (17, 5, 9, 1, "f32", "f16", 1)])
