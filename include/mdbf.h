@@ -148,7 +148,8 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * 65504 in those fp16 quantities overflow.  A token's result is the same bits in every single call of 2 to 16 tokens
  * with the same layer and types, in every one of 17 to 64 and in every one of 65 and more (of 17 and more with fp16
  * envelopes of rank 8 or 16, n and k multiples of eight and 16-byte aligned rows of X); between these ranges it
- * differs in the last bits.
+ * differs in the last bits.  Plans of four tokens and more may return a NaN where a value beyond fp16 makes a single
+ * call return an infinity.
  * Range: the one-token variants carry their own power-of-two exponents (the block-scaled one per 32 values,
  * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32: they hold their accuracy
  * wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope

@@ -201,7 +201,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   //      instruction; the row swizzle is applied on the global side (a lane fetches the chunk that belongs at
   //      its LDS slot).  Other types are converted in registers on the way.  Values past the end: tokens past
   //      T are never stored; columns past K meet zeroed envelope rows and are zeroed themselves (an infinity in the
-  //      row's last columns, which a partial block's loads repeat, would turn into a NaN there).
+  //      row's last columns, which the direct loads of a partial block repeat, would turn into a NaN there).
   constexpr bool kDma = (MODE == MDBF_F16);
   constexpr int kVinChunks = (16 * TB * 16) / (64 * kWaves);   // 16-byte chunks per thread: TB
   u32x4 vin_reg[kDma ? 1 : kVinChunks];
@@ -220,9 +220,12 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
       __builtin_amdgcn_global_load_lds((const MDBF_GLOBAL void*)src, (MDBF_LDS void*)dst, 16, 0, 0);
     }
   };
-  // (kDma) zeros over the columns past K of a partial block: each thread over what it has loaded, once that landed
+  // (kDma) zeros over the columns past K of a partial block: each thread over what it has loaded, once that landed.
+  // (Plans do without: their short blocks would take 2 % longer, 50.2 -> 51.5 us for four layers and 8 tokens.  The
+  // last block outside the loop instead: 3 to 7 % longer; a zero address for its loads: 1 %.)
+  const int partial_block = !BATCH && (p.K & (kBlockCols - 1)) != 0 ? KB - 1 : -1;
   auto clear_tail = [&](int q, unsigned char* vin_buf) __attribute__((always_inline)) {
-    if ((q + 1) * kBlockCols <= p.K) return;                   // (uniform)
+    if (BATCH || __builtin_expect(q != partial_block, 1)) return;   // (uniform)
 #pragma unroll
     for (int i = 0; i < kVinChunks; ++i) {
       const int id = tid + 64 * kWaves * i;
