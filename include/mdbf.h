@@ -168,7 +168,9 @@ int mdbf_forward(const mdbf_desc_t* desc,
 
 /* mdbf_forward without a workspace argument, for callers that cannot allocate device memory at all (code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc) and therefore have no
- * workspace to pass.  Same arguments, kernels, arithmetic and results as mdbf_forward; the scratch memory
+ * workspace to pass.  Same arguments and arithmetic as mdbf_forward with a workspace of mdbf_workspace_bytes(),
+ * and the same results bit for bit (a call of 65 or more tokens whose fp16 copies do not fit loads its operands one by
+ * one instead: slower); the scratch memory
  * (the inner vector z and the scaled activations) lives in a static device array of
  * MDBF_STATIC_SCRATCH_BYTES inside the library, which every GPU the library runs on holds until the process
  * ends.  The call allocates and frees nothing.  A request for which the least workspace mdbf_forward takes exceeds

@@ -65,16 +65,10 @@ bool mx_worthwhile(long launch_tiles) {
 }
 size_t plan_layer_ws_bytes(const mdbf_desc_t* d, int T) { return z_bytes(d, T) + xs1_bytes(d, T) + xs2_bytes(d, T); }
 
-// A single call with one token splits the contraction of each factor across workgroups (split_geom); its
-// partial sums and the completion counters of the second factor lie behind the plan-style workspace.
-bool wants_split(const mdbf_desc_t* d, int T) {
-  return T == 1 && !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED));
-}
-// ... and does without them where the caller's workspace has no room (ranks and envelope types that the general
-// kernel serves too: a one-token call of those never needed more than z before it was split)
-bool must_split(const mdbf_desc_t* d, int T) {
-  return wants_split(d, T) && (d->l == 16 || d->l == 8) && d->env_dtype == MDBF_F16;
-}
+// mdbf_forward_static serves every call whose least workspace fits its scratch array, and returns what mdbf_forward
+// returns for it: where partial sums change the order of the additions, their number is chosen so that they fit too.
+constexpr size_t kStaticScratchBytes = MDBF_STATIC_SCRATCH_BYTES;
+
 struct SplitLayout {
   SplitGeom g[2];
   int64_t ld[2];                 // floats between the partial vectors of factor 1 / 2
@@ -92,8 +86,22 @@ SplitLayout split_layout(const mdbf_desc_t* d) {
   L.bytes = L.ctr_off + align_up((size_t)L.g[1].ngroup * 4u, 256);
   return L;
 }
+// A single call with one token splits the contraction of each factor across workgroups (split_geom); its
+// partial sums and the completion counters of the second factor lie behind the plan-style workspace.  Ranks and
+// envelope types that the general kernel serves too (a one-token call of those never needed more than z before it was
+// split) do without where the caller's workspace has no room, and where the sums would not fit the static scratch
+// (contractions of some 30000 entries and more on both factors).
+bool must_split(const mdbf_desc_t* d, int T) {
+  return T == 1 && !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED)) && (d->l == 16 || d->l == 8) &&
+         d->env_dtype == MDBF_F16;
+}
+bool wants_split(const mdbf_desc_t* d, int T) {
+  return T == 1 && !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED)) &&
+         (must_split(d, T) || plan_layer_ws_bytes(d, T) + split_layout(d).bytes <= kStaticScratchBytes);
+}
 // A single call with few tokens splits both contractions as well; the two factors' partial sums take turns in one
-// buffer (the first factor's are added up before the second one starts).  Up to 16 tokens always.  From 17 to
+// buffer (the first factor's are added up before the second one starts) right behind z, in the room of the scaled
+// activations, which these kernels do without.  Up to 16 tokens always.  From 17 to
 // kFewMaxTokens only where the many-token kernel would load its operands element by element (172 against 25 us
 // at 5000 x 3001, k = 2003, l = 3, 37 tokens); the shapes it loads as vectors keep one run over the contraction from
 // 17 tokens on: a token's result is the same bits in a call of 40 and of 2048 tokens.
@@ -118,10 +126,14 @@ bool wants_few(const mdbf_desc_t* d, int T) {
 }
 SplitLayout few_layout(const mdbf_desc_t* d, int T) {
   SplitLayout L;
-  L.g[0] = few_geom(num_tiles(d->k), num_blocks(d->n), T, vector_shape(d));
-  L.g[1] = few_geom(num_tiles(d->m), num_blocks(d->k), T, vector_shape(d));
   L.ld[0] = (int64_t)align_up((size_t)d->k, 64);
   L.ld[1] = (int64_t)align_up((size_t)d->m, 64);
+  // (the longest call of the range that shares the split has to fit the static scratch)
+  const int most = T > 16 ? kFewMaxTokens : 16;
+  const size_t z = z_bytes(d, most), room = z < kStaticScratchBytes ? kStaticScratchBytes - z : 0;
+  const size_t fit[2] = {room / ((size_t)most * (size_t)L.ld[0] * 4u), room / ((size_t)most * (size_t)L.ld[1] * 4u)};
+  L.g[0] = few_geom(num_tiles(d->k), num_blocks(d->n), T, vector_shape(d), fit[0]);
+  L.g[1] = few_geom(num_tiles(d->m), num_blocks(d->k), T, vector_shape(d), fit[1]);
   L.part_off[0] = L.part_off[1] = L.ctr_off = 0;
   L.bytes = 0;
   for (int i = 0; i < 2; ++i)
@@ -153,7 +165,10 @@ HalfLayout half_layout(const mdbf_desc_t* d, int T) {
   return L;
 }
 size_t layer_ws_bytes(const mdbf_desc_t* d, int T) {
-  return plan_layer_ws_bytes(d, T) + (wants_split(d, T) ? split_layout(d).bytes : wants_few(d, T) ? few_layout(d, T).bytes : wants_half(d, T) ? half_layout(d, T).bytes : 0);
+  const size_t least = plan_layer_ws_bytes(d, T);
+  if (wants_split(d, T)) return least + split_layout(d).bytes;
+  if (wants_few(d, T)) return std::max(least, z_bytes(d, T) + few_layout(d, T).bytes);
+  return least + (wants_half(d, T) ? half_layout(d, T).bytes : 0);
 }
 // the least a call is accepted with
 size_t least_ws_bytes(const mdbf_desc_t* d, int T) {
@@ -371,8 +386,7 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
   }
   if (wants_few(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
     const SplitLayout L = few_layout(desc, T);
-    unsigned char* base = (unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T);
-    float* part = (float*)(base + L.part_off[0]);
+    float* part = (float*)((unsigned char*)workspace_dev + z_bytes(desc, T));
     int e = launch_stage_gemm_few(&sp[0], L.g[0], part, L.ld[0], s);
     if (!e) e = launch_stage_gemm_few(&sp[1], L.g[1], part, L.ld[1], s);
     return hip_fail(e);
@@ -413,7 +427,6 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
 }  // extern "C"
 static __device__ __align__(256) unsigned char scratch[MDBF_STATIC_SCRATCH_BYTES];
 namespace {
-constexpr size_t kStaticScratchBytes = MDBF_STATIC_SCRATCH_BYTES;
 struct ScratchSlots {
   std::once_flag once[kMaxDevices];
   void* ptr[kMaxDevices];

@@ -218,8 +218,9 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const Sta
 // kernel does for one token, and the partial sums added by a second launch.  part: g.nsplit x T vectors part_ld
 // apart (unused when g.nsplit == 1: the result goes to p->out).
 constexpr int kFewMaxTokens = 64;
-// host arithmetic only; vectors: the shape qualifies for the vector-load modes (gemm_load_mode)
-SplitGeom few_geom(int ntiles, int KB, int T, bool vectors);
+// host arithmetic only; vectors: the shape qualifies for the vector-load modes (gemm_load_mode); max_splits: partial
+// sums per output there is room for
+SplitGeom few_geom(int ntiles, int KB, int T, bool vectors, size_t max_splits);
 int launch_stage_gemm_few(const StageProb* p, const SplitGeom& g, float* part, int64_t part_ld, hipStream_t s);
 
 // Copies in fp16 with padded rows (one launch, at most six): dst (rows x dst_cols, dst_ld apart; both multiples of

@@ -1020,7 +1020,7 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const Sta
   return launch_stage_gemm_few(p, one, nullptr, 0, s);
 }
 
-SplitGeom few_geom(int ntiles, int KB, int T, bool vectors) {
+SplitGeom few_geom(int ntiles, int KB, int T, bool vectors, size_t max_splits) {
   // Host arithmetic only (the workspace layout follows from it), for a device of 256 compute units that hold two
   // workgroups each.  In tenths of the time of a chunk, 0.3 us: a workgroup by itself on a unit takes 10 per
   // chunk, two that share one 17 each, further ones queue; partial sums cost 22 for their launch and 4 TB/s.  Measured
@@ -1039,7 +1039,7 @@ SplitGeom few_geom(int ntiles, int KB, int T, bool vectors) {
   int64_t least = -1;
   for (int64_t bs = ck;; bs += ck) {
     const int64_t nsplit = (KB + bs - 1) / bs, wgs = nsplit * best.ngroup;
-    if (nsplit <= gemm::kFewSplits) {
+    if (nsplit == 1 || (nsplit <= gemm::kFewSplits && (size_t)nsplit <= max_splits)) {
       int64_t cost = (bs < KB ? bs / ck : (KB + ck - 1) / ck) * (wgs <= 256 ? 10 : 17 * ((wgs + 511) / 512));
       if (nsplit > 1) cost += 22 + nsplit * tokens * ntiles * kTileRows * 8 / 1200000;
       if (least < 0 || cost < least) {

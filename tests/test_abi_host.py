@@ -109,6 +109,16 @@ def test_workspace_of_a_one_token_call_holds_its_partial_sums():
         assert mb.mdbf_workspace_bytes(d, 1) < mb.mdbf_workspace_bytes(split, 1)
 
 
+@pytest.mark.parametrize("env", [mb.MDBF_F16, mb.MDBF_BF16, mb.MDBF_F32])
+def test_workspace_of_the_layers_that_the_static_scratch_serves(env):
+    """Every layer up to 11008 x 11008 with k <= 8192 and 16 tokens: the partial sums of its fastest kernels fit the
+    16 MiB of the static scratch as well, so that both entry points run the same ones."""
+    for m, n, k in ((4096, 4096, 2656), (4096, 11008, 8192), (11008, 4096, 4096), (11008, 11008, 8192), (11001, 10999, 8191)):
+        for l in (1, 3, 8, 12, 16):
+            for T in range(1, 17):
+                assert mb.mdbf_workspace_bytes(mb.Desc(m, n, k, l, mb.MDBF_F16, env, mb.MDBF_F32, 0), T) <= 16 << 20, (m, n, k, l, T)
+
+
 def test_pack_argument_errors():
     L = mb.lib()
     assert L.mdbf_pack(None, 4, 4, 4, FAKE, 1 << 20, None) == -1

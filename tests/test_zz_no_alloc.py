@@ -55,6 +55,26 @@ def test_static_scratch_equals_workspace_call_twice_in_a_row(gpu):
         assert orc.max_rel_error(Y.cpu().numpy(), ref) <= TOL
 
 
+@pytest.mark.parametrize("m,n,k,l,T,dt", [
+    (11008, 11008, 8192, 16, 16, "f16"), (4096, 11008, 8192, 8, 16, "f16"), (11008, 11008, 8191, 3, 64, "bf16"),
+    (11008, 11008, 8191, 3, 17, "bf16"), (40960, 40960, 40960, 3, 1, "f32"), (4096, 11008, 4097, 3, 700, "bf16")])
+def test_static_scratch_equals_workspace_call_where_the_scratch_is_short(gpu, m, n, k, l, T, dt):
+    """Calls whose z and scaled activations fit the scratch array while unlimited partial sums or copies would not."""
+    torch, mb = gpu
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(m + k + T)
+    words = lambda rows, cols: torch.randint(-2 ** 31, 2 ** 31 - 1, (mb.mdbf_packed_bytes(rows, cols) // 4,), dtype=torch.int32,
+                                             generator=g, device="cuda:0").view(torch.uint8)
+    td = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dt]
+    env = [torch.randn((r, l), generator=g, device="cuda:0").to(td) * 0.03 for r in (m, k, k, n)]
+    dl = mb.DeviceLayer(m, n, k, l, words(m, k), words(k, n), *env)
+    X = torch.randn((T, n), generator=g, device="cuda:0").to(td)
+    want = mb.mdbf_forward(dl, X, y_dtype="f32")
+    Y = torch.full((T, m), float("nan"), dtype=torch.float32, device="cuda:0")
+    mb.mdbf_forward_static(dl, X, Y)
+    assert torch.isfinite(want).all() and torch.equal(Y, want)
+
+
 def test_static_scratch_rejects_what_does_not_fit(gpu):
     torch, mb = gpu
     L = synth.make_layer(64, 4096, 2656, 16, seed=3, env_dtype="f16", env_kind="llama")
