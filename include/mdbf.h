@@ -123,11 +123,12 @@ int mdbf_unpack(const void* packed_dev, int rows, int cols,
 int mdbf_pad_envelope(const void* env_dev, int rows, int l, int dtype, void* out_dev, int l_to, void* stream);
 
 /* ---- forward product ------------------------------------------------------------------
- * Workspace bytes needed by mdbf_forward for T tokens (room for the inner vector z in fp32, for the
- * scaled activations and for the partial sums of few-token calls).  Host arithmetic
- * only: the same value on every machine.  (mdbf_forward also takes less where it can do without the partial sums:
- * with one token if the rank is not 8 or 16 or the envelopes are not fp16, and with more tokens always.  Such a
- * call runs slower kernels; its results differ in the last bits.) */
+ * Workspace bytes needed by mdbf_forward for up to T tokens (room for the inner vector z in fp32, for the scaled
+ * activations, for the partial sums of few-token calls and for the fp16 copies of long ones).  Host arithmetic only: the
+ * same value on every machine, and never less for a larger T: a buffer of the longest call's size serves every
+ * shorter call with the same kernels and the same bits as one of its own.  (mdbf_forward also takes less where it can do
+ * without partial sums and copies: with one token if the rank is not 8 or 16 or the envelopes are not fp16, and
+ * with more tokens always.  Such a call runs slower kernels; up to 64 tokens its results differ in the last bits.) */
 int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
 
 /* Y[b,:] = What X[b,:] for b < T.

@@ -170,6 +170,14 @@ size_t layer_ws_bytes(const mdbf_desc_t* d, int T) {
   if (wants_few(d, T)) return std::max(least, z_bytes(d, T) + few_layout(d, T).bytes);
   return least + (wants_half(d, T) ? half_layout(d, T).bytes : 0);
 }
+// The size a caller is told: enough for every shorter call on the fastest kernels too (a buffer is sized for the longest
+// one).  What a call takes grows with its tokens except past 1, 16 and kFewMaxTokens, where other kernels begin.
+size_t full_ws_bytes(const mdbf_desc_t* d, int T) {
+  size_t most = layer_ws_bytes(d, T);
+  for (int last : {1, 16, kFewMaxTokens})
+    if (last < T) most = std::max(most, layer_ws_bytes(d, last));
+  return most;
+}
 // the least a call is accepted with
 size_t least_ws_bytes(const mdbf_desc_t* d, int T) {
   return plan_layer_ws_bytes(d, T) + (must_split(d, T) ? split_layout(d).bytes : 0);
@@ -323,7 +331,7 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out) {
   int st = check_desc(desc);
   if (st) return st;
   if (!bytes_out || T < 1) return MDBF_EINVAL;
-  *bytes_out = layer_ws_bytes(desc, T);
+  *bytes_out = full_ws_bytes(desc, T);
   return MDBF_OK;
 }
 

@@ -119,6 +119,16 @@ def test_workspace_of_the_layers_that_the_static_scratch_serves(env):
                 assert mb.mdbf_workspace_bytes(mb.Desc(m, n, k, l, mb.MDBF_F16, env, mb.MDBF_F32, 0), T) <= 16 << 20, (m, n, k, l, T)
 
 
+@pytest.mark.parametrize("flags", [0, mb.MDBF_FLAG_FP16_STAGED, mb.MDBF_FLAG_BLOCK_SCALED, mb.MDBF_FLAG_PRECISE])
+def test_workspace_never_shrinks_with_the_number_of_tokens(flags):
+    """A buffer sized for the longest call is enough for every shorter one, at the edges of the kernels' ranges too."""
+    for m, n, k in ((5000, 3001, 2003), (11008, 4096, 4096), (4096, 4096, 2656), (1, 1, 1), (300, 9000, 57), (40960, 40960, 40960)):
+        for l, x, env in ((3, mb.MDBF_BF16, mb.MDBF_BF16), (16, mb.MDBF_F16, mb.MDBF_F16), (8, mb.MDBF_F32, mb.MDBF_F16), (16, mb.MDBF_F32, mb.MDBF_F32)):
+            d = mb.Desc(m, n, k, l, x, env, mb.MDBF_F32, flags)
+            sizes = [mb.mdbf_workspace_bytes(d, T) for T in list(range(1, 131)) + [1000, 2048]]
+            assert sizes == sorted(sizes), (m, n, k, l, flags)
+
+
 def test_pack_argument_errors():
     L = mb.lib()
     assert L.mdbf_pack(None, 4, 4, 4, FAKE, 1 << 20, None) == -1

@@ -359,6 +359,20 @@ def test_a_token_of_a_short_call_does_not_depend_on_its_length(gpu, m, n, k, l, 
             assert torch.equal(mb.mdbf_forward(dl, X[:T], y_dtype="f32"), full[:T]), T
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", [
+    (5000, 3001, 2003, 3, "bf16", "bf16"), (2064, 1032, 2056, 16, "f16", "f16"), (300, 649, 1515, 12, "f32", "f32")])
+def test_a_longer_calls_workspace_serves_the_shorter_ones_alike(gpu, m, n, k, l, env_dtype, x_dtype):
+    """One buffer, sized for 130 tokens: every shorter call returns the bits it returns with a buffer of its own."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    dl = mb.DeviceLayer.from_host(L)
+    X = _to_dev(torch, synth.make_activations(n, 130, seed=5, x_dtype=x_dtype), x_dtype)
+    ws = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32"), 130), dtype=torch.uint8, device="cuda:0")
+    for T in (1, 2, 16, 17, 40, 64, 65, 128):
+        got = mb.mdbf_forward(dl, X[:T], y_dtype="f32", workspace=ws)
+        assert torch.equal(got, mb.mdbf_forward(dl, X[:T], y_dtype="f32")), T
+
+
 @pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype,pad", [
     (530, 1032, 1000, 16, "f16", "f16", 8), (2064, 520, 1160, 8, "f16", "bf16", 1), (300, 649, 515, 3, "bf16", "bf16", 0),
     (130, 1025, 2049, 16, "f32", "f32", 3), (17, 5, 9, 1, "f32", "f16", 1)])
