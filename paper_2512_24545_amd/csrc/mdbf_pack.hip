@@ -11,7 +11,8 @@ namespace mdbf {
 // and the whole 128-byte line over the four groups; a wave takes kPackBlocks consecutive blocks with all their
 // loads in flight, the four waves of a workgroup four consecutive tiles (1 KB of words per block).  Byte by
 // byte, 32 loads per word, packing 11008 x 4096 took 91 us and unpacking 82 us; now 14 and
-// 17 us (3.6 and 3.0 TB/s; a large copy reaches 5.1 TB/s).
+// 17 us (3.6 and 3.0 TB/s; a large copy reaches 5.1 TB/s).  (Sizes are compared as blocks or as differences: a column
+// index and a block's end may lie past the largest int.)
 constexpr int kPackBlocks = 4;
 
 typedef uint32_t Octet __attribute__((ext_vector_type(2), aligned(1)));   // eight consecutive signs of a row
@@ -36,7 +37,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ si
   const MDBF_GLOBAL int8_t* src = (const MDBF_GLOBAL int8_t*)signs + (int64_t)min(row, rows - 1) * ld;
   for (int q0 = blockIdx.y * kPackBlocks; q0 < KB; q0 += gridDim.y * kPackBlocks) {
     uint32_t w[kPackBlocks];
-    if ((q0 + kPackBlocks) * kBlockCols <= cols) {            // (uniform) whole blocks: no bounds to respect
+    if (q0 + kPackBlocks <= cols / kBlockCols) {              // (uniform) whole blocks: no bounds to respect
       Octet o[kPackBlocks][4];
 #pragma unroll
       for (int j = 0; j < kPackBlocks; ++j)
@@ -57,12 +58,12 @@ __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ si
         for (int f = 0; f < 4; ++f) {
           const int c0 = (q0 + j) * kBlockCols + f * 32 + kg * 8;
           uint32_t bits = 0;
-          if (c0 + 8 <= cols) {
+          if (c0 <= cols - 8) {
             const Octet o = *(const MDBF_GLOBAL Octet*)(src + c0);
             bits = gather4(o.x) | (gather4(o.y) << 2);
           } else {
             for (int e = 0; e < 8; ++e)
-              if (c0 + e < cols && src[c0 + e] < 0) bits |= 1u << ((e >> 1) + 16 * (e & 1));
+              if (e < cols - c0 && src[c0 + e] < 0) bits |= 1u << ((e >> 1) + 16 * (e & 1));
           }
           w[j] |= bits << (8 * (f >> 1) + 4 * (f & 1));
         }
@@ -97,11 +98,11 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint32_t* __restrict_
         Octet o;
         o.x = spread4(bits);
         o.y = spread4(bits >> 2);
-        if (c0 + 8 <= cols) {
+        if (c0 <= cols - 8) {
           *(MDBF_GLOBAL Octet*)(dst + c0) = o;
         } else {
           for (int e = 0; e < 8; ++e)
-            if (c0 + e < cols) dst[c0 + e] = (int8_t)((e < 4 ? o.x >> (8 * e) : o.y >> (8 * e - 32)) & 0xFFu);
+            if (e < cols - c0) dst[c0 + e] = (int8_t)((e < 4 ? o.x >> (8 * e) : o.y >> (8 * e - 32)) & 0xFFu);
         }
       }
     }

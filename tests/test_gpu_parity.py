@@ -101,6 +101,28 @@ def test_packed_words_are_where_the_layout_says(gpu, rows, cols, pad):
     np.testing.assert_array_equal(mb.mdbf_unpack(packed, rows, cols).cpu().numpy() < 0, neg)
 
 
+@pytest.mark.parametrize("cols", [2 ** 31 - 128, 2 ** 31 - 131])
+def test_pack_a_row_near_the_largest_int(gpu, cols):
+    """The last blocks of a row whose padded end is no int any more: what lies behind the row (negative bytes: bits
+    that would be set) is neither packed nor written."""
+    torch, mb = gpu
+    if torch.cuda.get_device_properties(0).total_memory < 32 << 30:
+        pytest.skip("needs four buffers of 2 GiB")
+    buf = torch.full((cols + 4096,), -1, dtype=torch.int8, device="cuda:0")
+    buf[:cols] = 1
+    where = torch.cat([torch.arange(0, cols, 9973, device="cuda:0"), torch.tensor([cols - 1, cols - 7, cols - 600], device="cuda:0")])
+    buf[where] = -1
+    packed = mb.mdbf_pack(buf[:cols].view(1, cols))
+    words = packed.view(torch.int32)
+    assert words.numel() == (2 ** 24 - 1) * 64
+    got = sum(int((words >> b & 1).sum()) for b in range(32))
+    assert got == torch.unique(where).numel()
+    back = torch.full_like(buf, -1)
+    L = mb.lib()
+    assert L.mdbf_unpack(packed.data_ptr(), 1, cols, back.data_ptr(), cols, torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(back, buf)
+
+
 # ---------------------------------------------------------------- forward: small and ragged
 SMALL = [
     # m, n, k, l, T
