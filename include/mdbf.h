@@ -263,7 +263,8 @@ int mdbf_stream_read(const void* src_dev, size_t bytes, uint32_t* sink_dev, int 
  *   S_dev      rows x cols int8 (+1 / -1), row-major, ld = cols: the input mdbf_pack takes
  *   A_dev, Q_dev   rows x l and cols x l fp32, row-major;  sigma_dev  b Ritz values (fp32, descending; the first l
  *              are the singular values of A Q^T)
- *   workspace_dev  caller-owned, >= mdbf_msvid_workspace_bytes (a transposed copy of Z and the iteration's blocks)
+ *   workspace_dev  caller-owned, >= mdbf_msvid_workspace_bytes (partial sums of the products and the iteration's blocks;
+ *              the size has room for a copy of Z too, which is not made any more)
  * Needs b <= min(rows, cols) (else MDBF_EUNSUPPORTED), 1 <= l <= MDBF_MAX_L, pointers 16-byte aligned.
  * A Z with a NaN or an infinity in it has no projection: S is still its mask (a NaN counts as +1), the entries of A
  * and Q are zeros or NaNs and those of sigma zeros or infinities, the same ones in every call.
