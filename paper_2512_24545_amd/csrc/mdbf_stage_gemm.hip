@@ -1028,7 +1028,8 @@ SplitGeom few_geom(int ntiles, int KB, int T, bool vectors, size_t max_splits) {
   // call; 32 blocks on 86 groups, 4 splits of 8 against 3 of 12 (258 workgroups), 24.7 and 27.3 us.
   // Few row tiles or blocks: the kernel with one tile per workgroup needs no partial sums; 4 per iteration of
   // four blocks and 8 KB of staging per tile and block at 10 TB/s (1856 x 2848, k = 128, 11 tokens: 13.8 us
-  // against 16.1 split).
+  // against 16.1 split).  Where both cost the same it has one launch less (24 x 4096, k = 24, 2 tokens: 14.3 against
+  // 14.5 to 16.2 split).
   // The partial sums are priced for 4 or 32 tokens whatever T is: one split for 2 to 16 tokens and one for 17 to 64,
   // so that a token's result is the same bits in every call of such a range.  Against pricing them for T: 9920 x 640,
   // k = 1790, l = 3, 16 tokens 21.1 -> 19.4 us; 9920 x 896, k = 1792, l = 16, 16 tokens 16.2 -> 16.6 us; 5000 x 3001,
@@ -1052,7 +1053,7 @@ SplitGeom few_geom(int ntiles, int KB, int T, bool vectors, size_t max_splits) {
   }
   if (vectors && T <= 16) {
     const int64_t rounds = ntiles > 512 ? 2 : 1;                // (two tiles per workgroup then)
-    if ((KB + 3) / 4 * 4 * rounds + (int64_t)ntiles * KB / 366 < least) best = SplitGeom{KB, 1, ntiles};
+    if ((KB + 3) / 4 * 4 * rounds + (int64_t)ntiles * KB / 366 <= least) best = SplitGeom{KB, 1, ntiles};
   }
   return best;
 }
