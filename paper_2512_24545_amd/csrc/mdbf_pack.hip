@@ -54,6 +54,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ si
 #pragma unroll
       for (int j = 0; j < kPackBlocks; ++j) {
         w[j] = 0;
+        if (q0 + j >= KB) continue;
 #pragma unroll 1
         for (int f = 0; f < 4; ++f) {
           const int c0 = (q0 + j) * kBlockCols + f * 32 + kg * 8;
@@ -91,6 +92,7 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint32_t* __restrict_
     if (row >= rows) return;
 #pragma unroll
     for (int j = 0; j < kPackBlocks; ++j) {
+      if (q0 + j >= KB) continue;
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
         const int c0 = (q0 + j) * kBlockCols + f * 32 + kg * 8;
