@@ -32,15 +32,17 @@ constexpr int kSmallThreads = 1024;   // the b x b kernels (a thread per matrix 
                                       // (few workgroups: many loads in flight in each)
 constexpr int kGramRows = 64;         // rows per workgroup of the reduce + Gram kernel
 
-// ---- S = sign(Z) as int8 (+1 / -1, sign(0) = +1: Sec. 2, Notation), four entries per thread; clears the counter
-// of reduce_gram_kernel's launches
-__global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
+// ---- S = sign(Z) as int8 (+1 / -1, sign(0) = +1: Sec. 2, Notation), four entries per thread, 2^sh threads per row
+// (a workgroup takes several rows of a narrow matrix: with one each 10^6 x 24 took 0.5 ms); clears the counter of
+// reduce_gram_kernel's launches
+__global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld, int sh,
                                                         int8_t* __restrict__ S, uint32_t* __restrict__ counter) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *counter = 0u;
-  const int c = (blockIdx.y * kThreads + threadIdx.x) * 4;
-  if (c >= cols) return;
-  const MDBF_GLOBAL float* z = (const MDBF_GLOBAL float*)Z + (int64_t)blockIdx.x * ld + c;
-  MDBF_GLOBAL int8_t* out = (MDBF_GLOBAL int8_t*)S + (int64_t)blockIdx.x * cols + c;
+  const int64_t row = (int64_t)blockIdx.x * (kThreads >> sh) + (threadIdx.x >> sh);
+  const int c = (int)((blockIdx.y << sh) + (threadIdx.x & ((1u << sh) - 1u))) * 4;
+  if (row >= rows || c >= cols) return;
+  const MDBF_GLOBAL float* z = (const MDBF_GLOBAL float*)Z + row * ld + c;
+  MDBF_GLOBAL int8_t* out = (MDBF_GLOBAL int8_t*)S + row * cols + c;
   if (c + 4 <= cols) {
     const floatx4 v = *(const MDBF_GLOBAL floatx4_any*)z;
     *(MDBF_GLOBAL u32_any*)out = (v.x < 0.f ? 0xFFu : 1u) | (v.y < 0.f ? 0xFF00u : 0x100u) |
@@ -479,7 +481,11 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
   double* MQ = (double*)(ws + L.mq);
   uint32_t* ctr = (uint32_t*)(ws + L.ctr);
   const dim3 blk(kThreads);
-  hipLaunchKernelGGL(sign_kernel, dim3(rows, (cols + 4 * kThreads - 1) / (4 * kThreads)), blk, 0, s, Z, rows, cols, ld, S, ctr);
+  int sh = 0;
+  while ((4 << sh) < cols && (1 << sh) < kThreads) ++sh;
+  const int rows_per_wg = kThreads >> sh;
+  hipLaunchKernelGGL(sign_kernel, dim3((rows + rows_per_wg - 1) / rows_per_wg, (cols + (4 << sh) - 1) / (4 << sh)), blk, 0, s,
+                     Z, rows, cols, ld, sh, S, ctr);
   // Y = Yin's sums (nchunks of them), its Gram parts and (Tout) the inverse of its Cholesky factor
   auto reduce = [&](const float* Yin, int nchunks, int n, float* Y, double* Tout) {
     const int nparts = (n + kGramRows - 1) / kGramRows;
