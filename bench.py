@@ -343,7 +343,8 @@ def main():
             return {"ms_per_call": ms, "tokens_per_s": T / ms * 1e3,
                     "dense_equivalent_TFLOPs": 2.0 * m * n * T / ms / 1e9,
                     "issued_TFLOPs": issued / ms / 1e9,
-                    "roofline": {"bound": "mfma", "kernel": "stage_gemm_kernel", "achieved": issued / ms / 1e9,
+                    "roofline": {"bound": "mfma", "kernel": "stage_gemm_few_kernel" if T <= 16 else "stage_gemm_kernel",
+                                 "achieved": issued / ms / 1e9,
                                  "peak": 2500.0, "unit": "TFLOP/s", "frac": issued / ms / 1e9 / 2500.0,
                                  "flops_per_call": issued}}
 

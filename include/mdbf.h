@@ -59,7 +59,7 @@ typedef enum { MDBF_F16 = 0, MDBF_BF16 = 1, MDBF_F32 = 2 } mdbf_dtype;
                                    "Residual Compensation", Eq. "dbf-residual-comp") are applied by one call each
                                    on the same Y; the additions happen in the precision of Y.  Two terms of
                                    one Y must not sit in the same plan: a plan's layers run in no defined order */
-#define MDBF_FLAG_BLOCK_SCALED 2u /* take the block-scaled matrix-core variant wherever it applies (l = 16, fp16
+#define MDBF_FLAG_BLOCK_SCALED 2u /* take the block-scaled matrix-core variant wherever it applies (l = 8 or 16, fp16
                                      envelopes, T <= 16), also for launches too small to fill the device with it;
                                      without the flag the library picks the variant by launch size */
 #define MDBF_FLAG_FP16_STAGED 8u  /* never take the block-scaled variant: the scaled activations are staged in fp16
@@ -118,7 +118,8 @@ int mdbf_unpack(const void* packed_dev, int rows, int cols,
  * receives env_dev (rows x l, row-major, elements of `dtype`) in its first l columns and zeros in the rest.
  * A layer whose four envelope factors are padded this way and whose descriptor says l_to denotes the same
  * What (paper Eq. "me-dbf-basis": the added modes are zero terms of the rank-l sums); ranks 8 and 16 with fp16
- * envelopes are the ones the matrix-core decode kernels serve, other ranks run the slower generic kernel.
+ * envelopes are the ones the decode kernels of plans serve, where other ranks run the slower generic kernel.  Single
+ * calls of any rank and type run matrix-core kernels, those of ranks 8 and 16 in fp16 the ones with vector loads.
  * l_to >= l, l_to <= MDBF_MAX_L; both pointers 16-byte aligned; the buffers must not overlap. */
 int mdbf_pad_envelope(const void* env_dev, int rows, int l, int dtype, void* out_dev, int l_to, void* stream);
 

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict_
 // its 64 rows of X' and contracts a 64 x 64 piece of Z in four rounds of 16 entries: four 16-byte loads per lane, a
 // round ahead, then 4 steps of v_mfma_f32_16x16x4_f32 (fp32 operands and sums) per 16 outputs and 16 columns of X'.
 // The four waves meet in LDS in wave order.
-// What bounds it: 9 us for one read of Z beside 5 us of matrix-core work and 9 us of launch, staging and partial
+// What bounds it: 9 us for one read of Z beside 6 us of matrix-core work and 9 us of launch, staging and partial
 // sums, which only partly overlap.  (All of a wave's sixteen loads in flight: no change; X as single elements in
 // operand order: 8 us more.)  Lanes that own columns and fused multiply-adds took 24 us per product of 4096 x 2656 and b = 24, and a transposed
 // copy of Z for |Z| X another 20 us per call; now 18 to 20 us.
