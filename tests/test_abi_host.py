@@ -96,8 +96,9 @@ def test_workspace_of_a_one_token_call_holds_its_partial_sums():
     """A single one-token call of rank 16 / fp16 envelopes splits each factor's contraction across workgroups:
     its workspace has room for the partial sums (4096x4096, k = 2656: 21 tile groups x 8 splits of the first
     factor, 32 x 7 of the second) and the second factor's completion counters, on top of what the same layer
-    needs with MDBF_FLAG_FP16_STAGED (no split).  Two tokens of this layer keep theirs in the room of the scaled
-    activations, the fp32 path has none, and fp32 envelopes have sums but no room for scaled activations."""
+    needs with MDBF_FLAG_FP16_STAGED (no split).  Other token counts and the fp32 path are not affected."""
+    # (two tokens of this layer keep their partial sums in the room of the scaled activations; fp32 envelopes with one
+    # token have partial sums too, but no room for scaled activations)
     split = mb.Desc(4096, 4096, 2656, 16, mb.MDBF_F16, mb.MDBF_F16, mb.MDBF_F32, 0)
     staged = mb.Desc(4096, 4096, 2656, 16, mb.MDBF_F16, mb.MDBF_F16, mb.MDBF_F32, mb.MDBF_FLAG_FP16_STAGED)
     extra = mb.mdbf_workspace_bytes(split, 1) - mb.mdbf_workspace_bytes(staged, 1)
