@@ -313,7 +313,7 @@ def main():
         e1.record()
         torch.cuda.synchronize()
         extras["hot_in_cache"] = {"GB/s": 64 * bytes_call * 100 / e0.elapsed_time(e1) / 1e6}
-        # (3) latency of one isolated call (two launches: each factor's contraction split across workgroups),
+        # (3) latency of one isolated call (two launches),
         #     stream-ordered
         e0.record()
         for _ in range(200):
@@ -458,7 +458,7 @@ def main():
             {"config": 2, "workload": "attn decode 4096x4096 k=2656 l=16 T=1, %d layers per plan" % a.copies,
              "kernel": plan.kernel(1), "ms_per_pass": ms_step, "roofline": hbm_roof(gbs),
              "max_rel_err_vs_oracle": max(err, err_last)},
-            {"config": 2, "workload": "the same layer, one mdbf_forward call (two launches)", "kernel": "stage_mx_split_kernel",
+            {"config": 2, "workload": "the same layer, one mdbf_forward call (two launches)", "kernel": "stage_one_kernel",
              "us_per_call": extras["single_call_stream"]["us_per_call"],
              "roofline": hbm_roof(bytes_call / extras["single_call_stream"]["us_per_call"] / 1e3)},
             {"config": 3, "workload": "MLP projections 11008x4096 / 4096x11008 k=4096 l=16 T=1, 96 layers per plan",

@@ -61,7 +61,8 @@ typedef enum { MDBF_F16 = 0, MDBF_BF16 = 1, MDBF_F32 = 2 } mdbf_dtype;
                                    one Y must not sit in the same plan: a plan's layers run in no defined order */
 #define MDBF_FLAG_BLOCK_SCALED 2u /* take the block-scaled matrix-core variant wherever it applies (l = 8 or 16, fp16
                                      envelopes, T <= 16), also for launches too small to fill the device with it;
-                                     without the flag the library picks the variant by launch size */
+                                     without the flag the library picks the variant by launch size.  (A single call
+                                     with one token runs its own kernel with the flag too) */
 #define MDBF_FLAG_FP16_STAGED 8u  /* never take the block-scaled variant: the scaled activations are staged in fp16
                                      (a plan takes the block-scaled variant only if none of its layers carries
                                      this flag); excludes MDBF_FLAG_BLOCK_SCALED (MDBF_EINVAL) */
@@ -137,14 +138,13 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  *   X_dev  T x n row-major, leading dimension ldx >= n (elements of x_dtype)
  *   Y_dev  T x m row-major, leading dimension ldy >= m (elements of y_dtype); overwritten
  *   workspace_dev / workspace_bytes  caller-owned scratch, >= mdbf_workspace_bytes()
- * Default arithmetic: fp32 accumulation on the matrix cores.  One token: z kept in fp32; the l-way
- * scaled activations (b^(s) o x and q^(t) o z) are quantised once -- to three fp6 limbs under a shared
- * power-of-two scale per 32 values (about 13 bits; the block-scaled variant, taken by single calls and large
- * plans of rank 8 or 16 with fp16 envelopes), to four such limbs (about 17 bits; single calls of other ranks and
- * envelope types), or to fp16 (small plans, MDBF_FLAG_FP16_STAGED) -- and contracted with the sign words.  A single one-token call of the block-scaled variant is two launches: each
- * factor's contraction is split across workgroups (a layer by itself cannot fill the device otherwise) and
- * the fp32 partial sums are added in a fixed order, so repeated calls return the same bits; they differ in
- * the last bits from what a plan returns for the same layer (another fixed order).  Two tokens or more: the factors
+ * Default arithmetic: fp32 accumulation on the matrix cores; z kept in fp32 with one token.  A single one-token call
+ * rebuilds the factors S_A o (A Q^T), S_B o (G B^T) piece by piece in fp32 and applies them to the unrounded activations
+ * in fp32, in two launches: what remains is the rounding of fp32 sums, added in a fixed order, so repeated calls return
+ * the same bits.  Plans with one to three tokens quantise the l-way scaled activations (b^(s) o x and q^(t) o z) once --
+ * to three fp6 limbs under a shared power-of-two scale per 32 values (about 13 bits; the block-scaled variant, taken by
+ * large plans of rank 8 or 16 with fp16 envelopes), or to fp16 (small plans, MDBF_FLAG_FP16_STAGED) -- and contract them
+ * with the sign words.  Two tokens or more: the factors
  * S_A o (A Q^T), S_B o (G B^T) are rebuilt piece by piece in fp16 and applied as dense products to the
  * fp16-rounded activations (x and z; z is stored in fp16 between the two products).  Magnitudes above
  * 65504 in those fp16 quantities overflow.  A token's result is the same bits in every single call of 2 to 16 tokens
@@ -152,9 +152,9 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * envelopes of rank 8 or 16, n and k multiples of eight and 16-byte aligned rows of X); between these ranges it
  * differs in the last bits.  Plans of four tokens and more may return a NaN where a value beyond fp16 makes a single
  * call return an infinity.
- * Range: the one-token variants carry their own power-of-two exponents (the block-scaled one per 32 values,
- * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32: they hold their accuracy
- * wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope
+ * Range: the one-token variants of plans carry their own power-of-two exponents (the block-scaled one per 32 values,
+ * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32; single one-token calls work in fp32
+ * throughout: they hold their accuracy wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope
  * types, and single calls of those with MDBF_FLAG_FP16_STAGED) stages
  * b^(s) o x and q^(t) o z in plain fp16, divided by up to 8: magnitudes below about 5e-4 lose accuracy.  The
  * many-token variant needs the entries of A Q^T and

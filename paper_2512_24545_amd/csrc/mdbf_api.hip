@@ -72,32 +72,31 @@ constexpr size_t kStaticScratchBytes = MDBF_STATIC_SCRATCH_BYTES;
 struct SplitLayout {
   SplitGeom g[2];
   int64_t ld[2];                 // floats between the partial vectors of factor 1 / 2
-  size_t part_off[2], ctr_off, bytes;   // offsets from the start of the split region
+  size_t bytes;
 };
-SplitLayout split_layout(const mdbf_desc_t* d) {
-  SplitLayout L;
-  L.g[0] = split_geom(num_tiles(d->k), num_blocks(d->n));
-  L.g[1] = split_geom(num_tiles(d->m), num_blocks(d->k));
-  L.ld[0] = (int64_t)align_up((size_t)d->k, 64);
-  L.ld[1] = (int64_t)align_up((size_t)d->m, 64);
-  L.part_off[0] = 0;
-  L.part_off[1] = align_up((size_t)L.g[0].nsplit * (size_t)L.ld[0] * 4u, 256);
-  L.ctr_off = L.part_off[1] + align_up((size_t)L.g[1].nsplit * (size_t)L.ld[1] * 4u, 256);
-  L.bytes = L.ctr_off + align_up((size_t)L.g[1].ngroup * 4u, 256);
-  return L;
+// Room that a one-token call is asked for behind the plan-style workspace: partial sums of up to eight runs of at most
+// four blocks (more where the contraction is longer) of both factors and a counter per eight row tiles of the second.
+// The first factor's partial sums (one_geom: at most kOneMaxSplits of them) take the front of it.  The size is the one
+// that callers have always been asked for.
+size_t one_room(const mdbf_desc_t* d) {
+  auto parts = [](int rows, int K) {
+    const int groups = (num_tiles(rows) + 7) / 8, KB = num_blocks(K);
+    const int want = (256 + groups - 1) / groups;
+    const int bs = std::min(4, std::max((KB + want - 1) / want, (KB + 7) / 8));
+    return align_up((size_t)((KB + bs - 1) / bs) * align_up((size_t)rows, 64) * 4u, 256);
+  };
+  return parts(d->k, d->n) + parts(d->m, d->k) + align_up((size_t)((num_tiles(d->m) + 7) / 8) * 4u, 256);
 }
-// A single call with one token splits the contraction of each factor across workgroups (split_geom); its
-// partial sums and the completion counters of the second factor lie behind the plan-style workspace.  Ranks and
-// envelope types that the general kernel serves too (a one-token call of those never needed more than z before it was
-// split) do without where the caller's workspace has no room, and where the sums would not fit the static scratch
-// (contractions of some 30000 entries and more on both factors).
-bool must_split(const mdbf_desc_t* d, int T) {
+// Single calls with one token run their own kernel where the workspace has that room.  Ranks and envelope types that the
+// general kernel serves too (a call of those once needed no more than z) do without where the caller's workspace has
+// none, and where it would not fit the static scratch (contractions of some 30000 entries and more on both factors).
+bool must_have_room(const mdbf_desc_t* d, int T) {
   return T == 1 && !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED)) && (d->l == 16 || d->l == 8) &&
          d->env_dtype == MDBF_F16;
 }
-bool wants_split(const mdbf_desc_t* d, int T) {
+bool wants_one(const mdbf_desc_t* d, int T) {
   return T == 1 && !(d->flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_FP16_STAGED)) &&
-         (must_split(d, T) || plan_layer_ws_bytes(d, T) + split_layout(d).bytes <= kStaticScratchBytes);
+         (must_have_room(d, T) || plan_layer_ws_bytes(d, T) + one_room(d) <= kStaticScratchBytes);
 }
 // A single call with few tokens splits both contractions as well; the two factors' partial sums take turns in one
 // buffer (the first factor's are added up before the second one starts) right behind z, in the room of the scaled
@@ -134,7 +133,6 @@ SplitLayout few_layout(const mdbf_desc_t* d, int T) {
   const size_t fit[2] = {room / ((size_t)most * (size_t)L.ld[0] * 4u), room / ((size_t)most * (size_t)L.ld[1] * 4u)};
   L.g[0] = few_geom(num_tiles(d->k), num_blocks(d->n), T, vector_shape(d), fit[0]);
   L.g[1] = few_geom(num_tiles(d->m), num_blocks(d->k), T, vector_shape(d), fit[1]);
-  L.part_off[0] = L.part_off[1] = L.ctr_off = 0;
   L.bytes = 0;
   for (int i = 0; i < 2; ++i)
     if (L.g[i].nsplit > 1) L.bytes = std::max(L.bytes, (size_t)L.g[i].nsplit * (size_t)T * (size_t)L.ld[i] * 4u);
@@ -166,7 +164,7 @@ HalfLayout half_layout(const mdbf_desc_t* d, int T) {
 }
 size_t layer_ws_bytes(const mdbf_desc_t* d, int T) {
   const size_t least = plan_layer_ws_bytes(d, T);
-  if (wants_split(d, T)) return least + split_layout(d).bytes;
+  if (wants_one(d, T)) return least + one_room(d);
   if (wants_few(d, T)) return std::max(least, z_bytes(d, T) + few_layout(d, T).bytes);
   return least + (wants_half(d, T) ? half_layout(d, T).bytes : 0);
 }
@@ -180,7 +178,7 @@ size_t full_ws_bytes(const mdbf_desc_t* d, int T) {
 }
 // the least a call is accepted with
 size_t least_ws_bytes(const mdbf_desc_t* d, int T) {
-  return plan_layer_ws_bytes(d, T) + (must_split(d, T) ? split_layout(d).bytes : 0);
+  return plan_layer_ws_bytes(d, T) + (must_have_room(d, T) ? one_room(d) : 0);
 }
 
 int check_layer(const mdbf_desc_t* d, const void* SA, const void* SB, const mdbf_env_t* env, const void* X,
@@ -346,18 +344,14 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
   StageProb sp[2];
   make_stages(desc, SA_packed_dev, SB_packed_dev, env, X_dev, ldx, Y_dev, ldy, T, workspace_dev, sp);
   hipStream_t s = (hipStream_t)stream;
-  if (wants_split(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
-    // two launches, no scale-in launch: the second factor's workgroups add up the first factor's partial sums
-    const SplitLayout L = split_layout(desc);
-    unsigned char* base = (unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T);
-    float* part1 = (float*)(base + L.part_off[0]);
-    float* part2 = (float*)(base + L.part_off[1]);
-    uint32_t* ctr = (uint32_t*)(base + L.ctr_off);
-    const bool direct1 = L.g[0].nsplit == 1;         // then z itself is written and read
-    int e = launch_stage_mx_split(&sp[0], L.g[0], nullptr, 0, 0, part1, L.ld[0], nullptr, ctr, L.g[1].ngroup, s);
-    if (e) return hip_fail(e);
-    e = launch_stage_mx_split(&sp[1], L.g[1], direct1 ? nullptr : part1, direct1 ? 0 : L.g[0].nsplit, L.ld[0], part2,
-                              L.ld[1], ctr, nullptr, 0, s);
+  if (wants_one(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T) && stage_is_one(sp[0]) && stage_is_one(sp[1])) {
+    // two launches; the second factor's workgroups add up the first factor's partial sums as they load them
+    const int64_t ld = (int64_t)align_up((size_t)desc->k, 64);
+    const OneGeom g[2] = {one_geom(sp[0].ntiles, sp[0].KB, one_room(desc) / (size_t)(4 * ld)),
+                          one_geom(sp[1].ntiles, sp[1].KB, 1)};
+    float* part = g[0].nsplit == 1 ? nullptr : (float*)((unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T));
+    int e = launch_stage_one(&sp[0], g[0], nullptr, 0, 0, part, ld, s);
+    if (!e) e = launch_stage_one(&sp[1], g[1], part, g[0].nsplit, ld, nullptr, 0, s);
     return hip_fail(e);
   }
   {

@@ -173,21 +173,23 @@ int launch_scale_in_mx(const StageProb* probs_dev, int count, int max_units, con
 // for it) and does not store its own results.  Needs that factor to be served by this variant too.
 int launch_stage_mx(const WorkItem* items_dev, int nitems, const StageProb* single, const StageProb* next_probs_dev,
                     hipStream_t s);
-// Split variant of the block-scaled kernel for one small problem with one token, any rank and types: workgroup (g, s) takes row
-// tiles 8g .. 8g + 7 and `bs` blocks of the contraction dimension and builds its activation records itself;
-// the partial sums of the nsplit workgroups of a tile group are added in a fixed order, by the reader
-// (part_in of the next launch) or by the last workgroup of the group to finish (counters).
+// A contraction split across workgroups: column blocks per workgroup, workgroups per row group, row groups.
 struct SplitGeom {
   int bs, nsplit, ngroup;
 };
-SplitGeom split_geom(int ntiles, int KB);    // host arithmetic only: the same on every machine
+// One-token single problem, any rank and types: a row tile's blocks on nsplit workgroups, bs on each, dealt out to its
+// `waves` waves.
+struct OneGeom {
+  int waves, bs, nsplit;
+};
+// host arithmetic only; max_splits: partial sums per row there is room for
+OneGeom one_geom(int ntiles, int KB, size_t max_splits);
+constexpr int kOneMaxSplits = 4;
+bool stage_is_one(const StageProb& p);       // its operands are addressable with 32-bit offsets
 // part_in (or null: p->vin): nsplit_in vectors part_in_ld apart whose sum is the activation vector.
 // part_out: g.nsplit vectors part_out_ld apart (unused when g.nsplit == 1: the result goes to p->out).
-// counters (or null): g.ngroup zeroed words; with them the launch itself stores the sums to p->out.
-// clear (or null): nclear words this launch sets to zero.
-int launch_stage_mx_split(const StageProb* p, const SplitGeom& g, const float* part_in, int nsplit_in,
-                          int64_t part_in_ld, float* part_out, int64_t part_out_ld, uint32_t* counters,
-                          uint32_t* clear, int nclear, hipStream_t s);
+int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in, int nsplit_in, int64_t part_in_ld,
+                     float* part_out, int64_t part_out_ld, hipStream_t s);
 constexpr int kMaxPreTokens = 16;   // token counts up to this use the scale-in kernel
 // true if the fast matrix-core variant can run the problem (l == 16, fp16 envelopes, K % 8 == 0,
 // 16-byte aligned activation rows); otherwise the general variant is used
@@ -214,8 +216,8 @@ int gemm_plan_max_tokens();
 // gemm_plan_max_tokens() tokens per problem); p->T = the longest token count among its problems, mode as above.
 int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s);
 
-// Few-token single problem (at most kFewMaxTokens tokens): contraction split across workgroups, as split_geom's
-// kernel does for one token, and the partial sums added by a second launch.  part: g.nsplit x T vectors part_ld
+// Few-token single problem (at most kFewMaxTokens tokens): contraction split across workgroups, the partial sums added
+// by a second launch.  part: g.nsplit x T vectors part_ld
 // apart (unused when g.nsplit == 1: the result goes to p->out).
 constexpr int kFewMaxTokens = 64;
 // host arithmetic only; vectors: the shape qualifies for the vector-load modes (gemm_load_mode); max_splits: partial

@@ -71,4 +71,416 @@ int launch_stage_precise(const StageProb* probs_dev, const WorkItem* items_dev, 
   return (int)hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------------
+// One-token evaluation of one envelope-scaled binary product by itself, in reconstruct order and fp32.
+//
+//   out[r] = sum_j S[r, j] * E[r, j] * vin[j],     E = Eout * Ein^T  (rank l)
+//
+// (paper Eq. "me-dbf-basis" for a single token).  A wave owns R row tiles of 16 rows and walks 128-column blocks:
+// the matrix cores rebuild its 16 x 128 piece of E from the envelope rows (fp32 sums of exact products), the vector
+// ALUs flip the signs with the packed bits and multiply-add with the activations, all in fp32; the waves of a
+// workgroup split the blocks and meet once, in LDS, in wave order.
+//
+// What bounds it: the launch and the chain load -> rebuild -> sum -> store; from some 20000 (tile, block) pieces on the
+// vector ALUs (three instructions per entry: shift the sign up, flip, multiply-add; 96 of them and 8 products a piece).
+// Nothing else lies between a wave's loads and its result: no scaled activations are built or shared, no barrier stands
+// before the last one, and a row tile's contraction meets in memory only between the two factors, where the reader adds
+// the (at most four) partial sums as it loads them.
+// Against building block-scaled records of the scaled activations in every workgroup and adding partial sums of both
+// factors in memory, per call: 4096 x 4096, k = 2656, l = 16 13.1 -> 8.4 us; 256 x 256, k = 128, l = 4 in fp32 9.7 ->
+// 5.5; 11008 x 4096, k = 4096, l = 16 20.1 -> 13.4; two calls of 4096 x 4096, k = 1601, l = 1 25.9 -> 18.6; 3000 x 5000,
+// k = 1777, l = 16 in fp32 19.6 -> 13.5; an empty pair of launches is 3 us.  Errors against 64 bits 6e-6 .. 2e-4 -> 2e-7.
+// (Two row tiles per workgroup, which halve the reads of the envelope rows, are slower throughout: 8.7 -> 11.0 us.)
+// ---------------------------------------------------------------------------------------------------
+namespace one {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bhalf8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // a vector at any element's address
+
+constexpr int kMaxWaves = 16;       // waves of a workgroup, each with blocks of its own
+
+struct OneArgs {
+  StageProb p;
+  int32_t bs, nsplit;               // blocks per workgroup, workgroups per row tile
+  int32_t nsplit_in;
+  const float* part_in;             // PARTS: vin[j] = sum over s < nsplit_in of part_in[s * part_in_ld + j]
+  int64_t part_in_ld;
+  float* part_out;                  // [nsplit][part_out_ld] partial sums (unused when nsplit == 1)
+  int64_t part_out_ld;
+};
+
+// element i of an array whose bytes are addressable with 32 bits
+template <class T>
+__device__ __forceinline__ T at(const void* base, uint32_t i) {
+  return *(const MDBF_GLOBAL T*)((const MDBF_GLOBAL char*)base + i * (uint32_t)sizeof(T));
+}
+
+// Envelope rows of a block as operands of the rebuild.  Lane (m, g) = (lane & 15, lane >> 4).  M: modes there is room for.
+//   16-bit types: v_mfma_f32_16x16x32, eight consecutive modes of a column per lane.  M = 8: a load is 64 columns, the
+//   four lane groups hold four sets of 16; M = 16: 32 columns, two sets, a column's modes on two lane groups.  A product
+//   takes the columns of one set: its other operand is zero for the other groups.  All 64 lanes load different data; of
+//   rank 8 or 16 a load is 1 KB without a gap.
+//   fp32: M / 4 products v_mfma_f32_16x16x4 per set, of M / 4 consecutive modes of a column per lane, one from each.
+// In set h of 32-column step f, row m of the product is column 32 f + 8 (m / 4) + 4 h + m % 4, so that lane (r, g) of the
+// results holds columns 32 f + 8 g + 0 .. 7 of row r: those of its packed sign word.
+//   VEC: rows of exactly M modes.  Other rows are read past their last mode: what is there meets zeros.
+template <int ENV, int M>
+struct EinBlock {
+  static constexpr int kPer = ENV == MDBF_F32 ? M / 4 : 8;          // modes per lane and load
+  static constexpr int kLoads = ENV == MDBF_F32 ? 8 : M / 4;        // per block
+  uint32_t v[kLoads][ENV == MDBF_F32 ? kPer : 4];
+};
+
+// where the lane's modes of load i of block q begin
+template <int ENV, int M>
+__device__ __forceinline__ uint32_t ein_first(int K, uint32_t l, int q, int i, int lane) {
+  const int m = lane & 15, g = lane >> 4;
+  int col = q * kBlockCols + 8 * (m >> 2) + (m & 3);
+  if constexpr (ENV == MDBF_F32) col += 32 * (i >> 1) + 4 * (i & 1);
+  else if constexpr (M == 8) col += 64 * i + 32 * (g >> 1) + 4 * (g & 1);
+  else col += 32 * i + 4 * (g >> 1);
+  return (uint32_t)min(col, K - 1) * l + (ENV == MDBF_F32 ? (uint32_t)(g * (M / 4)) : M == 8 ? 0u : 8u * (g & 1));
+}
+
+template <int ENV, int M, bool VEC>
+__device__ __forceinline__ void load_ein(const StageProb& p, int q, int lane, EinBlock<ENV, M>& e) {
+  typedef EinBlock<ENV, M> EB;
+  const uint32_t l = VEC ? (uint32_t)M : (uint32_t)p.l;
+  const uint32_t count = (uint32_t)p.K * l;
+  constexpr int kWords = sizeof(e.v[0]) / 4;
+  typedef uint32_t vec __attribute__((ext_vector_type(kWords), aligned(ENV == MDBF_F32 ? 4 : 2)));
+#pragma unroll
+  for (int i = 0; i < EB::kLoads; ++i) {
+    uint32_t first = ein_first<ENV, M>(p.K, l, q, i, lane);
+    if (!VEC) first = min(first, count < EB::kPer ? 0u : count - EB::kPer);       // (ein_tail moves the rest)
+    const vec v = *(const MDBF_GLOBAL vec*)((const MDBF_GLOBAL char*)p.Ein + (uint32_t)dtype_size(ENV) * first);
+#pragma unroll
+    for (int t = 0; t < kWords; ++t) {
+      if constexpr (kWords == 1) e.v[i][t] = v.x;
+      else e.v[i][t] = v[t];
+    }
+  }
+}
+
+// Blocks near the end of rows that are read past their last mode: where that would leave the factor, a vector from further down was
+// loaded (of a 16-bit factor of fewer than eight elements, some from behind it, in the same 16 bytes).
+template <int ENV, int M>
+__device__ __forceinline__ void ein_tail(const StageProb& p, int q, int lane, EinBlock<ENV, M>& e) {
+  typedef EinBlock<ENV, M> EB;
+  const int count = p.K * p.l;
+#pragma unroll
+  for (int i = 0; i < EB::kLoads; ++i) {
+    const int first = (int)ein_first<ENV, M>(p.K, (uint32_t)p.l, q, i, lane);
+    const int have = count - first;                                     // elements from `first` to the end
+    const int down = max(0, first - max(0, count - EB::kPer));
+    if constexpr (ENV == MDBF_F32) {
+#pragma unroll
+      for (int t = 0; t < EB::kPer; ++t) {
+        uint32_t x = 0;
+#pragma unroll
+        for (int u = t; u < EB::kPer; ++u) x = t + down == u ? e.v[i][u] : x;
+        e.v[i][t] = x;
+      }
+    } else {
+      const int sh = 16 * down;
+      uint64_t lo = (uint64_t)e.v[i][0] | ((uint64_t)e.v[i][1] << 32), hi = (uint64_t)e.v[i][2] | ((uint64_t)e.v[i][3] << 32);
+      if (sh >= 64) {
+        lo = sh >= 128 ? 0 : hi >> (sh - 64);
+        hi = 0;
+      } else if (sh > 0) {
+        lo = (lo >> sh) | (hi << (64 - sh));
+        hi >>= sh;
+      }
+      lo = have <= 0 ? 0 : have < 4 ? lo & ((1ull << (16 * have)) - 1) : lo;
+      hi = have <= 4 ? 0 : have < 8 ? hi & ((1ull << (16 * (have - 4))) - 1) : hi;
+      e.v[i][0] = (uint32_t)lo;
+      e.v[i][1] = (uint32_t)(lo >> 32);
+      e.v[i][2] = (uint32_t)hi;
+      e.v[i][3] = (uint32_t)(hi >> 32);
+    }
+  }
+}
+
+// The other operand: this lane's modes of row `row` times 2^-e, zeros past the rank.
+template <int ENV, int M>
+struct EoutRow {
+  uint32_t v[ENV == MDBF_F32 ? M / 4 : 4];
+  int e;
+};
+
+template <int ENV, int M, bool VEC>
+__device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row, int g) {
+  EoutRow<ENV, M> o;
+  constexpr int kN = EinBlock<ENV, M>::kPer;
+  const uint32_t l = VEC ? (uint32_t)M : (uint32_t)p.l;
+  const uint32_t m0 = ENV == MDBF_F32 ? (uint32_t)(g * kN) : M == 8 ? 0u : 8u * (g & 1);
+  const uint32_t first = (uint32_t)row * l;
+  o.e = 0;
+  if constexpr (VEC && ENV != MDBF_F32) {
+    const u32x4 v = at<u32x4>(p.Eout, (first + m0) >> 3);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) o.v[t] = v[t];
+  } else {
+    uint32_t b[kN];
+#pragma unroll
+    for (int t = 0; t < kN; ++t)
+      b[t] = ENV == MDBF_F32 ? at<uint32_t>(p.Eout, first + min(m0 + t, l - 1u)) : (uint32_t)at<uint16_t>(p.Eout, first + min(m0 + t, l - 1u));
+#pragma unroll
+    for (int t = 0; t < kN; ++t) b[t] = m0 + t < l ? b[t] : 0u;
+    if constexpr (ENV == MDBF_F32) {
+#pragma unroll
+      for (int t = 0; t < kN; ++t) o.v[t] = b[t];
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) o.v[t] = b[2 * t] | (b[2 * t + 1] << 16);
+    }
+  }
+  if constexpr (ENV != MDBF_F16) {
+    // The products of two envelope entries of these types can leave the range of fp32 where entry times activation
+    // does not: the row's largest entry goes to [1, 2), the power of two comes back with the result.
+    float v[kN];
+    float big = 0.f;
+#pragma unroll
+    for (int t = 0; t < kN; ++t) {
+      v[t] = __builtin_bit_cast(float, ENV == MDBF_F32 ? o.v[t] : t & 1 ? o.v[t >> 1] & 0xFFFF0000u : o.v[t >> 1] << 16);
+      big = fmaxf(big, fabsf(v[t]));
+    }
+    big = fmaxf(big, __shfl_xor(big, 16));
+    big = fmaxf(big, __shfl_xor(big, 32));
+    if (big > 0.f && big < __builtin_huge_valf()) o.e = ilogbf(big);
+#pragma unroll
+    for (int t = 0; t < kN; ++t) v[t] = ldexpf(v[t], -o.e);
+    if constexpr (ENV == MDBF_F32) {
+#pragma unroll
+      for (int t = 0; t < kN; ++t) o.v[t] = __builtin_bit_cast(uint32_t, v[t]);
+    } else {                                              // (still eight significant bits)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        o.v[t] = (__builtin_bit_cast(uint32_t, v[2 * t]) >> 16) | (__builtin_bit_cast(uint32_t, v[2 * t + 1]) & 0xFFFF0000u);
+    }
+  }
+  return o;
+}
+
+template <int ENV>
+__device__ __forceinline__ floatx4 rebuild16(u32x4 a, u32x4 b) {
+  const floatx4 z = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (ENV == MDBF_F16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), z, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bhalf8, a), __builtin_bit_cast(bhalf8, b), z, 0, 0, 0);
+}
+
+// the lanes of a wave have finished their LDS accesses (which execute in order: this is for the compiler)
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int ENV, int M, bool VEC, bool PARTS>
+__global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  typedef EinBlock<ENV, M> EB;
+  const StageProb& p = a.p;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nwaves = (int)blockDim.x >> 6;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int tile = blockIdx.x, split = blockIdx.y;      // a row tile; the split's blocks q_lo, q_lo + nwaves, ... are this wave's
+  const int q_lo = split * a.bs + wave, q_hi = min((split + 1) * a.bs, p.KB);
+  float* xs = reinterpret_cast<float*>(smem) + wave * (2 * kBlockCols);   // two blocks' activations, this wave's only
+  const MDBF_GLOBAL uint32_t* sbase = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(tile, p.KB) + lane;
+  const size_t sstride = (size_t)group_tiles(tile, p.ntiles) * 64u;
+
+  // What a block needs from memory: columns lane and lane + 64 of the activations (the words they are in, or their
+  // parts), envelope rows, signs.
+  struct Block {
+    uint32_t x[2][PARTS ? kOneMaxSplits : 1];
+    EB ein;
+    uint32_t sw;
+  };
+  const uint32_t xshift = p.vin_dt == MDBF_F32 ? 2u : 1u;
+  auto fetch = [&](int q, Block& b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t col = (uint32_t)min(q * kBlockCols + lane + 64 * h, p.K - 1);
+      if constexpr (PARTS) {
+#pragma unroll
+        for (int s = 0; s < kOneMaxSplits; ++s) b.x[h][s] = at<uint32_t>(a.part_in + min(s, a.nsplit_in - 1) * a.part_in_ld, col);
+      } else {
+        b.x[h][0] = at<uint32_t>(p.vin, (col << xshift) >> 2);
+      }
+    }
+    load_ein<ENV, M, VEC>(p, q, lane, b.ein);
+    b.sw = sbase[(size_t)q * sstride];
+  };
+  auto park = [&](int q, const Block& b, float* buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int col = q * kBlockCols + lane + 64 * h;
+      float x;
+      if constexpr (PARTS) {
+        x = __builtin_bit_cast(float, b.x[h][0]);
+#pragma unroll
+        for (int s = 1; s < kOneMaxSplits; ++s) x += s < a.nsplit_in ? __builtin_bit_cast(float, b.x[h][s]) : 0.f;
+      } else {
+        const uint32_t half = (min(col, p.K - 1) & 1) ? b.x[h][0] >> 16 : b.x[h][0] & 0xFFFFu;
+        const float xh = (float)__builtin_bit_cast(_Float16, (uint16_t)half);
+        x = p.vin_dt == MDBF_F32 ? __builtin_bit_cast(float, b.x[h][0]) : p.vin_dt == MDBF_F16 ? xh : __builtin_bit_cast(float, half << 16);
+      }
+      buf[lane + 64 * h] = col < p.K ? x : 0.f;
+    }
+    wave_lds_order();
+  };
+  float acc[2] = {0.f, 0.f};
+  EoutRow<ENV, M> eo;
+  auto contract = [&](int q, Block& b, const float* buf) __attribute__((always_inline)) {
+    // (the block's last row may be read past the factor's end: fewer than sixteen elements lie behind its first)
+    if (!VEC && (int64_t)(p.K - (q + 1) * kBlockCols + 1) * p.l < 16) ein_tail<ENV, M>(p, q, lane, b.ein);
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const floatx4 x0 = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g);
+      const floatx4 x1 = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g + 4);
+      floatx4 d[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if constexpr (ENV == MDBF_F32) {
+          d[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < EB::kPer; ++s)
+            d[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, b.ein.v[2 * f + h][s]),
+                                                        __builtin_bit_cast(float, eo.v[s]), d[h], 0, 0, 0);
+        } else {
+          const bool on = M == 8 ? g == 2 * (f & 1) + h : (g >> 1) == h;
+          const uint32_t (&x)[4] = b.ein.v[M == 8 ? f >> 1 : f];
+          d[h] = rebuild16<ENV>(u32x4{x[0], x[1], x[2], x[3]},
+                                u32x4{on ? eo.v[0] : 0u, on ? eo.v[1] : 0u, on ? eo.v[2] : 0u, on ? eo.v[3] : 0u});
+        }
+      }
+      // the packed word keeps the signs of columns 2 t and 2 t + 1 at bits c and c + 16, c = 8 (f / 2) + 4 (f % 2) + t
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int bit = 8 * (f >> 1) + 4 * (f & 1) + (t >> 1) + 16 * (t & 1);
+        const float ev = t < 4 ? d[0][t & 3] : d[1][t & 3];
+        const float sv = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, ev) ^ ((b.sw << (31 - bit)) & 0x80000000u));
+        acc[t & 1] = fmaf(sv, t < 4 ? x0[t & 3] : x1[t & 3], acc[t & 1]);
+      }
+      // (a step at a time: without this the products of a block are all made first, in 64 registers)
+      asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  eo.e = 0;
+  if (q_lo < q_hi) {
+    Block b0, b1;
+    fetch(q_lo, b0);
+    eo = load_eout<ENV, M, VEC>(p, min(tile * kTileRows + r16, p.rows - 1), g);
+    park(q_lo, b0, xs);
+    int q = q_lo;
+    for (;;) {
+      if (q + nwaves < q_hi) fetch(q + nwaves, b1);
+      contract(q, b0, xs);
+      q += nwaves;
+      if (q >= q_hi) break;
+      park(q, b1, xs + kBlockCols);
+      if (q + nwaves < q_hi) fetch(q + nwaves, b0);
+      contract(q, b1, xs + kBlockCols);
+      q += nwaves;
+      if (q >= q_hi) break;
+      park(q, b0, xs);
+    }
+  }
+
+  // ---- the lane groups' sums, then the waves', in wave order
+  float* red = reinterpret_cast<float*>(smem) + nwaves * (2 * kBlockCols);
+  float v = acc[0] + acc[1];
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  if constexpr (ENV != MDBF_F16) v = ldexpf(v, eo.e);
+  if (lane < kTileRows) red[wave * kTileRows + lane] = v;
+  __syncthreads();
+  if (tid < kTileRows) {
+    float sum = red[tid];
+    for (int w = 1; w < nwaves; ++w) sum += red[w * kTileRows + tid];
+    const int row = tile * kTileRows + tid;
+    if (row < p.rows) {
+      if (a.nsplit == 1) emit_result(p.out, row, p.out_dt, sum, p.flags);
+      else ((MDBF_GLOBAL float*)a.part_out)[split * a.part_out_ld + row] = sum;
+    }
+  }
+}
+
+template <int ENV, int M, bool VEC>
+static int launch_emv(const OneArgs& a, int waves, hipStream_t s) {
+  const dim3 grid((unsigned)a.p.ntiles, (unsigned)a.nsplit), block(64u * (unsigned)waves);
+  const size_t smem = (size_t)waves * (2 * kBlockCols + kTileRows) * 4u;
+  if (a.part_in) hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, true>), grid, block, smem, s, a);
+  else hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, false>), grid, block, smem, s, a);
+  return (int)hipGetLastError();
+}
+template <int ENV, int M>
+static int launch_em(const OneArgs& a, int waves, hipStream_t s) {
+  if (ENV != MDBF_BF16 && a.p.l == M) return launch_emv<ENV, M, ENV != MDBF_BF16>(a, waves, s);
+  return launch_emv<ENV, M, false>(a, waves, s);
+}
+template <int ENV>
+static int launch_e(const OneArgs& a, int waves, hipStream_t s) {
+  if constexpr (ENV == MDBF_F32) {
+    if (a.p.l <= 4) return launch_em<ENV, 4>(a, waves, s);
+  }
+  if (a.p.l <= 8) return launch_em<ENV, 8>(a, waves, s);
+  return launch_em<ENV, 16>(a, waves, s);
+}
+
+}  // namespace one
+
+OneGeom one_geom(int ntiles, int KB, size_t max_splits) {
+  // For a device of 256 compute units.  A unit's four SIMDs take four blocks of its workgroups at a time, whichever
+  // waves hold them; a partial sum costs its reader a load: 166 row tiles of 32 blocks on three workgroups each leave 22
+  // blocks on the busiest unit instead of 32 (8.8 -> 8.4 us per 4096 x 4096 call), 19 tiles of 86 blocks on four
+  // 22 (10.4 -> 6.5 us for 200 x 11008, k = 300).
+  // Eight waves; sixteen where a unit has one workgroup of a long contraction, whose loads then hide behind each other
+  // (4096 x 11008, k = 4096: 13.8 -> 13.1 us; with more workgroups than units eight are better: 11008 x 4096 15.7 -> 13.1).
+  OneGeom g = {1, KB, 1};
+  int64_t least = -1;
+  for (int n = 1; n <= kOneMaxSplits && (n == 1 || (size_t)n <= max_splits); ++n) {
+    const int bs = (KB + n - 1) / n;
+    const int64_t cost = 8 * (((int64_t)ntiles * n + 255) / 256) * ((bs + 3) / 4) + n;
+    if (least < 0 || cost < least) {
+      least = cost;
+      g.bs = bs;
+    }
+  }
+  g.nsplit = (KB + g.bs - 1) / g.bs;
+  while (g.waves < 8 && g.waves < g.bs) g.waves *= 2;
+  if (g.bs >= 16 && (int64_t)ntiles * g.nsplit <= 256) g.waves = one::kMaxWaves;
+  return g;
+}
+
+bool stage_is_one(const StageProb& p) {
+  const int64_t row = (int64_t)p.l * dtype_size(p.env_dt), most = (int64_t)1 << 32;
+  return p.K < (1 << 30) && p.rows < (1 << 30) && p.K * row < most && p.rows * row < most;
+}
+
+int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in, int nsplit_in, int64_t part_in_ld,
+                     float* part_out, int64_t part_out_ld, hipStream_t s) {
+  one::OneArgs a;
+  a.p = *p;
+  a.bs = g.bs;
+  a.nsplit = g.nsplit;
+  a.nsplit_in = nsplit_in;
+  a.part_in = part_in;
+  a.part_in_ld = part_in_ld;
+  a.part_out = part_out;
+  a.part_out_ld = part_out_ld;
+  if (p->env_dt == MDBF_F16) return one::launch_e<MDBF_F16>(a, g.waves, s);
+  if (p->env_dt == MDBF_BF16) return one::launch_e<MDBF_BF16>(a, g.waves, s);
+  return one::launch_e<MDBF_F32>(a, g.waves, s);
+}
+
 }  // namespace mdbf

@@ -28,8 +28,6 @@
 // loads beyond the stage that is due) and run two stages ahead; the contraction waves read everything
 // from LDS and issue no global loads in their loop, so a saturated memory pipeline stalls only the
 // loaders.  One barrier per stage hands a filled stage to the contraction waves and a drained one back.
-#include <type_traits>
-
 #include "mdbf_internal.h"
 
 namespace mdbf {
@@ -43,7 +41,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef const MDBF_GLOBAL u32x4* g_u32x4_ptr;
 typedef const MDBF_GLOBAL uint32_t* g_u32_ptr;
 typedef const MDBF_GLOBAL uint16_t* g_u16_ptr;
-typedef const MDBF_GLOBAL float* g_f32_ptr;
 
 // ---- activation stream: one record per 128-column block
 constexpr int kLimbBytes = 64 * 24;            // 1536: [64 lanes x 16 B][64 lanes x 8 B]
@@ -169,13 +166,12 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// one 16-, 8- or 4-byte piece of a record: to global memory with the non-temporal hint (the records are read
+// one 16-, 8- or 4-byte piece of a record, with the non-temporal hint (the records are read
 // once, by the product launch that follows; with plain stores the write-back of 40 to 55 MB of dirty lines
-// runs into that launch: measured on the 336-layer workload, 257 -> 248 us per step with the hint), or to LDS
-template <bool TO_LDS, class V>
+// runs into that launch: measured on the 336-layer workload, 257 -> 248 us per step with the hint)
+template <class V>
 __device__ __forceinline__ void record_store(unsigned char* base, int index, V v) {
-  if constexpr (TO_LDS) ((MDBF_LDS V*)base)[index] = v;
-  else __builtin_nontemporal_store(v, &((MDBF_GLOBAL V*)base)[index]);
+  __builtin_nontemporal_store(v, &((MDBF_GLOBAL V*)base)[index]);
 }
 
 // A lane's 32 values of a block in operand order (val, divided by their nibble values; m = their largest
@@ -183,13 +179,9 @@ __device__ __forceinline__ void record_store(unsigned char* base, int index, V v
 // The limbs saturate.  An infinity or NaN among the first three registers' columns reaches the result through the
 // column sum; the fourth register's columns are not in it, so that their products with zero start it (without them
 // a quarter of the columns could hold one and every output stayed finite).  They go into m first: taken at the
-// end they held eight registers through the conversions (124 -> 132 in the split kernel, one workgroup per
-// compute unit instead of two: 11008 x 4096, k = 4096, one token 20.4 -> 23.7 us).
-// FOUR: a fourth limb, 2^-4 of the third's scale: rank 8 in the half of slot 1 that is zero otherwise, rank 16 at
-// `limb4` (its scale is byte 3 of the scale words).
-template <bool RANK8, bool TO_LDS, bool FOUR = false>
-__device__ __forceinline__ void quantise_store(const float (&val)[32], float m, int lane, unsigned char* blk,
-                                               unsigned char* limb4 = nullptr) {
+// end they hold eight registers through the conversions.
+template <bool RANK8>
+__device__ __forceinline__ void quantise_store(const float (&val)[32], float m, int lane, unsigned char* blk) {
   constexpr bool rank8 = RANK8;   // the launch's rank: every problem of it has l = 8, or every one l = 16
   const int n = lane & 15;
 #pragma unroll
@@ -216,35 +208,26 @@ __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, 
   for (int j = 0; j < 32; ++j) r[j] -= b2[j];
   const v6u l3 = fp6_encode32(r, sc3);
   const v32f b3 = fp6_decode32(l3, sc3);
-  v6u l4 = {0, 0, 0, 0, 0, 0};
-  v32f b4;
-  if constexpr (FOUR) {
-    const float sc4 = __builtin_bit_cast(float, (uint32_t)(E + 115) << 23);
-#pragma unroll
-    for (int j = 0; j < 32; ++j) r[j] -= b3[j];
-    l4 = fp6_encode32(r, sc4);
-    b4 = fp6_decode32(l4, sc4);
-  }
   // quantised value = val - (last residual); back at the scale of xs, summed over the lane's columns, from 0 or NaN
   float part = m * 0.f;
 #pragma unroll
   for (int j = 0; j < 32; ++j) {
     const float inv = (j < 8) ? 0.5f : (j < 16 ? 1.f : 2.f);
-    if (j < 24) part += (val[j] - (r[j] - (FOUR ? b4[j] : b3[j]))) * inv;   // the fourth register's columns need no fix-up
+    if (j < 24) part += (val[j] - (r[j] - b3[j])) * inv;   // the fourth register's columns need no fix-up
   }
   // record slots: rank 16: limbs 1, 2, 3 of mode n.  Rank 8: slot 0 = limb 1 (n < 8) or limb 2 (n >= 8) of
-  // mode n & 7, slot 1 = limb 3 (n < 8) or zeros (FOUR: limb 4), slot 2 unused and not written; each lane's scale bytes
+  // mode n & 7, slot 1 = limb 3 (n < 8) or zeros, slot 2 unused and not written; each lane's scale bytes
   // follow its slots.
   const bool upper = rank8 && n >= 8;
   v6u slot[3];
 #pragma unroll
   for (int c = 0; c < 6; ++c) {
     slot[0][c] = upper ? l2[c] : l1[c];
-    slot[1][c] = rank8 ? (upper ? l4[c] : l3[c]) : l2[c];
+    slot[1][c] = rank8 ? (upper ? 0u : l3[c]) : l2[c];
     slot[2][c] = l3[c];
   }
   const uint32_t e0 = (uint32_t)(upper ? E + 123 : E + 127);
-  const uint32_t e1 = (uint32_t)(FOUR && upper ? E + 115 : rank8 ? E + 119 : E + 123);
+  const uint32_t e1 = (uint32_t)(rank8 ? E + 119 : E + 123);
 #pragma unroll
   for (int L = 0; L < 3; ++L) {
     if (L < 2 || !rank8) {
@@ -252,53 +235,28 @@ __device__ __forceinline__ void quantise_store(const float (&val)[32], float m, 
       a.x = slot[L][0]; a.y = slot[L][1]; a.z = slot[L][2]; a.w = slot[L][3];
       u32x2 bpart;
       bpart.x = slot[L][4]; bpart.y = slot[L][5];
-      record_store<TO_LDS>(blk + L * kLimbBytes, lane, a);
-      record_store<TO_LDS>(blk + L * kLimbBytes + 64 * 16, lane, bpart);
+      record_store(blk + L * kLimbBytes, lane, a);
+      record_store(blk + L * kLimbBytes + 64 * 16, lane, bpart);
     }
   }
-  uint32_t scales = e0 | (e1 << 8) | ((uint32_t)(E + 119) << 16);
-  if constexpr (FOUR && !RANK8) {
-    scales |= (uint32_t)(E + 115) << 24;
-    record_store<TO_LDS>(limb4, lane, u32x4{l4[0], l4[1], l4[2], l4[3]});
-    record_store<TO_LDS>(limb4 + 64 * 16, lane, u32x2{l4[4], l4[5]});
-  }
-  record_store<TO_LDS>(blk + kScaleOff, lane, scales);
+  const uint32_t scales = e0 | (e1 << 8) | ((uint32_t)(E + 119) << 16);
+  record_store(blk + kScaleOff, lane, scales);
   if (upper) part = 0.f;   // the column sum of a mode is stored once
 
   // ---- 3. column sums of the block
   part += __shfl_xor(part, 16);
   part += __shfl_xor(part, 32);
-  if (lane < 16) record_store<TO_LDS>(blk + kColsumOff, lane, part);
+  if (lane < 16) record_store(blk + kColsumOff, lane, part);
 }
 
 
-// step 2 of a record, from the products in LDS: a lane's values in operand order, quantised and stored.  Rank 8:
-// lanes n and n + 8 both take mode n; the first keeps limbs 1 and 3, the second limb 2, so that two matrix-core
-// instructions cover three limbs.  ANY: any rank; modes from l on are zero (pr need not hold them); with a
-// fourth limb, so that the path is nowhere less accurate than the fp16-staged kernel it took over from (three
-// limbs leave about the error of fp16 staging; up to rank 8 the fourth costs no instruction of the contraction).
-template <bool RANK8, bool TO_LDS, bool ANY>
-__device__ __forceinline__ void gather_quantise(float* pr, int l, int lane, unsigned char* blk) {
-  const int kg = lane >> 4, n = lane & 15;
-  const int nsrc = RANK8 ? (n & 7) : n;
-  float val[32];
-  float m = 0.f;
-#pragma unroll
-  for (int j = 0; j < 32; ++j) {
-    const float presc = (j < 8) ? 2.f : (j < 16 ? 1.f : (j < 24 ? 0.5f : -0.5f));   // undo the nibble values 0.5, 1, 2, -2
-    const float v = pr[(local_col_of_element(j, 0) + 8 * kg) * kProdStride + nsrc];
-    val[j] = !ANY || nsrc < l ? v * presc : 0.f;
-    m = fmaxf(m, fabsf(val[j]));
-  }
-  wave_lds_sync();   // the next record's products may overwrite the buffer
-  // (ANY: a fourth limb; of rank 16 it takes the place of the products, which have been read)
-  quantise_store<RANK8, TO_LDS, ANY>(val, m, lane, blk, (unsigned char*)pr);
-}
-
-// the record of block q of the problem's contraction dimension, from the inputs `in`, written to `blk`
-template <bool RANK8, bool TO_LDS>
-__device__ __forceinline__ void prep_record_to(const StageProb& p, int q, int lane, const PrepInput& in, float* pr,
-                                               unsigned char* blk) {
+// the record of unit (token, block) of the problem's activation stream, from the inputs `in`.  Rank 8: lanes n and
+// n + 8 both take mode n; the first keeps limbs 1 and 3, the second limb 2, so that two matrix-core instructions cover
+// three limbs.
+template <bool RANK8>
+__device__ __forceinline__ void prep_record(const StageProb& p, int unit, int lane, const PrepInput& in, float* pr) {
+  const int b = unit / p.KB, q = unit - b * p.KB;
+  unsigned char* blk = (unsigned char*)p.xs + ((size_t)b * p.KB + q) * (size_t)kBlockBytes;
   const bool has_modes = (lane & 1) < (p.l >> 3);
 
   // ---- 1. products
@@ -319,15 +277,21 @@ __device__ __forceinline__ void prep_record_to(const StageProb& p, int q, int la
     }
   }
   wave_lds_sync();
-  gather_quantise<RANK8, TO_LDS, false>(pr, RANK8 ? 8 : 16, lane, blk);
-}
 
-// record of unit (token, block) of the problem's activation stream in global memory
-template <bool RANK8>
-__device__ __forceinline__ void prep_record(const StageProb& p, int unit, int lane, const PrepInput& in, float* pr) {
-  const int b = unit / p.KB, q = unit - b * p.KB;
-  unsigned char* blk = (unsigned char*)p.xs + ((size_t)b * p.KB + q) * (size_t)kBlockBytes;
-  prep_record_to<RANK8, false>(p, q, lane, in, pr, blk);
+  // ---- 2. the lane's values in operand order, quantised and stored
+  const int kg = lane >> 4, n = lane & 15;
+  const int nsrc = RANK8 ? (n & 7) : n;
+  float val[32];
+  float m = 0.f;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const float presc = (j < 8) ? 2.f : (j < 16 ? 1.f : (j < 24 ? 0.5f : -0.5f));   // undo the nibble values 0.5, 1, 2, -2
+    const float v = pr[(local_col_of_element(j, 0) + 8 * kg) * kProdStride + nsrc];
+    val[j] = v * presc;
+    m = fmaxf(m, fabsf(val[j]));
+  }
+  wave_lds_sync();   // the next record's products may overwrite the buffer
+  quantise_store<RANK8>(val, m, lane, blk);
 }
 
 template <bool RANK8>
@@ -383,8 +347,7 @@ __device__ __forceinline__ floatx4 mx_mfma(v8i a, v8i b, floatx4 c, int L, uint3
   // A: fp4 (format 4), scale 2^0; B: fp6 e2m3 (format 2), scale byte L of sc
   if (L == 0) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 0, (int)sc);
   if (L == 1) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 1, (int)sc);
-  if (L == 2) return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 2, (int)sc);
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 3, (int)sc);
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 4, 2, 0, 0x7F7F7F7F, 2, (int)sc);
 }
 
 __device__ __forceinline__ float row16_sum(float v) {
@@ -774,7 +737,7 @@ void stage_mx_kernel(const WorkItem* __restrict__ items, int nitems, StageProb s
             val[j] = prod * presc;
             m = fmaxf(m, fabsf(val[j]));
           }
-          quantise_store<RANK == 8, false>(val, m, lane,
+          quantise_store<RANK == 8>(val, m, lane,
                                            it.xs_next + ((size_t)b * it.KB_next + q2) * (size_t)kBlockBytes);
         }
       }
@@ -782,227 +745,6 @@ void stage_mx_kernel(const WorkItem* __restrict__ items, int nitems, StageProb s
     item += stride;
     if (item >= i_hi) break;
     it = load_item<BATCH, R, FUSE>(items, single, item, next_probs);
-  }
-}
-
-// ---------------------------------------------------------------------------------------------------
-// Split variant for one small problem (a single layer, one token): 64-tile items would leave most of the
-// device idle and a workgroup would walk the whole contraction dimension by itself.  Here workgroup (g, s)
-// takes row tiles 8g .. 8g + 7 (one per wave) and blocks [s * bs, s * bs + bs) of the contraction
-// dimension, builds the records of its blocks in LDS itself (no scale-in launch), contracts, applies the
-// envelope rows and ends up with one partial sum per row: the envelope-accumulate of Eq. "me-dbf-expand"
-// is linear in P, so 16 floats per tile leave the workgroup instead of 16 x 16.
-//  * first factor: the partial sums go to part_out[s][row]; the second factor's workgroups add them up in
-//    the order of s as they load their activations (vin = the sum), so no launch or wait lies between.
-//  * second factor: the partial sums are written through to memory (device-scope stores) and a counter per
-//    tile group is raised; whichever workgroup raises it to nsplit adds the nsplit partial sums of the
-//    group's rows in the order of s and stores the result.  Nobody waits for anybody, and the order of the
-//    additions is fixed: the result is the same bits every time.
-// The counters are cleared by the first factor's launch of the same call.
-// ---------------------------------------------------------------------------------------------------
-constexpr int kSplitWaves = 8;      // row tiles per workgroup
-constexpr int kSplitMaxBs = 4;      // blocks per workgroup at most (one record-building wave each)
-
-// sum of count values `ld` floats apart, added in index order.  The loads go out eight at a time before the
-// first addition (each one is a trip to memory: partial sums are never in this workgroup's caches).
-// COHERENT: written by other workgroups of the same launch with device-scope stores; read the same way.
-template <bool COHERENT>
-__device__ __forceinline__ float ordered_sum(const MDBF_GLOBAL float* first, int count, int64_t ld) {
-  float sum = 0.f;
-  for (int t0 = 0; t0 < count; t0 += 8) {
-    float v[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const MDBF_GLOBAL float* src = first + (size_t)min(t0 + j, count - 1) * ld;
-      v[j] = COHERENT ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (t0 + j < count) sum += v[j];
-  }
-  return sum;
-}
-
-// The record of block q for any rank and type of the envelope factor (one token).  A block's 128 rows of the
-// factor are 128 l consecutive elements: lane i takes elements i, i + 64, ... (coalesced whatever the rank), the
-// activations, x0 and x1 = columns lane and lane + 64 of the block, meet them through LDS.
-template <bool RANK8>
-__device__ __forceinline__ void prep_record_any(const StageProb& p, int q, int lane, float x0, float x1, float* xbuf,
-                                                float* pr, unsigned char* blk) {
-  constexpr int kMaxT = RANK8 ? 16 : 32;        // elements per lane at most
-  const int l = p.l;
-  const int64_t e0 = (int64_t)q * kBlockCols * l;
-  const int last = (int)min((int64_t)p.K * l - 1 - e0, (int64_t)kBlockCols * l - 1);   // of the block's elements
-  float ev[kMaxT];
-  if (p.env_dt == MDBF_F32) {
-#pragma unroll
-    for (int t = 0; t < kMaxT; ++t)
-      if (t < 2 * l) ev[t] = ((g_f32_ptr)p.Ein)[e0 + min(lane + 64 * t, last)];
-  } else {
-    uint32_t bits[kMaxT];
-#pragma unroll
-    for (int t = 0; t < kMaxT; ++t)
-      if (t < 2 * l) bits[t] = ((g_u16_ptr)p.Ein)[e0 + min(lane + 64 * t, last)];
-#pragma unroll
-    for (int t = 0; t < kMaxT; ++t)
-      ev[t] = p.env_dt == MDBF_F16 ? (float)__builtin_bit_cast(_Float16, (uint16_t)bits[t]) : __builtin_bit_cast(float, bits[t] << 16);
-  }
-  xbuf[lane] = q * kBlockCols + lane < p.K ? x0 : 0.f;
-  xbuf[64 + lane] = q * kBlockCols + 64 + lane < p.K ? x1 : 0.f;
-  wave_lds_sync();
-  const float rl = 1.f / (float)l;
-#pragma unroll
-  for (int t = 0; t < kMaxT; ++t) {
-    if (t < 2 * l) {
-      const int e = lane + 64 * t;
-      const int col = (int)(((float)e + 0.5f) * rl);       // e / l: e < 2048, half a unit away from every edge
-      pr[col * kProdStride + (e - col * l)] = q * kBlockCols + col < p.K ? ev[t] * xbuf[col] : 0.f;
-    }
-  }
-  wave_lds_sync();
-  gather_quantise<RANK8, true, true>(pr, l, lane, blk);
-}
-
-struct SplitArgs {
-  StageProb p;
-  int32_t bs, nsplit;               // blocks per workgroup; workgroups per tile group
-  const float* part_in;             // vin[j] = sum over s < nsplit_in of part_in[s * part_in_ld + j]; null: p.vin
-  int64_t part_in_ld;
-  float* part_out;                  // [nsplit][part_out_ld] partial sums (unused when nsplit == 1)
-  int64_t part_out_ld;
-  uint32_t* counters;               // one per tile group: this launch finishes its rows itself; null: the reader adds
-  uint32_t* clear;                  // counters to clear for the launch that follows (null: none)
-  int32_t nsplit_in, nclear;
-};
-
-// VEC: fp16 envelope factors of rank 8 or 16, read as 16-byte vectors; otherwise any rank up to 8 (RANK8) or 16 and
-// any type, element by element.  The fp16-staged general kernel that ranks other than 8 and 16 used to take by
-// themselves rebuilt all scaled activations in every workgroup: two 4096 x 4096 calls, k = 1601, l = 1: 114 -> 27 us;
-// 256 x 256, k = 128, l = 4 in fp32: 21.9 -> 12.0 us, errors
-// against 64 bits 1e-4 .. 4e-4 -> 1e-5 .. 2e-5.
-template <bool RANK8, bool VEC>
-__global__ __launch_bounds__(64 * kSplitWaves) void stage_mx_split_kernel(SplitArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char recs[kSplitMaxBs * kBlockBytes];
-  __shared__ __attribute__((aligned(16))) float prod[kSplitMaxBs][128 * kProdStride];
-  __shared__ float xbuf[VEC ? 1 : kSplitMaxBs][kBlockCols];
-  __shared__ uint32_t is_last;
-  constexpr int RANK = RANK8 ? 8 : 16;
-  constexpr int NL = RANK8 ? 2 : VEC ? 3 : 4;
-  const StageProb& p = a.p;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int kg = lane >> 4, n = lane & 15;
-  const int g = (int)blockIdx.x / a.nsplit, s = (int)blockIdx.x - g * a.nsplit;
-  const int q0 = s * a.bs;
-  const int nb = min(a.bs, p.KB - q0);                 // >= 1: nsplit = ceil(KB / bs)
-  if (a.clear && blockIdx.x == 0)
-    for (int i = tid; i < a.nclear; i += 64 * kSplitWaves)
-      __hip_atomic_store((MDBF_GLOBAL uint32_t*)a.clear + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
-  // ---- this wave's tile: sign words of the workgroup's blocks and the envelope rows (issued first)
-  const int tile = g * kSplitWaves + wave;
-  const int tile_c = min(tile, p.ntiles - 1);
-  uint32_t w[kSplitMaxBs];
-#pragma unroll
-  for (int i = 0; i < kSplitMaxBs; ++i)
-    w[i] = ((g_u32_ptr)p.S)[word_offset(tile_c, min(q0 + i, p.KB - 1), lane, p.KB, p.ntiles)];
-  const int mode = n & (RANK - 1);
-  typename std::conditional<VEC, _Float16, float>::type ev[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = min(tile_c * kTileRows + 4 * kg + i, p.rows - 1);
-    if constexpr (VEC) ev[i] = ((const MDBF_GLOBAL _Float16*)p.Eout)[(size_t)row * RANK + mode];
-    else ev[i] = load_as_float(p.Eout, (int64_t)row * p.l + min(mode, p.l - 1), p.env_dt);
-  }
-
-  // ---- records of the workgroup's blocks: wave i builds block q0 + i
-  if (wave < nb) {
-    const int q = q0 + wave;
-    if constexpr (VEC) {
-      PrepInput in = prep_load(p, q, lane);            // (token 0; with part_in the activations read here are not used)
-      StageProb pp = p;
-      if (a.part_in) {
-        pp.vin_dt = MDBF_F32;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int kc = min(q * kBlockCols + (lane >> 1) + 32 * i, p.K - 1);
-          const float sum = ordered_sum<false>((g_f32_ptr)a.part_in + kc, a.nsplit_in, a.part_in_ld);
-          in.xbits[i] = __builtin_bit_cast(uint32_t, sum);
-        }
-      }
-      prep_record_to<RANK8, true>(pp, q, lane, in, prod[wave], recs + wave * kBlockBytes);
-    } else {
-      float x[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int kc = min(q * kBlockCols + lane + 64 * i, p.K - 1);
-        x[i] = a.part_in ? ordered_sum<false>((g_f32_ptr)a.part_in + kc, a.nsplit_in, a.part_in_ld)
-                         : load_as_float(p.vin, kc, p.vin_dt);
-      }
-      prep_record_any<RANK8>(p, q, lane, x[0], x[1], xbuf[wave], prod[wave], recs + wave * kBlockBytes);
-    }
-  }
-  __syncthreads();
-
-  // ---- contraction of the tile against the records
-  const SignConsts sconst = sign_consts();
-  floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
-  float colsum = 0.f;
-#pragma unroll
-  for (int i = 0; i < kSplitMaxBs; ++i) {
-    if (i < nb) {
-      const unsigned char* rec = recs + i * kBlockBytes;
-      const uint32_t scales = reinterpret_cast<const uint32_t*>(rec + kScaleOff)[lane];
-      colsum += reinterpret_cast<const float*>(rec + kColsumOff)[n];
-      const v8i sa = sign_operand(w[i], sconst);
-#pragma unroll
-      for (int L = 0; L < NL; ++L) {
-        const unsigned char* limbs = L < 3 ? rec + L * kLimbBytes : (const unsigned char*)prod[i];
-        const u32x4 x = reinterpret_cast<const u32x4*>(limbs)[lane];
-        const u32x2 y = reinterpret_cast<const u32x2*>(limbs + 64 * 16)[lane];
-        v8i limb;
-        limb[0] = (int)x.x; limb[1] = (int)x.y; limb[2] = (int)x.z; limb[3] = (int)x.w;
-        limb[4] = (int)y.x; limb[5] = (int)y.y; limb[6] = 0; limb[7] = 0;
-        acc = mx_mfma(sa, limb, acc, L, scales);
-      }
-    }
-  }
-
-  // ---- envelope rows: fix-up, accumulate over the modes; one partial sum per row
-  float v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float e = VEC || mode < p.l ? (float)ev[i] : 0.f;
-    v[i] = row16_sum(e * (colsum - 2.f * acc[i]));
-  }
-  const int sel = n & 3;
-  const float res = sel == 0 ? v[0] : sel == 1 ? v[1] : sel == 2 ? v[2] : v[3];
-  const int row = tile * kTileRows + 4 * kg + n;
-  const bool mine = n < 4 && tile < p.ntiles && row < p.rows;
-  if (a.nsplit == 1) {
-    if (mine) emit_result(p.out, row, p.out_dt, res, p.flags);
-    return;
-  }
-  // read by another workgroup, possibly on another XCD: written through to memory
-  if (mine)
-    __hip_atomic_store((MDBF_GLOBAL float*)a.part_out + (size_t)s * a.part_out_ld + row, res, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  if (!a.counters) return;
-
-  // ---- the last workgroup of the tile group adds the partial sums up
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's partial sums are in memory
-  __syncthreads();
-  if (tid == 0) {
-    const uint32_t old = __hip_atomic_fetch_add((MDBF_GLOBAL uint32_t*)a.counters + g, 1u, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    is_last = (old + 1u == (uint32_t)a.nsplit) ? 1u : 0u;
-  }
-  __syncthreads();
-  if (!is_last) return;
-  const int frow = g * (kSplitWaves * kTileRows) + tid;
-  if (tid < kSplitWaves * kTileRows && frow < p.rows) {
-    const float sum = ordered_sum<true>((g_f32_ptr)a.part_out + frow, a.nsplit, a.part_out_ld);
-    emit_result(p.out, frow, p.out_dt, sum, p.flags);
   }
 }
 
@@ -1113,47 +855,6 @@ int launch_stage_mx(const WorkItem* items_dev, int nitems, const StageProb* sing
   }
   // single->ntiles carries the plan's tiles per item of this stage
   return mx::launch_b<true>(items_dev, nitems, single->ntiles, single, next_probs_dev, s);
-}
-
-SplitGeom split_geom(int ntiles, int KB) {
-  // enough workgroups for a device of 256 compute units whatever the device: the workspace layout follows
-  // from these numbers and must not depend on where it is computed
-  constexpr int kTargetWgs = 256;
-  SplitGeom g;
-  g.ngroup = (ntiles + mx::kSplitWaves - 1) / mx::kSplitWaves;
-  const int want = (kTargetWgs + g.ngroup - 1) / g.ngroup;
-  int bs = (KB + want - 1) / want;
-  // at most eight partial sums per row where the block limit allows: whoever adds them up fetches eight at a
-  // time, and every further round is another trip to memory
-  if (bs < (KB + 7) / 8) bs = (KB + 7) / 8;
-  bs = bs < 1 ? 1 : bs > mx::kSplitMaxBs ? mx::kSplitMaxBs : bs;
-  g.bs = bs;
-  g.nsplit = (KB + bs - 1) / bs;
-  return g;
-}
-
-int launch_stage_mx_split(const StageProb* p, const SplitGeom& g, const float* part_in, int nsplit_in,
-                          int64_t part_in_ld, float* part_out, int64_t part_out_ld, uint32_t* counters,
-                          uint32_t* clear, int nclear, hipStream_t s) {
-  mx::SplitArgs a;
-  a.p = *p;
-  a.bs = g.bs;
-  a.nsplit = g.nsplit;
-  a.part_in = part_in;
-  a.part_in_ld = part_in_ld;
-  a.part_out = part_out;
-  a.part_out_ld = part_out_ld;
-  a.counters = counters;
-  a.clear = clear;
-  a.nsplit_in = nsplit_in;
-  a.nclear = nclear;
-  const dim3 grid((unsigned)(g.ngroup * g.nsplit)), block(64 * mx::kSplitWaves);
-  const bool vec = (p->l == 16 || p->l == 8) && p->env_dt == MDBF_F16;
-  if (vec && p->l == 8) hipLaunchKernelGGL((mx::stage_mx_split_kernel<true, true>), grid, block, 0, s, a);
-  else if (vec) hipLaunchKernelGGL((mx::stage_mx_split_kernel<false, true>), grid, block, 0, s, a);
-  else if (p->l <= 8) hipLaunchKernelGGL((mx::stage_mx_split_kernel<true, false>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((mx::stage_mx_split_kernel<false, false>), grid, block, 0, s, a);
-  return (int)hipGetLastError();
 }
 
 }  // namespace mdbf

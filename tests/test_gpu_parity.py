@@ -479,6 +479,35 @@ def test_one_token_calls_of_any_rank_and_type(gpu, m, n, k, l, env_dtype, x_dtyp
             assert not torch.isfinite(mb.mdbf_forward(dl, Xb, y_dtype="f32")).any()
 
 
+ONE_TOKEN_EDGES = [
+    # m, n, k, l, env, x: factors of fewer elements than a vector; last vectors that begin before the last block; rows that
+    # end in the middle of one, for each number of modes a lane holds; blocks on one to four workgroups and on 1 to 16
+    # waves, one to six blocks a wave
+    (3, 2, 1, 3, "f16", "f16"), (17, 1, 5, 1, "bf16", "bf16"), (16, 129, 257, 1, "f16", "bf16"), (40, 130, 3, 7, "bf16", "f16"),
+    (33, 257, 1030, 9, "f16", "f32"), (31, 385, 129, 15, "bf16", "f32"), (90, 130, 129, 2, "f32", "f32"), (90, 129, 257, 6, "f32", "f16"),
+    (90, 257, 129, 13, "f32", "bf16"), (2600, 1100, 700, 16, "f32", "f32"), (200, 11008, 300, 16, "f16", "f16"), (4100, 5000, 4096, 8, "f16", "f16"),
+]
+
+
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", ONE_TOKEN_EDGES)
+def test_one_token_calls_are_fp32(gpu, m, n, k, l, env_dtype, x_dtype):
+    """Products of envelope entries, signs and activations in fp32, sums of at most a few dozen per lane, then over lanes,
+    waves and workgroups: the gate of the fp32 path.  The second layer's products of two envelope entries lie outside
+    the range of fp32 (its What is the first one's)."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 1, seed=9 + m, x_dtype=x_dtype)
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    Xd = _to_dev(torch, X, x_dtype)
+    got = mb.mdbf_forward(mb.DeviceLayer.from_host(L), Xd, y_dtype="f32")
+    assert orc.max_rel_error(got.cpu().numpy(), ref) <= 2e-5
+    assert torch.equal(got, mb.mdbf_forward(mb.DeviceLayer.from_host(L), Xd, y_dtype="f32"))
+    if env_dtype != "f16":
+        H = dict(L, A=L["A"] * np.float32(2.0 ** 70), Q=L["Q"] * np.float32(2.0 ** 70), G=L["G"] * np.float32(2.0 ** -70), B=L["B"] * np.float32(2.0 ** -30))
+        got = mb.mdbf_forward(mb.DeviceLayer.from_host(H), Xd, y_dtype="f32").cpu().numpy() * 2.0 ** -40
+        assert orc.max_rel_error(got, ref) <= 2e-5
+
+
 @pytest.mark.parametrize("where", ["single", "forced", "plan"])
 @pytest.mark.parametrize("l,T", [(8, 1), (16, 1), (16, 3)])
 def test_non_finite_input_reaches_every_output_of_the_block_scaled_kernels(gpu, l, T, where):
