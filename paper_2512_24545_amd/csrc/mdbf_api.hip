@@ -611,7 +611,7 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
       }
       tpi_mx = mx_pick_item_tiles(count, nt.data(), kb.data());
     }
-    h->tiles_per_item[s] = h->gemm ? gemm_tiles_per_item() : mx[s] ? tpi_mx : tpi_fp16;
+    h->tiles_per_item[s] = h->gemm ? gemm_tiles_per_item(tiles[s], h->max_tokens) : mx[s] ? tpi_mx : tpi_fp16;
   }
   h->fuse2 = (!precise && !h->gemm && h->mx[0] != 0 && h->mx[0] == h->mx[1]) ? 1 : 0;
   for (int i = 0; i < count; ++i) {
@@ -763,6 +763,7 @@ int mdbf_forward_batch_part(const void* plan_host, const void* plan_dev, size_t 
       StageProb launch;
       memset(&launch, 0, sizeof(launch));
       launch.T = h.max_tokens;
+      launch.ntiles = h.tiles_per_item[st];
       int e = launch_stage_gemm((const WorkItem*)(dev + h.items_off[st]), h.nitems[st], h.gemm_mode[st], &launch, s);
       if (e) return hip_fail(e);
     }

@@ -210,10 +210,11 @@ constexpr int kGemmMinTokensPlan = 4;
 int gemm_load_mode(const StageProb& p);
 // compute units of the current device (cached after the first call; 256 if the query fails)
 int compute_units();
-int gemm_tiles_per_item();
+int gemm_tiles_per_item(long launch_tiles, int max_tokens);   // of a plan
 int gemm_plan_max_tokens();
 // items_dev null: the single problem *p (mode ignored).  Else the work items of a plan (at most
-// gemm_plan_max_tokens() tokens per problem); p->T = the longest token count among its problems, mode as above.
+// gemm_plan_max_tokens() tokens per problem); p->T = the longest token count among its problems, p->ntiles = the row
+// tiles per work item the plan was cut with (gemm_tiles_per_item), mode as above.
 int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s);
 
 // Few-token single problem (at most kFewMaxTokens tokens): contraction split across workgroups, the partial sums added

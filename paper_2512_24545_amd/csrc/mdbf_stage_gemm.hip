@@ -125,10 +125,11 @@ __device__ __forceinline__ half4 load4_modes(const StageProb& p, const void* env
 // vector, issued without a branch (addresses are clamped, values past the end replaced by zero).  MODE 3:
 // any types, ranks and alignments, element by element.
 // BATCH: the rows come from a plan's work items instead of the single problem.
+// NW waves, each with R row tiles, share a staging of a block; KS such groups take a run over the contraction each and
+// add their sums at the end, in order (small plans).
 constexpr int kGeneric = 3;
-constexpr int kPlanR = 2;   // row tiles per wave in a plan's work items
-template <int R, int TB, int MODE, bool BATCH>
-__global__ __launch_bounds__(64 * kWaves, min_waves(TB))
+template <int NW, int R, int TB, int MODE, bool BATCH, int KS>
+__global__ __launch_bounds__(64 * NW * KS, min_waves(TB))
 void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   // Two buffers each, as objects of their own and chosen at compile time (the loop is written out twice).  With one
   // array and a run-time offset no LDS read could move across the direct-to-LDS loads of the next block: they were
@@ -136,12 +137,12 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   // go ahead and the loads follow between its products (2048 tokens on 4096 x 4096, k = 2656: 139 -> 124 us; 40
   // tokens: 61 -> 42 us).
   constexpr int kVinBufBytes = vin_buf_bytes(TB);
-  __shared__ __attribute__((aligned(1024))) unsigned char vin_a[kVinBufBytes];   // [16*TB tokens][16 chunks of 16 B], swizzled
-  __shared__ __attribute__((aligned(1024))) unsigned char vin_b[kVinBufBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char ein_a[kEinBufBytes];   // [128 columns][16 modes]
-  __shared__ __attribute__((aligned(1024))) unsigned char ein_b[kEinBufBytes];
-  // the rows of this workgroup: a work item of a plan (at most kWaves * R row tiles of one problem), or
-  // the blockIdx.x-th run of kWaves * R tiles of the single problem
+  __shared__ __attribute__((aligned(1024))) unsigned char vin_lds_a[KS * kVinBufBytes];   // [16*TB tokens][16 chunks of 16 B], swizzled
+  __shared__ __attribute__((aligned(1024))) unsigned char vin_lds_b[KS * kVinBufBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char ein_lds_a[KS * kEinBufBytes];   // [128 columns][16 modes]
+  __shared__ __attribute__((aligned(1024))) unsigned char ein_lds_b[KS * kEinBufBytes];
+  // the rows of this workgroup: a work item of a plan (at most NW * R row tiles of one problem), or
+  // the blockIdx.x-th run of NW * R tiles of the single problem
   StageProb p;
   int item_tile0, item_end, slab_group;
   if (BATCH) {
@@ -155,19 +156,25 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     // of its own; the (token slab group, row group) pairs, token-major, are dealt out in eight contiguous
     // runs, one per die: the workgroups that read the same activations share an L2.
     p = single;
-    const int row_groups = (p.ntiles + kWaves * R - 1) / (kWaves * R);
+    const int row_groups = (p.ntiles + NW * R - 1) / (NW * R);
     const int slab_groups = (p.T + 16 * TB - 1) / (16 * TB);
     const int total = row_groups * slab_groups;
     const int per_die = (total + kDies - 1) / kDies;
     const int unit = (blockIdx.x % kDies) * per_die + blockIdx.x / kDies;
     if (unit >= total) return;
     slab_group = unit / row_groups;
-    item_tile0 = (unit - slab_group * row_groups) * (kWaves * R);
-    item_end = min(item_tile0 + kWaves * R, p.ntiles);
+    item_tile0 = (unit - slab_group * row_groups) * (NW * R);
+    item_end = min(item_tile0 + NW * R, p.ntiles);
   }
-  const int tid = threadIdx.x, lane = tid & 63;
+  // the run over the contraction that this thread's four waves take, and the thread's and the wave's place in it
+  const int run = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
+  const int tid = threadIdx.x - run * (64 * NW), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
+  unsigned char* const vin_a = vin_lds_a + run * kVinBufBytes;
+  unsigned char* const vin_b = vin_lds_b + run * kVinBufBytes;
+  unsigned char* const ein_a = ein_lds_a + run * kEinBufBytes;
+  unsigned char* const ein_b = ein_lds_b + run * kEinBufBytes;
   const int tile0 = item_tile0 + wave * R;                     // first row tile of this wave
   const int tok0 = slab_group * (16 * TB);
   if (tok0 >= p.T) return;                                     // a plan's grid covers its longest problem
@@ -203,20 +210,21 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   //      T are never stored; columns past K meet zeroed envelope rows and are zeroed themselves (an infinity in the
   //      row's last columns, which the direct loads of a partial block repeat, would turn into a NaN there).
   constexpr bool kDma = (MODE == MDBF_F16);
-  constexpr int kVinChunks = (16 * TB * 16) / (64 * kWaves);   // 16-byte chunks per thread: TB
+  constexpr int kVinChunks = (16 * TB * 16) / (64 * NW);   // 16-byte chunks per thread: TB
   u32x4 vin_reg[kDma ? 1 : kVinChunks];
-  u32x4 ein_reg;
-  bool ein_ok = true;
+  constexpr int kEinChunks = 256 / (64 * NW);                  // 16-byte halves of envelope rows per thread
+  u32x4 ein_reg[kEinChunks];
+  bool ein_ok[kEinChunks];
   uint32_t sw_next[R];
   auto dma_block = [&](int q, unsigned char* vin_buf) {
 #pragma unroll
     for (int i = 0; i < kVinChunks; ++i) {
-      const int id = tid + 64 * kWaves * i;
+      const int id = tid + 64 * NW * i;
       const int tok = id >> 4, c = (id & 15) ^ (tok & 15);
       const int col = min(q * kBlockCols + c * 8, p.K - 8);
       const int b = min(tok0 + tok, p.T - 1);
       const MDBF_GLOBAL _Float16* src = (const MDBF_GLOBAL _Float16*)p.vin + ((int64_t)b * p.vin_ld + col);
-      unsigned char* dst = vin_buf + (wave * 64 + 64 * kWaves * i) * 16;   // wave-uniform
+      unsigned char* dst = vin_buf + (wave * 64 + 64 * NW * i) * 16;   // wave-uniform
       __builtin_amdgcn_global_load_lds((const MDBF_GLOBAL void*)src, (MDBF_LDS void*)dst, 16, 0, 0);
     }
   };
@@ -228,7 +236,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     if (BATCH || __builtin_expect(q != partial_block, 1)) return;   // (uniform)
 #pragma unroll
     for (int i = 0; i < kVinChunks; ++i) {
-      const int id = tid + 64 * kWaves * i;
+      const int id = tid + 64 * NW * i;
       const int c = (id & 15) ^ ((id >> 4) & 15);
       if (q * kBlockCols + c * 8 >= p.K) *reinterpret_cast<u32x4*>(vin_buf + id * 16) = u32x4{0u, 0u, 0u, 0u};
     }
@@ -237,7 +245,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     if (!kDma) {
 #pragma unroll
       for (int i = 0; i < kVinChunks; ++i) {
-        const int id = tid + 64 * kWaves * i;
+        const int id = tid + 64 * NW * i;
         const int tok = id >> 4, c = id & 15;
         const int col = q * kBlockCols + c * 8;
         const int b = tok0 + tok;
@@ -251,24 +259,28 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
         }
       }
     }
-    if (MODE != kGeneric) {
-      const int col = q * kBlockCols + (tid >> 1);
-      // rank 8: a row is one 16-byte vector; the half that would hold modes 8..15 becomes zero
-      const int hl = p.l >> 3;
-      const bool has_modes = (tid & 1) < hl;
-      ein_reg = ((const MDBF_GLOBAL u32x4*)p.Ein)[(size_t)min(col, p.K - 1) * hl + (has_modes ? (tid & 1) : 0)];
-      ein_ok = (col < p.K) && has_modes;               // (the zeros go in when the row is parked: a select here
-                                                       //  would make the wave wait for the load here)
-    } else {
-      const int colr = tid >> 1, half = tid & 1;
-      const int col = q * kBlockCols + colr;
-      float v[8];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int mode = half * 8 + t;
-        v[t] = (col < p.K && mode < p.l) ? load_as_float(p.Ein, (int64_t)col * p.l + mode, p.env_dt) : 0.f;
+    for (int i = 0; i < kEinChunks; ++i) {
+      const int id = tid + 64 * NW * i;
+      const int col = q * kBlockCols + (id >> 1);
+      if (MODE != kGeneric) {
+        // rank 8: a row is one 16-byte vector; the half that would hold modes 8..15 becomes zero
+        const int hl = p.l >> 3;
+        const bool has_modes = (id & 1) < hl;
+        ein_reg[i] = ((const MDBF_GLOBAL u32x4*)p.Ein)[(size_t)min(col, p.K - 1) * hl + (has_modes ? (id & 1) : 0)];
+        ein_ok[i] = (col < p.K) && has_modes;          // (the zeros go in when the row is parked: a select here
+                                                       //  would make the wave wait for the load here)
+      } else {
+        const int half = id & 1;
+        float v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int mode = half * 8 + t;
+          v[t] = (col < p.K && mode < p.l) ? load_as_float(p.Ein, (int64_t)col * p.l + mode, p.env_dt) : 0.f;
+        }
+        ein_reg[i] = u32x4{pack_half2(v[0], v[1]), pack_half2(v[2], v[3]), pack_half2(v[4], v[5]), pack_half2(v[6], v[7])};
+        ein_ok[i] = true;
       }
-      ein_reg = u32x4{pack_half2(v[0], v[1]), pack_half2(v[2], v[3]), pack_half2(v[4], v[5]), pack_half2(v[6], v[7])};
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) sw_next[r] = sbase[r][(size_t)min(q, KB - 1) * sstride[r]];
@@ -277,31 +289,38 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     if (!kDma) {
 #pragma unroll
       for (int i = 0; i < kVinChunks; ++i) {
-        const int id = tid + 64 * kWaves * i;
+        const int id = tid + 64 * NW * i;
         const int tok = id >> 4, c = id & 15;
         *reinterpret_cast<u32x4*>(vin_buf + tok * 256 + ((c ^ (tok & 15)) << 4)) = vin_reg[i];
       }
     }
-    *reinterpret_cast<u32x4*>(ein_buf + ein_row(tid >> 1) * 32 +
-                              (((tid & 1) ^ ((tid >> 5) & 1)) << 4)) =
-        u32x4{ein_ok ? ein_reg.x : 0u, ein_ok ? ein_reg.y : 0u, ein_ok ? ein_reg.z : 0u, ein_ok ? ein_reg.w : 0u};
+#pragma unroll
+    for (int i = 0; i < kEinChunks; ++i) {
+      const int id = tid + 64 * NW * i;
+      const u32x4 v = ein_reg[i];
+      const bool ok = ein_ok[i];
+      *reinterpret_cast<u32x4*>(ein_buf + ein_row(id >> 1) * 32 + (((id & 1) ^ ((id >> 5) & 1)) << 4)) =
+          u32x4{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
+    }
   };
 
   // Register staging runs two blocks ahead (a block is requested at the end of one iteration and parked at
   // the end of the next).  Direct staging runs one block ahead: block q + 1 is requested right after the
   // barrier that opens iteration q, into the buffer iteration q - 1 has just released, and every wave waits
   // for its own requests before it reaches the next barrier.
+  const int per_run = (KB + KS - 1) / KS;
+  const int q_lo = run * per_run, q_hi = min(q_lo + per_run, KB);    // (the last run may be shorter, or empty)
   uint32_t sw[R];
-  if (kDma) dma_block(0, vin_a);
-  fetch_block(0);
+  if (kDma) dma_block(min(q_lo, KB - 1), vin_a);
+  fetch_block(min(q_lo, KB - 1));
   stash_block(vin_a, ein_a);
 #pragma unroll
   for (int r = 0; r < R; ++r) sw[r] = sw_next[r];
   if (kDma) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    clear_tail(0, vin_a);
+    clear_tail(min(q_lo, KB - 1), vin_a);
   } else {
-    fetch_block(min(1, KB - 1));
+    fetch_block(min(q_lo + 1, KB - 1));
   }
 
   auto block = [&](int q, const unsigned char* vin, const unsigned char* ein, unsigned char* vin_next,
@@ -315,6 +334,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     // ---- per contraction step f (32 columns): rebuild the wave's pieces of W, wop[r] = B operand of the
     //      token product, then run the step over all token slabs.  The steps are independent of each other,
     //      which lets the rebuild of one step overlap the matrix-core work of the previous one.
+    if (KS == 1 || q < q_hi)                                   // (uniform; the barriers are kept)
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
       // A operands of the two reconstruction products: rows mi -> columns 32f + 8(mi/4) + mi%4 (+4)
@@ -366,9 +386,34 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     }
   };
 #pragma unroll 1
-  for (int q = 0; q < KB; q += 2) {
-    block(q, vin_a, ein_a, vin_b, ein_b);
-    if (q + 1 < KB) block(q + 1, vin_b, ein_b, vin_a, ein_a);
+  for (int i = 0; i < per_run; i += 2) {
+    block(q_lo + i, vin_a, ein_a, vin_b, ein_b);
+    if (i + 1 < per_run) block(q_lo + i + 1, vin_b, ein_b, vin_a, ein_a);
+  }
+
+  // ---- the runs' sums, added by the first run's waves in the order of the runs
+  if constexpr (KS > 1) {
+    constexpr int kRunBytes = NW * TB * R * 64 * 16;         // a run's sums
+    static_assert(kRunBytes <= KS * kVinBufBytes && (KS == 2 || 2 * kRunBytes <= KS * kVinBufBytes), "they take the staging buffers");
+    auto sums = [&](int s) { return reinterpret_cast<floatx4*>(s < 3 ? vin_lds_a + (s - 1) * kRunBytes : vin_lds_b); };
+    __syncthreads();                                           // every wave is done with the staging buffers
+    if (run > 0)
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int r = 0; r < R; ++r) sums(run)[((wave * TB + tb) * R + r) * 64 + lane] = acc[tb][r];
+    __syncthreads();
+    if (run > 0) return;
+#pragma unroll
+    for (int s = 1; s < KS; ++s)
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const floatx4 v = sums(s)[((wave * TB + tb) * R + r) * 64 + lane];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[tb][r][i] += v[i];
+        }
   }
 
   // ---- store: lane (r16, g) holds out[token 16 tb + 4g + i][row r16 of tile r]
@@ -840,11 +885,20 @@ static int launch_few_m(const FewArgs& a, hipStream_t s) {
   return evec ? launch_few_me<MODE, true>(a, s) : launch_few_me<MODE, false>(a, s);
 }
 
+// Runs over the contraction in a workgroup of a plan's launch (gemm_tiles_per_item has the measurements).
+template <int NW, int R>
+static int plan_runs(int nitems, int TB) {
+  if (TB > 2) return 1;
+  if (NW * R == 2) return TB == 1 ? 4 : 2;
+  if (NW * R == 4) return TB == 1 && nitems <= 288 ? 4 : 2;
+  return nitems <= 4096 ? 2 : 1;
+}
+
 // items_dev null: the single problem *p.  Else nitems work items of a plan, `p` describing the launch:
 // p->T = the longest token count among the problems.
-template <int R, int TB, int MODE, bool BATCH>
+template <int NW, int R, int TB, int MODE, bool BATCH, int KS>
 static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
-  const int rows_per_wg = kWaves * R;   // tiles
+  const int rows_per_wg = NW * R;   // tiles
   unsigned gx = BATCH ? (unsigned)nitems : (unsigned)((p->ntiles + rows_per_wg - 1) / rows_per_wg);
   unsigned gy = (unsigned)((p->T + 16 * TB - 1) / (16 * TB));
   if (!BATCH) {
@@ -852,29 +906,50 @@ static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p
     gx = kDies * ((total + kDies - 1) / kDies);
     gy = 1;
   }
-  hipLaunchKernelGGL((stage_gemm_kernel<R, TB, MODE, BATCH>), dim3(gx, gy), dim3(64 * kWaves), 0, s,
+  hipLaunchKernelGGL((stage_gemm_kernel<NW, R, TB, MODE, BATCH, KS>), dim3(gx, gy), dim3(64 * NW * KS), 0, s,
                      items_dev, *p);
   return (int)hipGetLastError();
 }
 
 template <int R, int TB, int MODE>
-static int launch_rtm(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
-  if (items_dev) {
-    // plans: items of kPlanR tiles per wave, short token slabs
-    if constexpr (R == kPlanR && TB <= 4) return launch_rtmb<R, TB, MODE, true>(items_dev, nitems, p, s);
-    return (int)hipErrorInvalidValue;
-  } else {
-    if constexpr (TB >= 6 || (R == 1 && MODE != kGeneric)) return launch_rtmb<R, TB, MODE, false>(nullptr, 0, p, s);
-    return (int)hipErrorInvalidValue;
+static int launch_rtm(const StageProb* p, hipStream_t s) {
+  if constexpr (TB >= 6 || (R == 1 && MODE != kGeneric)) return launch_rtmb<kWaves, R, TB, MODE, false, 1>(nullptr, 0, p, s);
+  return (int)hipErrorInvalidValue;
+}
+
+// a plan's work items, of NW R row tiles
+template <int NW, int R, int TB, int MODE>
+static int launch_items_rtm(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
+  const int ks = plan_runs<NW, R>(nitems, TB);
+  if constexpr (TB == 1 && NW * R <= 4) {
+    if (ks == 4) return launch_rtmb<NW, R, TB, MODE, true, 4>(items_dev, nitems, p, s);
   }
+  if constexpr (TB <= 2) {
+    if (ks >= 2) return launch_rtmb<NW, R, TB, MODE, true, 2>(items_dev, nitems, p, s);
+  }
+  if constexpr (TB > 2 || NW * R == 8) return launch_rtmb<NW, R, TB, MODE, true, 1>(items_dev, nitems, p, s);
+  return (int)hipErrorInvalidValue;
+}
+template <int NW, int R, int TB>
+static int launch_items_rt(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
+  if (mode == kGeneric) return launch_items_rtm<NW, R, TB, kGeneric>(items_dev, nitems, p, s);
+  if (mode == MDBF_F16) return launch_items_rtm<NW, R, TB, MDBF_F16>(items_dev, nitems, p, s);
+  if (mode == MDBF_BF16) return launch_items_rtm<NW, R, TB, MDBF_BF16>(items_dev, nitems, p, s);
+  return launch_items_rtm<NW, R, TB, MDBF_F32>(items_dev, nitems, p, s);
+}
+template <int NW, int R>
+static int launch_items_r(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
+  if (p->T > 32) return launch_items_rt<NW, R, 4>(items_dev, nitems, mode, p, s);
+  if (p->T > 16) return launch_items_rt<NW, R, 2>(items_dev, nitems, mode, p, s);
+  return launch_items_rt<NW, R, 1>(items_dev, nitems, mode, p, s);
 }
 
 template <int R, int TB>
-static int launch_rt(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
-  if (mode == kGeneric) return launch_rtm<R, TB, kGeneric>(items_dev, nitems, p, s);
-  if (mode == MDBF_F16) return launch_rtm<R, TB, MDBF_F16>(items_dev, nitems, p, s);
-  if (mode == MDBF_BF16) return launch_rtm<R, TB, MDBF_BF16>(items_dev, nitems, p, s);
-  return launch_rtm<R, TB, MDBF_F32>(items_dev, nitems, p, s);
+static int launch_rt(int mode, const StageProb* p, hipStream_t s) {
+  if (mode == kGeneric) return launch_rtm<R, TB, kGeneric>(p, s);
+  if (mode == MDBF_F16) return launch_rtm<R, TB, MDBF_F16>(p, s);
+  if (mode == MDBF_BF16) return launch_rtm<R, TB, MDBF_BF16>(p, s);
+  return launch_rtm<R, TB, MDBF_F32>(p, s);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -997,26 +1072,40 @@ int launch_half_copies(const HalfMatrix* m, int count, hipStream_t s) {
   return (int)hipGetLastError();
 }
 
-int gemm_tiles_per_item() { return gemm::kWaves * gemm::kPlanR; }
+// Row tiles per work item of a plan whose launch has launch_tiles of them in all, at most max_tokens tokens each.  Small
+// plans leave most of the device idle with items of eight tiles and one run over the contraction, and a block of such
+// a run takes its 0.6 us however few there are: smaller items, and two or four runs of the contraction side by side in
+// a workgroup.  Up to 16 tokens, per pass with (tiles per item)/(runs):
+//   1 attention layer (166 and 256 tiles): 8/1 37.7, 4/4 21.3, 2/4 17.6 us; 4 of them: 39.2, 21.8, 24.5; 16: 55.8, 4/2
+//   48.9, 8/2 50.1; 32: 8/1 79.1, 8/2 78.8, 4/2 87.0
+//   a decoder layer (1432 and 2656): 8/1 97.2, 8/2 66.0, 4/2 55.5, 4/4 55.8; two: 109, 85.4, 81.9, 92.4; 8: 252, 243, 263;
+//   16: 447, 437, 504; 32: 820, 838, 966
+// 17 to 32: an attention layer 8/1 47.5, 4/2 26.0, 2/2 24.4; a decoder layer 119, 68.0, 76.1; 4: 184, 8/2 178, 189.
+// 33 to 64 (one run: two would take the room of a second workgroup): 62.4, 4/1 45.2; 150, 118.
+int gemm_tiles_per_item(long launch_tiles, int max_tokens) {
+  if (max_tokens <= 16) return launch_tiles <= 512 ? 2 : launch_tiles <= 5400 ? 4 : 8;
+  if (max_tokens <= 32) return launch_tiles <= 300 ? 2 : launch_tiles <= 2700 ? 4 : 8;
+  return launch_tiles <= 2700 ? 4 : 8;
+}
 int gemm_plan_max_tokens() { return 64; }   // plans with longer problems launch the single-problem kernel per problem
 
 int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
-  if (items_dev) {
-    if (p->T > 32) return gemm::launch_rt<gemm::kPlanR, 4>(items_dev, nitems, mode, p, s);
-    if (p->T > 16) return gemm::launch_rt<gemm::kPlanR, 2>(items_dev, nitems, mode, p, s);
-    return gemm::launch_rt<gemm::kPlanR, 1>(items_dev, nitems, mode, p, s);
+  if (items_dev) {       // p->ntiles: the row tiles per item the plan was cut with
+    if (p->ntiles == 2) return gemm::launch_items_r<2, 1>(items_dev, nitems, mode, p, s);
+    if (p->ntiles == 4) return gemm::launch_items_r<4, 1>(items_dev, nitems, mode, p, s);
+    return gemm::launch_items_r<4, 2>(items_dev, nitems, mode, p, s);
   }
   mode = gemm_load_mode(*p);
   const bool vectors = mode != gemm::kGeneric;
   if (p->T > kFewMaxTokens || (p->T > 32 && vectors)) {
     const LongShape f = long_problem_shape(*p, vectors);
-    if (f.R == 1 && f.TB == 2) return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
-    if (f.R == 1) return gemm::launch_rt<1, 4>(nullptr, 0, mode, p, s);
-    if (f.TB == 6) return gemm::launch_rt<2, 6>(nullptr, 0, mode, p, s);
-    if (f.TB == 7) return gemm::launch_rt<2, 7>(nullptr, 0, mode, p, s);
-    return gemm::launch_rt<2, 8>(nullptr, 0, mode, p, s);
+    if (f.R == 1 && f.TB == 2) return gemm::launch_rt<1, 2>(mode, p, s);
+    if (f.R == 1) return gemm::launch_rt<1, 4>(mode, p, s);
+    if (f.TB == 6) return gemm::launch_rt<2, 6>(mode, p, s);
+    if (f.TB == 7) return gemm::launch_rt<2, 7>(mode, p, s);
+    return gemm::launch_rt<2, 8>(mode, p, s);
   }
-  if (p->T > 16 && vectors) return gemm::launch_rt<1, 2>(nullptr, 0, mode, p, s);
+  if (p->T > 16 && vectors) return gemm::launch_rt<1, 2>(mode, p, s);
   const SplitGeom one = {p->KB, 1, 0};                          // (no room for partial sums)
   return launch_stage_gemm_few(p, one, nullptr, 0, s);
 }

@@ -719,6 +719,36 @@ def test_residual_stack_in_a_plan(gpu):
     assert orc.max_rel_error(Y.cpu().numpy(), ref) <= TOL
 
 
+PLAN_FORMS = [
+    # copies of the layers, tokens: 2, 4 and 8 row tiles per item, one to four runs over the contraction, each slab count
+    (1, 16), (1, 9), (1, 32), (1, 64), (8, 5), (8, 17), (8, 33), (16, 16), (45, 4), (45, 40), (260, 6),
+]
+
+
+@pytest.mark.parametrize("copies,T", PLAN_FORMS)
+@pytest.mark.parametrize("l,x_dtype", [(16, "f16"), (8, "bf16"), (5, "f32")])
+def test_item_forms_of_many_token_plans(gpu, copies, T, l, x_dtype):
+    """Contractions of one block (three of four runs are empty), five and nine; row tiles that do not fill the last
+    item.  Against the oracle at the fp16 gate, copies among each other bit for bit."""
+    torch, mb = gpu
+    layers, Xs, Ys, refs = [], [], [], []
+    for i, (m, n, k) in enumerate([(2100, 72, 600), (52, 1100, 120)]):
+        L = synth.make_layer(m, n, k, l, seed=40 + i, env_dtype="f16", env_kind="unit", signed_env=True)
+        X = synth.make_activations(n, T, seed=50 + i, x_dtype=x_dtype)
+        refs.append(orc.forward_factored(*_oracle_args(L), X))
+        dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, x_dtype)
+        layers += [dl] * copies
+        Xs += [Xd] * copies
+        Ys.append(torch.zeros((copies, T, m), dtype=torch.float32, device="cuda:0"))
+    plan = mb.BatchPlan(layers, Xs, [y for Y in Ys for y in Y])
+    assert plan.kernel(1) == "stage_gemm_kernel" and plan.launches() == 2
+    for _ in range(2):
+        plan.run()
+    for Y, ref in zip(Ys, refs):
+        assert orc.max_rel_error(Y[0].cpu().numpy(), ref) <= TOL
+        assert torch.equal(Y, Y[:1].expand_as(Y))
+
+
 # ---------------------------------------------------------------- the synthetic decoder stack
 @pytest.mark.parametrize("budget", ["1.0", "1.5", "2.0"])
 @pytest.mark.parametrize("T", [1, 8])
