@@ -141,10 +141,12 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * Default arithmetic: fp32 accumulation on the matrix cores; z kept in fp32 with one token.  A single one-token call
  * rebuilds the factors S_A o (A Q^T), S_B o (G B^T) piece by piece in fp32 and applies them to the unrounded activations
  * in fp32, in two launches: what remains is the rounding of fp32 sums, added in a fixed order, so repeated calls return
- * the same bits.  Plans with one to three tokens quantise the l-way scaled activations (b^(s) o x and q^(t) o z) once --
+ * the same bits.  Plans with one to three tokens do the same if their layers are of other ranks than 16, of mixed ones or
+ * not of fp16 envelopes, unless they are large and the block-scaled variant serves them.  The other plans quantise the
+ * l-way scaled activations (b^(s) o x and q^(t) o z) once --
  * to three fp6 limbs under a shared power-of-two scale per 32 values (about 13 bits; the block-scaled variant, taken by
- * large plans of rank 8 or 16 with fp16 envelopes), or to fp16 (small plans, MDBF_FLAG_FP16_STAGED) -- and contract them
- * with the sign words.  Two tokens or more: the factors
+ * large plans of rank 8 or 16 with fp16 envelopes), or to fp16 (small plans of rank 16, MDBF_FLAG_FP16_STAGED) -- and
+ * contract them with the sign words.  Two tokens or more: the factors
  * S_A o (A Q^T), S_B o (G B^T) are rebuilt piece by piece in fp16 and applied as dense products to the
  * fp16-rounded activations (x and z; z is stored in fp16 between the two products).  Magnitudes above
  * 65504 in those fp16 quantities overflow.  A token's result is the same bits in every single call of 2 to 16 tokens

@@ -553,6 +553,20 @@ static void balance_mx_items(WorkItem* items, int n, int max_wgs) {
   }
 }
 
+// Plans of one to three tokens on stage_one_kernel (two launches, fp32).  Against the block-scaled kernel, whose three
+// launches are paid off by large plans only: 5 us and 0.27 us per 1000 pieces of 16 rows x 128 columns x token, against 9 us
+// and 0.95 us for each stage (two blocks, or the envelope rows) of the longest item, token by token, as long as the items
+// fit one round of workgroups.  Rank 8, one token, us per pass: one attention layer 34.5 -> 9.8, four 35.0 -> 14.5, sixteen
+// 36.1 against 41.4; a decoder layer 60.2 -> 38.5, two 61.5 against 61.2; three tokens: four attention layers 85.9 ->
+// 31.1, a decoder layer 162 -> 80.9.  Against the general kernel always (224 matrices of rank 8: 2.4 ms there).
+static bool one_plan_pays(long pieces, int max_tokens, const int max_blocks[2], const int mx[2], const int fast[2]) {
+  if (fast[0] && fast[1]) return false;           // the fp16-staged kernels' plans stay there
+  for (int s = 0; s < 2; ++s)
+    if (!mx[s] && !fast[s]) return true;
+  const long stages = (max_blocks[0] + 1) / 2 + (max_blocks[1] + 1) / 2 + 2;
+  return 5.0 + 0.00027 * (double)pieces < 9.0 + 0.95 * (double)(max_tokens * stages);
+}
+
 static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, size_t* ws_bytes) {
   if (count < 1 || !layers) return MDBF_EINVAL;
   long tiles[2] = {0, 0};
@@ -576,6 +590,10 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
   // a stage whose problems all qualify for the block-scaled variant is cut into that variant's items
   int mx[2] = {1, 1};
   int all_fast[2] = {1, 1};
+  bool one = true;               // every problem is one for stage_one_kernel, with envelopes of one type
+  int rank = layers[0].desc.l;
+  long pieces = 0;               // 16 x 128 pieces of all tokens
+  int max_blocks[2] = {0, 0};
   for (int i = 0; i < count; ++i) {
     const mdbf_layer_t* L = &layers[i];
     StageProb sp[2];
@@ -586,7 +604,12 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
       if (!use_mx(sp[s], L->desc.flags) || (mx[s] != 1 && mx[s] != sp[s].l)) mx[s] = 0;
       else mx[s] = sp[s].l;
       if (!stage_is_fast(sp[s])) all_fast[s] = 0;
+      one = one && L->T < kGemmMinTokensPlan && stage_is_one(sp[s]) && sp[s].env_dt == layers[0].desc.env_dtype;
+      if (sp[s].l != rank) rank = kOneMixedRanks;
+      pieces += (long)sp[s].ntiles * sp[s].KB * L->T;
+      max_blocks[s] = std::max(max_blocks[s], (int)sp[s].KB);
     }
+    if (L->desc.flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_BLOCK_SCALED | MDBF_FLAG_FP16_STAGED)) one = false;
   }
   int forced = 0, many = 0;
   for (int i = 0; i < count; ++i) {
@@ -597,6 +620,8 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
   h->gemm = (many == count && !precise && forced != count) ? 1 : 0;
   for (int s = 0; s < 2; ++s)
     if (h->gemm || (forced != count && !mx_worthwhile(tiles[s]) && all_fast[s])) mx[s] = 0;
+  h->one = one && one_plan_pays(pieces, h->max_tokens, max_blocks, mx, all_fast) ? rank + 32 * layers[0].desc.env_dtype : 0;
+  if (h->one) mx[0] = mx[1] = 0;
   // otherwise one tile count per work item for both stages keeps one kernel instantiation per plan
   const int tpi_fp16 = mfma_tiles_per_item(tiles[0] < tiles[1] ? tiles[0] : tiles[1]);
   long nitems[2] = {0, 0};
@@ -611,7 +636,7 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
       }
       tpi_mx = mx_pick_item_tiles(count, nt.data(), kb.data());
     }
-    h->tiles_per_item[s] = h->gemm ? gemm_tiles_per_item(tiles[s], h->max_tokens) : mx[s] ? tpi_mx : tpi_fp16;
+    h->tiles_per_item[s] = h->one ? one_item_tiles() : h->gemm ? gemm_tiles_per_item(tiles[s], h->max_tokens) : mx[s] ? tpi_mx : tpi_fp16;
   }
   h->fuse2 = (!precise && !h->gemm && h->mx[0] != 0 && h->mx[0] == h->mx[1]) ? 1 : 0;
   for (int i = 0; i < count; ++i) {
@@ -769,6 +794,15 @@ int mdbf_forward_batch_part(const void* plan_host, const void* plan_dev, size_t 
     }
     return MDBF_OK;
   }
+  if (h.one) {
+    for (int st = 0; st < 2; ++st) {
+      if (!(stages & (1 << st)) || !(kernels & 2)) continue;
+      int e = launch_stage_one_items((const WorkItem*)(dev + h.items_off[st]), h.nitems[st], h.one >> 5, h.one & 31,
+                                     h.max_tokens, s);
+      if (e) return hip_fail(e);
+    }
+    return MDBF_OK;
+  }
   for (int st = 0; st < 2; ++st) {
     const StageProb* probs = (const StageProb*)(dev + h.probs_off[st]);
     const WorkItem* items = (const WorkItem*)(dev + h.items_off[st]);
@@ -807,6 +841,7 @@ const char* mdbf_batch_plan_kernel(const void* plan_host, size_t plan_bytes, int
   const int st = stage - 1;
   if (h.precise) return "stage_precise_kernel";
   if (h.gemm) return "stage_gemm_kernel";
+  if (h.one) return "stage_one_kernel";
   if (h.mx[st]) return "stage_mx_kernel";
   if (h.fast[st]) return "stage_fast_kernel";
   return "stage_generic_kernel";
@@ -818,7 +853,7 @@ int mdbf_batch_plan_launches(const void* plan_host, size_t plan_bytes) {
   memcpy(&h, plan_host, sizeof(h));
   if (h.magic != kPlanMagic || h.count < 1) return MDBF_EINVAL;
   if (h.gemm) return h.max_tokens > gemm_plan_max_tokens() ? 2 * h.count : 2;
-  if (h.precise) return 2;
+  if (h.precise || h.one) return 2;
   int n = 0;
   for (int st = 0; st < 2; ++st) {
     if (h.mx[st]) n += (st == 1 && h.fuse2) ? 1 : 2;

@@ -116,7 +116,8 @@ struct PlanHeader {
   uint64_t total_bytes;
   int32_t fuse2;              // both stages run the block-scaled variant at one rank: the first stage's launch
                               // writes the second stage's activation records (no scale-in launch for stage 2)
-  int32_t pad_;
+  int32_t one;                // few tokens on stage_one_kernel, two launches: the layers' rank or kOneMixedRanks, and
+                              // 32 times the type of their envelopes; else 0
 };
 constexpr uint32_t kPlanMagic = 0x4D444246u;  // "MDBF"
 
@@ -190,6 +191,11 @@ bool stage_is_one(const StageProb& p);       // its operands are addressable wit
 // part_out: g.nsplit vectors part_out_ld apart (unused when g.nsplit == 1: the result goes to p->out).
 int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in, int nsplit_in, int64_t part_in_ld,
                      float* part_out, int64_t part_out_ld, hipStream_t s);
+// The same for the work items of a plan with few tokens (at most one_item_tiles() row tiles each), their envelopes all of
+// one type, of one rank or of several (kOneMixedRanks).
+constexpr int kOneMixedRanks = MDBF_MAX_L + 1;
+int one_item_tiles();
+int launch_stage_one_items(const WorkItem* items_dev, int nitems, int env_dt, int rank, int max_tokens, hipStream_t s);
 constexpr int kMaxPreTokens = 16;   // token counts up to this use the scale-in kernel
 // true if the fast matrix-core variant can run the problem (l == 16, fp16 envelopes, K % 8 == 0,
 // 16-byte aligned activation rows); otherwise the general variant is used

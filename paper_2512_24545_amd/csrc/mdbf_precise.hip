@@ -102,8 +102,11 @@ typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   //
 
 constexpr int kMaxWaves = 16;       // waves of a workgroup, each with blocks of its own
 
+constexpr int kOneItemTiles = 8;    // row tiles of a plan's work item, one workgroup each
+
 struct OneArgs {
   StageProb p;
+  const WorkItem* items;            // a plan's: workgroup (i, t, b) = row tile t of item i, token b; null: p
   int32_t bs, nsplit;               // blocks per workgroup, workgroups per row tile
   int32_t nsplit_in;
   const float* part_in;             // PARTS: vin[j] = sum over s < nsplit_in of part_in[s * part_in_ld + j]
@@ -281,17 +284,27 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int ENV, int M, bool VEC, bool PARTS>
+template <int ENV, int M, bool VEC, bool PARTS, bool BATCH>
 __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   typedef EinBlock<ENV, M> EB;
-  const StageProb& p = a.p;
+  int tile = blockIdx.x, split = blockIdx.y, token = 0;
+  if constexpr (BATCH) {
+    const WorkItem& w = a.items[blockIdx.x];             // (uniform: scalar loads)
+    if ((int)blockIdx.y >= w.ntiles || (int)blockIdx.z >= w.p.T) return;
+    tile = w.tile0 + (int)blockIdx.y;
+    split = 0;
+    token = blockIdx.z;
+  }
+  const StageProb p = BATCH ? a.items[blockIdx.x].p : a.p;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nwaves = (int)blockDim.x >> 6;
   const int r16 = lane & 15, g = lane >> 4;
-  const int tile = blockIdx.x, split = blockIdx.y;      // a row tile; the split's blocks q_lo, q_lo + nwaves, ... are this wave's
-  const int q_lo = split * a.bs + wave, q_hi = min((split + 1) * a.bs, p.KB);
+  // this wave's blocks: q_lo, q_lo + nwaves, ...
+  const int bs = BATCH ? p.KB : a.bs;
+  const int q_lo = split * bs + wave, q_hi = min((split + 1) * bs, p.KB);
+  const uint32_t x0 = BATCH ? (uint32_t)token * (uint32_t)p.vin_ld : 0u;   // the token's first element
   float* xs = reinterpret_cast<float*>(smem) + wave * (2 * kBlockCols);   // two blocks' activations, this wave's only
   const MDBF_GLOBAL uint32_t* sbase = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(tile, p.KB) + lane;
   const size_t sstride = (size_t)group_tiles(tile, p.ntiles) * 64u;
@@ -312,7 +325,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
 #pragma unroll
         for (int s = 0; s < kOneMaxSplits; ++s) b.x[h][s] = at<uint32_t>(a.part_in + min(s, a.nsplit_in - 1) * a.part_in_ld, col);
       } else {
-        b.x[h][0] = at<uint32_t>(p.vin, (col << xshift) >> 2);
+        b.x[h][0] = at<uint32_t>(p.vin, ((x0 + col) << xshift) >> 2);   // (the aligned word that holds it)
       }
     }
     load_ein<ENV, M, VEC>(p, q, lane, b.ein);
@@ -328,7 +341,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
 #pragma unroll
         for (int s = 1; s < kOneMaxSplits; ++s) x += s < a.nsplit_in ? __builtin_bit_cast(float, b.x[h][s]) : 0.f;
       } else {
-        const uint32_t half = (min(col, p.K - 1) & 1) ? b.x[h][0] >> 16 : b.x[h][0] & 0xFFFFu;
+        const uint32_t half = ((x0 + min(col, p.K - 1)) & 1u) ? b.x[h][0] >> 16 : b.x[h][0] & 0xFFFFu;
         const float xh = (float)__builtin_bit_cast(_Float16, (uint16_t)half);
         x = p.vin_dt == MDBF_F32 ? __builtin_bit_cast(float, b.x[h][0]) : p.vin_dt == MDBF_F16 ? xh : __builtin_bit_cast(float, half << 16);
       }
@@ -343,8 +356,8 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
     if (!VEC && (int64_t)(p.K - (q + 1) * kBlockCols + 1) * p.l < 16) ein_tail<ENV, M>(p, q, lane, b.ein);
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
-      const floatx4 x0 = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g);
-      const floatx4 x1 = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g + 4);
+      const floatx4 xa = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g);
+      const floatx4 xb = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g + 4);
       floatx4 d[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -367,7 +380,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
         const int bit = 8 * (f >> 1) + 4 * (f & 1) + (t >> 1) + 16 * (t & 1);
         const float ev = t < 4 ? d[0][t & 3] : d[1][t & 3];
         const float sv = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, ev) ^ ((b.sw << (31 - bit)) & 0x80000000u));
-        acc[t & 1] = fmaf(sv, t < 4 ? x0[t & 3] : x1[t & 3], acc[t & 1]);
+        acc[t & 1] = fmaf(sv, t < 4 ? xa[t & 3] : xb[t & 3], acc[t & 1]);
       }
       // (a step at a time: without this the products of a block are all made first, in 64 registers)
       asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
@@ -409,32 +422,38 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
     for (int w = 1; w < nwaves; ++w) sum += red[w * kTileRows + tid];
     const int row = tile * kTileRows + tid;
     if (row < p.rows) {
-      if (a.nsplit == 1) emit_result(p.out, row, p.out_dt, sum, p.flags);
+      if (BATCH || a.nsplit == 1) emit_result(p.out, (int64_t)token * p.out_ld + row, p.out_dt, sum, p.flags);
       else ((MDBF_GLOBAL float*)a.part_out)[split * a.part_out_ld + row] = sum;
     }
   }
 }
 
 template <int ENV, int M, bool VEC>
-static int launch_emv(const OneArgs& a, int waves, hipStream_t s) {
-  const dim3 grid((unsigned)a.p.ntiles, (unsigned)a.nsplit), block(64u * (unsigned)waves);
+static int launch_emv(const OneArgs& a, dim3 grid, int waves, hipStream_t s) {
+  const dim3 block(64u * (unsigned)waves);
   const size_t smem = (size_t)waves * (2 * kBlockCols + kTileRows) * 4u;
-  if (a.part_in) hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, true>), grid, block, smem, s, a);
-  else hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, false>), grid, block, smem, s, a);
+  if (a.items) hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, false, true>), grid, block, smem, s, a);
+  else if (a.part_in) hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, true, false>), grid, block, smem, s, a);
+  else hipLaunchKernelGGL((stage_one_kernel<ENV, M, VEC, false, false>), grid, block, smem, s, a);
   return (int)hipGetLastError();
 }
 template <int ENV, int M>
-static int launch_em(const OneArgs& a, int waves, hipStream_t s) {
-  if (ENV != MDBF_BF16 && a.p.l == M) return launch_emv<ENV, M, ENV != MDBF_BF16>(a, waves, s);
-  return launch_emv<ENV, M, false>(a, waves, s);
+static int launch_em(const OneArgs& a, dim3 grid, int waves, hipStream_t s) {
+  if (ENV != MDBF_BF16 && a.p.l == M) return launch_emv<ENV, M, ENV != MDBF_BF16>(a, grid, waves, s);
+  return launch_emv<ENV, M, false>(a, grid, waves, s);
 }
 template <int ENV>
-static int launch_e(const OneArgs& a, int waves, hipStream_t s) {
+static int launch_e(const OneArgs& a, dim3 grid, int waves, hipStream_t s) {
   if constexpr (ENV == MDBF_F32) {
-    if (a.p.l <= 4) return launch_em<ENV, 4>(a, waves, s);
+    if (a.p.l <= 4) return launch_em<ENV, 4>(a, grid, waves, s);
   }
-  if (a.p.l <= 8) return launch_em<ENV, 8>(a, waves, s);
-  return launch_em<ENV, 16>(a, waves, s);
+  if (a.p.l <= 8) return launch_em<ENV, 8>(a, grid, waves, s);
+  return launch_em<ENV, 16>(a, grid, waves, s);
+}
+static int launch(const OneArgs& a, dim3 grid, int waves, hipStream_t s) {
+  if (a.p.env_dt == MDBF_F16) return launch_e<MDBF_F16>(a, grid, waves, s);
+  if (a.p.env_dt == MDBF_BF16) return launch_e<MDBF_BF16>(a, grid, waves, s);
+  return launch_e<MDBF_F32>(a, grid, waves, s);
 }
 
 }  // namespace one
@@ -464,13 +483,17 @@ OneGeom one_geom(int ntiles, int KB, size_t max_splits) {
 
 bool stage_is_one(const StageProb& p) {
   const int64_t row = (int64_t)p.l * dtype_size(p.env_dt), most = (int64_t)1 << 32;
-  return p.K < (1 << 30) && p.rows < (1 << 30) && p.K * row < most && p.rows * row < most;
+  return p.K < (1 << 30) && p.rows < (1 << 30) && p.K * row < most && p.rows * row < most &&
+         (p.T == 1 || p.vin_ld < ((int64_t)1 << 30) / p.T);
 }
+
+int one_item_tiles() { return one::kOneItemTiles; }
 
 int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in, int nsplit_in, int64_t part_in_ld,
                      float* part_out, int64_t part_out_ld, hipStream_t s) {
   one::OneArgs a;
   a.p = *p;
+  a.items = nullptr;
   a.bs = g.bs;
   a.nsplit = g.nsplit;
   a.nsplit_in = nsplit_in;
@@ -478,9 +501,16 @@ int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in,
   a.part_in_ld = part_in_ld;
   a.part_out = part_out;
   a.part_out_ld = part_out_ld;
-  if (p->env_dt == MDBF_F16) return one::launch_e<MDBF_F16>(a, g.waves, s);
-  if (p->env_dt == MDBF_BF16) return one::launch_e<MDBF_BF16>(a, g.waves, s);
-  return one::launch_e<MDBF_F32>(a, g.waves, s);
+  return one::launch(a, dim3((unsigned)p->ntiles, (unsigned)g.nsplit), g.waves, s);
+}
+
+int launch_stage_one_items(const WorkItem* items_dev, int nitems, int env_dt, int rank, int max_tokens, hipStream_t s) {
+  one::OneArgs a = {};
+  a.p.env_dt = env_dt;
+  a.p.l = rank;                  // (chooses the kernel; kOneMixedRanks: room for 16 modes, rows of any length)
+  a.items = items_dev;
+  const int waves = (int64_t)nitems * one::kOneItemTiles * max_tokens <= 256 ? one::kMaxWaves : 8;
+  return one::launch(a, dim3((unsigned)nitems, one::kOneItemTiles, (unsigned)max_tokens), waves, s);
 }
 
 }  // namespace mdbf

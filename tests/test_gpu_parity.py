@@ -749,6 +749,41 @@ def test_item_forms_of_many_token_plans(gpu, copies, T, l, x_dtype):
         assert torch.equal(Y, Y[:1].expand_as(Y))
 
 
+ONE_PLANS = [
+    # specs (m, n, k, l), envelopes, activations, tokens: ranks of every class and mixed ones, odd row pitches, contractions of
+    # one block and of more than one per wave, row tiles that do not fill the last item
+    ([(530, 2101, 1107, 8), (16, 100, 40, 8)], "f16", "f16", 3), ([(300, 257, 2100, 3), (130, 129, 5, 3)], "bf16", "bf16", 2),
+    ([(260, 300, 130, 4), (200, 1030, 515, 2)], "f32", "f32", 3), ([(256, 256, 128, 4), (530, 2100, 1100, 16), (100, 1030, 200, 8)], "f16", "bf16", 1),
+    ([(90, 700, 650, 16), (33, 1, 3, 1)], "f32", "f16", 2), ([(40, 131, 200, 15), (40, 131, 200, 9)], "bf16", "f32", 3),
+]
+
+
+@pytest.mark.parametrize("specs,env_dtype,x_dtype,T", ONE_PLANS)
+def test_plans_of_few_tokens_in_fp32(gpu, specs, env_dtype, x_dtype, T):
+    """Plans that neither the fp16-staged nor (at their size) the block-scaled kernel serves: the arithmetic of single
+    one-token calls, the gate of the fp32 path; an infinity stays in its layer and token."""
+    torch, mb = gpu
+    layers, Xs, Ys, refs = [], [], [], []
+    for i, (m, n, k, l) in enumerate(specs):
+        L = synth.make_layer(m, n, k, l, seed=70 + i, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+        X = synth.make_activations(n, T, seed=80 + i, x_dtype=x_dtype)
+        refs.append(orc.forward_factored(*_oracle_args(L), X))
+        layers.append(mb.DeviceLayer.from_host(L))
+        Xs.append(_to_dev(torch, X, x_dtype))
+        Ys.append(torch.zeros((T, m + 3), dtype=torch.float32, device="cuda:0")[:, :m])
+    plan = mb.BatchPlan(layers, Xs, Ys)
+    assert plan.kernel(1) == plan.kernel(2) == "stage_one_kernel" and plan.launches() == 2
+    plan.run()
+    for Y, ref in zip(Ys, refs):
+        assert orc.max_rel_error(Y.cpu().numpy(), ref) <= 2e-5
+    first = [Y.clone() for Y in Ys]
+    Xs[0][T - 1, -1] = float("inf")
+    plan.run()
+    assert not torch.isfinite(Ys[0][T - 1]).any() and torch.equal(Ys[0][:T - 1], first[0][:T - 1])
+    for Y, before in zip(Ys[1:], first[1:]):
+        assert torch.equal(Y, before)
+
+
 # ---------------------------------------------------------------- the synthetic decoder stack
 @pytest.mark.parametrize("budget", ["1.0", "1.5", "2.0"])
 @pytest.mark.parametrize("T", [1, 8])
