@@ -594,6 +594,8 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
   int rank = layers[0].desc.l;
   long pieces = 0;               // 16 x 128 pieces of all tokens
   int max_blocks[2] = {0, 0};
+  long blocks[2] = {0, 0};
+  bool all_pre = true;
   for (int i = 0; i < count; ++i) {
     const mdbf_layer_t* L = &layers[i];
     StageProb sp[2];
@@ -608,6 +610,8 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
       if (sp[s].l != rank) rank = kOneMixedRanks;
       pieces += (long)sp[s].ntiles * sp[s].KB * L->T;
       max_blocks[s] = std::max(max_blocks[s], (int)sp[s].KB);
+      blocks[s] += (long)sp[s].ntiles * sp[s].KB;
+      all_pre = all_pre && sp[s].xs;
     }
     if (L->desc.flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_BLOCK_SCALED | MDBF_FLAG_FP16_STAGED)) one = false;
   }
@@ -623,7 +627,9 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
   h->one = one && one_plan_pays(pieces, h->max_tokens, max_blocks, mx, all_fast) ? rank + 32 * layers[0].desc.env_dtype : 0;
   if (h->one) mx[0] = mx[1] = 0;
   // otherwise one tile count per work item for both stages keeps one kernel instantiation per plan
-  const int tpi_fp16 = mfma_tiles_per_item(tiles[0] < tiles[1] ? tiles[0] : tiles[1]);
+  const int tpi_fp16 = all_fast[0] && all_fast[1] && all_pre
+                           ? mfma_plan_tiles_per_item(tiles, blocks, max_blocks, h->max_tokens)
+                           : mfma_tiles_per_item(tiles[0] < tiles[1] ? tiles[0] : tiles[1]);
   long nitems[2] = {0, 0};
   for (int s = 0; s < 2; ++s) {
     h->mx[s] = mx[s];
@@ -809,6 +815,7 @@ int mdbf_forward_batch_part(const void* plan_host, const void* plan_dev, size_t 
     StageProb dummy;
     memset(&dummy, 0, sizeof(dummy));
     dummy.ntiles = h.tiles_per_item[st];
+    dummy.T = h.max_tokens;
     if (!(stages & (1 << st))) continue;
     const bool pre_k = (kernels & 1) != 0, main_k = (kernels & 2) != 0;
     int e = 0;

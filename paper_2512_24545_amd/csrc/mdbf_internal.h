@@ -145,7 +145,8 @@ int launch_pad_envelope(const void* src, int rows, int l, void* dst, int l_to, i
 int launch_stream_read(const void* src, size_t bytes, uint32_t* sink, int sink_words, hipStream_t s);
 int launch_stage_precise(const StageProb* probs_dev, const WorkItem* items_dev, int nitems,
                          const StageProb* single, hipStream_t s);
-// pre: the problems' xs buffers hold the pre-scaled activations (launch_scale_in ran before)
+// pre: the problems' xs buffers hold the pre-scaled activations (launch_scale_in ran before); probs_dev: a plan, single->T
+// its longest token count
 int launch_stage_mfma(const StageProb* probs_dev, const WorkItem* items_dev, int nitems, int tiles_per_item,
                       const StageProb* single, bool pre, hipStream_t s);
 int launch_stage_generic(const StageProb* probs_dev, const WorkItem* items_dev, int nitems, int tiles_per_item,
@@ -203,6 +204,9 @@ bool stage_is_fast(const StageProb& p);
 // tiles per work item the matrix-core kernel wants for a problem with `ntiles` row tiles when
 // `total_tiles` tiles are in flight in the same launch
 int mfma_tiles_per_item(long total_tiles);
+// the same for a plan with pre-scaled activations: per stage the row tiles, the sum over them of their contractions' blocks
+// and the longest contraction
+int mfma_plan_tiles_per_item(const long tiles[2], const long blocks[2], const int max_blocks[2], int max_tokens);
 
 // Many-token variant: the product as a dense GEMM against the factor rebuilt on the fly (any l <= 16, any
 // dtypes and shapes); one launch per problem, grid = row blocks x token blocks.

@@ -593,6 +593,130 @@ void stage_fast_kernel(const WorkItem* __restrict__ items, int nitems, StageProb
   }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The same for small plans with pre-scaled activations, items of up to four row tiles: one workgroup of eight waves per
+// item and token, the waves taking an eighth of the contraction each.  A wave reads its blocks' activations and sign
+// words straight into registers, a block ahead (in B-operand order they need no LDS), and the waves meet once, after the
+// envelope rows are applied: the envelope-accumulate is linear in P, so a wave leaves 16 floats per tile.
+// What bounds it: small plans are launches and trips to memory; the kernel above took its workgroups through the whole
+// contraction chunk by chunk, on a quarter to a half of the device, and token after token.  Three attention layers, one
+// token: 10.1 + 7.7 -> 7.0 + 5.2 us for the two launches, 24.2 -> 18.8 us per pass; four layers, three tokens: 46.3 -> 28.6; a decoder
+// layer: 47.0 -> 33.2.  The column sums are a fifth of its matrix products (every workgroup takes them again); items of
+// eight tiles, which halve that and the reads of the activations, leave a unit one workgroup: 22.8 against 18.2 us for one
+// layer, 54.2 against 47.7 for two decoder layers.
+// ---------------------------------------------------------------------------------------------------
+constexpr int kShortWaves = 8;
+
+constexpr int kShortTiles = 4;
+__global__ __launch_bounds__(64 * kShortWaves) void stage_fast_short_kernel(const WorkItem* __restrict__ items) {
+  __shared__ u32x4 eo[kShortTiles * kTileRows * 2];
+  __shared__ float red[kShortWaves][kShortTiles * kTileRows];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = lane >> 4, n = lane & 15;
+  const int b = blockIdx.y;
+  const WorkItem& item = items[blockIdx.x];              // (uniform: scalar loads)
+  if (b >= item.p.T) return;
+  const StageProb p = item.p;
+  const int tile0 = item.tile0, ntl = item.ntiles;
+  const int KB = p.KB, nch = (KB + CB - 1) / CB;
+  const int per = (KB + kShortWaves - 1) / kShortWaves;
+  const int q_lo = wave * per, q_hi = min(q_lo + per, KB);
+  g_u32x4_ptr xs = (g_u32x4_ptr)p.xs + (size_t)b * (size_t)nch * (size_t)kChunkVecs;
+  const MDBF_GLOBAL int* exps = (const MDBF_GLOBAL int*)((g_u32x4_ptr)p.xs + (size_t)p.T * (size_t)nch * (size_t)kChunkVecs) + (size_t)b * nch;
+  // slots of the lane in a block's four steps (the swizzle of the scale-in kernel's stores)
+  const int rd_even = kg * 16 + ((n & 8) | ((n & 7) ^ (kg & 7)));
+  const int rd_odd = kg * 16 + ((n & 8) | ((n & 7) ^ ((kg + 4) & 7)));
+  const half8 ones0 = expand(0xFFFFFFFFu, 0), ones1 = expand(0xFFFFFFFFu, 1);   // the virtual row of column sums, per class
+
+  g_u32_ptr sbase[kShortTiles];
+#pragma unroll
+  for (int r = 0; r < kShortTiles; ++r)                  // (tiles past the item's end repeat its last, unstored)
+    sbase[r] = (g_u32_ptr)p.S + tile_base_words(tile0 + min(r, ntl - 1), KB) + lane;
+  const size_t bstride = (size_t)group_tiles(tile0, p.ntiles) * 64u;
+
+  struct Block {
+    u32x4 x[4];
+    uint32_t w[kShortTiles];
+  };
+  auto fetch = [&](int q, Block& blk) __attribute__((always_inline)) {
+    g_u32x4_ptr src = xs + (size_t)(q / CB) * kChunkVecs + (q % CB) * 256;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) blk.x[f] = src[f * 64 + ((f & 1) ? rd_odd : rd_even)];
+#pragma unroll
+    for (int r = 0; r < kShortTiles; ++r) blk.w[r] = sbase[r][(size_t)q * bstride];
+  };
+  floatx4 acc[kShortTiles][2], accv[2];
+  accv[0] = accv[1] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < kShortTiles; ++r) acc[r][0] = acc[r][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+  int e_cur = 0;
+  auto contract = [&](int q, const Block& blk) __attribute__((always_inline)) {
+    if (q % CB == 0 && q != q_lo) {                      // the next chunk's power of two
+      const int e = __builtin_amdgcn_readfirstlane(exps[q / CB]);
+      const float s = pow2i(max(-126, min(127, e - e_cur)));
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        accv[c] *= s;
+#pragma unroll
+        for (int r = 0; r < kShortTiles; ++r) acc[r][c] *= s;
+      }
+      e_cur = e;
+    }
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const half8 x = __builtin_bit_cast(half8, blk.x[f]);
+#pragma unroll
+      for (int r = 0; r < kShortTiles; ++r)
+        acc[r][f & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(expand(f < 2 ? blk.w[r] : blk.w[r] >> 8, f & 1), x, acc[r][f & 1], 0, 0, 0);
+      accv[f & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16((f & 1) ? ones1 : ones0, x, accv[f & 1], 0, 0, 0);
+    }
+  };
+  static_assert(kShortTiles * kTileRows * 2 <= 64 * kShortWaves, "a thread per 16 bytes of envelope rows");
+  u32x4 eoreg = {0u, 0u, 0u, 0u};
+  if (tid < kShortTiles * kTileRows * 2)
+    eoreg = ((g_u32x4_ptr)p.Eout)[(size_t)min(tile0 * kTileRows + (tid >> 1), p.rows - 1) * 2 + (tid & 1)];
+  if (q_lo < q_hi) {
+    Block b0, b1;
+    fetch(q_lo, b0);
+    e_cur = __builtin_amdgcn_readfirstlane(exps[q_lo / CB]);
+#pragma unroll 1
+    for (int q = q_lo;;) {
+      if (q + 1 < q_hi) fetch(q + 1, b1);
+      contract(q, b0);
+      if (++q >= q_hi) break;
+      if (q + 1 < q_hi) fetch(q + 1, b0);
+      contract(q, b1);
+      if (++q >= q_hi) break;
+    }
+  }
+  if (tid < kShortTiles * kTileRows * 2) eo[tid] = eoreg;
+  __syncthreads();
+  const _Float16* eoh = reinterpret_cast<const _Float16*>(eo);
+  const float colsum = accv[0][0] * 16777216.f + accv[1][0] * 1048576.f;   // 2^24, 2^20; all rows of the virtual tile are equal
+  const float unscale = pow2i(-e_cur);
+#pragma unroll
+  for (int r = 0; r < kShortTiles; ++r) {
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float ev = (float)eoh[(r * kTileRows + 4 * kg + i) * 16 + n];
+      const float P = colsum - acc[r][0][i] * 33554432.f - acc[r][1][i] * 2097152.f;  // 2^25, 2^21
+      v[i] = row16_sum(ev * P);
+    }
+    const int sel = n & 3;
+    if (n < 4) red[wave][r * kTileRows + 4 * kg + n] = (sel == 0 ? v[0] : sel == 1 ? v[1] : sel == 2 ? v[2] : v[3]) * unscale;
+  }
+  __syncthreads();
+  if (tid < kShortTiles * kTileRows) {
+    float sum = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < kShortWaves; ++w) sum += red[w][tid];
+    const int row = tile0 * kTileRows + tid;
+    if (tid < ntl * kTileRows && row < p.rows) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, sum, p.flags);
+  }
+}
+
 template <int R, bool BATCH, bool PRE>
 static int launch_rbp(const WorkItem* items_dev, int nitems, int tiles_per_item, const StageProb* single,
                       hipStream_t s) {
@@ -613,7 +737,8 @@ template <int R>
 static int launch_r(const StageProb* probs_dev, const WorkItem* items_dev, int nitems, int tiles_per_item,
                     const StageProb* single, bool pre, hipStream_t s) {
   if (probs_dev) {
-    if (pre) return launch_rbp<R, true, true>(items_dev, nitems, tiles_per_item, single, s);
+    if constexpr (R * 4 > kShortTiles)
+      if (pre) return launch_rbp<R, true, true>(items_dev, nitems, tiles_per_item, single, s);
     return launch_rbp<R, true, false>(items_dev, nitems, tiles_per_item, single, s);
   }
   if (pre) return launch_rbp<R, false, true>(items_dev, nitems, tiles_per_item, single, s);
@@ -683,8 +808,25 @@ int mfma_tiles_per_item(long total_tiles) {
   return tpi;
 }
 
+int mfma_plan_tiles_per_item(const long tiles[2], const long blocks[2], const int max_blocks[2], int max_tokens) {
+  // Four tiles are items of stage_fast_short_kernel; more, of the persistent kernel.  That one is as good or better only
+  // where its workgroups stay busy: one token, many row tiles, contractions of one length (one token, us per pass, short
+  // against persistent: 16 attention layers 33.7 and 35.5, 24 41.9 and 40.6, 64 78.8 and 77.3; 2 decoder layers 47.7 and
+  // 56.4, 8 116 and 119; 16 attention layers with three tokens 68.1 and 75.0), or where the launch is long.
+  const long least = tiles[0] < tiles[1] ? tiles[0] : tiles[1];
+  bool even = true;
+  for (int s = 0; s < 2; ++s) even = even && 4 * max_blocks[s] * tiles[s] <= 5 * blocks[s];
+  if (least <= 12000 && (least <= 3500 || !even || max_tokens > 1)) return kShortTiles;
+  return mfma_tiles_per_item(least);
+}
+
 int launch_stage_mfma(const StageProb* probs_dev, const WorkItem* items_dev, int nitems, int tiles_per_item,
                       const StageProb* single, bool pre, hipStream_t s) {
+  if (probs_dev && pre && tiles_per_item == kShortTiles) {
+    // (single->T: the plan's longest token count)
+    hipLaunchKernelGGL(stage_fast_short_kernel, dim3((unsigned)nitems, (unsigned)single->T), dim3(64 * kShortWaves), 0, s, items_dev);
+    return (int)hipGetLastError();
+  }
   if (!probs_dev) nitems = (single->ntiles + tiles_per_item - 1) / tiles_per_item;
   switch (tiles_per_item) {
     case 4: return launch_r<1>(probs_dev, items_dev, nitems, tiles_per_item, single, pre, s);

@@ -749,6 +749,30 @@ def test_item_forms_of_many_token_plans(gpu, copies, T, l, x_dtype):
         assert torch.equal(Y, Y[:1].expand_as(Y))
 
 
+@pytest.mark.parametrize("tokens", [(1, 1, 1), (3, 3, 3), (1, 9, 2)])
+@pytest.mark.parametrize("x_dtype,y_dtype", [("f16", "f32"), ("f32", "f16")])
+def test_small_plans_of_rank_16(gpu, tokens, x_dtype, y_dtype):
+    """Items of four row tiles, each wave an eighth of the contraction: one block per wave, two (the last waves have one or
+    none), eleven in three chunks of their own scale; a last item of one, two and three tiles; the second pass adds."""
+    torch, mb = gpu
+    layers, Xs, Ys, refs = [], [], [], []
+    for i, ((m, n, k), T) in enumerate(zip([(530, 1024, 1160), (16, 1160, 2050 // 8 * 8), (176, 11008, 1040)], tokens)):
+        L = synth.make_layer(m, n, k, 16, seed=70 + i, env_dtype="f16", env_kind="llama", signed_env=True)
+        X = synth.make_activations(n, T, seed=80 + i, x_dtype=x_dtype)
+        X[:, : n // 2] *= 2.0 ** -9                       # chunks of other magnitudes
+        X = synth.round_to_dtype(X, x_dtype)
+        refs.append(orc.forward_factored(*_oracle_args(L), X))
+        layers.append(mb.DeviceLayer.from_host(L))
+        Xs.append(_to_dev(torch, X, x_dtype))
+        Ys.append(torch.zeros((T, m), dtype=torch.float32 if y_dtype == "f32" else torch.float16, device="cuda:0"))
+    plan = mb.BatchPlan(layers, Xs, Ys, accumulate=True)
+    assert plan.kernel(1) == plan.kernel(2) == "stage_fast_kernel" and plan.launches() == 4
+    for passes in (1, 2):
+        plan.run()
+        for Y, ref in zip(Ys, refs):
+            assert orc.max_rel_error(Y.float().cpu().numpy(), passes * ref) <= TOL + (2.0 ** -10 if y_dtype == "f16" else 0.0)
+
+
 ONE_PLANS = [
     # specs (m, n, k, l), envelopes, activations, tokens: ranks of every class and mixed ones, odd row pitches, contractions of
     # one block and of more than one per wave, row tiles that do not fill the last item
