@@ -53,6 +53,15 @@ __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
+// Sign flips of rebuilt pairs, with the signs of the word's top bits (15 and 31), which then makes way for the next pair: a
+// word's pairs are taken from bits 15 and 31 downwards.  (Left shifts by constants take the vector ALUs four cycles,
+// additions less: 1.9 and 1.3 ns per wave and SIMD measured.  The compiler would turn x + x into a shift.)
+__device__ __forceinline__ uint32_t flip_next(uint32_t pair, uint32_t& signs) {
+  const uint32_t out = pair ^ (signs & 0x80008000u);
+  asm("v_add_u32 %0, %0, %0" : "+v"(signs));
+  return out;
+}
+
 // eight consecutive elements p[idx0 .. idx0+7] as fp16 pairs; elements at or past `nvalid` read as zero
 __device__ __forceinline__ u32x4 load8_as_half(const void* p, int64_t idx0, int nvalid, int dt) {
   u32x4 out = {0u, 0u, 0u, 0u};
@@ -127,8 +136,13 @@ __device__ __forceinline__ half4 load4_modes(const StageProb& p, const void* env
 // BATCH: the rows come from a plan's work items instead of the single problem.
 // NW waves, each with R row tiles, share a staging of a block; KS such groups take a run over the contraction each and
 // add their sums at the end, in order (small plans).
+// PAIR (plans of at most eight tokens): two row tiles at a time.  With up to 16 tokens a piece takes 128 cycles for its
+// rebuild on the matrix cores, 64 for the token product, half of whose rows are idle with eight, and some 50 vector
+// instructions, which do not overlap with them; one 32 x 32 product rebuilds both tiles' columns in half of the time, and the
+// idle rows take the second tile's tokens.  The signs' shifts as additions (flip_next) take another 4 %.  224 matrices, 8
+// tokens: 802 -> 737 us per pass with the two and items of 16 tiles (the same sums: bit-identical to 16-row products).
 constexpr int kGeneric = 3;
-template <int NW, int R, int TB, int MODE, bool BATCH, int KS>
+template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR = false>
 __global__ __launch_bounds__(64 * NW * KS, min_waves(TB))
 void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   // Two buffers each, as objects of their own and chosen at compile time (the loop is written out twice).  With one
@@ -181,27 +195,32 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   const int KB = p.KB;
 
   // ---- per-unit operands: Eout rows of the wave's tiles (B operand of the reconstruction), 4 modes per lane
+  // (PAIR: pairs of tiles 2u, 2u + 1; lane (n, h) = (lane & 31, lane >> 5): eight modes 8h .. of row n of a pair's 32)
   half4 eo_op[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int row = min((tile0 + r) * kTileRows + r16, p.rows - 1);      // (rows past the end are not stored)
-    eo_op[r] = load4_modes(p, p.Eout, row, 4 * g);
+    const int tile = tile0 + (PAIR ? (r & ~1) + (g & 1) : r);
+    const int row = min(tile * kTileRows + r16, p.rows - 1);           // (rows past the end are not stored)
+    eo_op[r] = load4_modes(p, p.Eout, row, PAIR ? 8 * (g >> 1) + 4 * (r & 1) : 4 * g);
   }
-  // sign words: tiles past the end read the last tile (their rows are never stored)
+  // sign words: tiles past the end read the last tile (their rows are never stored).  PAIR: word 2u + s of the lane holds
+  // columns 16 s + 8 h + 0 .. 7 of each step of its row.
   const MDBF_GLOBAL uint32_t* sbase[R];
   size_t sstride[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int t = min(tile0 + r, item_end - 1);
-    sbase[r] = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(t, KB) + lane;
-    sstride[r] = (size_t)group_tiles(t, p.ntiles) * 64u;
+    const int t = min(tile0 + (PAIR ? (r & ~1) + (g & 1) : r), item_end - 1);
+    sbase[r] = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(t, KB) + (PAIR ? 16 * (2 * (r & 1) + (g >> 1)) + r16 : lane);
+    // (an item's tiles are in one group)
+    sstride[r] = (size_t)group_tiles(PAIR ? item_tile0 : t, p.ntiles) * 64u;
   }
 
-  floatx4 acc[TB][R];
+  constexpr int AR = PAIR ? R / 2 : R;                         // accumulators per slab: a pair's tiles share one
+  floatx4 acc[TB][AR];
 #pragma unroll
   for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-    for (int r = 0; r < R; ++r) acc[tb][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < AR; ++r) acc[tb][r] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   // ---- staging of one block.  Envelope rows and sign words go through registers.  fp16 activations
   //      (kDma) go from global memory straight into LDS, 16 bytes per lane and 1 KB (four token rows) per
@@ -219,6 +238,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   auto dma_block = [&](int q, unsigned char* vin_buf) {
 #pragma unroll
     for (int i = 0; i < kVinChunks; ++i) {
+      if (PAIR && wave >= 2) continue;                         // rows 8 .. 15 stay zero
       const int id = tid + 64 * NW * i;
       const int tok = id >> 4, c = (id & 15) ^ (tok & 15);
       const int col = min(q * kBlockCols + c * 8, p.K - 8);
@@ -291,7 +311,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
       for (int i = 0; i < kVinChunks; ++i) {
         const int id = tid + 64 * NW * i;
         const int tok = id >> 4, c = id & 15;
-        *reinterpret_cast<u32x4*>(vin_buf + tok * 256 + ((c ^ (tok & 15)) << 4)) = vin_reg[i];
+        if (!PAIR || tok < 8) *reinterpret_cast<u32x4*>(vin_buf + tok * 256 + ((c ^ (tok & 15)) << 4)) = vin_reg[i];
       }
     }
 #pragma unroll
@@ -299,7 +319,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
       const int id = tid + 64 * NW * i;
       const u32x4 v = ein_reg[i];
       const bool ok = ein_ok[i];
-      *reinterpret_cast<u32x4*>(ein_buf + ein_row(id >> 1) * 32 + (((id & 1) ^ ((id >> 5) & 1)) << 4)) =
+      *reinterpret_cast<u32x4*>(ein_buf + ein_row(id >> 1) * 32 + (((id & 1) ^ ((id >> (PAIR ? 4 : 5)) & 1)) << 4)) =
           u32x4{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
     }
   };
@@ -311,6 +331,10 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   const int per_run = (KB + KS - 1) / KS;
   const int q_lo = run * per_run, q_hi = min(q_lo + per_run, KB);    // (the last run may be shorter, or empty)
   uint32_t sw[R];
+  if (PAIR) {
+    const int id = tid & 127;
+    *reinterpret_cast<u32x4*>((tid < 128 ? vin_a : vin_b) + 8 * 256 + id * 16) = u32x4{0u, 0u, 0u, 0u};
+  }
   if (kDma) dma_block(min(q_lo, KB - 1), vin_a);
   fetch_block(min(q_lo, KB - 1));
   stash_block(vin_a, ein_a);
@@ -336,7 +360,38 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     //      which lets the rebuild of one step overlap the matrix-core work of the previous one.
     if (KS == 1 || q < q_hi)                                   // (uniform; the barriers are kept)
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
+    for (int ff = 0; ff < 4; ++ff) {
+      const int f = BATCH ? 3 - ff : ff;
+      if constexpr (PAIR) {
+        // 32 rows x 32 columns of E in one product (half the time of four 16 x 16 x 16).  Its row m is column m with bits
+        // 2 and 3 exchanged, row m of the step in LDS, so that lane (n, h) receives columns 16 s + 8 h + 0 .. 7 of row n
+        // in registers 8 s + 0 .. 7.  Seen as an operand of a 16 x 16 x 32 product, its lane groups alternate between the
+        // two tiles; rows 0 .. 7 of the other operand hold the tokens for the first tile's groups and zeros for the
+        // second's, rows 8 .. 15 the other way round.
+        typedef float floatx16 __attribute__((ext_vector_type(16)));
+        const int m = lane & 31, h = lane >> 5;
+        const half8 ea = *reinterpret_cast<const half8*>(ein + (32 * f + m) * 32 + ((h ^ ((m >> 2) & 1)) << 4));
+        floatx16 z16;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z16[i] = 0.f;
+        const int tok = (r16 & 7) + 8 * ((r16 >> 3) ^ (g & 1));
+        half8 x[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) x[s] = *reinterpret_cast<const half8*>(vin + tok * 256 + (((4 * f + 2 * s + h) ^ tok) << 4));
+#pragma unroll
+        for (int u = 0; u < R / 2; ++u) {
+          const half8 eo = __builtin_shufflevector(eo_op[2 * u], eo_op[2 * u + (R > 1)], 0, 1, 2, 3, 4, 5, 6, 7);
+          const floatx16 e = __builtin_amdgcn_mfma_f32_32x32x16_f16(ea, eo, z16, 0, 0, 0);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            u32x4 w;
+#pragma unroll
+            for (int i = 3; i >= 0; --i) w[i] = flip_next(pack_half2(e[8 * s + 2 * i], e[8 * s + 2 * i + 1]), sw[2 * u + s]);
+            acc[0][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x[s], __builtin_bit_cast(half8, w), acc[0][u], 0, 0, 0);
+          }
+        }
+        continue;
+      }
       // A operands of the two reconstruction products: rows mi -> columns 32f + 8(mi/4) + mi%4 (+4)
       const int col0 = 32 * f + 8 * (r16 >> 2) + (r16 & 3);
       const int eoff = ein_row(col0) * 32 + ((g ^ ((r16 >> 2) & 2)) << 3);
@@ -350,12 +405,19 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
         const floatx4 e1 = __builtin_amdgcn_mfma_f32_16x16x16f16(ea1, eo_op[r], z4, 0, 0, 0);
         // lane (r16, g) now holds E[row r16][32f + 8g + e], e = 0..3 in e0 and 4..7 in e1.  The packed word
         // keeps the signs of columns e = 2i and 2i+1 at bits p and p + 16, p = 8(f/2) + 4(f%2) + i.
-        const int pbase = 8 * (f >> 1) + 4 * (f & 1);
         uint32_t w4[4];
-        w4[0] = pack_half2(e0[0], e0[1]) ^ ((sw[r] << (15 - (pbase + 0))) & 0x80008000u);
-        w4[1] = pack_half2(e0[2], e0[3]) ^ ((sw[r] << (15 - (pbase + 1))) & 0x80008000u);
-        w4[2] = pack_half2(e1[0], e1[1]) ^ ((sw[r] << (15 - (pbase + 2))) & 0x80008000u);
-        w4[3] = pack_half2(e1[2], e1[3]) ^ ((sw[r] << (15 - (pbase + 3))) & 0x80008000u);
+        if (BATCH) {
+          w4[3] = flip_next(pack_half2(e1[2], e1[3]), sw[r]);
+          w4[2] = flip_next(pack_half2(e1[0], e1[1]), sw[r]);
+          w4[1] = flip_next(pack_half2(e0[2], e0[3]), sw[r]);
+          w4[0] = flip_next(pack_half2(e0[0], e0[1]), sw[r]);
+        } else {
+          const int pbase = 8 * (f >> 1) + 4 * (f & 1);
+          w4[0] = pack_half2(e0[0], e0[1]) ^ ((sw[r] << (15 - (pbase + 0))) & 0x80008000u);
+          w4[1] = pack_half2(e0[2], e0[3]) ^ ((sw[r] << (15 - (pbase + 1))) & 0x80008000u);
+          w4[2] = pack_half2(e1[0], e1[1]) ^ ((sw[r] << (15 - (pbase + 2))) & 0x80008000u);
+          w4[3] = pack_half2(e1[2], e1[3]) ^ ((sw[r] << (15 - (pbase + 3))) & 0x80008000u);
+        }
         wop[r] = __builtin_bit_cast(half8, u32x4{w4[0], w4[1], w4[2], w4[3]});
       }
       // the step's A operands (one per token slab) are all requested before the first product
@@ -393,7 +455,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 
   // ---- the runs' sums, added by the first run's waves in the order of the runs
   if constexpr (KS > 1) {
-    constexpr int kRunBytes = NW * TB * R * 64 * 16;         // a run's sums
+    constexpr int kRunBytes = NW * TB * AR * 64 * 16;         // a run's sums
     static_assert(kRunBytes <= KS * kVinBufBytes && (KS == 2 || 2 * kRunBytes <= KS * kVinBufBytes), "they take the staging buffers");
     auto sums = [&](int s) { return reinterpret_cast<floatx4*>(s < 3 ? vin_lds_a + (s - 1) * kRunBytes : vin_lds_b); };
     __syncthreads();                                           // every wave is done with the staging buffers
@@ -401,7 +463,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-        for (int r = 0; r < R; ++r) sums(run)[((wave * TB + tb) * R + r) * 64 + lane] = acc[tb][r];
+        for (int r = 0; r < AR; ++r) sums(run)[((wave * TB + tb) * AR + r) * 64 + lane] = acc[tb][r];
     __syncthreads();
     if (run > 0) return;
 #pragma unroll
@@ -409,16 +471,30 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 #pragma unroll
       for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const floatx4 v = sums(s)[((wave * TB + tb) * R + r) * 64 + lane];
+        for (int r = 0; r < AR; ++r) {
+          const floatx4 v = sums(s)[((wave * TB + tb) * AR + r) * 64 + lane];
 #pragma unroll
           for (int i = 0; i < 4; ++i) acc[tb][r][i] += v[i];
         }
   }
 
+  if constexpr (PAIR) {
+    // ---- lane (r16, g) holds out[token 4 (g & 1) + i][row r16 of tile g >> 1 of the pair]
+#pragma unroll
+    for (int u = 0; u < AR; ++u) {
+      const int tile = tile0 + 2 * u + (g >> 1), row = tile * kTileRows + r16;
+      if (tile < item_end && row < p.rows)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int b = 4 * (g & 1) + i;
+          if (b < p.T) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, acc[0][u][i], p.flags);
+        }
+    }
+    return;
+  }
   // ---- store: lane (r16, g) holds out[token 16 tb + 4g + i][row r16 of tile r]
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
+  for (int r = 0; r < AR; ++r) {
     const int row = (tile0 + r) * kTileRows + r16;
     if (tile0 + r < item_end && row < p.rows) {
 #pragma unroll
@@ -887,16 +963,16 @@ static int launch_few_m(const FewArgs& a, hipStream_t s) {
 
 // Runs over the contraction in a workgroup of a plan's launch (gemm_tiles_per_item has the measurements).
 template <int NW, int R>
-static int plan_runs(int nitems, int TB) {
-  if (TB > 2) return 1;
-  if (NW * R == 2) return TB == 1 ? 4 : 2;
-  if (NW * R == 4) return TB == 1 && nitems <= 288 ? 4 : 2;
-  return nitems <= 4096 ? 2 : 1;
+static int plan_runs(int nitems, int T) {
+  if (T > 32 || NW * R == 16) return 1;
+  if (NW * R == 2) return T <= 16 ? 4 : 2;
+  if (NW * R == 4) return T <= 16 && nitems <= 288 ? 4 : 2;
+  return nitems <= (T <= 8 ? 1400 : 4096) ? 2 : 1;
 }
 
 // items_dev null: the single problem *p.  Else nitems work items of a plan, `p` describing the launch:
 // p->T = the longest token count among the problems.
-template <int NW, int R, int TB, int MODE, bool BATCH, int KS>
+template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR = false>
 static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
   const int rows_per_wg = NW * R;   // tiles
   unsigned gx = BATCH ? (unsigned)nitems : (unsigned)((p->ntiles + rows_per_wg - 1) / rows_per_wg);
@@ -906,7 +982,7 @@ static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p
     gx = kDies * ((total + kDies - 1) / kDies);
     gy = 1;
   }
-  hipLaunchKernelGGL((stage_gemm_kernel<NW, R, TB, MODE, BATCH, KS>), dim3(gx, gy), dim3(64 * NW * KS), 0, s,
+  hipLaunchKernelGGL((stage_gemm_kernel<NW, R, TB, MODE, BATCH, KS, PAIR>), dim3(gx, gy), dim3(64 * NW * KS), 0, s,
                      items_dev, *p);
   return (int)hipGetLastError();
 }
@@ -920,14 +996,21 @@ static int launch_rtm(const StageProb* p, hipStream_t s) {
 // a plan's work items, of NW R row tiles
 template <int NW, int R, int TB, int MODE>
 static int launch_items_rtm(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
-  const int ks = plan_runs<NW, R>(nitems, TB);
+  const int ks = plan_runs<NW, R>(nitems, p->T);
+  if constexpr (NW * R >= 8 && TB == 1) {
+    if (p->T <= 8) {
+      if constexpr (NW * R == 8)
+        if (ks == 2) return launch_rtmb<NW, R, TB, MODE, true, 2, true>(items_dev, nitems, p, s);
+      return launch_rtmb<NW, R, TB, MODE, true, 1, true>(items_dev, nitems, p, s);
+    }
+  }
   if constexpr (TB == 1 && NW * R <= 4) {
     if (ks == 4) return launch_rtmb<NW, R, TB, MODE, true, 4>(items_dev, nitems, p, s);
   }
-  if constexpr (TB <= 2) {
-    if (ks >= 2) return launch_rtmb<NW, R, TB, MODE, true, 2>(items_dev, nitems, p, s);
+  if constexpr (TB <= 2 && NW * R <= 8) {
+    if (ks == 2) return launch_rtmb<NW, R, TB, MODE, true, 2>(items_dev, nitems, p, s);
   }
-  if constexpr (TB > 2 || NW * R == 8) return launch_rtmb<NW, R, TB, MODE, true, 1>(items_dev, nitems, p, s);
+  if constexpr (NW * R == 8 || (TB > 2 && NW * R < 8)) return launch_rtmb<NW, R, TB, MODE, true, 1>(items_dev, nitems, p, s);
   return (int)hipErrorInvalidValue;
 }
 template <int NW, int R, int TB>
@@ -1080,10 +1163,13 @@ int launch_half_copies(const HalfMatrix* m, int count, hipStream_t s) {
 //   48.9, 8/2 50.1; 32: 8/1 79.1, 8/2 78.8, 4/2 87.0
 //   a decoder layer (1432 and 2656): 8/1 97.2, 8/2 66.0, 4/2 55.5, 4/4 55.8; two: 109, 85.4, 81.9, 92.4; 8: 252, 243, 263;
 //   16: 447, 437, 504; 32: 820, 838, 966
+// Up to 8 tokens, larger items share a product over pairs of tiles (PAIR): 32 attention layers 8/1 76.5, 8/2 78.0, 16/1
+//   81; 300: 567, 592, 528; 4 decoder layers of rank 16 and k = 5536: 205, 185, 207; 8: 224, 236, 221; 16: 417, 418, 403;
+//   32: 769, 799, 737
 // 17 to 32: an attention layer 8/1 47.5, 4/2 26.0, 2/2 24.4; a decoder layer 119, 68.0, 76.1; 4: 184, 8/2 178, 189.
 // 33 to 64 (one run: two would take the room of a second workgroup): 62.4, 4/1 45.2; 150, 118.
 int gemm_tiles_per_item(long launch_tiles, int max_tokens) {
-  if (max_tokens <= 16) return launch_tiles <= 512 ? 2 : launch_tiles <= 5400 ? 4 : 8;
+  if (max_tokens <= 16) return launch_tiles <= 512 ? 2 : launch_tiles <= 5400 ? 4 : launch_tiles <= 11000 || max_tokens > 8 ? 8 : 16;
   if (max_tokens <= 32) return launch_tiles <= 300 ? 2 : launch_tiles <= 2700 ? 4 : 8;
   return launch_tiles <= 2700 ? 4 : 8;
 }
@@ -1093,6 +1179,7 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const Sta
   if (items_dev) {       // p->ntiles: the row tiles per item the plan was cut with
     if (p->ntiles == 2) return gemm::launch_items_r<2, 1>(items_dev, nitems, mode, p, s);
     if (p->ntiles == 4) return gemm::launch_items_r<4, 1>(items_dev, nitems, mode, p, s);
+    if (p->ntiles == 16) return gemm::launch_items_rt<4, 4, 1>(items_dev, nitems, mode, p, s);
     return gemm::launch_items_r<4, 2>(items_dev, nitems, mode, p, s);
   }
   mode = gemm_load_mode(*p);

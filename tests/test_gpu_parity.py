@@ -720,8 +720,8 @@ def test_residual_stack_in_a_plan(gpu):
 
 
 PLAN_FORMS = [
-    # copies of the layers, tokens: 2, 4 and 8 row tiles per item, one to four runs over the contraction, each slab count
-    (1, 16), (1, 9), (1, 32), (1, 64), (8, 5), (8, 17), (8, 33), (16, 16), (45, 4), (45, 40), (260, 6),
+    # copies of the layers, tokens: 2, 4, 8 and 16 row tiles per item, one to four runs over the contraction, each slab count
+    (1, 16), (1, 9), (1, 32), (1, 64), (8, 5), (8, 17), (8, 33), (16, 16), (45, 4), (45, 40), (50, 8), (260, 6), (260, 9),
 ]
 
 
