@@ -354,8 +354,17 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
   auto contract = [&](int q, Block& b, const float* buf) __attribute__((always_inline)) {
     // (the block's last row may be read past the factor's end: fewer than sixteen elements lie behind its first)
     if (!VEC && (int64_t)(p.K - (q + 1) * kBlockCols + 1) * p.l < 16) ein_tail<ENV, M>(p, q, lane, b.ein);
+    // the packed word keeps the signs of columns 2 t and 2 t + 1 of step f at bits c and c + 16, c = 8 (f / 2) + 4 (f % 2) + t:
+    // they are taken from the top of two registers, which double from entry to entry (a left shift by a constant takes the
+    // vector ALUs four cycles, an addition less)
+    uint32_t odd = b.sw, even = b.sw << 16;
+    auto flip = [](float v, uint32_t& signs) __attribute__((always_inline)) {
+      const uint32_t out = __builtin_bit_cast(uint32_t, v) ^ (signs & 0x80000000u);
+      asm("v_add_u32 %0, %0, %0" : "+v"(signs));
+      return __builtin_bit_cast(float, out);
+    };
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
+    for (int f = 3; f >= 0; --f) {
       const floatx4 xa = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g);
       const floatx4 xb = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g + 4);
       floatx4 d[2];
@@ -374,13 +383,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
                                 u32x4{on ? eo.v[0] : 0u, on ? eo.v[1] : 0u, on ? eo.v[2] : 0u, on ? eo.v[3] : 0u});
         }
       }
-      // the packed word keeps the signs of columns 2 t and 2 t + 1 at bits c and c + 16, c = 8 (f / 2) + 4 (f % 2) + t
 #pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int bit = 8 * (f >> 1) + 4 * (f & 1) + (t >> 1) + 16 * (t & 1);
-        const float ev = t < 4 ? d[0][t & 3] : d[1][t & 3];
-        const float sv = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, ev) ^ ((b.sw << (31 - bit)) & 0x80000000u));
-        acc[t & 1] = fmaf(sv, t < 4 ? xa[t & 3] : xb[t & 3], acc[t & 1]);
+      for (int t = 3; t >= 0; --t) {
+        const floatx4 e = d[t >> 1], x = t < 2 ? xa : xb;
+        acc[0] = fmaf(flip(e[2 * (t & 1)], even), x[2 * (t & 1)], acc[0]);
+        acc[1] = fmaf(flip(e[2 * (t & 1) + 1], odd), x[2 * (t & 1) + 1], acc[1]);
       }
       // (a step at a time: without this the products of a block are all made first, in 64 registers)
       asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
