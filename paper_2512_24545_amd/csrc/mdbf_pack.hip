@@ -6,28 +6,63 @@ namespace mdbf {
 
 // One wave packs the 64 words of a (row tile, block): lane (kg, r) owns row r and the 8-column groups
 // f * 32 + kg * 8, f = 0..3, whose entries go to bits 8 (f / 2) + 4 (f % 2) + (e / 2) + 16 (e % 2) of its word.
-// Both kernels stream: one byte per sign on one side, one bit on the other, so HBM bounds them.  A lane moves a
-// column group at a time, eight bytes (any alignment: the target allows it), 32 bytes of a row per instruction
-// and the whole 128-byte line over the four groups; a wave takes kPackBlocks consecutive blocks with all their
-// loads in flight, the four waves of a workgroup four consecutive tiles (1 KB of words per block).  Byte by
-// byte, 32 loads per word, packing 11008 x 4096 took 91 us and unpacking 82 us; now 14 and
-// 17 us (3.6 and 3.0 TB/s; a large copy reaches 5.1 TB/s).  (Sizes are compared as blocks or as differences: a column
+// Both kernels stream: one byte per sign on one side, one bit on the other, so HBM bounds them.  A wave takes
+// kPackBlocks consecutive blocks with all their loads in flight, the four waves of a workgroup four consecutive tiles
+// (1 KB of words per block).  Whole runs of blocks go between memory and the lanes' column groups through LDS: 16 bytes a
+// lane at any alignment (the target allows it), 512 consecutive bytes of a row per half wave.  With every lane on its own
+// column groups, eight bytes of a row and a quarter of its line per access, packing 11008 x 4096 took 14 us and unpacking 17;
+// both together now 19.5 against 28.6 (5.2 TB/s; a large copy reaches 5.1), whichever way the bits are moved (below).  The
+// non-temporal hint: 18.9 with it on both sides, 21.4 on the loads alone; left out, the signs may be read again.  Runs
+// that the row's end cuts go group by group.  (Sizes are compared as blocks or as differences: a column
 // index and a block's end may lie past the largest int.)
 constexpr int kPackBlocks = 4;
 
+// Whole runs of kPackBlocks blocks go through LDS, a row's 512 bytes by 32 lanes at a time.
+constexpr int kRunBytes = kPackBlocks * kBlockCols;
+constexpr int kRunStride = kRunBytes + 16;                                // of a row in LDS
+typedef uint32_t Piece __attribute__((ext_vector_type(4), aligned(1)));   // sixteen consecutive signs of a row
+typedef uint32_t PieceLds __attribute__((ext_vector_type(4)));
+typedef uint32_t OctetLds __attribute__((ext_vector_type(2)));
+
+// a wave's LDS operations execute in order: this keeps the compiler from moving them across
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 typedef uint32_t Octet __attribute__((ext_vector_type(2), aligned(1)));   // eight consecutive signs of a row
 
-// sign bits of four bytes (entries e, e + 1, e + 2, e + 3; e = 0 or 4) to bits 0, 16, 1, 17
-__device__ __forceinline__ uint32_t gather4(uint32_t d) {
-  const uint32_t y = d >> 7;
-  return (y & 1u) | ((y & 0x100u) << 8) | ((y & 0x10000u) >> 15) | ((y & 0x1000000u) >> 7);
+// A lane's word from its four column groups, and back.  A dword holds four entries' bytes: entry e of a group's first one
+// goes to bit e / 2 + 16 (e % 2) of the group's nibbles, of its second one two bits further.  The sign bits of two groups
+// are first put side by side inside each byte (group 0 at bits 0 and 2, group 1 at 4 and 6), then bytes 2 and 3 between
+// those of 0 and 1: 21 and 46 vector instructions a word (entry by entry some 90 and 100).
+__device__ __forceinline__ uint32_t pack_groups(const Octet (&o)[4]) {
+  uint32_t c[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const uint32_t a = ((o[2 * g].x >> 7) & 0x01010101u) | ((o[2 * g].y >> 5) & 0x04040404u) |
+                       ((o[2 * g + 1].x >> 3) & 0x10101010u) | ((o[2 * g + 1].y >> 1) & 0x40404040u);
+    c[g] = a | (a >> 15);
+  }
+  return __builtin_amdgcn_perm(c[1], c[0], 0x05010400u);       // bytes: c0.0, c1.0, c0.1, c1.1
 }
-// the inverse: bits 0, 16, 1, 17 to the bytes +1 (0x01) or -1 (0xFF)
-__device__ __forceinline__ uint32_t spread4(uint32_t b) {
-  const uint32_t y = (b & 1u) | ((b >> 8) & 0x100u) | ((b << 15) & 0x10000u) | ((b << 7) & 0x1000000u);
-  return 0x01010101u | (y * 0xFEu);
+__device__ __forceinline__ void unpack_groups(uint32_t w, Octet (&o)[4]) {
+  // +1 (0x01) or -1 (0xFF) per byte from bit 0 of each: (b << 8) - b has all bits of the bytes whose bit is set
+  auto bytes = [](uint32_t b) __attribute__((always_inline)) { return ((b << 8) - b) | 0x01010101u; };
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const uint32_t c = __builtin_amdgcn_perm(0u, w, g == 0 ? 0x0c0c0200u : 0x0c0c0301u);   // bytes g and g + 2
+    const uint32_t a = (c & 0x5555u) | ((c & 0xAAAAu) << 15);
+    o[2 * g].x = bytes(a & 0x01010101u);
+    o[2 * g].y = bytes((a >> 2) & 0x01010101u);
+    o[2 * g + 1].x = bytes((a >> 4) & 0x01010101u);
+    o[2 * g + 1].y = bytes((a >> 6) & 0x01010101u);
+  }
 }
 
+// RUNS: rows hold whole runs (narrower ones do without the LDS)
+template <bool RUNS>
 __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ signs, int rows, int cols, int64_t ld,
                                                    uint32_t* __restrict__ packed, int KB, int ntiles) {
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
@@ -35,39 +70,49 @@ __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ si
   if (tile >= ntiles) return;
   const int row = tile * kTileRows + r;
   const MDBF_GLOBAL int8_t* src = (const MDBF_GLOBAL int8_t*)signs + (int64_t)min(row, rows - 1) * ld;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[4][RUNS ? kTileRows * kRunStride : 16];
+  unsigned char* buf = lds[threadIdx.x >> 6];
   for (int q0 = blockIdx.y * kPackBlocks; q0 < KB; q0 += gridDim.y * kPackBlocks) {
     uint32_t w[kPackBlocks];
-    if (q0 + kPackBlocks <= cols / kBlockCols) {              // (uniform) whole blocks: no bounds to respect
-      Octet o[kPackBlocks][4];
+    if (RUNS && q0 + kPackBlocks <= cols / kBlockCols) {      // (uniform) whole blocks: no bounds to respect
+      Piece v[8];
 #pragma unroll
-      for (int j = 0; j < kPackBlocks; ++j)
+      for (int i = 0; i < 8; ++i) {
+        const int rr = min(tile * kTileRows + 2 * i + (lane >> 5), rows - 1);
+        v[i] = *(const MDBF_GLOBAL Piece*)((const MDBF_GLOBAL int8_t*)signs + (int64_t)rr * ld + (int64_t)q0 * kBlockCols + (lane & 31) * 16);
+      }
 #pragma unroll
-        for (int f = 0; f < 4; ++f) o[j][f] = *(const MDBF_GLOBAL Octet*)(src + (q0 + j) * kBlockCols + f * 32 + kg * 8);
+      for (int i = 0; i < 8; ++i) *reinterpret_cast<PieceLds*>(buf + (2 * i + (lane >> 5)) * kRunStride + (lane & 31) * 16) = v[i];
+      wave_lds_order();
 #pragma unroll
       for (int j = 0; j < kPackBlocks; ++j) {
-        w[j] = 0;
+        Octet o[4];
 #pragma unroll
-        for (int f = 0; f < 4; ++f)
-          w[j] |= (gather4(o[j][f].x) | (gather4(o[j][f].y) << 2)) << (8 * (f >> 1) + 4 * (f & 1));
+        for (int f = 0; f < 4; ++f) o[f] = *reinterpret_cast<const OctetLds*>(buf + r * kRunStride + j * kBlockCols + f * 32 + kg * 8);
+        w[j] = pack_groups(o);
       }
+      wave_lds_order();
     } else {
 #pragma unroll
       for (int j = 0; j < kPackBlocks; ++j) {
         w[j] = 0;
         if (q0 + j >= KB) continue;
-#pragma unroll 1
+        Octet o[4];
+#pragma unroll
         for (int f = 0; f < 4; ++f) {
           const int c0 = (q0 + j) * kBlockCols + f * 32 + kg * 8;
-          uint32_t bits = 0;
+          o[f] = Octet{0u, 0u};
           if (c0 <= cols - 8) {
-            const Octet o = *(const MDBF_GLOBAL Octet*)(src + c0);
-            bits = gather4(o.x) | (gather4(o.y) << 2);
+            o[f] = *(const MDBF_GLOBAL Octet*)(src + c0);
           } else {
             for (int e = 0; e < 8; ++e)
-              if (e < cols - c0 && src[c0 + e] < 0) bits |= 1u << ((e >> 1) + 16 * (e & 1));
+              if (e < cols - c0 && src[c0 + e] < 0) {
+                if (e < 4) o[f].x |= 0x80u << (8 * e);
+                else o[f].y |= 0x80u << (8 * e - 32);
+              }
           }
-          w[j] |= bits << (8 * (f >> 1) + 4 * (f & 1));
         }
+        w[j] = pack_groups(o);
       }
     }
 #pragma unroll
@@ -77,6 +122,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const int8_t* __restrict__ si
   }
 }
 
+template <bool RUNS>
 __global__ __launch_bounds__(256) void unpack_kernel(const uint32_t* __restrict__ packed, int rows, int cols,
                                                      int8_t* __restrict__ signs, int64_t ld, int KB, int ntiles) {
   const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
@@ -84,22 +130,41 @@ __global__ __launch_bounds__(256) void unpack_kernel(const uint32_t* __restrict_
   if (tile >= ntiles) return;
   const int row = tile * kTileRows + r;
   MDBF_GLOBAL int8_t* dst = (MDBF_GLOBAL int8_t*)signs + (int64_t)row * ld;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[4][RUNS ? kTileRows * kRunStride : 16];
+  unsigned char* buf = lds[threadIdx.x >> 6];
   for (int q0 = blockIdx.y * kPackBlocks; q0 < KB; q0 += gridDim.y * kPackBlocks) {
     uint32_t w[kPackBlocks];
 #pragma unroll
     for (int j = 0; j < kPackBlocks; ++j)
       w[j] = ((const MDBF_GLOBAL uint32_t*)packed)[word_offset(tile, min(q0 + j, KB - 1), lane, KB, ntiles)];
+    if (RUNS && q0 + kPackBlocks <= cols / kBlockCols) {      // (uniform)
+#pragma unroll
+      for (int j = 0; j < kPackBlocks; ++j) {
+        Octet o[4];
+        unpack_groups(w[j], o);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) *reinterpret_cast<OctetLds*>(buf + r * kRunStride + j * kBlockCols + f * 32 + kg * 8) = o[f];
+      }
+      wave_lds_order();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int rr = tile * kTileRows + 2 * i + (lane >> 5);
+        const PieceLds v = *reinterpret_cast<const PieceLds*>(buf + (2 * i + (lane >> 5)) * kRunStride + (lane & 31) * 16);
+        if (rr < rows) *(MDBF_GLOBAL Piece*)((MDBF_GLOBAL int8_t*)signs + (int64_t)rr * ld + (int64_t)q0 * kBlockCols + (lane & 31) * 16) = v;
+      }
+      wave_lds_order();
+      continue;
+    }
     if (row >= rows) return;
 #pragma unroll
     for (int j = 0; j < kPackBlocks; ++j) {
       if (q0 + j >= KB) continue;
+      Octet all[4];
+      unpack_groups(w[j], all);
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
         const int c0 = (q0 + j) * kBlockCols + f * 32 + kg * 8;
-        const uint32_t bits = w[j] >> (8 * (f >> 1) + 4 * (f & 1));
-        Octet o;
-        o.x = spread4(bits);
-        o.y = spread4(bits >> 2);
+        const Octet o = all[f];
         if (c0 <= cols - 8) {
           *(MDBF_GLOBAL Octet*)(dst + c0) = o;
         } else {
@@ -119,13 +184,15 @@ static dim3 pack_grid(int KB, int ntiles) {
 
 int launch_pack(const int8_t* signs, int rows, int cols, int64_t ld, uint32_t* packed, hipStream_t s) {
   const int KB = num_blocks(cols), nt = num_tiles(rows);
-  hipLaunchKernelGGL(pack_kernel, pack_grid(KB, nt), dim3(256), 0, s, signs, rows, cols, ld, packed, KB, nt);
+  if (cols >= kRunBytes) hipLaunchKernelGGL(pack_kernel<true>, pack_grid(KB, nt), dim3(256), 0, s, signs, rows, cols, ld, packed, KB, nt);
+  else hipLaunchKernelGGL(pack_kernel<false>, pack_grid(KB, nt), dim3(256), 0, s, signs, rows, cols, ld, packed, KB, nt);
   return (int)hipGetLastError();
 }
 
 int launch_unpack(const uint32_t* packed, int rows, int cols, int8_t* signs, int64_t ld, hipStream_t s) {
   const int KB = num_blocks(cols), nt = num_tiles(rows);
-  hipLaunchKernelGGL(unpack_kernel, pack_grid(KB, nt), dim3(256), 0, s, packed, rows, cols, signs, ld, KB, nt);
+  if (cols >= kRunBytes) hipLaunchKernelGGL(unpack_kernel<true>, pack_grid(KB, nt), dim3(256), 0, s, packed, rows, cols, signs, ld, KB, nt);
+  else hipLaunchKernelGGL(unpack_kernel<false>, pack_grid(KB, nt), dim3(256), 0, s, packed, rows, cols, signs, ld, KB, nt);
   return (int)hipGetLastError();
 }
 

@@ -101,6 +101,26 @@ def test_packed_words_are_where_the_layout_says(gpu, rows, cols, pad):
     np.testing.assert_array_equal(mb.mdbf_unpack(packed, rows, cols).cpu().numpy() < 0, neg)
 
 
+@pytest.mark.parametrize("rows,cols,first,pitch", [(1, 512, 1, 515), (16, 1024, 0, 1024), (17, 511, 3, 700), (37, 1537, 5, 1543), (70, 1151, 0, 1151)])
+def test_pack_runs_of_blocks_at_any_alignment(gpu, rows, cols, first, pitch):
+    """Whole runs of four blocks (through LDS) and cut ones, rows at odd addresses, the last row at the end of the buffer,
+    rows that do not fill the last tile; what lies between the rows is neither packed nor written."""
+    torch, mb = gpu
+    L = mb.lib()
+    rng = np.random.default_rng(rows + cols)
+    S = synth.random_signs(rng, rows, cols)
+    buf = torch.full((first + (rows - 1) * pitch + cols,), -7, dtype=torch.int8, device="cuda:0")
+    view = buf[first:].as_strided((rows, cols), (pitch, 1))
+    view.copy_(torch.from_numpy(S))
+    packed = mb.mdbf_pack(view)
+    assert torch.equal(packed, mb.mdbf_pack(torch.from_numpy(S).cuda()))
+    back = torch.full_like(buf, -7)
+    stream = torch.cuda.current_stream().cuda_stream
+    assert L.mdbf_unpack(packed.data_ptr(), rows, cols, back[first:].data_ptr(), pitch, stream) == 0
+    assert torch.equal(back, buf)
+    np.testing.assert_array_equal(mb.mdbf_unpack(packed, rows, cols).cpu().numpy(), S)
+
+
 @pytest.mark.parametrize("cols", [2 ** 31 - 128, 2 ** 31 - 131])
 def test_pack_a_row_near_the_largest_int(gpu, cols):
     """The last blocks of a row whose padded end is no int any more: what lies behind the row (negative bytes: bits
