@@ -142,19 +142,13 @@ __device__ __forceinline__ half4 load4_modes(const StageProb& p, const void* env
 // idle rows take the second tile's tokens.  The signs' shifts as additions (flip_next) take another 4 %.  224 matrices, 8
 // tokens: 802 -> 737 us per pass with the two and items of 16 tiles (the same sums: bit-identical to 16-row products).
 constexpr int kGeneric = 3;
-template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR = false>
-__global__ __launch_bounds__(64 * NW * KS, min_waves(TB))
-void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
-  // Two buffers each, as objects of their own and chosen at compile time (the loop is written out twice).  With one
-  // array and a run-time offset no LDS read could move across the direct-to-LDS loads of the next block: they were
-  // all issued first, and the first read then waited for them to land, in every block.  Now the reads of a block
-  // go ahead and the loads follow between its products (2048 tokens on 4096 x 4096, k = 2656: 139 -> 124 us; 40
-  // tokens: 61 -> 42 us).
+// first: row tiles of the work item in front of this workgroup's.  True (PAIR): some results are infinities or NaNs, and none
+// has been stored.
+template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR>
+__device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ items, const StageProb& single, int thread, int first,
+                                                unsigned char* vin_lds_a, unsigned char* vin_lds_b,
+                                                unsigned char* ein_lds_a, unsigned char* ein_lds_b) {
   constexpr int kVinBufBytes = vin_buf_bytes(TB);
-  __shared__ __attribute__((aligned(1024))) unsigned char vin_lds_a[KS * kVinBufBytes];   // [16*TB tokens][16 chunks of 16 B], swizzled
-  __shared__ __attribute__((aligned(1024))) unsigned char vin_lds_b[KS * kVinBufBytes];
-  __shared__ __attribute__((aligned(1024))) unsigned char ein_lds_a[KS * kEinBufBytes];   // [128 columns][16 modes]
-  __shared__ __attribute__((aligned(1024))) unsigned char ein_lds_b[KS * kEinBufBytes];
   // the rows of this workgroup: a work item of a plan (at most NW * R row tiles of one problem), or
   // the blockIdx.x-th run of NW * R tiles of the single problem
   StageProb p;
@@ -162,7 +156,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   if (BATCH) {
     const WorkItem& w = items[blockIdx.x];   // uniform address: scalar loads
     p = w.p;
-    item_tile0 = w.tile0;
+    item_tile0 = w.tile0 + first;
     item_end = w.tile0 + w.ntiles;
     slab_group = blockIdx.y;
   } else {
@@ -175,14 +169,14 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
     const int total = row_groups * slab_groups;
     const int per_die = (total + kDies - 1) / kDies;
     const int unit = (blockIdx.x % kDies) * per_die + blockIdx.x / kDies;
-    if (unit >= total) return;
+    if (unit >= total) return false;
     slab_group = unit / row_groups;
     item_tile0 = (unit - slab_group * row_groups) * (NW * R);
     item_end = min(item_tile0 + NW * R, p.ntiles);
   }
   // the run over the contraction that this thread's four waves take, and the thread's and the wave's place in it
-  const int run = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
-  const int tid = threadIdx.x - run * (64 * NW), lane = tid & 63;
+  const int run = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(thread / (64 * NW));
+  const int tid = thread - run * (64 * NW), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, g = lane >> 4;
   unsigned char* const vin_a = vin_lds_a + run * kVinBufBytes;
@@ -191,7 +185,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
   unsigned char* const ein_b = ein_lds_b + run * kEinBufBytes;
   const int tile0 = item_tile0 + wave * R;                     // first row tile of this wave
   const int tok0 = slab_group * (16 * TB);
-  if (tok0 >= p.T) return;                                     // a plan's grid covers its longest problem
+  if (tok0 >= p.T) return false;                                  // a plan's grid covers its longest problem
   const int KB = p.KB;
 
   // ---- per-unit operands: Eout rows of the wave's tiles (B operand of the reconstruction), 4 modes per lane
@@ -465,7 +459,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 #pragma unroll
         for (int r = 0; r < AR; ++r) sums(run)[((wave * TB + tb) * AR + r) * 64 + lane] = acc[tb][r];
     __syncthreads();
-    if (run > 0) return;
+    if (!PAIR && run > 0) return false;
 #pragma unroll
     for (int s = 1; s < KS; ++s)
 #pragma unroll
@@ -480,6 +474,13 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
 
   if constexpr (PAIR) {
     // ---- lane (r16, g) holds out[token 4 (g & 1) + i][row r16 of tile g >> 1 of the pair]
+    bool bad = false;
+#pragma unroll
+    for (int u = 0; u < AR; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bad |= (__builtin_bit_cast(uint32_t, acc[0][u][i]) & 0x7F800000u) == 0x7F800000u;
+    if (__syncthreads_or(run == 0 && bad)) return true;
+    if (run > 0) return false;
 #pragma unroll
     for (int u = 0; u < AR; ++u) {
       const int tile = tile0 + 2 * u + (g >> 1), row = tile * kTileRows + r16;
@@ -490,7 +491,7 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
           if (b < p.T) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, acc[0][u][i], p.flags);
         }
     }
-    return;
+    return false;
   }
   // ---- store: lane (r16, g) holds out[token 16 tb + 4g + i][row r16 of tile r]
 #pragma unroll
@@ -505,6 +506,37 @@ void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
           if (b < p.T) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, acc[tb][r][i], p.flags);
         }
     }
+  }
+  return false;
+}
+
+template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR = false>
+__global__ __launch_bounds__(64 * NW * KS, min_waves(TB))
+void stage_gemm_kernel(const WorkItem* __restrict__ items, StageProb single) {
+  // Two buffers each, as objects of their own and chosen at compile time (the loop is written out twice).  With one
+  // array and a run-time offset no LDS read could move across the direct-to-LDS loads of the next block: they were
+  // all issued first, and the first read then waited for them to land, in every block.  Now the reads of a block
+  // go ahead and the loads follow between its products (2048 tokens on 4096 x 4096, k = 2656: 139 -> 124 us; 40
+  // tokens: 61 -> 42 us).
+  constexpr int kVinBufBytes = vin_buf_bytes(TB);
+  __shared__ __attribute__((aligned(1024))) unsigned char vin_lds_a[KS * kVinBufBytes];   // [16*TB tokens][16 chunks of 16 B], swizzled
+  __shared__ __attribute__((aligned(1024))) unsigned char vin_lds_b[KS * kVinBufBytes];
+  __shared__ __attribute__((aligned(1024))) unsigned char ein_lds_a[KS * kEinBufBytes];   // [128 columns][16 modes]
+  __shared__ __attribute__((aligned(1024))) unsigned char ein_lds_b[KS * kEinBufBytes];
+  const bool bad = stage_gemm_rows<NW, R, TB, MODE, BATCH, KS, PAIR>(items, single, threadIdx.x, 0, vin_lds_a, vin_lds_b, ein_lds_a, ein_lds_b);
+  if constexpr (PAIR) {
+    // An entry of E beyond fp16 in a row of one tile has met the zeros of the other tile's tokens and left a NaN in that
+    // tile's row too: the tiles one by one (the same sums).  Looking for such results takes 0.4 % of a pass of 224 matrices
+    // with 8 tokens (722.7 -> 725.8 us).  The operands are hidden from the compiler, which would keep
+    // addresses of the first pass for this one in the registers of its loop.
+    int thread = threadIdx.x;
+    asm volatile("" : "+s"(items), "+v"(thread));
+    if (__builtin_expect(bad, 0))
+#pragma unroll 1
+      for (int r = 0; r < R; ++r) {
+        __syncthreads();                                       // every wave is done with the staging buffers
+        stage_gemm_rows<NW, 1, TB, MODE, BATCH, KS, false>(items, single, thread, r * NW, vin_lds_a, vin_lds_b, ein_lds_a, ein_lds_b);
+      }
   }
 }
 

@@ -769,6 +769,33 @@ def test_item_forms_of_many_token_plans(gpu, copies, T, l, x_dtype):
         assert torch.equal(Y, Y[:1].expand_as(Y))
 
 
+@pytest.mark.parametrize("m,k,copies,T", [(2100, 600, 50, 8), (2100, 600, 100, 5), (52, 300, 1500, 6)])
+@pytest.mark.parametrize("l,x_dtype", [(16, "f16"), (8, "bf16"), (5, "f32")])
+def test_rows_beyond_fp16_stay_by_themselves(gpu, m, k, copies, T, l, x_dtype):
+    """Plans that take two row tiles in one product (items of 8 and 16 tiles, one and two runs): a row whose entries leave
+    fp16 and one of NaNs are not finite, the other rows the same bits as without them; results are added once."""
+    torch, mb = gpu
+    L = synth.make_layer(m, 72, k, l, seed=60, env_dtype="f16", env_kind="unit", signed_env=True)
+    L["Q"][:, 0] = 2.0                                      # row 5 of A: every entry of its E beyond fp16
+    bad = dict(L, A=L["A"].copy())
+    bad["A"][5], bad["A"][5, 0], bad["A"][m - 1, l - 1] = 0.0, 60000.0, np.nan
+    X = synth.make_activations(72, T, seed=61, x_dtype=x_dtype)
+    outs = []
+    for which in (L, bad):
+        dl, Xd = mb.DeviceLayer.from_host(which), _to_dev(torch, X, x_dtype)
+        Y = torch.ones((copies, T, m), dtype=torch.float32, device="cuda:0")
+        plan = mb.BatchPlan([dl] * copies, [Xd] * copies, list(Y), accumulate=True)
+        assert plan.kernel(2) == "stage_gemm_kernel"
+        plan.run()
+        outs.append(Y)
+    clean, got = outs
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    assert orc.max_rel_error(clean[0].cpu().numpy() - 1.0, ref) <= TOL + 2.0 ** -23 / np.abs(ref).max()
+    assert not torch.isfinite(got[:, :, [5, m - 1]]).any()
+    keep = [r for r in range(m) if r not in (5, m - 1)]
+    assert torch.equal(got[:, :, keep], clean[:, :, keep])
+
+
 @pytest.mark.parametrize("tokens", [(1, 1, 1), (3, 3, 3), (1, 9, 2)])
 @pytest.mark.parametrize("x_dtype,y_dtype", [("f16", "f32"), ("f32", "f16")])
 def test_small_plans_of_rank_16(gpu, tokens, x_dtype, y_dtype):
