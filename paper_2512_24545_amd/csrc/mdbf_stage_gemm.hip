@@ -149,6 +149,15 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
                                                 unsigned char* vin_lds_a, unsigned char* vin_lds_b,
                                                 unsigned char* ein_lds_a, unsigned char* ein_lds_b) {
   constexpr int kVinBufBytes = vin_buf_bytes(TB);
+  // The wave's tiles in pairs: both tiles' rows in one 32 x 32 rebuild, and (kWide, single problems) in 32 x 32 products
+  // with 32 tokens each, whose sums are the same bits as those of 16 x 16.  The rebuild takes half of the matrix cores' time,
+  // and a step's activations are all requested before its rebuild (after it: 3 to 10 % longer).  4096 x 4096, k = 2656,
+  // fp16, with the same tile shapes: 512 tokens 83.5 -> 69.6 us, 1024 92.3 -> 79.4, 4096 235.6 -> 230.7; 2048 (two
+  // workgroups a unit hide each other's waits) 122.4 -> 121.2, nothing on another box; bf16, 1024 tokens 100 -> 85.
+  // (Plans of 17 to 64 tokens are not faster for it: 200 attention layers, 30 tokens 484 -> 486 us, 60 tokens 714 -> 733.)
+  constexpr bool kWide = !BATCH && R == 2;
+  static_assert(!kWide || (TB % 2 == 0 && KS == 1), "32 tokens at a time, one run");
+  constexpr bool kPairs = PAIR || kWide;
   // the rows of this workgroup: a work item of a plan (at most NW * R row tiles of one problem), or
   // the blockIdx.x-th run of NW * R tiles of the single problem
   StageProb p;
@@ -189,24 +198,24 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
   const int KB = p.KB;
 
   // ---- per-unit operands: Eout rows of the wave's tiles (B operand of the reconstruction), 4 modes per lane
-  // (PAIR: pairs of tiles 2u, 2u + 1; lane (n, h) = (lane & 31, lane >> 5): eight modes 8h .. of row n of a pair's 32)
+  // (kPairs: pairs of tiles 2u, 2u + 1; lane (n, h) = (lane & 31, lane >> 5): eight modes 8h .. of row n of a pair's 32)
   half4 eo_op[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int tile = tile0 + (PAIR ? (r & ~1) + (g & 1) : r);
+    const int tile = tile0 + (kPairs ? (r & ~1) + (g & 1) : r);
     const int row = min(tile * kTileRows + r16, p.rows - 1);           // (rows past the end are not stored)
-    eo_op[r] = load4_modes(p, p.Eout, row, PAIR ? 8 * (g >> 1) + 4 * (r & 1) : 4 * g);
+    eo_op[r] = load4_modes(p, p.Eout, row, kPairs ? 8 * (g >> 1) + 4 * (r & 1) : 4 * g);
   }
-  // sign words: tiles past the end read the last tile (their rows are never stored).  PAIR: word 2u + s of the lane holds
+  // sign words: tiles past the end read the last tile (their rows are never stored).  kPairs: word 2u + s of the lane holds
   // columns 16 s + 8 h + 0 .. 7 of each step of its row.
   const MDBF_GLOBAL uint32_t* sbase[R];
   size_t sstride[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const int t = min(tile0 + (PAIR ? (r & ~1) + (g & 1) : r), item_end - 1);
-    sbase[r] = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(t, KB) + (PAIR ? 16 * (2 * (r & 1) + (g >> 1)) + r16 : lane);
+    const int t = min(tile0 + (kPairs ? (r & ~1) + (g & 1) : r), item_end - 1);
+    sbase[r] = (const MDBF_GLOBAL uint32_t*)p.S + tile_base_words(t, KB) + (kPairs ? 16 * (2 * (r & 1) + (g >> 1)) + r16 : lane);
     // (an item's tiles are in one group)
-    sstride[r] = (size_t)group_tiles(PAIR ? item_tile0 : t, p.ntiles) * 64u;
+    sstride[r] = (size_t)group_tiles(kPairs ? item_tile0 : t, p.ntiles) * 64u;
   }
 
   constexpr int AR = PAIR ? R / 2 : R;                         // accumulators per slab: a pair's tiles share one
@@ -215,6 +224,13 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
   for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
     for (int r = 0; r < AR; ++r) acc[tb][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+  typedef float floatx16 __attribute__((ext_vector_type(16)));
+  floatx16 z16;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z16[i] = 0.f;
+  floatx16 wacc[(TB + 1) / 2];                                 // kWide: per 32 tokens
+#pragma unroll
+  for (int tb = 0; tb < TB / 2; ++tb) wacc[tb] = z16;
 
   // ---- staging of one block.  Envelope rows and sign words go through registers.  fp16 activations
   //      (kDma) go from global memory straight into LDS, 16 bytes per lane and 1 KB (four token rows) per
@@ -313,7 +329,7 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
       const int id = tid + 64 * NW * i;
       const u32x4 v = ein_reg[i];
       const bool ok = ein_ok[i];
-      *reinterpret_cast<u32x4*>(ein_buf + ein_row(id >> 1) * 32 + (((id & 1) ^ ((id >> (PAIR ? 4 : 5)) & 1)) << 4)) =
+      *reinterpret_cast<u32x4*>(ein_buf + ein_row(id >> 1) * 32 + (((id & 1) ^ ((id >> (kPairs ? 4 : 5)) & 1)) << 4)) =
           u32x4{ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u};
     }
   };
@@ -355,19 +371,36 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
     if (KS == 1 || q < q_hi)                                   // (uniform; the barriers are kept)
 #pragma unroll
     for (int ff = 0; ff < 4; ++ff) {
-      const int f = BATCH ? 3 - ff : ff;
-      if constexpr (PAIR) {
+      const int f = 3 - ff;
+      if constexpr (kPairs) {
         // 32 rows x 32 columns of E in one product (half the time of four 16 x 16 x 16).  Its row m is column m with bits
         // 2 and 3 exchanged, row m of the step in LDS, so that lane (n, h) receives columns 16 s + 8 h + 0 .. 7 of row n
-        // in registers 8 s + 0 .. 7.  Seen as an operand of a 16 x 16 x 32 product, its lane groups alternate between the
-        // two tiles; rows 0 .. 7 of the other operand hold the tokens for the first tile's groups and zeros for the
-        // second's, rows 8 .. 15 the other way round.
-        typedef float floatx16 __attribute__((ext_vector_type(16)));
+        // in registers 8 s + 0 .. 7: an operand of a 32 x 32 x 16 product with the tokens.
         const int m = lane & 31, h = lane >> 5;
         const half8 ea = *reinterpret_cast<const half8*>(ein + (32 * f + m) * 32 + ((h ^ ((m >> 2) & 1)) << 4));
-        floatx16 z16;
+        if constexpr (kWide) {
+          const half8 eo = __builtin_shufflevector(eo_op[0], eo_op[R - 1], 0, 1, 2, 3, 4, 5, 6, 7);
+          half8 x[2][TB / 2];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) z16[i] = 0.f;
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int tb = 0; tb < TB / 2; ++tb)
+              x[s][tb] = *reinterpret_cast<const half8*>(vin + (32 * tb + m) * 256 + (((4 * f + 2 * s + h) ^ (m & 15)) << 4));
+          const floatx16 e = __builtin_amdgcn_mfma_f32_32x32x16_f16(ea, eo, z16, 0, 0, 0);
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            u32x4 w;
+#pragma unroll
+            for (int i = 3; i >= 0; --i) w[i] = flip_next(pack_half2(e[8 * s + 2 * i], e[8 * s + 2 * i + 1]), sw[s]);
+#pragma unroll
+            for (int tb = 0; tb < TB / 2; ++tb)
+              wacc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[s][tb], __builtin_bit_cast(half8, w), wacc[tb], 0, 0, 0);
+          }
+          continue;
+        }
+        // PAIR: seen as an operand of a 16 x 16 x 32 product, its lane groups alternate between the
+        // two tiles; rows 0 .. 7 of the other operand hold the tokens for the first tile's groups and zeros for the
+        // second's, rows 8 .. 15 the other way round.
         const int tok = (r16 & 7) + 8 * ((r16 >> 3) ^ (g & 1));
         half8 x[2];
 #pragma unroll
@@ -400,18 +433,10 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
         // lane (r16, g) now holds E[row r16][32f + 8g + e], e = 0..3 in e0 and 4..7 in e1.  The packed word
         // keeps the signs of columns e = 2i and 2i+1 at bits p and p + 16, p = 8(f/2) + 4(f%2) + i.
         uint32_t w4[4];
-        if (BATCH) {
-          w4[3] = flip_next(pack_half2(e1[2], e1[3]), sw[r]);
-          w4[2] = flip_next(pack_half2(e1[0], e1[1]), sw[r]);
-          w4[1] = flip_next(pack_half2(e0[2], e0[3]), sw[r]);
-          w4[0] = flip_next(pack_half2(e0[0], e0[1]), sw[r]);
-        } else {
-          const int pbase = 8 * (f >> 1) + 4 * (f & 1);
-          w4[0] = pack_half2(e0[0], e0[1]) ^ ((sw[r] << (15 - (pbase + 0))) & 0x80008000u);
-          w4[1] = pack_half2(e0[2], e0[3]) ^ ((sw[r] << (15 - (pbase + 1))) & 0x80008000u);
-          w4[2] = pack_half2(e1[0], e1[1]) ^ ((sw[r] << (15 - (pbase + 2))) & 0x80008000u);
-          w4[3] = pack_half2(e1[2], e1[3]) ^ ((sw[r] << (15 - (pbase + 3))) & 0x80008000u);
-        }
+        w4[3] = flip_next(pack_half2(e1[2], e1[3]), sw[r]);
+        w4[2] = flip_next(pack_half2(e1[0], e1[1]), sw[r]);
+        w4[1] = flip_next(pack_half2(e0[2], e0[3]), sw[r]);
+        w4[0] = flip_next(pack_half2(e0[0], e0[1]), sw[r]);
         wop[r] = __builtin_bit_cast(half8, u32x4{w4[0], w4[1], w4[2], w4[3]});
       }
       // the step's A operands (one per token slab) are all requested before the first product
@@ -491,6 +516,19 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
           if (b < p.T) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, acc[0][u][i], p.flags);
         }
     }
+    return false;
+  }
+  if constexpr (kWide) {
+    // ---- lane (n, h) holds out[token 32 tb + 8 (i / 4) + 4 h + i % 4][row n of the pair's 32]
+    const int row = tile0 * kTileRows + (lane & 31);
+    if (tile0 + (g & 1) < item_end && row < p.rows)
+#pragma unroll
+      for (int tb = 0; tb < TB / 2; ++tb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int b = tok0 + 32 * tb + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+          if (b < p.T) emit_result(p.out, (int64_t)b * p.out_ld + row, p.out_dt, wacc[tb][i], p.flags);
+        }
     return false;
   }
   // ---- store: lane (r16, g) holds out[token 16 tb + 4g + i][row r16 of tile r]
@@ -1021,7 +1059,7 @@ static int launch_rtmb(const WorkItem* items_dev, int nitems, const StageProb* p
 
 template <int R, int TB, int MODE>
 static int launch_rtm(const StageProb* p, hipStream_t s) {
-  if constexpr (TB >= 6 || (R == 1 && MODE != kGeneric)) return launch_rtmb<kWaves, R, TB, MODE, false, 1>(nullptr, 0, p, s);
+  if constexpr (R == 2 || MODE != kGeneric) return launch_rtmb<kWaves, R, TB, MODE, false, 1>(nullptr, 0, p, s);
   return (int)hipErrorInvalidValue;
 }
 
@@ -1126,22 +1164,23 @@ __global__ __launch_bounds__(256) void half_copy_kernel(HalfCopies a) {
 
 }  // namespace gemm
 
-// Row tiles per wave and token slabs per workgroup for a single problem of more than 32 tokens.  A column block takes
-// a workgroup that has a compute unit to itself about 600 + 110 TB ns with two tiles per wave (rebuilding its piece
-// of the factor, then the slabs), 800 and 700 ns with one tile and four or two slabs (mostly the wait for the next
-// block's activations); every further workgroup on the unit adds two thirds of that.  Fewer slabs make more,
-// lighter workgroups: worth it when that evens out the last round (166 row tiles x 2048 tokens: 336 workgroups of 8
-// slabs leave most units with one workgroup and some with two; 462 of 6 slabs fill them) or fills the device at all
-// (300 tokens on 4096 x 4096, k = 2656: 63 workgroups of 2 x 8 take 79 us, 210 of 1 x 4 61 us).  Each output is
-// the same sum in the same order whatever the choice.  The element-wise mode has the two-tile forms only.
+// Row tiles per wave and token slabs per workgroup for a single problem of more than 32 tokens.  In ns per column block: what a
+// workgroup takes that has a compute unit to itself (mostly the wait for the next block's activations), and what each adds
+// to a unit with several, between the mean number per unit and the busiest unit's (fitted to 200 to 1048 us long calls of
+// 70 to 4096 tokens on 4096 x 4096, k = 2656, 11008 x 4096 and 4096 x 11008, k = 4096, and 1024 x 1024, k = 512).  Fewer slabs
+// make more, lighter workgroups: worth it when that evens out the last round or fills the device at all.  4096 x 11008,
+// k = 4096, us per call with 2 x 8, 2 x 6, 2 x 4, 2 x 2, 1 x 2: 256 tokens 155, 131, 122, 96, 106; 512: 156, 136, 123, 121,
+// 144; 777: 165, 172, 149, 200, 249; 1300: 225, 202, 226, 300, 362; 4096: 538, 604, 610, 816, 1039.  (2 x 7 and 1 x 4 are
+// nowhere the best.)  Each output is the same sum in the same order whatever the choice.  The element-wise mode has the
+// two-tile forms only.
 struct LongShape {
   int R, TB;
 };
 static LongShape long_problem_shape(const StageProb& p, bool vectors) {
   static const struct {
     LongShape shape;
-    int ns;
-  } forms[] = {{{2, 8}, 1480}, {{2, 7}, 1370}, {{2, 6}, 1260}, {{1, 4}, 800}, {{1, 2}, 700}};
+    int alone, more;
+  } forms[] = {{{2, 8}, 1320, 1140}, {{2, 6}, 1080, 900}, {{2, 4}, 960, 690}, {{2, 2}, 710, 470}, {{1, 2}, 620, 360}};
   const int cus = compute_units();
   LongShape best = {2, 8};
   double least = -1.0;
@@ -1149,7 +1188,7 @@ static LongShape long_problem_shape(const StageProb& p, bool vectors) {
     if (f.shape.R == 1 && !vectors) continue;
     const int tiles = f.shape.R * gemm::kWaves;
     const int64_t wgs = (int64_t)((p.ntiles + tiles - 1) / tiles) * ((p.T + 16 * f.shape.TB - 1) / (16 * f.shape.TB));
-    const double cost = f.ns * (1.0 + (double)((wgs + cus - 1) / cus - 1) * (2.0 / 3.0));
+    const double cost = std::max((double)f.alone, f.more * 0.5 * ((double)wgs / cus + (double)((wgs + cus - 1) / cus)));
     if (least < 0.0 || cost < least) {
       least = cost;
       best = f.shape;
@@ -1218,10 +1257,10 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const Sta
   const bool vectors = mode != gemm::kGeneric;
   if (p->T > kFewMaxTokens || (p->T > 32 && vectors)) {
     const LongShape f = long_problem_shape(*p, vectors);
-    if (f.R == 1 && f.TB == 2) return gemm::launch_rt<1, 2>(mode, p, s);
-    if (f.R == 1) return gemm::launch_rt<1, 4>(mode, p, s);
+    if (f.R == 1) return gemm::launch_rt<1, 2>(mode, p, s);
+    if (f.TB == 2) return gemm::launch_rt<2, 2>(mode, p, s);
+    if (f.TB == 4) return gemm::launch_rt<2, 4>(mode, p, s);
     if (f.TB == 6) return gemm::launch_rt<2, 6>(mode, p, s);
-    if (f.TB == 7) return gemm::launch_rt<2, 7>(mode, p, s);
     return gemm::launch_rt<2, 8>(mode, p, s);
   }
   if (p->T > 16 && vectors) return gemm::launch_rt<1, 2>(mode, p, s);

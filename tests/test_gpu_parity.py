@@ -769,6 +769,25 @@ def test_item_forms_of_many_token_plans(gpu, copies, T, l, x_dtype):
         assert torch.equal(Y, Y[:1].expand_as(Y))
 
 
+@pytest.mark.parametrize("n,k,l,x_dtype", [(264, 136, 16, "f16"), (136, 264, 8, "bf16"), (264, 136, 16, "f32"), (131, 137, 5, "f16")])
+def test_tile_shapes_of_long_calls(gpu, n, k, l, x_dtype):
+    """256 row tiles with lengths that take each tile shape on the second factor (2 x 8, 2 x 6, 2 x 4, 2 x 2, 1 x 2), the last
+    slabs cut, the last rows missing: the same bits as the longest call's, which meets the oracle; fp16 copies and operands
+    as they are."""
+    torch, mb = gpu
+    m = 4090
+    L = synth.make_layer(m, n, k, l, seed=n + k + l, env_dtype="f16", env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 2041, seed=7, x_dtype=x_dtype)
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, x_dtype)
+    full = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    rows = list(range(0, 2041, 51)) + list(range(2009, 2041))
+    assert orc.max_rel_error(full[rows].cpu().numpy(), orc.forward_factored(*_oracle_args(L), X[rows])) <= TOL
+    for T in (65, 97, 290, 383, 639, 769, 1300, 2041):
+        ws = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32", precise=True), T), dtype=torch.uint8, device="cuda:0")
+        assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32"), full[:T]), T
+        assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32", workspace=ws), full[:T]), T
+
+
 @pytest.mark.parametrize("m,k,copies,T", [(2100, 600, 50, 8), (2100, 600, 100, 5), (52, 300, 1500, 6)])
 @pytest.mark.parametrize("l,x_dtype", [(16, "f16"), (8, "bf16"), (5, "f32")])
 def test_rows_beyond_fp16_stay_by_themselves(gpu, m, k, copies, T, l, x_dtype):
