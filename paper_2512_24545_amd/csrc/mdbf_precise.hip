@@ -155,11 +155,13 @@ __device__ __forceinline__ void load_ein(const StageProb& p, int q, int lane, Ei
   const uint32_t count = (uint32_t)p.K * l;
   constexpr int kWords = sizeof(e.v[0]) / 4;
   typedef uint32_t vec __attribute__((ext_vector_type(kWords), aligned(ENV == MDBF_F32 ? 4 : 2)));
+  const bool few = !VEC && count < EB::kPer;                                      // (uniform) no vector fits in:
+  const void* from = few ? (const void*)p.S : p.Ein;                              // any will do, ein_tail takes them one by one
 #pragma unroll
   for (int i = 0; i < EB::kLoads; ++i) {
     uint32_t first = ein_first<ENV, M>(p.K, l, q, i, lane);
-    if (!VEC) first = min(first, count < EB::kPer ? 0u : count - EB::kPer);       // (ein_tail moves the rest)
-    const vec v = *(const MDBF_GLOBAL vec*)((const MDBF_GLOBAL char*)p.Ein + (uint32_t)dtype_size(ENV) * first);
+    if (!VEC) first = min(first, few ? 0u : count - EB::kPer);                    // (ein_tail moves the rest)
+    const vec v = *(const MDBF_GLOBAL vec*)((const MDBF_GLOBAL char*)from + (uint32_t)dtype_size(ENV) * first);
 #pragma unroll
     for (int t = 0; t < kWords; ++t) {
       if constexpr (kWords == 1) e.v[i][t] = v.x;
@@ -168,17 +170,37 @@ __device__ __forceinline__ void load_ein(const StageProb& p, int q, int lane, Ei
   }
 }
 
-// Blocks near the end of rows that are read past their last mode: where that would leave the factor, a vector from further down was
-// loaded (of a 16-bit factor of fewer than eight elements, some from behind it, in the same 16 bytes).
+// Blocks near the end of rows that are read past their last mode: where that would leave the factor, the factor's last
+// vector was loaded (of a factor of fewer elements than a vector, none).  What lies behind the end is no number of the
+// layer's and would survive its product with a zero mode if it were an infinity or NaN: zeros take its place.
 template <int ENV, int M>
 __device__ __forceinline__ void ein_tail(const StageProb& p, int q, int lane, EinBlock<ENV, M>& e) {
   typedef EinBlock<ENV, M> EB;
   const int count = p.K * p.l;
+  if (count < EB::kPer) {                                               // (uniform)
+#pragma unroll
+    for (int i = 0; i < EB::kLoads; ++i) {
+      const int first = (int)ein_first<ENV, M>(p.K, (uint32_t)p.l, q, i, lane);
+      uint32_t x[EB::kPer];
+#pragma unroll
+      for (int t = 0; t < EB::kPer; ++t) {
+        const uint32_t j = (uint32_t)min(first + t, count - 1);
+        x[t] = ENV == MDBF_F32 ? at<uint32_t>(p.Ein, j) : (uint32_t)at<uint16_t>(p.Ein, j);
+        x[t] = first + t < count ? x[t] : 0u;
+      }
+#pragma unroll
+      for (int t = 0; t < EB::kPer; ++t) {
+        if constexpr (ENV == MDBF_F32) e.v[i][t] = x[t];
+        else if (t % 2 == 0) e.v[i][t / 2] = x[t] | (x[t + 1] << 16);
+      }
+      __builtin_amdgcn_sched_barrier(0);                                // (one vector at a time: registers)
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < EB::kLoads; ++i) {
     const int first = (int)ein_first<ENV, M>(p.K, (uint32_t)p.l, q, i, lane);
-    const int have = count - first;                                     // elements from `first` to the end
-    const int down = max(0, first - max(0, count - EB::kPer));
+    const int down = max(0, first - (count - EB::kPer));
     if constexpr (ENV == MDBF_F32) {
 #pragma unroll
       for (int t = 0; t < EB::kPer; ++t) {
@@ -197,8 +219,6 @@ __device__ __forceinline__ void ein_tail(const StageProb& p, int q, int lane, Ei
         lo = (lo >> sh) | (hi << (64 - sh));
         hi >>= sh;
       }
-      lo = have <= 0 ? 0 : have < 4 ? lo & ((1ull << (16 * have)) - 1) : lo;
-      hi = have <= 4 ? 0 : have < 8 ? hi & ((1ull << (16 * (have - 4))) - 1) : hi;
       e.v[i][0] = (uint32_t)lo;
       e.v[i][1] = (uint32_t)(lo >> 32);
       e.v[i][2] = (uint32_t)hi;

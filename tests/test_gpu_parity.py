@@ -874,6 +874,48 @@ def test_plans_of_few_tokens_in_fp32(gpu, specs, env_dtype, x_dtype, T):
         assert torch.equal(Y, before)
 
 
+def _between_nans(torch, dl):
+    """The layer with every envelope factor a 16-byte aligned view into a buffer of NaNs."""
+    def view(e):
+        buf = torch.full((16 + e.numel() + 16,), float("nan"), dtype=e.dtype, device=e.device)
+        v = buf[16:16 + e.numel()].view(e.shape)
+        v.copy_(e)
+        return v
+    return type(dl)(dl.m, dl.n, dl.k, dl.l, dl.SA_packed, dl.SB_packed, *[view(e) for e in (dl.A, dl.Q, dl.G, dl.B)])
+
+
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", ONE_TOKEN_EDGES)
+def test_one_token_calls_use_nothing_behind_the_envelopes(gpu, m, n, k, l, env_dtype, x_dtype):
+    """The last rows' vectors end with the factor: what lies behind it meets zero modes only, and a NaN there would stay one."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    Xd = _to_dev(torch, synth.make_activations(n, 1, seed=9 + m, x_dtype=x_dtype), x_dtype)
+    dl = mb.DeviceLayer.from_host(L)
+    assert torch.equal(mb.mdbf_forward(_between_nans(torch, dl), Xd), mb.mdbf_forward(dl, Xd))
+
+
+@pytest.mark.parametrize("env_dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("m,n,k,l", [(33, 1, 3, 1), (17, 3, 1, 1), (20, 2, 2, 1), (18, 1, 1, 2), (40, 1, 2, 3), (5, 4, 1, 1), (9, 7, 1, 1)])
+def test_plans_of_mixed_ranks_with_the_smallest_factors(gpu, m, n, k, l, env_dtype):
+    """Rows of 16 modes at most next to a factor of fewer entries than a lane's vector holds (four in fp32, eight in the
+    16-bit types)."""
+    torch, mb = gpu
+    specs = [(90, 700, 650, 16), (m, n, k, l)]
+    layers, Xs, Ys, refs = [], [], [], []
+    for i, s in enumerate(specs):
+        L = synth.make_layer(*s, seed=70 + i, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+        X = synth.make_activations(s[1], 2, seed=80 + i, x_dtype="f32")
+        refs.append(orc.forward_factored(*_oracle_args(L), X))
+        layers.append(_between_nans(torch, mb.DeviceLayer.from_host(L)))
+        Xs.append(_to_dev(torch, X, "f32"))
+        Ys.append(torch.zeros((2, s[0]), dtype=torch.float32, device="cuda:0"))
+    plan = mb.BatchPlan(layers, Xs, Ys)
+    assert plan.kernel(1) == plan.kernel(2) == "stage_one_kernel"
+    plan.run()
+    for Y, ref in zip(Ys, refs):
+        assert orc.max_rel_error(Y.cpu().numpy(), ref) <= 2e-5
+
+
 # ---------------------------------------------------------------- the synthetic decoder stack
 @pytest.mark.parametrize("budget", ["1.0", "1.5", "2.0"])
 @pytest.mark.parametrize("T", [1, 8])
