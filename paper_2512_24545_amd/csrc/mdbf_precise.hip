@@ -263,7 +263,8 @@ __device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row
   }
   if constexpr (ENV != MDBF_F16) {
     // The products of two envelope entries of these types can leave the range of fp32 where entry times activation
-    // does not: the row's largest entry goes to [1, 2), the power of two comes back with the result.
+    // does not: the row's largest entry goes below 1 / M, so that a sum of M products with entries of any size stays in
+    // range (the smallest, 2^-126, keep 19 of their bits with M = 16); the power of two comes back with the result.
     float v[kN];
     float big = 0.f;
 #pragma unroll
@@ -273,7 +274,7 @@ __device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row
     }
     big = fmaxf(big, __shfl_xor(big, 16));
     big = fmaxf(big, __shfl_xor(big, 32));
-    if (big > 0.f && big < __builtin_huge_valf()) o.e = ilogbf(big);
+    if (big > 0.f && big < __builtin_huge_valf()) o.e = ilogbf(big) + (M == 4 ? 3 : M == 8 ? 4 : 5);
 #pragma unroll
     for (int t = 0; t < kN; ++t) v[t] = ldexpf(v[t], -o.e);
     if constexpr (ENV == MDBF_F32) {

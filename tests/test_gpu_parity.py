@@ -528,6 +528,34 @@ def test_one_token_calls_are_fp32(gpu, m, n, k, l, env_dtype, x_dtype):
         assert orc.max_rel_error(got, ref) <= 2e-5
 
 
+@pytest.mark.parametrize("where", ["single", "plan"])
+@pytest.mark.parametrize("l", [1, 4, 8, 13, 16])
+@pytest.mark.parametrize("env_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("ein,eout,x", [(127, -110, -100), (127, 0, -100), (-125, 100, 100), (-123, 0, 100)])
+def test_one_token_calls_with_envelopes_near_the_ends_of_fp32(gpu, ein, eout, x, env_dtype, l, where):
+    """Entries of one factor's input side in [2^ein, 2^(ein + 1)), of its output side in [2^eout, 2^(eout + 1)): sums of
+    their products leave fp32, or its normal range, although every entry times its activation and every result is in it.
+    At the lower end an entry of the rebuilt factor is rounded at 2^-150, 2^-18 of it at most."""
+    torch, mb = gpu
+    m, n, k = 40, 300, 150
+    L = synth.make_layer(m, n, k, l, seed=l, env_dtype="f32", env_kind="unit", signed_env=True)
+    for f in "AQGB":
+        L[f] = synth.round_to_dtype(np.sign(L[f]) * (1.0 + np.abs(L[f]) % 0.98), env_dtype)
+    X = synth.make_activations(n, 1, seed=3, x_dtype="f32")
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    Xd = _to_dev(torch, X * np.float32(2.0 ** x), "f32")
+    for inner, outer in (("B", "G"), ("Q", "A")):
+        H = dict(L, env_dtype=env_dtype)
+        H[inner] = L[inner] * np.float32(2.0 ** ein)
+        H[outer] = L[outer] * np.float32(2.0 ** eout)
+        dl, Y = mb.DeviceLayer.from_host(H), torch.zeros((1, m), device="cuda:0")
+        if where == "single":
+            mb.mdbf_forward(dl, Xd, Y=Y)
+        else:
+            mb.BatchPlan([dl], [Xd], [Y]).run()
+        assert orc.max_rel_error(Y.cpu().numpy().astype(np.float64) * 2.0 ** -(ein + eout + x), ref) <= 2e-5
+
+
 @pytest.mark.parametrize("where", ["single", "forced", "plan"])
 @pytest.mark.parametrize("l,T", [(8, 1), (16, 1), (16, 3)])
 def test_non_finite_input_reaches_every_output_of_the_block_scaled_kernels(gpu, l, T, where):
