@@ -624,12 +624,24 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
   h->gemm = (many == count && !precise && forced != count) ? 1 : 0;
   for (int s = 0; s < 2; ++s)
     if (h->gemm || (forced != count && !mx_worthwhile(tiles[s]) && all_fast[s])) mx[s] = 0;
-  h->one = one && one_plan_pays(pieces, h->max_tokens, max_blocks, mx, all_fast) ? rank + 32 * layers[0].desc.env_dtype : 0;
+  // (work items of `tpi` row tiles in stage s, and whether a launch takes that many)
+  auto count_items = [&](int s, int tpi) {
+    long n = 0;
+    for (int i = 0; i < count; ++i) n += (num_tiles(s == 0 ? layers[i].desc.k : layers[i].desc.m) + tpi - 1) / tpi;
+    return n;
+  };
+  auto fits = [&](int s, int tpi) { return count_items(s, tpi) + mx_max_workgroups() <= 65535; };
+  h->one = one && one_plan_pays(pieces, h->max_tokens, max_blocks, mx, all_fast) && fits(0, one_item_tiles()) &&
+                   fits(1, one_item_tiles())
+               ? rank + 32 * layers[0].desc.env_dtype
+               : 0;
   if (h->one) mx[0] = mx[1] = 0;
   // otherwise one tile count per work item for both stages keeps one kernel instantiation per plan
-  const int tpi_fp16 = all_fast[0] && all_fast[1] && all_pre
-                           ? mfma_plan_tiles_per_item(tiles, blocks, max_blocks, h->max_tokens)
-                           : mfma_tiles_per_item(tiles[0] < tiles[1] ? tiles[0] : tiles[1]);
+  const int tpi_long = mfma_tiles_per_item(tiles[0] < tiles[1] ? tiles[0] : tiles[1]);
+  int tpi_fp16 = all_fast[0] && all_fast[1] && all_pre
+                     ? mfma_plan_tiles_per_item(tiles, blocks, max_blocks, h->max_tokens)
+                     : tpi_long;
+  if (!fits(0, tpi_fp16) || !fits(1, tpi_fp16)) tpi_fp16 = tpi_long;   // (the smaller factor alone says little about the other)
   long nitems[2] = {0, 0};
   for (int s = 0; s < 2; ++s) {
     h->mx[s] = mx[s];
@@ -645,11 +657,10 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
     h->tiles_per_item[s] = h->one ? one_item_tiles() : h->gemm ? gemm_tiles_per_item(tiles[s], h->max_tokens) : mx[s] ? tpi_mx : tpi_fp16;
   }
   h->fuse2 = (!precise && !h->gemm && h->mx[0] != 0 && h->mx[0] == h->mx[1]) ? 1 : 0;
-  for (int i = 0; i < count; ++i) {
-    nitems[0] += (num_tiles(layers[i].desc.k) + h->tiles_per_item[0] - 1) / h->tiles_per_item[0];
-    nitems[1] += (num_tiles(layers[i].desc.m) + h->tiles_per_item[1] - 1) / h->tiles_per_item[1];
+  for (int s = 0; s < 2; ++s) {
+    if (!fits(s, h->tiles_per_item[s])) return MDBF_EUNSUPPORTED;
+    nitems[s] = count_items(s, h->tiles_per_item[s]);
   }
-  if (nitems[0] + mx_max_workgroups() > 65535 || nitems[1] + mx_max_workgroups() > 65535) return MDBF_EUNSUPPORTED;
   h->nitems[0] = (int)nitems[0];
   h->nitems[1] = (int)nitems[1];
   size_t off = align_up(sizeof(PlanHeader), 256);

@@ -357,6 +357,35 @@ def test_launches_per_plan():
     assert L.mdbf_batch_plan_launches(None, 0) == -1
 
 
+def test_plans_of_many_row_tiles_take_larger_items():
+    """A launch takes fewer than 65535 work items.  Few tokens of rank 3: items of eight row tiles are the fp32 kernel's,
+    the general kernel has larger ones; rank 16 in fp16: items of four as long as both factors have few enough."""
+    L = mb.lib()
+
+    def plan(count, m, n, k, l, T, flags=0):
+        arr = (mb.Layer * count)()
+        for i in range(count):
+            arr[i].desc = mb.Desc(m, n, k, l, 0, 0, 0, flags)
+            arr[i].SA_packed_dev = arr[i].SB_packed_dev = arr[i].X_dev = arr[i].Y_dev = FAKE
+            arr[i].env = mb.Env(FAKE, FAKE, FAKE, FAKE)
+            arr[i].ldx, arr[i].ldy, arr[i].T = n, m, T
+        pb, wb = C.c_size_t(0), C.c_size_t(0)
+        status = L.mdbf_batch_plan_bytes(count, arr, C.byref(pb), C.byref(wb))
+        if status:
+            return status
+        buf = C.create_string_buffer(pb.value)
+        assert L.mdbf_batch_plan_build(count, arr, FAKE, wb.value, buf, pb.value) == 0
+        h = _PlanHeader.from_buffer_copy(buf.raw[:C.sizeof(_PlanHeader)])
+        return L.mdbf_batch_plan_kernel(buf, pb.value, 2).decode(), h.nitems[1]
+
+    assert plan(1, 16 * 500000, 300, 16 * 3000, 3, 1) == ("stage_one_kernel", 62500)
+    assert plan(1, 16 * 600000, 300, 16 * 10000, 3, 1) == ("stage_generic_kernel", 37500)
+    assert plan(1, 16 * 600000, 300, 300, 3, 1) == -5              # (what the general kernel refuses stays refused)
+    staged = mb.MDBF_FLAG_FP16_STAGED
+    assert plan(63, 16 * 800, 2560, 2560, 16, 2, staged) == ("stage_fast_kernel", 63 * 200)
+    assert plan(63, 16 * 5120, 2560, 2560, 16, 2, staged) == ("stage_fast_kernel", 63 * 320)
+
+
 def test_block_scaled_plan_picks_the_item_size_that_wastes_fewest_tile_slots():
     """166 row tiles are three items of 56 tiles (56 + 56 + 54), not 64 + 64 + 38: the same number of items, an
     eighth fewer sign words moved per item and no idle waves in the third.  256 row tiles stay four items of
