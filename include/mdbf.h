@@ -153,7 +153,8 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * with the same layer and types, in every one of 17 to 64 and in every one of 65 and more (of 17 and more with fp16
  * envelopes of rank 8 or 16, n and k multiples of eight and 16-byte aligned rows of X); between these ranges it
  * differs in the last bits.  Plans of four tokens and more may return a NaN where a value beyond fp16 makes a single
- * call return an infinity.
+ * call return an infinity.  An infinity among the envelopes leaves no finite output it reaches; whether those are
+ * infinities or NaNs is not specified (its products with entries of either sign are added, in parts).
  * Range: the one-token variants of plans carry their own power-of-two exponents (the block-scaled one per 32 values,
  * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32; single one-token calls work in fp32
  * throughout: they hold their accuracy wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope

@@ -705,7 +705,10 @@ __global__ __launch_bounds__(64 * kShortWaves) void stage_fast_short_kernel(cons
       v[i] = row16_sum(ev * P);
     }
     const int sel = n & 3;
-    if (n < 4) red[wave][r * kTileRows + 4 * kg + n] = (sel == 0 ? v[0] : sel == 1 ? v[1] : sel == 2 ? v[2] : v[3]) * unscale;
+    // (a wave without blocks leaves zeros: an infinite envelope entry times nothing would be a NaN)
+    if (n < 4)
+      red[wave][r * kTileRows + 4 * kg + n] =
+          q_lo < q_hi ? (sel == 0 ? v[0] : sel == 1 ? v[1] : sel == 2 ? v[2] : v[3]) * unscale : 0.f;
   }
   __syncthreads();
   if (tid < kShortTiles * kTileRows) {

@@ -867,6 +867,26 @@ def test_small_plans_of_rank_16(gpu, tokens, x_dtype, y_dtype):
             assert orc.max_rel_error(Y.float().cpu().numpy(), passes * ref) <= TOL + (2.0 ** -10 if y_dtype == "f16" else 0.0)
 
 
+@pytest.mark.parametrize("k", [1024, 1152, 1288, 1808])
+def test_small_plans_of_rank_16_with_an_infinite_envelope_entry(gpu, k):
+    """8, 9, 11 and 15 blocks on eight waves, some of which have none: terms of one sign times an infinity are one."""
+    torch, mb = gpu
+    L = synth.make_layer(40, 1024, k, 16, seed=k, env_dtype="f16", env_kind="unit")
+    L["SA"], L["SB"] = np.abs(L["SA"]), np.abs(L["SB"])
+    X = np.abs(synth.make_activations(1024, 1, seed=1, x_dtype="f16")) * np.float32(2.0 ** -6)
+    Xd, outs = _to_dev(torch, X, "f16"), []
+    for value in (1.0, np.inf):
+        L["A"][5, 3] = value
+        Y = torch.zeros((1, 40), dtype=torch.float32, device="cuda:0")
+        plan = mb.BatchPlan([mb.DeviceLayer.from_host(L)], [Xd], [Y])
+        assert plan.kernel(2) == "stage_fast_kernel"
+        plan.run()
+        outs.append(Y[0])
+    clean, got = outs
+    assert torch.isfinite(clean).all() and got[5] == float("inf")
+    assert torch.equal(torch.cat((got[:5], got[6:])), torch.cat((clean[:5], clean[6:])))
+
+
 ONE_PLANS = [
     # specs (m, n, k, l), envelopes, activations, tokens: ranks of every class and mixed ones, odd row pitches, contractions of
     # one block and of more than one per wave, row tiles that do not fill the last item
