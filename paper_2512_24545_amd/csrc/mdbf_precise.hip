@@ -2,6 +2,8 @@
 // One wavefront per 16-row tile; lane = (row r, 8-column group kg) as in the packed layout.
 // Per lane: acc[c] += (+-1) * Ein[j,c] * vin[j] over its columns, then the four kg lanes of a
 // row are summed, and out[r] = sum_c Eout[r,c] * acc[c]   (paper Eq. "me-dbf-expand").
+#include <algorithm>
+
 #include "mdbf_internal.h"
 
 namespace mdbf {
@@ -103,6 +105,7 @@ typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   //
 constexpr int kMaxWaves = 16;       // waves of a workgroup, each with blocks of its own
 
 constexpr int kOneItemTiles = 8;    // row tiles of a plan's work item, one workgroup each
+constexpr int kGridTiles = 1 << 21; // row tiles of a single problem along x: a grid dimension has at most 2^32 - 1 threads
 
 struct OneArgs {
   StageProb p;
@@ -309,8 +312,10 @@ template <int ENV, int M, bool VEC, bool PARTS, bool BATCH>
 __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   typedef EinBlock<ENV, M> EB;
-  int tile = blockIdx.x, split = blockIdx.y, token = 0;
-  if constexpr (BATCH) {
+  int tile = blockIdx.x + blockIdx.z * kGridTiles, split = blockIdx.y, token = 0;
+  if constexpr (!BATCH) {
+    if (tile >= a.p.ntiles) return;                      // (the last run of kGridTiles)
+  } else {
     const WorkItem& w = a.items[blockIdx.x];             // (uniform: scalar loads)
     if ((int)blockIdx.y >= w.ntiles || (int)blockIdx.z >= w.p.T) return;
     tile = w.tile0 + (int)blockIdx.y;
@@ -529,7 +534,8 @@ int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in,
   a.part_in_ld = part_in_ld;
   a.part_out = part_out;
   a.part_out_ld = part_out_ld;
-  return one::launch(a, dim3((unsigned)p->ntiles, (unsigned)g.nsplit), g.waves, s);
+  const int gx = std::min(p->ntiles, one::kGridTiles);
+  return one::launch(a, dim3((unsigned)gx, (unsigned)g.nsplit, (unsigned)((p->ntiles + gx - 1) / gx)), g.waves, s);
 }
 
 int launch_stage_one_items(const WorkItem* items_dev, int nitems, int env_dt, int rank, int max_tokens, hipStream_t s) {

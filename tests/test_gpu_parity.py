@@ -528,6 +528,23 @@ def test_one_token_calls_are_fp32(gpu, m, n, k, l, env_dtype, x_dtype):
         assert orc.max_rel_error(got, ref) <= 2e-5
 
 
+def test_one_token_call_of_more_threads_than_a_grid_dimension_holds(gpu):
+    """8.4 million row tiles on eight waves each: the last tiles' rows are those of a layer that has them alone."""
+    torch, mb = gpu
+    n, k, rows = 64, 640, 64 * 16
+    m = 2 ** 27 + rows                                   # (whole groups of 64 row tiles, stored one after the other)
+    g = torch.Generator(device="cuda:0").manual_seed(1)
+    words = lambda r, c: torch.randint(-2 ** 31, 2 ** 31 - 1, (mb.mdbf_packed_bytes(r, c) // 4,), dtype=torch.int32, generator=g, device="cuda:0")
+    env = lambda r: torch.rand((r, 8), generator=g, device="cuda:0").to(torch.float16)
+    SA, SB, A, Q, G, B = words(m, k), words(k, n), env(m), env(k), env(k), env(n)
+    X = torch.randn((1, n), generator=g, device="cuda:0").to(torch.float16)
+    Y = mb.mdbf_forward(mb.DeviceLayer(m, n, k, 8, SA, SB, A, Q, G, B), X, y_dtype="f16")
+    part = mb.mdbf_packed_bytes(rows, k) // 4
+    for t0, r0 in ((-part, m - rows), (0, 0)):
+        end = mb.DeviceLayer(rows, n, k, 8, SA[t0:][:part], SB, A[r0:][:rows], Q, G, B)
+        assert torch.equal(Y[:, r0:][:, :rows], mb.mdbf_forward(end, X, y_dtype="f16"))
+
+
 @pytest.mark.parametrize("where", ["single", "plan"])
 @pytest.mark.parametrize("l", [1, 4, 8, 13, 16])
 @pytest.mark.parametrize("env_dtype", ["bf16", "f32"])
