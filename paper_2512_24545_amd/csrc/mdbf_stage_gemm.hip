@@ -53,8 +53,8 @@ __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
-// Sign flips of rebuilt pairs, with the signs of the word's top bits (15 and 31), which then makes way for the next pair: a
-// word's pairs are taken from bits 15 and 31 downwards.  (Left shifts by constants take the vector ALUs four cycles,
+// Sign flips of rebuilt pairs where two row tiles share a product, with the signs of the word's top bits (15 and 31), which
+// then makes way for the next pair: a word's pairs are taken from bits 15 and 31 downwards.  (Left shifts by constants take the vector ALUs four cycles,
 // additions less: 1.9 and 1.3 ns per wave and SIMD measured.  The compiler would turn x + x into a shift.)
 __device__ __forceinline__ uint32_t flip_next(uint32_t pair, uint32_t& signs) {
   const uint32_t out = pair ^ (signs & 0x80008000u);
@@ -432,11 +432,15 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
         const floatx4 e1 = __builtin_amdgcn_mfma_f32_16x16x16f16(ea1, eo_op[r], z4, 0, 0, 0);
         // lane (r16, g) now holds E[row r16][32f + 8g + e], e = 0..3 in e0 and 4..7 in e1.  The packed word
         // keeps the signs of columns e = 2i and 2i+1 at bits p and p + 16, p = 8(f/2) + 4(f%2) + i.
+        // (shifted up one by one: four independent chains beside the products.  As one chain of additions, flip_next,
+        // they hold a workgroup of one row tile per wave up: 4096 x 4096, k = 2656, as a plan of 16 tokens 20.5 and 23.3 us
+        // for the first factor with items of eight tiles, one run; 8 decoder layers of 32 tokens 305 and 316 us.)
+        const int pbase = 8 * (f >> 1) + 4 * (f & 1);
         uint32_t w4[4];
-        w4[3] = flip_next(pack_half2(e1[2], e1[3]), sw[r]);
-        w4[2] = flip_next(pack_half2(e1[0], e1[1]), sw[r]);
-        w4[1] = flip_next(pack_half2(e0[2], e0[3]), sw[r]);
-        w4[0] = flip_next(pack_half2(e0[0], e0[1]), sw[r]);
+        w4[0] = pack_half2(e0[0], e0[1]) ^ ((sw[r] << (15 - (pbase + 0))) & 0x80008000u);
+        w4[1] = pack_half2(e0[2], e0[3]) ^ ((sw[r] << (15 - (pbase + 1))) & 0x80008000u);
+        w4[2] = pack_half2(e1[0], e1[1]) ^ ((sw[r] << (15 - (pbase + 2))) & 0x80008000u);
+        w4[3] = pack_half2(e1[2], e1[3]) ^ ((sw[r] << (15 - (pbase + 3))) & 0x80008000u);
         wop[r] = __builtin_bit_cast(half8, u32x4{w4[0], w4[1], w4[2], w4[3]});
       }
       // the step's A operands (one per token slab) are all requested before the first product
