@@ -301,13 +301,25 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
         ein_ok[i] = (col < p.K) && has_modes;          // (the zeros go in when the row is parked: a select here
                                                        //  would make the wave wait for the load here)
       } else {
-        const int half = id & 1;
+        // (The type is asked for once and every lane loads, inside its row: asked for element by element, each load would
+        // be waited for before the next one is issued.  In bytes from the block's first row, which 32 bits hold.)
+        const int qb = min(q, KB - 1), mode0 = 8 * (id & 1), left = col < p.K ? p.l - mode0 : 0;
+        const MDBF_GLOBAL char* base = (const MDBF_GLOBAL char*)p.Ein + (size_t)qb * (size_t)(kBlockCols * p.l * dtype_size(p.env_dt));
+        const uint32_t first = (uint32_t)((min(col, p.K - 1) - qb * kBlockCols) * p.l);
         float v[8];
+        if (p.env_dt == MDBF_F32) {
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int mode = half * 8 + t;
-          v[t] = (col < p.K && mode < p.l) ? load_as_float(p.Ein, (int64_t)col * p.l + mode, p.env_dt) : 0.f;
+          for (int t = 0; t < 8; ++t) v[t] = *(const MDBF_GLOBAL float*)(base + 4u * (first + (uint32_t)min(mode0 + t, p.l - 1)));
+        } else {
+          uint16_t raw[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) raw[t] = *(const MDBF_GLOBAL uint16_t*)(base + 2u * (first + (uint32_t)min(mode0 + t, p.l - 1)));
+#pragma unroll
+          for (int t = 0; t < 8; ++t)
+            v[t] = p.env_dt == MDBF_F16 ? (float)__builtin_bit_cast(_Float16, raw[t]) : __builtin_bit_cast(float, (uint32_t)raw[t] << 16);
         }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = t < left ? v[t] : 0.f;
         ein_reg[i] = u32x4{pack_half2(v[0], v[1]), pack_half2(v[2], v[3]), pack_half2(v[4], v[5]), pack_half2(v[6], v[7])};
         ein_ok[i] = true;
       }
