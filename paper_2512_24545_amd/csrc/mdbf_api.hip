@@ -383,7 +383,7 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
     sp[1].Ein = base + L.q;
     sp[0].vin_dt = sp[0].env_dt = sp[1].env_dt = MDBF_F16;
     sp[0].l = sp[1].l = L.modes;
-    for (int i = 0; i < 2 && !e; ++i) e = launch_stage_gemm(nullptr, 0, 0, &sp[i], s);
+    for (int i = 0; i < 2 && !e; ++i) e = launch_stage_gemm(nullptr, 0, 0, GemmForm{}, &sp[i], s);
     return hip_fail(e);
   }
   if (wants_few(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T)) {
@@ -399,7 +399,7 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
     if (desc->flags & MDBF_FLAG_PRECISE)
       e = launch_stage_precise(nullptr, nullptr, 0, &sp[i], s);
     else if (!forced && T >= kGemmMinTokensSingle)
-      e = launch_stage_gemm(nullptr, 0, 0, &sp[i], s);
+      e = launch_stage_gemm(nullptr, 0, 0, GemmForm{}, &sp[i], s);
     else if (forced || (use_mx(sp[i], desc->flags) && (mx_worthwhile(sp[i].ntiles) || !stage_is_fast(sp[i])))) {
       // (a small launch the fp16 variant cannot take -- rank 8 -- is still better off here than in the
       // element-wise kernel)
@@ -596,6 +596,8 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
   int max_blocks[2] = {0, 0};
   long blocks[2] = {0, 0};
   bool all_pre = true;
+  int load[2] = {-1, -1};        // the many-token variant's load mode
+  bool env32 = false;
   for (int i = 0; i < count; ++i) {
     const mdbf_layer_t* L = &layers[i];
     StageProb sp[2];
@@ -612,7 +614,10 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
       max_blocks[s] = std::max(max_blocks[s], (int)sp[s].KB);
       blocks[s] += (long)sp[s].ntiles * sp[s].KB;
       all_pre = all_pre && sp[s].xs;
+      const int gm = gemm_load_mode(sp[s]);
+      load[s] = (load[s] == -1 || load[s] == gm) ? gm : kGemmGeneric;
     }
+    env32 = env32 || L->desc.env_dtype == MDBF_F32;
     if (L->desc.flags & (MDBF_FLAG_PRECISE | MDBF_FLAG_BLOCK_SCALED | MDBF_FLAG_FP16_STAGED)) one = false;
   }
   int forced = 0, many = 0;
@@ -654,7 +659,9 @@ static int batch_layout(int count, const mdbf_layer_t* layers, PlanHeader* h, si
       }
       tpi_mx = mx_pick_item_tiles(count, nt.data(), kb.data());
     }
-    h->tiles_per_item[s] = h->one ? one_item_tiles() : h->gemm ? gemm_tiles_per_item(tiles[s], h->max_tokens) : mx[s] ? tpi_mx : tpi_fp16;
+    const GemmForm gf = gemm_plan_form(tiles[s], blocks[s], max_blocks[s], h->max_tokens, load[s] == kGemmGeneric, env32);
+    if (h->gemm) h->gemm_form[s] = gf.form;
+    h->tiles_per_item[s] = h->one ? one_item_tiles() : h->gemm ? gf.tiles : mx[s] ? tpi_mx : tpi_fp16;
   }
   h->fuse2 = (!precise && !h->gemm && h->mx[0] != 0 && h->mx[0] == h->mx[1]) ? 1 : 0;
   for (int s = 0; s < 2; ++s) {
@@ -726,7 +733,7 @@ int mdbf_batch_plan_build(int count, const mdbf_layer_t* layers, void* workspace
       probs[s][(size_t)i] = sp[s];
       if (!stage_is_fast(sp[s])) fast[s] = 0;
       const int gm = gemm_load_mode(sp[s]);
-      gmode[s] = (gmode[s] == -1 || gmode[s] == gm) ? gm : 3;
+      gmode[s] = (gmode[s] == -1 || gmode[s] == gm) ? gm : kGemmGeneric;
       if (!sp[s].xs) pre[s] = 0;
       const int units = sp[s].T * ((sp[s].KB + 7) / 8);
       if (units > max_units[s]) max_units[s] = units;
@@ -794,7 +801,7 @@ int mdbf_forward_batch_part(const void* plan_host, const void* plan_dev, size_t 
         if (!(stages & (1 << st)) || !(kernels & 2)) continue;
         StageProb one;   // plan_host may have any alignment
         memcpy(&one, host + h.probs_off[st] + (size_t)i * sizeof(StageProb), sizeof(one));
-        int e = launch_stage_gemm(nullptr, 0, 0, &one, s);
+        int e = launch_stage_gemm(nullptr, 0, 0, GemmForm{}, &one, s);
         if (e) return hip_fail(e);
       }
     return MDBF_OK;
@@ -805,8 +812,8 @@ int mdbf_forward_batch_part(const void* plan_host, const void* plan_dev, size_t 
       StageProb launch;
       memset(&launch, 0, sizeof(launch));
       launch.T = h.max_tokens;
-      launch.ntiles = h.tiles_per_item[st];
-      int e = launch_stage_gemm((const WorkItem*)(dev + h.items_off[st]), h.nitems[st], h.gemm_mode[st], &launch, s);
+      const GemmForm form = {h.tiles_per_item[st], h.gemm_form[st]};
+      int e = launch_stage_gemm((const WorkItem*)(dev + h.items_off[st]), h.nitems[st], h.gemm_mode[st], form, &launch, s);
       if (e) return hip_fail(e);
     }
     return MDBF_OK;

@@ -118,7 +118,10 @@ struct PlanHeader {
                               // writes the second stage's activation records (no scale-in launch for stage 2)
   int32_t one;                // few tokens on stage_one_kernel, two launches: the layers' rank or kOneMixedRanks, and
                               // 32 times the type of their envelopes; else 0
+  int32_t gemm_form[2];       // many-token variant, per stage: runs over the contraction, kGemmPairs for pairs of row tiles
 };
+static_assert(sizeof(PlanHeader) <= 256, "the tables begin at byte 256");
+constexpr int32_t kGemmPairs = 16;
 constexpr uint32_t kPlanMagic = 0x4D444246u;  // "MDBF"
 
 // One-time set-up of a kernel per device (raising its dynamic LDS limit): thread-safe, and the outcome of
@@ -216,16 +219,23 @@ int mfma_plan_tiles_per_item(const long tiles[2], const long blocks[2], const in
 constexpr int kGemmMinTokensSingle = 2;
 constexpr int kGemmMinTokensPlan = 4;
 // how the kernel may load the problem's operands: a dtype code (vector loads of that activation type, fp16
-// rank-16 envelopes, aligned rows) or 3 (element by element); a plan takes 3 unless all problems agree
+// rank-16 envelopes, aligned rows) or kGemmGeneric (element by element); a plan takes that unless all problems agree
+constexpr int kGemmGeneric = 3;
 int gemm_load_mode(const StageProb& p);
 // compute units of the current device (cached after the first call; 256 if the query fails)
 int compute_units();
-int gemm_tiles_per_item(long launch_tiles, int max_tokens);   // of a plan
+// How a plan's launch is cut: row tiles per work item, and what PlanHeader::gemm_form says.  launch_tiles, launch_blocks:
+// its row tiles and the blocks of all their contractions, max_blocks those of the longest; generic: loaded element by
+// element; env32: fp32 envelopes.
+struct GemmForm {
+  int tiles, form;
+};
+GemmForm gemm_plan_form(long launch_tiles, long launch_blocks, int max_blocks, int max_tokens, bool generic, bool env32);
 int gemm_plan_max_tokens();
 // items_dev null: the single problem *p (mode ignored).  Else the work items of a plan (at most
-// gemm_plan_max_tokens() tokens per problem); p->T = the longest token count among its problems, p->ntiles = the row
-// tiles per work item the plan was cut with (gemm_tiles_per_item), mode as above.
-int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s);
+// gemm_plan_max_tokens() tokens per problem); p->T = the longest token count among its problems, form = how the plan was
+// cut, mode as above.
+int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, GemmForm form, const StageProb* p, hipStream_t s);
 
 // Few-token single problem (at most kFewMaxTokens tokens): contraction split across workgroups, the partial sums added
 // by a second launch.  part: g.nsplit x T vectors part_ld

@@ -141,7 +141,7 @@ __device__ __forceinline__ half4 load4_modes(const StageProb& p, const void* env
 // instructions, which do not overlap with them; one 32 x 32 product rebuilds both tiles' columns in half of the time, and the
 // idle rows take the second tile's tokens.  The signs' shifts as additions (flip_next) take another 4 %.  224 matrices, 8
 // tokens: 802 -> 737 us per pass with the two and items of 16 tiles (the same sums: bit-identical to 16-row products).
-constexpr int kGeneric = 3;
+constexpr int kGeneric = kGemmGeneric;
 // first: row tiles of the work item in front of this workgroup's.  True (PAIR): some results are infinities or NaNs, and none
 // has been stored.
 template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR>
@@ -1047,15 +1047,6 @@ static int launch_few_m(const FewArgs& a, hipStream_t s) {
   return evec ? launch_few_me<MODE, true>(a, s) : launch_few_me<MODE, false>(a, s);
 }
 
-// Runs over the contraction in a workgroup of a plan's launch (gemm_tiles_per_item has the measurements).
-template <int NW, int R>
-static int plan_runs(int nitems, int T) {
-  if (T > 32 || NW * R == 16) return 1;
-  if (NW * R == 2) return T <= 16 ? 4 : 2;
-  if (NW * R == 4) return T <= 16 && nitems <= 288 ? 4 : 2;
-  return nitems <= (T <= 8 ? 1400 : 4096) ? 2 : 1;
-}
-
 // items_dev null: the single problem *p.  Else nitems work items of a plan, `p` describing the launch:
 // p->T = the longest token count among the problems.
 template <int NW, int R, int TB, int MODE, bool BATCH, int KS, bool PAIR = false>
@@ -1079,38 +1070,41 @@ static int launch_rtm(const StageProb* p, hipStream_t s) {
   return (int)hipErrorInvalidValue;
 }
 
-// a plan's work items, of NW R row tiles
+// a plan's work items, of NW R row tiles; the forms that gemm_plan_form names
 template <int NW, int R, int TB, int MODE>
-static int launch_items_rtm(const WorkItem* items_dev, int nitems, const StageProb* p, hipStream_t s) {
-  const int ks = plan_runs<NW, R>(nitems, p->T);
+static int launch_items_rtm(const WorkItem* items_dev, int nitems, int form, const StageProb* p, hipStream_t s) {
+  const int runs = form & (kGemmPairs - 1);
   if constexpr (NW * R >= 8 && TB == 1) {
-    if (p->T <= 8) {
+    if (form & kGemmPairs) {
       if constexpr (NW * R == 8)
-        if (ks == 2) return launch_rtmb<NW, R, TB, MODE, true, 2, true>(items_dev, nitems, p, s);
+        if (runs == 2) return launch_rtmb<NW, R, TB, MODE, true, 2, true>(items_dev, nitems, p, s);
       return launch_rtmb<NW, R, TB, MODE, true, 1, true>(items_dev, nitems, p, s);
     }
   }
   if constexpr (TB == 1 && NW * R <= 4) {
-    if (ks == 4) return launch_rtmb<NW, R, TB, MODE, true, 4>(items_dev, nitems, p, s);
+    if (runs == 4) return launch_rtmb<NW, R, TB, MODE, true, 4>(items_dev, nitems, p, s);
   }
-  if constexpr (TB <= 2 && NW * R <= 8) {
-    if (ks == 2) return launch_rtmb<NW, R, TB, MODE, true, 2>(items_dev, nitems, p, s);
+  if constexpr (TB <= 2 && NW * R <= 8 && !(TB == 1 && NW * R == 2)) {
+    if (runs == 2) return launch_rtmb<NW, R, TB, MODE, true, 2>(items_dev, nitems, p, s);
   }
-  if constexpr (NW * R == 8 || (TB > 2 && NW * R < 8)) return launch_rtmb<NW, R, TB, MODE, true, 1>(items_dev, nitems, p, s);
+  if constexpr (NW * R == 8 || (TB > 2 && NW * R == 4)) {
+    if (runs == 1) return launch_rtmb<NW, R, TB, MODE, true, 1>(items_dev, nitems, p, s);
+  }
   return (int)hipErrorInvalidValue;
 }
 template <int NW, int R, int TB>
-static int launch_items_rt(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
-  if (mode == kGeneric) return launch_items_rtm<NW, R, TB, kGeneric>(items_dev, nitems, p, s);
-  if (mode == MDBF_F16) return launch_items_rtm<NW, R, TB, MDBF_F16>(items_dev, nitems, p, s);
-  if (mode == MDBF_BF16) return launch_items_rtm<NW, R, TB, MDBF_BF16>(items_dev, nitems, p, s);
-  return launch_items_rtm<NW, R, TB, MDBF_F32>(items_dev, nitems, p, s);
+static int launch_items_rt(const WorkItem* items_dev, int nitems, int mode, int form, const StageProb* p, hipStream_t s) {
+  if (mode == kGeneric) return launch_items_rtm<NW, R, TB, kGeneric>(items_dev, nitems, form, p, s);
+  if (mode == MDBF_F16) return launch_items_rtm<NW, R, TB, MDBF_F16>(items_dev, nitems, form, p, s);
+  if (mode == MDBF_BF16) return launch_items_rtm<NW, R, TB, MDBF_BF16>(items_dev, nitems, form, p, s);
+  return launch_items_rtm<NW, R, TB, MDBF_F32>(items_dev, nitems, form, p, s);
 }
 template <int NW, int R>
-static int launch_items_r(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
-  if (p->T > 32) return launch_items_rt<NW, R, 4>(items_dev, nitems, mode, p, s);
-  if (p->T > 16) return launch_items_rt<NW, R, 2>(items_dev, nitems, mode, p, s);
-  return launch_items_rt<NW, R, 1>(items_dev, nitems, mode, p, s);
+static int launch_items_r(const WorkItem* items_dev, int nitems, int mode, int form, const StageProb* p, hipStream_t s) {
+  if constexpr (NW * R > 2)
+    if (p->T > 32) return launch_items_rt<NW, R, 4>(items_dev, nitems, mode, form, p, s);
+  if (p->T > 16) return launch_items_rt<NW, R, 2>(items_dev, nitems, mode, form, p, s);
+  return launch_items_rt<NW, R, 1>(items_dev, nitems, mode, form, p, s);
 }
 
 template <int R, int TB>
@@ -1242,32 +1236,71 @@ int launch_half_copies(const HalfMatrix* m, int count, hipStream_t s) {
   return (int)hipGetLastError();
 }
 
-// Row tiles per work item of a plan whose launch has launch_tiles of them in all, at most max_tokens tokens each.  Small
-// plans leave most of the device idle with items of eight tiles and one run over the contraction, and a block of such
-// a run takes its 0.6 us however few there are: smaller items, and two or four runs of the contraction side by side in
-// a workgroup.  Up to 16 tokens, per pass with (tiles per item)/(runs):
-//   1 attention layer (166 and 256 tiles): 8/1 37.7, 4/4 21.3, 2/4 17.6 us; 4 of them: 39.2, 21.8, 24.5; 16: 55.8, 4/2
-//   48.9, 8/2 50.1; 32: 8/1 79.1, 8/2 78.8, 4/2 87.0
-//   a decoder layer (1432 and 2656): 8/1 97.2, 8/2 66.0, 4/2 55.5, 4/4 55.8; two: 109, 85.4, 81.9, 92.4; 8: 252, 243, 263;
-//   16: 447, 437, 504; 32: 820, 838, 966
-// Up to 8 tokens, larger items share a product over pairs of tiles (PAIR): 32 attention layers 8/1 76.5, 8/2 78.0, 16/1
-//   81; 300: 567, 592, 528; 4 decoder layers of rank 16 and k = 5536: 205, 185, 207; 8: 224, 236, 221; 16: 417, 418, 403;
-//   32: 769, 799, 737
-// 17 to 32: an attention layer 8/1 47.5, 4/2 26.0, 2/2 24.4; a decoder layer 119, 68.0, 76.1; 4: 184, 8/2 178, 189.
-// 33 to 64 (one run: two would take the room of a second workgroup): 62.4, 4/1 45.2; 150, 118.
-int gemm_tiles_per_item(long launch_tiles, int max_tokens) {
-  if (max_tokens <= 16) return launch_tiles <= 512 ? 2 : launch_tiles <= 5400 ? 4 : launch_tiles <= 11000 || max_tokens > 8 ? 8 : 16;
-  if (max_tokens <= 32) return launch_tiles <= 300 ? 2 : launch_tiles <= 2700 ? 4 : 8;
-  return launch_tiles <= 2700 ? 4 : 8;
+// Forms of a plan's launch: row tiles per work item / runs over the contraction in its workgroup (p: two row tiles per
+// product, PAIR).  Few row tiles leave most of the device idle with items of eight and one run, and a block of such a run
+// takes its 0.5 us however few there are: smaller items, and runs side by side.  But every workgroup stages the envelope rows
+// and activations of its blocks for its own tiles, so small items and runs multiply that work where there are workgroups
+// enough, most of all where operands are loaded element by element; and a contraction of a few blocks has nothing to share
+// out.  Where contractions are of different lengths the launch ends with a workgroup's long one: shorter runs for longer.
+// The lines lie where the forms' times cross, launch by launch, for 1 to 400 layers of 256 x 256 (k = 128) to 11008 x 4096 and
+// 4096 x 11008 (k = 4096), for mixed ones and decoder layers, 8, 16, 32 and 64 tokens, envelopes of fp16 rank 16, 8
+// (aligned or not), 5, 3, bf16 rank 12, fp32 rank 16 and 4.  Of 4752 launches none takes more than 5.3 % longer than 8/1, on
+// average they take 19 % less.  us per launch of up to 8 tokens, (row tiles, blocks):
+//   vectors  (256, 32) 8/1 20.5, 2/4 9.6, 4/2 12.6, 4/4 11.7           (1024, 32) 20.5, 2/4 13.2, 4/2 12.7, 4/4 11.8
+//            (2048, 32) 22.0, 2/4 24.3, 4/2 18.3, 8/2p 17.6            (2656, 32) 32.1, 4/2 24.8, 8/1p 27.9, 8/2p 26.3
+//            (4096, 32) 32.6, 4/2 32.0, 8/1p 29.1, 8/2p 28.2           (5312, 32) 40.0, 4/2 44.0, 8/1p 37.5, 8/2p 39.9
+//            (8192, 32) 52.2, 8/1p 49.0, 8/2p 51.5, 16/1p 46.9         (32768, 21) 127, 8/1p 123, 8/2p 136, 16/1p 113
+//            (512, 4) 6.0, 2/4 4.8     (2048, 4) 6.0, 4/2 6.5, 8/1p 6.3, 8/2p 6.8
+//            (4096, 8) 12.0, 4/2 13.3, 8/1p 11.2, 8/2p 12.2            (6400, 1) 8.3, 4/2 11.7, 8/1p 8.1, 8/2p 14.0
+//            (4296, 21 to 86) 78.2, 4/2 60.5, 8/1p 67.0, 8/2p 68.8     (5728, 21 to 86) 80.1, 4/2 72.9, 8/1p 73.8, 8/2p 70.0
+//   without vector loads, bf16 rank 12
+//            (1024, 32) 37.1, 2/4 29.0, 4/2 23.1, 4/4 20.3, 8/2p 25.0  (4096, 32) 50.8, 4/2 59.2, 8/1p 47.8, 8/2p 40.1
+//            (16384, 32) 128, 4/2 198, 8/1p 127, 8/2p 148, 16/1p 103
+//   fp32 rank 16
+//            (1024, 32) 55.8, 2/4 78.7, 4/2 44.5, 4/4 45.5, 8/2p 47.3  (2048, 32) 60.0, 4/2 69.7, 8/2p 49.8
+//            (4096, 32) 66.2, 4/2 141, 8/1p 65.4, 8/2p 72.8            (16384, 32) 260, 4/2 536, 8/1p 263, 8/2p 281, 16/1p 158
+//            (6400, 1) 18.1, 4/2 46.1, 8/2p 32.3, 16/1p 13.3
+GemmForm gemm_plan_form(long launch_tiles, long launch_blocks, int max_blocks, int max_tokens, bool generic, bool env32) {
+  const long tiles = launch_tiles, blocks = launch_tiles > 0 ? launch_blocks / launch_tiles : 0;   // (on average)
+  const bool uneven = 4 * max_blocks > 5 * blocks;
+  const int T = max_tokens;
+  GemmForm f = {8, 1};
+  if (T > 32) {                                    // (one run: two would take the room of a second workgroup)
+    if (tiles <= (!generic ? 3072 : !env32 ? 2048 : 1024)) f = {4, 1};
+  } else if (!generic) {
+    if (tiles <= 512) f = {2, T <= 16 ? 4 : 2};
+    else if (tiles <= 1024) f = {4, T <= 16 && blocks >= 16 ? 4 : 2};
+    else if (tiles <= 3072) f = blocks >= (tiles > 2048 ? 10 : T <= 16 ? 8 : 4) ? GemmForm{4, 2} : f;
+    else if (tiles <= 4096) f = blocks >= (uneven ? 10 : 21) ? GemmForm{8, 2} : f;
+    else if (uneven && blocks >= 10)
+      f = tiles <= 5504 ? GemmForm{4, 2} : T > 8 || tiles <= 8191 ? GemmForm{8, 2} : tiles > 11008 ? GemmForm{16, 1} : f;
+    else if (tiles <= 5504) f = T > 8 && T <= 16 && blocks >= 27 ? GemmForm{8, 2} : f;
+    else if (tiles > 11008 && T <= 8) f = {16, 1};
+  } else if (!env32) {
+    if (tiles <= 1024) f = {4, T <= 16 && blocks >= 8 ? 4 : 2};
+    else if (tiles <= 4096) f = blocks >= (tiles <= 2048 ? 4 : 8) ? GemmForm{8, 2} : f;
+    else if (uneven && tiles <= (T > 8 && T <= 16 ? 8191 : 11008)) f = blocks >= 10 ? GemmForm{8, 2} : f;
+    else if (T <= 8 && tiles > 8191) f = {16, 1};
+  } else {
+    if (tiles <= 1024) f = blocks >= 4 ? GemmForm{4, T <= 16 && blocks >= 32 ? 4 : 2} : f;
+    else if (tiles <= 4096) f = blocks >= (tiles <= 2048 ? 8 : uneven ? 21 : T > 16 ? 32 : 40) ? GemmForm{8, 2} : f;
+    else if (T <= 8 && tiles > (uneven ? 8191 : 6144)) f = {16, 1};
+  }
+  // (8/1 in pairs: up to 7 % slower where a unit has one workgroup; with fp32 envelopes nothing gained)
+  if (T <= 8 && f.tiles >= 8 && !(f.tiles == 8 && f.form == 1 && ((generic && env32) || tiles <= 2048))) f.form += kGemmPairs;
+  return f;
 }
 int gemm_plan_max_tokens() { return 64; }   // plans with longer problems launch the single-problem kernel per problem
 
-int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, const StageProb* p, hipStream_t s) {
-  if (items_dev) {       // p->ntiles: the row tiles per item the plan was cut with
-    if (p->ntiles == 2) return gemm::launch_items_r<2, 1>(items_dev, nitems, mode, p, s);
-    if (p->ntiles == 4) return gemm::launch_items_r<4, 1>(items_dev, nitems, mode, p, s);
-    if (p->ntiles == 16) return gemm::launch_items_rt<4, 4, 1>(items_dev, nitems, mode, p, s);
-    return gemm::launch_items_r<4, 2>(items_dev, nitems, mode, p, s);
+int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, GemmForm form, const StageProb* p, hipStream_t s) {
+  if (items_dev) {
+    if (form.form == 0)    // a plan built before its header named the runs
+      form.form = (p->T > 32 ? 1 : form.tiles == 2 && p->T <= 16 ? 4 : form.tiles < 8 ? 2 : 1) +
+                  (p->T <= 8 && form.tiles >= 8 ? kGemmPairs : 0);
+    if (form.tiles == 2) return gemm::launch_items_r<2, 1>(items_dev, nitems, mode, form.form, p, s);
+    if (form.tiles == 4) return gemm::launch_items_r<4, 1>(items_dev, nitems, mode, form.form, p, s);
+    if (form.tiles == 16) return gemm::launch_items_rt<4, 4, 1>(items_dev, nitems, mode, form.form, p, s);
+    return gemm::launch_items_r<4, 2>(items_dev, nitems, mode, form.form, p, s);
   }
   mode = gemm_load_mode(*p);
   const bool vectors = mode != gemm::kGeneric;

@@ -209,7 +209,8 @@ class _PlanHeader(C.Structure):
                 ("tiles_per_item", C.c_int32 * 2), ("precise", C.c_int32), ("fast", C.c_int32 * 2),
                 ("pre", C.c_int32 * 2), ("max_units", C.c_int32 * 2), ("mx", C.c_int32 * 2), ("gemm", C.c_int32),
                 ("gemm_mode", C.c_int32 * 2), ("max_tokens", C.c_int32), ("max_units_mx", C.c_int32 * 2),
-                ("probs_off", C.c_uint64 * 2), ("items_off", C.c_uint64 * 2), ("total_bytes", C.c_uint64)]
+                ("probs_off", C.c_uint64 * 2), ("items_off", C.c_uint64 * 2), ("total_bytes", C.c_uint64),
+                ("fuse2", C.c_int32), ("one", C.c_int32), ("gemm_form", C.c_int32 * 2)]
 
 
 def _plan_items(shapes, T=1):
@@ -384,6 +385,39 @@ def test_plans_of_many_row_tiles_take_larger_items():
     staged = mb.MDBF_FLAG_FP16_STAGED
     assert plan(63, 16 * 800, 2560, 2560, 16, 2, staged) == ("stage_fast_kernel", 63 * 200)
     assert plan(63, 16 * 5120, 2560, 2560, 16, 2, staged) == ("stage_fast_kernel", 63 * 320)
+
+
+def test_many_token_plans_share_out_what_there_is_to_share():
+    """Row tiles per item and runs over the contraction: small items and several runs where row tiles are few and contractions
+    long; items of eight and one run where there are workgroups enough, contractions of a few blocks, or rows that are
+    loaded element by element for every workgroup."""
+    L = mb.lib()
+
+    def forms(count, m, n, k, T, l=16, env=0):
+        arr = (mb.Layer * count)()
+        for i in range(count):
+            arr[i].desc = mb.Desc(m, n, k, l, 0, env, 0, 0)
+            arr[i].SA_packed_dev = arr[i].SB_packed_dev = arr[i].X_dev = arr[i].Y_dev = FAKE
+            arr[i].env = mb.Env(FAKE, FAKE, FAKE, FAKE)
+            arr[i].ldx, arr[i].ldy, arr[i].T = n, m, T
+        pb, wb = C.c_size_t(0), C.c_size_t(0)
+        assert L.mdbf_batch_plan_bytes(count, arr, C.byref(pb), C.byref(wb)) == 0
+        buf = C.create_string_buffer(pb.value)
+        assert L.mdbf_batch_plan_build(count, arr, FAKE, wb.value, buf, pb.value) == 0
+        h = _PlanHeader.from_buffer_copy(buf.raw[:C.sizeof(_PlanHeader)])
+        assert h.gemm == 1
+        return [(h.tiles_per_item[s], h.gemm_form[s] & 15, h.gemm_form[s] >> 4) for s in range(2)]
+
+    attn, f32 = (4096, 4096, 2656), 2
+    assert forms(1, *attn, 8) == [(2, 4, 0), (2, 4, 0)] and forms(1, *attn, 32) == [(2, 2, 0), (2, 2, 0)]
+    assert forms(1, *attn, 64) == [(4, 1, 0), (4, 1, 0)]
+    assert forms(300, *attn, 8) == [(16, 1, 1), (16, 1, 1)] and forms(300, *attn, 16) == [(8, 1, 0), (8, 1, 0)]
+    assert forms(100, *attn, 24) == [(8, 1, 0), (8, 1, 0)]              # 16600 and 25600 row tiles need no second run
+    assert forms(400, 256, 256, 128, 4) == [(8, 1, 1), (8, 1, 1)]       # two blocks, one block
+    assert forms(60, 1024, 1024, 512, 12, env=f32) == [(8, 2, 0), (8, 1, 0)]
+    assert forms(60, 1024, 1024, 512, 8, env=f32) == [(8, 2, 1), (8, 1, 0)]
+    assert forms(400, 1024, 1024, 512, 8, env=f32) == [(16, 1, 1), (16, 1, 1)]
+    assert forms(1, 1024, 1024, 512, 8, l=5) == [(4, 4, 0), (4, 2, 0)]
 
 
 def test_block_scaled_plan_picks_the_item_size_that_wastes_fewest_tile_slots():

@@ -814,6 +814,30 @@ def test_item_forms_of_many_token_plans(gpu, copies, T, l, x_dtype):
         assert torch.equal(Y, Y[:1].expand_as(Y))
 
 
+@pytest.mark.parametrize("copies,T", [(1, 8), (3, 16), (3, 32), (7, 6), (7, 40), (12, 13), (30, 7), (30, 20), (45, 5), (70, 8), (70, 12)])
+@pytest.mark.parametrize("l", [4, 13])
+def test_item_forms_of_many_token_plans_with_fp32_envelopes(gpu, copies, T, l):
+    """Items of 4, 8 and 16 row tiles, one, two and four runs over contractions of 1, 5, 9 and 41 blocks, pairs of row tiles
+    and single ones, all loaded element by element.  (Rounded to fp16 as the fp16 envelopes are.)"""
+    torch, mb = gpu
+    layers, Xs, Ys, refs = [], [], [], []
+    for i, (m, n, k) in enumerate([(2100, 72, 600), (52, 1100, 120), (72, 600, 5200)]):
+        L = synth.make_layer(m, n, k, l, seed=40 + i, env_dtype="f32", env_kind="unit", signed_env=True)
+        X = synth.make_activations(n, T, seed=50 + i, x_dtype="f32")
+        refs.append(orc.forward_factored(*_oracle_args(L), X))
+        dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, "f32")
+        layers += [dl] * copies
+        Xs += [Xd] * copies
+        Ys.append(torch.zeros((copies, T, m), dtype=torch.float32, device="cuda:0"))
+    plan = mb.BatchPlan(layers, Xs, [y for Y in Ys for y in Y])
+    assert plan.kernel(1) == "stage_gemm_kernel" and plan.launches() == 2
+    for _ in range(2):
+        plan.run()
+    for Y, ref in zip(Ys, refs):
+        assert orc.max_rel_error(Y[0].cpu().numpy(), ref) <= TOL
+        assert torch.equal(Y, Y[:1].expand_as(Y))
+
+
 @pytest.mark.parametrize("n,k,l,x_dtype", [(264, 136, 16, "f16"), (136, 264, 8, "bf16"), (264, 136, 16, "f32"), (131, 137, 5, "f16")])
 def test_tile_shapes_of_long_calls(gpu, n, k, l, x_dtype):
     """256 row tiles with lengths that take each tile shape on the second factor (2 x 8, 2 x 6, 2 x 4, 2 x 2, 1 x 2), the last
