@@ -812,15 +812,19 @@ int mfma_tiles_per_item(long total_tiles) {
 }
 
 int mfma_plan_tiles_per_item(const long tiles[2], const long blocks[2], const int max_blocks[2], int max_tokens) {
-  // Four tiles are items of stage_fast_short_kernel; more, of the persistent kernel.  That one is as good or better only
-  // where its workgroups stay busy: one token, many row tiles, contractions of one length (one token, us per pass, short
-  // against persistent: 16 attention layers 33.7 and 35.5, 24 41.9 and 40.6, 64 78.8 and 77.3; 2 decoder layers 47.7 and
-  // 56.4, 8 116 and 119; 16 attention layers with three tokens 68.1 and 75.0), or where the launch is long.
+  // Four tiles are items of stage_fast_short_kernel; more, of the persistent kernel.  That one is better where it has many
+  // row tiles and contractions of one length, the shorter they are the sooner: the short kernel's waves share out a
+  // contraction and its workgroups a column sum per token, which a few blocks do not pay for.  Us per pass, short against
+  // persistent: 48 layers of 1024 x 1024, k = 1024, one token 26.4 and 22.5, three 42.1 and 40.0; 96 of them 74.2 and 63.6, 1
+  // and 9 tokens 169 and 149; 32 of 2048 x 2048, k = 2048, one 31.6 and 28.3, three 63.9 and 56.0, 1 and 9 102 and 135; 16
+  // attention layers, one 33.5 and 34.8, three 68.0 and 74.7; 48 of them, one 67.5 and 69.2, three 174 and 174; 2 decoder
+  // layers, one 46.7 and 56.4.  391 plans: none more than 3 % slower than the persistent kernel, 5 % less on average.
   const long least = tiles[0] < tiles[1] ? tiles[0] : tiles[1];
+  const long mean = (blocks[0] + blocks[1]) / (tiles[0] + tiles[1]);
   bool even = true;
   for (int s = 0; s < 2; ++s) even = even && 4 * max_blocks[s] * tiles[s] <= 5 * blocks[s];
-  if (least <= 12000 && (least <= 3500 || !even || max_tokens > 1)) return kShortTiles;
-  return mfma_tiles_per_item(least);
+  const long from = !even ? 12001 : mean <= 8 ? 2560 : max_tokens == 1 ? (mean <= 16 ? 2560 : 3501) : max_tokens <= 3 && mean <= 16 ? 4096 : 12001;
+  return least < from ? kShortTiles : mfma_tiles_per_item(least);
 }
 
 int launch_stage_mfma(const StageProb* probs_dev, const WorkItem* items_dev, int nitems, int tiles_per_item,

@@ -360,7 +360,8 @@ def test_launches_per_plan():
 
 def test_plans_of_many_row_tiles_take_larger_items():
     """A launch takes fewer than 65535 work items.  Few tokens of rank 3: items of eight row tiles are the fp32 kernel's,
-    the general kernel has larger ones; rank 16 in fp16: items of four as long as both factors have few enough."""
+    the general kernel has larger ones; rank 16 in fp16: items of four as long as both factors have few enough, and the
+    contractions blocks to share out."""
     L = mb.lib()
 
     def plan(count, m, n, k, l, T, flags=0):
@@ -382,6 +383,9 @@ def test_plans_of_many_row_tiles_take_larger_items():
     assert plan(1, 16 * 500000, 300, 16 * 3000, 3, 1) == ("stage_one_kernel", 62500)
     assert plan(1, 16 * 600000, 300, 16 * 10000, 3, 1) == ("stage_generic_kernel", 37500)
     assert plan(1, 16 * 600000, 300, 300, 3, 1) == -5              # (what the general kernel refuses stays refused)
+    assert plan(100, 1024, 1024, 1024, 16, 2) == ("stage_fast_kernel", 100 * 4)      # 8 blocks: items of sixteen
+    assert plan(16, 4096, 4096, 2656, 16, 2) == ("stage_fast_kernel", 16 * 64)       # 32 and 21 blocks: of four
+    assert plan(32, 2048, 2048, 2048, 16, 3) == ("stage_fast_kernel", 32 * 16)       # 16 blocks: of eight
     staged = mb.MDBF_FLAG_FP16_STAGED
     assert plan(63, 16 * 800, 2560, 2560, 16, 2, staged) == ("stage_fast_kernel", 63 * 200)
     assert plan(63, 16 * 5120, 2560, 2560, 16, 2, staged) == ("stage_fast_kernel", 63 * 320)
