@@ -155,8 +155,8 @@ __device__ __forceinline__ bool stage_gemm_rows(const WorkItem* __restrict__ ite
   // fp16, with the same tile shapes: 512 tokens 83.5 -> 69.6 us, 1024 92.3 -> 79.4, 4096 235.6 -> 230.7; 2048 (two
   // workgroups a unit hide each other's waits) 122.4 -> 121.2, nothing on another box; bf16, 1024 tokens 100 -> 85.
   // (Plans of 17 to 64 tokens are not faster for it: 200 attention layers, 30 tokens 484 -> 486 us, 60 tokens 714 -> 733.)
-  constexpr bool kWide = !BATCH && R == 2;
-  static_assert(!kWide || (TB % 2 == 0 && KS == 1), "32 tokens at a time, one run");
+  constexpr bool kWide = !BATCH && R == 2 && TB % 2 == 0;              // (32 tokens at a time)
+  static_assert(!kWide || KS == 1, "one run");
   constexpr bool kPairs = PAIR || kWide;
   // the rows of this workgroup: a work item of a plan (at most NW * R row tiles of one problem), or
   // the blockIdx.x-th run of NW * R tiles of the single problem
@@ -1176,29 +1176,40 @@ __global__ __launch_bounds__(256) void half_copy_kernel(HalfCopies a) {
 
 // Row tiles per wave and token slabs per workgroup for a single problem of more than 32 tokens.  In ns per column block: what a
 // workgroup takes that has a compute unit to itself (mostly the wait for the next block's activations), and what each adds
-// to a unit with several, between the mean number per unit and the busiest unit's (fitted to 200 to 1048 us long calls of
-// 70 to 4096 tokens on 4096 x 4096, k = 2656, 11008 x 4096 and 4096 x 11008, k = 4096, and 1024 x 1024, k = 512).  Fewer slabs
-// make more, lighter workgroups: worth it when that evens out the last round or fills the device at all.  4096 x 11008,
-// k = 4096, us per call with 2 x 8, 2 x 6, 2 x 4, 2 x 2, 1 x 2: 256 tokens 155, 131, 122, 96, 106; 512: 156, 136, 123, 121,
-// 144; 777: 165, 172, 149, 200, 249; 1300: 225, 202, 226, 300, 362; 4096: 538, 604, 610, 816, 1039.  (2 x 7 and 1 x 4 are
-// nowhere the best.)  Each output is the same sum in the same order whatever the choice.  The element-wise mode has the
-// two-tile forms only.
+// to a unit with several, between the mean number per unit and the busiest unit's; and once, in ns, what a larger form's first
+// block and results take longer.  Fitted to 200 to 1048 us long calls of 70 to 4096 tokens on 4096 x 4096, k = 2656,
+// 11008 x 4096 and 4096 x 11008, k = 4096, and 1024 x 1024, k = 512; 2 x 7 and the third figure to 594 calls of 33 to
+// 3000 tokens on 512 x 512 to 28672 x 8192.  Fewer slabs make more, lighter workgroups: worth it when that evens out the
+// last round or fills the device at all.  4096 x 11008, k = 4096, us per call with 2 x 8, 2 x 6, 2 x 4, 2 x 2, 1 x 2:
+// 256 tokens 155, 131, 122, 96, 106; 512: 156, 136, 123, 121, 144; 777: 165, 172, 149, 200, 249; 1300: 225, 202, 226, 300,
+// 362; 4096: 538, 604, 610, 816, 1039.  2 x 7 is for lengths of seven slabs: 777 tokens on 8192 x 8192 280 -> 263,
+// 400 on 28672 x 8192 376 -> 344.  (1 x 4 is nowhere the best.)  bf16 activations as they are (calls of up to 64
+// tokens) cost the one-tile form most, a conversion for every tile and block: 64 tokens with 1 x 2 and 2 x 2, 8192 x 28672, k = 8192, 328
+// and 231 us, 4096 x 11008, k = 4096, 97 and 88, 1024 x 1024, k = 512, 15.6 and 17.5; fp16
+// and fp32 ones cost both forms the same.
+// Each output is the same sum in the same order whatever the choice.  The element-wise mode has the two-tile forms only.
 struct LongShape {
   int R, TB;
 };
 static LongShape long_problem_shape(const StageProb& p, bool vectors) {
   static const struct {
     LongShape shape;
-    int alone, more;
-  } forms[] = {{{2, 8}, 1320, 1140}, {{2, 6}, 1080, 900}, {{2, 4}, 960, 690}, {{2, 2}, 710, 470}, {{1, 2}, 620, 360}};
+    int alone, more, once;
+  } forms[] = {{{2, 8}, 1320, 1140, 1120}, {{2, 7}, 1600, 1095, 1000}, {{2, 6}, 1080, 900, 800}, {{2, 4}, 960, 690, 460},
+               {{2, 2}, 710, 470, 220},    {{1, 2}, 620, 360, 0}},
+    bf16_forms[] = {{{2, 2}, 680, 470, 1100}, {{1, 2}, 790, 1050, 0}};
   const int cus = compute_units();
+  const int nblk = (p.K + 127) >> 7;
   LongShape best = {2, 8};
   double least = -1.0;
-  for (const auto& f : forms) {
-    if (f.shape.R == 1 && !vectors) continue;
+  for (const auto& any : forms) {
+    if (any.shape.R == 1 && !vectors) continue;
+    const bool bf16 = vectors && p.vin_dt == MDBF_BF16 && any.shape.TB == 2;
+    const auto& f = bf16 ? bf16_forms[any.shape.R == 1] : any;
     const int tiles = f.shape.R * gemm::kWaves;
     const int64_t wgs = (int64_t)((p.ntiles + tiles - 1) / tiles) * ((p.T + 16 * f.shape.TB - 1) / (16 * f.shape.TB));
-    const double cost = std::max((double)f.alone, f.more * 0.5 * ((double)wgs / cus + (double)((wgs + cus - 1) / cus)));
+    const double mean = (double)wgs / cus, busiest = (double)((wgs + cus - 1) / cus);
+    const double cost = nblk * std::max((double)f.alone, f.more * 0.5 * (mean + busiest)) + f.once;
     if (least < 0.0 || cost < least) {
       least = cost;
       best = f.shape;
@@ -1310,6 +1321,7 @@ int launch_stage_gemm(const WorkItem* items_dev, int nitems, int mode, GemmForm 
     if (f.TB == 2) return gemm::launch_rt<2, 2>(mode, p, s);
     if (f.TB == 4) return gemm::launch_rt<2, 4>(mode, p, s);
     if (f.TB == 6) return gemm::launch_rt<2, 6>(mode, p, s);
+    if (f.TB == 7) return gemm::launch_rt<2, 7>(mode, p, s);
     return gemm::launch_rt<2, 8>(mode, p, s);
   }
   if (p->T > 16 && vectors) return gemm::launch_rt<1, 2>(mode, p, s);

@@ -857,6 +857,37 @@ def test_tile_shapes_of_long_calls(gpu, n, k, l, x_dtype):
         assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32", workspace=ws), full[:T]), T
 
 
+@pytest.mark.parametrize("n,k,l,x_dtype", [(300, 520, 16, "f16"), (301, 515, 8, "bf16"), (130, 260, 5, "f32")])
+def test_long_calls_of_seven_slabs_at_a_time(gpu, n, k, l, x_dtype):
+    """512 row tiles in seven pieces of seven slabs, the last slab of one row, of four, and whole: the same bits as a longer
+    call's, which meets the oracle; fp16 copies and operands as they are."""
+    torch, mb = gpu
+    L = synth.make_layer(8186, n, k, l, seed=n + k + l, env_dtype="f16", env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 1100, seed=8, x_dtype=x_dtype)
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, x_dtype)
+    full = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    rows = list(range(0, 1100, 51)) + list(range(752, 784))
+    assert orc.max_rel_error(full[rows].cpu().numpy(), orc.forward_factored(*_oracle_args(L), X[rows])) <= TOL
+    for T in (769, 772, 784):
+        ws = torch.empty(mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32", precise=True), T), dtype=torch.uint8, device="cuda:0")
+        assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32"), full[:T]), T
+        assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32", workspace=ws), full[:T]), T
+
+
+@pytest.mark.parametrize("n,k", [(640, 4090), (1160, 4096), (1536, 1100), (1544, 8200)])
+def test_bf16_calls_of_33_to_64_tokens(gpu, n, k):
+    """Both sides of the length from which two row tiles share the conversion of bf16 activations, few and many row tiles:
+    any length from 33 to 64 is the same bits as 64 tokens, which meet the oracle."""
+    torch, mb = gpu
+    L = synth.make_layer(72, n, k, 8, seed=n + k, env_dtype="f16", env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 64, seed=9, x_dtype="bf16")
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, "bf16")
+    full = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    assert orc.max_rel_error(full.cpu().numpy(), orc.forward_factored(*_oracle_args(L), X)) <= TOL
+    for T in (33, 47, 49, 63):
+        assert torch.equal(mb.mdbf_forward(dl, Xd[:T], y_dtype="f32"), full[:T]), T
+
+
 @pytest.mark.parametrize("m,k,copies,T", [(2100, 600, 50, 8), (2100, 600, 100, 5), (52, 300, 1500, 6)])
 @pytest.mark.parametrize("l,x_dtype", [(16, "f16"), (8, "bf16"), (5, "f32")])
 def test_rows_beyond_fp16_stay_by_themselves(gpu, m, k, copies, T, l, x_dtype):
