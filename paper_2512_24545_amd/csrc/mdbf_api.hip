@@ -76,8 +76,8 @@ struct SplitLayout {
 };
 // Room that a one-token call is asked for behind the plan-style workspace: partial sums of up to eight runs of at most
 // four blocks (more where the contraction is longer) of both factors and a counter per eight row tiles of the second.
-// The first factor's partial sums (one_geom: at most kOneMaxSplits of them) take the front of it.  The size is the one
-// that callers have always been asked for.
+// The first factor's partial sums (one_geom: at most kOneMaxSplits of them) take the front of it, the second one's
+// (one_geom_summed) what is behind.  The size is the one that callers have always been asked for.
 size_t one_room(const mdbf_desc_t* d) {
   auto parts = [](int rows, int K) {
     const int groups = (num_tiles(rows) + 7) / 8, KB = num_blocks(K);
@@ -345,13 +345,18 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
   make_stages(desc, SA_packed_dev, SB_packed_dev, env, X_dev, ldx, Y_dev, ldy, T, workspace_dev, sp);
   hipStream_t s = (hipStream_t)stream;
   if (wants_one(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T) && stage_is_one(sp[0]) && stage_is_one(sp[1])) {
-    // two launches; the second factor's workgroups add up the first factor's partial sums as they load them
-    const int64_t ld = (int64_t)align_up((size_t)desc->k, 64);
-    const OneGeom g[2] = {one_geom(sp[0].ntiles, sp[0].KB, one_room(desc) / (size_t)(4 * ld)),
-                          one_geom(sp[1].ntiles, sp[1].KB, 1)};
-    float* part = g[0].nsplit == 1 ? nullptr : (float*)((unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T));
-    int e = launch_stage_one(&sp[0], g[0], nullptr, 0, 0, part, ld, s);
-    if (!e) e = launch_stage_one(&sp[1], g[1], part, g[0].nsplit, ld, nullptr, 0, s);
+    // the second factor's workgroups add up the first factor's partial sums as they load them; its own, where it has few rows
+    // and a long contraction, take a third launch
+    const int64_t ld[2] = {(int64_t)align_up((size_t)desc->k, 64), (int64_t)align_up((size_t)desc->m, 64)};
+    const OneGeom g0 = one_geom(sp[0].ntiles, sp[0].KB, one_room(desc) / (size_t)(4 * ld[0]));
+    const size_t used = g0.nsplit == 1 ? 0 : (size_t)g0.nsplit * (size_t)ld[0] * 4u;
+    const OneGeom g1 = one_geom_summed(sp[1], (one_room(desc) - used) / (size_t)(4 * ld[1]));
+    unsigned char* room = (unsigned char*)workspace_dev + plan_layer_ws_bytes(desc, T);
+    float* z = g0.nsplit == 1 ? nullptr : (float*)room;
+    float* y = g1.nsplit == 1 ? nullptr : (float*)(room + used);
+    int e = launch_stage_one(&sp[0], g0, nullptr, 0, 0, z, ld[0], s);
+    if (!e) e = launch_stage_one(&sp[1], g1, z, g0.nsplit, ld[0], y, ld[1], s);
+    if (!e && y) e = launch_few_reduce(&sp[1], y, g1.nsplit, ld[1], s);
     return hip_fail(e);
   }
   {

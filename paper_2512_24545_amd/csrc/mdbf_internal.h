@@ -190,6 +190,8 @@ struct OneGeom {
 // host arithmetic only; max_splits: partial sums per row there is room for
 OneGeom one_geom(int ntiles, int KB, size_t max_splits);
 constexpr int kOneMaxSplits = 4;
+// the same for a factor whose partial sums, if any, a launch of its own adds up
+OneGeom one_geom_summed(const StageProb& p, size_t max_splits);
 bool stage_is_one(const StageProb& p);       // its operands are addressable with 32-bit offsets
 // part_in (or null: p->vin): nsplit_in vectors part_in_ld apart whose sum is the activation vector.
 // part_out: g.nsplit vectors part_out_ld apart (unused when g.nsplit == 1: the result goes to p->out).
@@ -245,6 +247,8 @@ constexpr int kFewMaxTokens = 64;
 // sums per output there is room for
 SplitGeom few_geom(int ntiles, int KB, int T, bool vectors, size_t max_splits);
 int launch_stage_gemm_few(const StageProb* p, const SplitGeom& g, float* part, int64_t part_ld, hipStream_t s);
+// p->out from nsplit x p->T vectors of partial sums, part_ld apart
+int launch_few_reduce(const StageProb* p, const float* part, int nsplit, int64_t part_ld, hipStream_t s);
 
 // Copies in fp16 with padded rows (one launch, at most six): dst (rows x dst_cols, dst_ld apart; both multiples of
 // eight) receives src (src_rows x cols of type dt, ld apart) and zeros in the rest; src null: zeros only.

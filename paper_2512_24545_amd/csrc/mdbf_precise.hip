@@ -87,7 +87,8 @@ int launch_stage_precise(const StageProb* probs_dev, const WorkItem* items_dev, 
 // vector ALUs (three instructions per entry: shift the sign up, flip, multiply-add; 96 of them and 8 products a piece).
 // Nothing else lies between a wave's loads and its result: no scaled activations are built or shared, no barrier stands
 // before the last one, and a row tile's contraction meets in memory only between the two factors, where the reader adds
-// the (at most four) partial sums as it loads them.
+// the (at most four) partial sums as it loads them, and, for the second one, where few row tiles would leave the device
+// idle for long (one_geom_summed).
 // Against building block-scaled records of the scaled activations in every workgroup and adding partial sums of both
 // factors in memory, per call: 4096 x 4096, k = 2656, l = 16 13.1 -> 8.4 us; 256 x 256, k = 128, l = 4 in fp32 9.7 ->
 // 5.5; 11008 x 4096, k = 4096, l = 16 20.1 -> 13.4; two calls of 4096 x 4096, k = 1601, l = 1 25.9 -> 18.6; 3000 x 5000,
@@ -491,13 +492,20 @@ static int launch(const OneArgs& a, dim3 grid, int waves, hipStream_t s) {
 
 }  // namespace one
 
+// Eight waves; sixteen where a unit has one workgroup of a long contraction, whose loads then hide behind each other
+// (4096 x 11008, k = 4096: 13.8 -> 13.1 us; with more workgroups than units eight are better: 11008 x 4096 15.7 -> 13.1).
+static OneGeom one_waves(OneGeom g, int ntiles, int KB) {
+  g.nsplit = (KB + g.bs - 1) / g.bs;
+  while (g.waves < 8 && g.waves < g.bs) g.waves *= 2;
+  if (g.bs >= 16 && (int64_t)ntiles * g.nsplit <= 256) g.waves = one::kMaxWaves;
+  return g;
+}
+
 OneGeom one_geom(int ntiles, int KB, size_t max_splits) {
   // For a device of 256 compute units.  A unit's four SIMDs take four blocks of its workgroups at a time, whichever
   // waves hold them; a partial sum costs its reader a load: 166 row tiles of 32 blocks on three workgroups each leave 22
   // blocks on the busiest unit instead of 32 (8.8 -> 8.4 us per 4096 x 4096 call), 19 tiles of 86 blocks on four
   // 22 (10.4 -> 6.5 us for 200 x 11008, k = 300).
-  // Eight waves; sixteen where a unit has one workgroup of a long contraction, whose loads then hide behind each other
-  // (4096 x 11008, k = 4096: 13.8 -> 13.1 us; with more workgroups than units eight are better: 11008 x 4096 15.7 -> 13.1).
   OneGeom g = {1, KB, 1};
   int64_t least = -1;
   for (int n = 1; n <= kOneMaxSplits && (n == 1 || (size_t)n <= max_splits); ++n) {
@@ -508,10 +516,30 @@ OneGeom one_geom(int ntiles, int KB, size_t max_splits) {
       g.bs = bs;
     }
   }
-  g.nsplit = (KB + g.bs - 1) / g.bs;
-  while (g.waves < 8 && g.waves < g.bs) g.waves *= 2;
-  if (g.bs >= 16 && (int64_t)ntiles * g.nsplit <= 256) g.waves = one::kMaxWaves;
-  return g;
+  return one_waves(g, ntiles, KB);
+}
+
+OneGeom one_geom_summed(const StageProb& p, size_t max_splits) {
+  // Few row tiles of a long contraction leave most of the device idle: up to eight workgroups each, for the 2.4 us that the
+  // launch costs which adds their sums up.  ns that a unit takes for the four blocks on its SIMDs: 245 where rows are whole
+  // vectors of 16-bit entries, 310 otherwise; fp32 rows of 4, 8, 16 modes 410, 530, 730.  us per call with 1, 2, 4, 8
+  // workgroups a row tile, 16 x 128, k = 16000, l = 16 in fp32 28.4, 19.3, 13.9, 10.6, in fp16 12.6, 10.5, 8.8, 7.7;
+  // 1000 x 130, k = 8000 (63 row tiles) 18.4, 15.0, 11.6, 11.5 and 9.4, 9.5, 8.6, 8.5; 2000 x 130, k = 8000, l = 8
+  // 14.1, 12.7, 12.6, 12.4 and 9.3, 9.7, 9.6, 10.1; 16 x 128, k = 1000 6.3, 7.4, 7.3, 7.2 and 5.2, 6.8, 6.7, 6.7.
+  const int modes = p.l <= 4 ? 0 : p.l <= 8 ? 1 : 2;
+  static const int fp32_ns[3] = {410, 530, 730};
+  const int64_t ns = p.env_dt == MDBF_F32 ? fp32_ns[modes] : p.env_dt == MDBF_F16 && (p.l == 8 || p.l == 16) ? 245 : 310;
+  OneGeom g = {1, p.KB, 1};
+  int64_t least = -1;
+  for (int n = 1; n <= 8 && (n == 1 || (size_t)n <= max_splits); ++n) {
+    const int bs = (p.KB + n - 1) / n, used = (p.KB + bs - 1) / bs;
+    const int64_t cost = ns * (((int64_t)p.ntiles * used + 255) / 256) * ((bs + 3) / 4) + (used > 1 ? 2400 : 0);
+    if (least < 0 || cost < least) {
+      least = cost;
+      g.bs = bs;
+    }
+  }
+  return one_waves(g, p.ntiles, p.KB);
 }
 
 bool stage_is_one(const StageProb& p) {

@@ -1385,6 +1385,15 @@ int launch_stage_gemm_few(const StageProb* p, const SplitGeom& g, float* part, i
   else if (p->vin_dt == MDBF_BF16) e = gemm::launch_few_m<MDBF_BF16>(a, s);
   else e = gemm::launch_few_m<MDBF_F32>(a, s);
   if (e || g.nsplit == 1) return e;
+  return launch_few_reduce(p, part, g.nsplit, part_ld, s);
+}
+
+int launch_few_reduce(const StageProb* p, const float* part, int nsplit, int64_t part_ld, hipStream_t s) {
+  gemm::FewArgs a = {};
+  a.p = *p;
+  a.nsplit = nsplit;
+  a.part = const_cast<float*>(part);
+  a.part_ld = part_ld;
   hipLaunchKernelGGL(gemm::few_reduce_kernel, dim3((unsigned)((p->rows + 255) / 256), (unsigned)p->T), dim3(256), 0, s, a);
   return (int)hipGetLastError();
 }

@@ -528,6 +528,38 @@ def test_one_token_calls_are_fp32(gpu, m, n, k, l, env_dtype, x_dtype):
         assert orc.max_rel_error(got, ref) <= 2e-5
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype,y_dtype", [
+    (16, 128, 16000, 16, "f32", "f32", "f32"), (17, 130, 9100, 5, "bf16", "f16", "f32"), (1000, 129, 8001, 8, "f16", "bf16", "f16"),
+    (2000, 72, 8009, 3, "f32", "f32", "f32"), (40, 11008, 2700, 16, "f32", "f16", "bf16"), (1, 1, 30000, 1, "f16", "f32", "f32"),
+])
+def test_one_token_calls_of_few_rows_and_long_contractions(gpu, m, n, k, l, env_dtype, x_dtype, y_dtype):
+    """The second factor's blocks on two to eight workgroups per row tile, the last with fewer, beside a first factor that is
+    split as well and others that are not; the sums are added in a launch of their own, which accumulates and converts; a
+    graph's replays; nothing is written behind the workspace."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 1, seed=9 + m, x_dtype=x_dtype)
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, x_dtype)
+    size = mb.mdbf_workspace_bytes(dl.desc(x_dtype, "f32"), 1)
+    ws = torch.full((size + 4096,), 77, dtype=torch.uint8, device="cuda:0")
+    got = mb.mdbf_forward(dl, Xd, y_dtype="f32", workspace=ws[:size])
+    assert orc.max_rel_error(got.cpu().numpy(), ref) <= 2e-5
+    assert (ws[size:] == 77).all()
+    assert torch.equal(mb.mdbf_forward(dl, Xd, y_dtype="f32", Y=got.clone(), accumulate=True), got + got)
+    out = mb.mdbf_forward(dl, Xd, y_dtype=y_dtype, workspace=ws[:size])
+    assert torch.equal(out, got.to(out.dtype))
+    Y = torch.empty_like(got)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mb.mdbf_forward(dl, Xd, y_dtype="f32", Y=Y, workspace=ws[:size])
+    for _ in range(3):
+        Y.fill_(-1.0)
+        ws[:size].fill_(255)                             # (NaNs where partial sums will be)
+        graph.replay()
+        assert torch.equal(Y, got)
+
+
 def test_one_token_call_of_more_threads_than_a_grid_dimension_holds(gpu):
     """8.4 million row tiles on eight waves each: the last tiles' rows are those of a layer that has them alone."""
     torch, mb = gpu
