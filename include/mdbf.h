@@ -140,8 +140,8 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  *   workspace_dev / workspace_bytes  caller-owned scratch, >= mdbf_workspace_bytes()
  * Default arithmetic: fp32 accumulation on the matrix cores; z kept in fp32 with one token.  A single one-token call
  * rebuilds the factors S_A o (A Q^T), S_B o (G B^T) piece by piece in fp32 and applies them to the unrounded activations
- * in fp32, in two launches: what remains is the rounding of fp32 sums, added in a fixed order, so repeated calls return
- * the same bits.  Plans with one to three tokens do the same if their layers are of other ranks than 16, of mixed ones or
+ * in fp32, in two launches (three where the second factor has few rows and a long contraction): what remains is the
+ * rounding of fp32 sums, added in a fixed order, so repeated calls return the same bits.  Plans with one to three tokens do the same if their layers are of other ranks than 16, of mixed ones or
  * not of fp16 envelopes, unless they are large and the block-scaled variant serves them.  The other plans quantise the
  * l-way scaled activations (b^(s) o x and q^(t) o z) once --
  * to three fp6 limbs under a shared power-of-two scale per 32 values (about 13 bits; the block-scaled variant, taken by
@@ -155,10 +155,12 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  * differs in the last bits.  Plans of four tokens and more may return a NaN where a value beyond fp16 makes a single
  * call return an infinity.  An infinity among the envelopes leaves no finite output it reaches; whether those are
  * infinities or NaNs is not specified (its products with entries of either sign are added, in parts).
- * Range: the one-token variants of plans carry their own power-of-two exponents (the block-scaled one per 32 values,
- * the fp16 one per 1024 columns of a scaled-activation vector) and keep z in fp32; single one-token calls work in fp32
- * throughout: they hold their accuracy wherever the inputs and results are representable.  The general kernel (plans with other ranks and envelope
- * types, and single calls of those with MDBF_FLAG_FP16_STAGED) stages
+ * Range: the block-scaled and fp16-staged variants carry their own power-of-two exponents (per 32 values, per 1024
+ * columns of a scaled-activation vector) and keep z in fp32; single one-token calls, and the plans named with them above,
+ * work in fp32 throughout: they hold their accuracy wherever the inputs and results are representable.  The general
+ * kernel (plans that mix envelope types, or up to three tokens with more, of ranks and types that the variants above do
+ * not serve; plans and single one-token calls of those with MDBF_FLAG_FP16_STAGED; single ones whose workspace has no
+ * room for partial sums) stages
  * b^(s) o x and q^(t) o z in plain fp16, divided by up to 8: magnitudes below about 5e-4 lose accuracy.  The
  * many-token variant needs the entries of A Q^T and
  * G B^T, the activations and z inside fp16's normal range (6e-5 .. 65504); What is unchanged when A is divided

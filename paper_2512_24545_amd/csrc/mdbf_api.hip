@@ -565,7 +565,7 @@ static void balance_mx_items(WorkItem* items, int n, int max_wgs) {
 // 36.1 against 41.4; a decoder layer 60.2 -> 38.5, two 61.5 against 61.2; three tokens: four attention layers 85.9 ->
 // 31.1, a decoder layer 162 -> 80.9.  Against the general kernel always (224 matrices of rank 8: 2.4 ms there).
 static bool one_plan_pays(long pieces, int max_tokens, const int max_blocks[2], const int mx[2], const int fast[2]) {
-  if (fast[0] && fast[1]) return false;           // the fp16-staged kernels' plans stay there
+  if (fast[0] && fast[1]) return false;           // (rank 16, fp16 envelopes: stage_fast_short_kernel's, not compared here)
   for (int s = 0; s < 2; ++s)
     if (!mx[s] && !fast[s]) return true;
   const long stages = (max_blocks[0] + 1) / 2 + (max_blocks[1] + 1) / 2 + 2;

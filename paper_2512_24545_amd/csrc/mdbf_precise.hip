@@ -84,15 +84,18 @@ int launch_stage_precise(const StageProb* probs_dev, const WorkItem* items_dev, 
 // workgroup split the blocks and meet once, in LDS, in wave order.
 //
 // What bounds it: the launch and the chain load -> rebuild -> sum -> store; from some 20000 (tile, block) pieces on the
-// vector ALUs (three instructions per entry: shift the sign up, flip, multiply-add; 96 of them and 8 products a piece).
+// vector ALUs (three instructions per entry: flip, multiply-add, and an addition that doubles the register whose top bit
+// is the next sign; 96 of them and 8 products a piece), with fp32 envelopes on the matrix cores.
 // Nothing else lies between a wave's loads and its result: no scaled activations are built or shared, no barrier stands
 // before the last one, and a row tile's contraction meets in memory only between the two factors, where the reader adds
 // the (at most four) partial sums as it loads them, and, for the second one, where few row tiles would leave the device
 // idle for long (one_geom_summed).
 // Against building block-scaled records of the scaled activations in every workgroup and adding partial sums of both
-// factors in memory, per call: 4096 x 4096, k = 2656, l = 16 13.1 -> 8.4 us; 256 x 256, k = 128, l = 4 in fp32 9.7 ->
-// 5.5; 11008 x 4096, k = 4096, l = 16 20.1 -> 13.4; two calls of 4096 x 4096, k = 1601, l = 1 25.9 -> 18.6; 3000 x 5000,
-// k = 1777, l = 16 in fp32 19.6 -> 13.5; an empty pair of launches is 3 us.  Errors against 64 bits 6e-6 .. 2e-4 -> 2e-7.
+// factors in memory, per call of one layer again and again from a graph: 4096 x 4096, k = 2656, l = 16 13.1 -> 8.4 us (10.6
+// with layers that come from memory); 256 x 256, k = 128, l = 4 in fp32 9.7 -> 5.5; 11008 x 4096, k = 4096, l = 16 20.1 ->
+// 12.8; two calls of 4096 x 4096, k = 1601, l = 1 25.9 -> 17.9; 3000 x 5000, k = 1777, l = 16 in fp32 19.6 -> 13.5; an empty
+// pair of launches is 3 us.  Errors against 64 bits 6e-6 .. 2e-4 -> 2e-7.  Not faster: 1024 x 4096, k = 11008 (second factor
+// of 64 row tiles), bf16 rank 16 37.8 -> 40.2, fp32 rank 5 24.5 -> 25.9.
 // (Two row tiles per workgroup, which halve the reads of the envelope rows, are slower throughout: 8.7 -> 11.0 us.)
 // ---------------------------------------------------------------------------------------------------
 namespace one {

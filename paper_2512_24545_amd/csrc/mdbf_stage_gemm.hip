@@ -13,9 +13,11 @@
 //  * per 128-column block: E piece per tile = 2 x v_mfma_f32_16x16x16_f16 per 32 columns.  The products'
 //    row index is chosen so that lane (r, g) receives columns 32f + 8g + 0..7 of row r: exactly the columns
 //    whose signs sit in the lane's packed word, and exactly the B-operand slot of v_mfma_f32_16x16x32_f16
-//    for contraction step f.  No cross-lane movement between reconstruction and use.
+//    for contraction step f.  No cross-lane movement between reconstruction and use.  Two row tiles at a time (plans of
+//    at most eight tokens, and waves of two tiles in single problems with an even number of slabs): one
+//    v_mfma_f32_32x32x16_f16 per 32 columns of both
 //  * token product: for every 16-token slab, 4 contraction steps; A operand = 8 consecutive fp16 activations
-//    read from LDS (rows swizzled by 16-byte chunks against bank conflicts)
+//    read from LDS (rows swizzled by 16-byte chunks against bank conflicts); 32 x 32 x 16 for two tiles and two slabs
 // Arithmetic: envelopes and activations rounded to fp16 on load, E accumulated in fp32 and rounded to fp16
 // once, token product accumulated in fp32.  Values beyond the fp16 range overflow.
 #include "mdbf_internal.h"
@@ -54,8 +56,9 @@ __device__ __forceinline__ uint32_t pack_half2(float lo, float hi) {
 }
 
 // Sign flips of rebuilt pairs where two row tiles share a product, with the signs of the word's top bits (15 and 31), which
-// then makes way for the next pair: a word's pairs are taken from bits 15 and 31 downwards.  (Left shifts by constants take the vector ALUs four cycles,
-// additions less: 1.9 and 1.3 ns per wave and SIMD measured.  The compiler would turn x + x into a shift.)
+// then makes way for the next pair: a word's pairs are taken from bits 15 and 31 downwards.  (Left shifts by constants take
+// the vector ALUs four cycles, additions less: 1.9 and 1.3 ns per wave and SIMD measured.  The compiler would turn x + x into
+// a shift.)
 __device__ __forceinline__ uint32_t flip_next(uint32_t pair, uint32_t& signs) {
   const uint32_t out = pair ^ (signs & 0x80008000u);
   asm("v_add_u32 %0, %0, %0" : "+v"(signs));
@@ -1184,8 +1187,8 @@ __global__ __launch_bounds__(256) void half_copy_kernel(HalfCopies a) {
 // 256 tokens 155, 131, 122, 96, 106; 512: 156, 136, 123, 121, 144; 777: 165, 172, 149, 200, 249; 1300: 225, 202, 226, 300,
 // 362; 4096: 538, 604, 610, 816, 1039.  2 x 7 is for lengths of seven slabs: 777 tokens on 8192 x 8192 280 -> 263,
 // 400 on 28672 x 8192 376 -> 344.  (1 x 4 is nowhere the best.)  bf16 activations as they are (calls of up to 64
-// tokens) cost the one-tile form most, a conversion for every tile and block: 64 tokens with 1 x 2 and 2 x 2, 8192 x 28672, k = 8192, 328
-// and 231 us, 4096 x 11008, k = 4096, 97 and 88, 1024 x 1024, k = 512, 15.6 and 17.5; fp16
+// tokens) cost the one-tile form most, a conversion for every four tiles and block: 64 tokens with 1 x 2 and 2 x 2,
+// 8192 x 28672, k = 8192, 328 and 231 us, 4096 x 11008, k = 4096, 97 and 88, 1024 x 1024, k = 512, 15.6 and 17.5; fp16
 // and fp32 ones cost both forms the same.
 // Each output is the same sum in the same order whatever the choice.  The element-wise mode has the two-tile forms only.
 struct LongShape {

@@ -474,8 +474,7 @@ ANY_RANK = [
 
 @pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", ANY_RANK)
 def test_one_token_calls_of_any_rank_and_type(gpu, m, n, k, l, env_dtype, x_dtype):
-    """Four fp6 limbs hold a scaled activation to 2^-16 of the largest of its 32 (a limb's step is an eighth of
-    its scale, the scales fall by 16): relative to the largest output some 1e-5 at these sizes, 1e-4 allowed.  A
+    """fp32 throughout (the gate of 1e-4 is wider than that needs: test_one_token_calls_are_fp32 has the narrow one).  A
     workspace without room for partial sums takes the fp16-staged general kernel instead; an infinity or NaN
     anywhere in the input reaches every output."""
     torch, mb = gpu
