@@ -12,8 +12,10 @@
 //   B = |Z| V;   B^T B = W L W^T (Jacobi, fp64);   sigma = sqrt(L);   A = B W_l Sigma_l^(-1/2),   Q = V W_l Sigma_l^(1/2)
 // The two products are the whole cost: each reads Z once (HBM-bound, 4 bytes per 2 b multiply-adds), row-major as
 // it stands: one kernel, with the roles of rows and columns as a template argument.
-// Orthonormalisation is Cholesky-QR: Gram matrix from per-workgroup partial sums (fp32) added in fp64, Cholesky
-// factor R in fp64 by the last workgroup of that launch, and the next product applies R^(-1) to the rows of its input block as it stages them.
+// Orthonormalisation is Cholesky-QR: Gram matrix in per-workgroup parts (fp64 sums, stored in fp32) added in fp64, its Cholesky
+// factorisation in fp64.  In the first passes the last workgroup of the launch that leaves the parts factorises, and the next
+// product applies R^(-1) to the rows of its input block as it stages them; later a workgroup beside the product factorises, and
+// R^(-1) is applied to the product's sums.
 #include <type_traits>
 
 #include "mdbf_internal.h"
@@ -22,6 +24,8 @@ namespace mdbf {
 namespace msvid {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));    // four elements at any element's address
 typedef uint32_t u32_any __attribute__((aligned(1)));
 
@@ -52,9 +56,143 @@ __global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict_
   }
 }
 
-// ---- P[chunk][o][:] = sum over the chunk's contraction entries q of |Z[.]| * X'[q, :],   X' = X Tm  (Tm null: X' = X)
+// G = sum of the workgroups' parts, in fp64, in a fixed order: a thread adds four neighbouring entries of every
+// (THREADS / quads)-th part, sixteen loads in flight, then the groups are added in order.  sums: LDS for a double per entry and
+// group.
+// COHERENT: the parts were written by other workgroups of the same launch, with device-scope stores
+template <int BB, int THREADS>
+constexpr int gram_groups() { return THREADS / (BB * BB / 4); }
+template <int BB, int THREADS, bool COHERENT>
+__device__ void gather_gram(const float* __restrict__ Gp, int nparts, double* __restrict__ sums, double (&G)[BB][BB]) {
+  constexpr int kQuads = BB * BB / 4, kGroups = gram_groups<BB, THREADS>();
+  static_assert(kGroups >= 1, "a thread per quad");
+  const int grp = threadIdx.x / kQuads, qd = threadIdx.x - grp * kQuads;
+  if (grp < kGroups) {
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int w0 = grp; w0 < nparts; w0 += 16 * kGroups) {
+      floatx4 v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const MDBF_GLOBAL floatx4* src = (const MDBF_GLOBAL floatx4*)Gp + (size_t)min(w0 + u * kGroups, nparts - 1) * kQuads + qd;
+        if constexpr (COHERENT) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const uint64_t x = __hip_atomic_load((const MDBF_GLOBAL uint64_t*)src + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
+            v[u][2 * h] = __builtin_bit_cast(float, lo);
+            v[u][2 * h + 1] = __builtin_bit_cast(float, hi);
+          }
+        } else {
+          v[u] = *src;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (w0 + u * kGroups < nparts) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[e] += (double)v[u][e];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sums[grp * (BB * BB) + 4 * qd + e] = s[e];
+  }
+  __syncthreads();
+  for (int p = threadIdx.x; p < BB * BB; p += THREADS) {
+    double sum = sums[p];
+#pragma unroll
+    for (int w = 1; w < kGroups; ++w) sum += sums[w * (BB * BB) + p];
+    G[p / BB][p % BB] = sum;
+  }
+  __syncthreads();
+}
+
+// a double held by lane `src` (a compile-time or wave-uniform index), in every lane
+__device__ __forceinline__ double lane_value(double v, int src) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// ---- Cholesky-QR: G = R^T R (R upper triangular), Tm = R^(-1): Y Tm has orthonormal columns (Tf: the same in fp32).
+// One wave; lane j < 32 holds column j of the matrix in registers (right-looking: after step k the trailing columns
+// hold the Schur complement), lane 32 + j column j of the identity, which the same steps turn into column j of
+// L^(-1), L D L^T = G, and the roots of the pivots at the end into row j of R^(-1).  Row k is passed round by lane reads: no
+// LDS traffic and no barrier inside the b steps, and no substitution after them.
+// A column that the earlier ones span (|Z| of lower rank than the block is wide: a member of the format is) has
+// a pivot at the level of the Gram matrix's rounding, 1e-6 of its diagonal entry (fp32 partial sums): such a
+// column is dropped (its column of Tm is zero, and stays zero through the products that follow).
+// What bounds it: instructions of one wave, 8 cycles each (two lane reads and a multiply-add per entry of the trailing
+// columns).  The next pivot's entry goes first, so that its reciprocal is worked out between the others' updates:
+// 12600 -> 8200 cycles for b = 24 against a root per step and a zero or one per row behind a branch.
+template <int BB>
+__device__ __forceinline__ void cholesky_inverse(const double (&G)[BB][BB], double* Tm, float* Tf) {
+  const int j = (int)threadIdx.x & 31;
+  const bool inv = (threadIdx.x & 32) != 0;
+  const int jc = min(j, BB - 1);                       // lanes past the last column shadow it and store nothing
+  const double* column = &G[0][jc];
+  double a[BB];
+#pragma unroll
+  for (int i = 0; i < BB; ++i) a[i] = column[i * BB];
+  const double least = 1e-6 * column[jc * BB];         // of the lane's pivot
+#pragma unroll
+  for (int i = 0; i < BB; ++i) {
+    asm volatile("" : "+v"(a[i]));                     // (no branch around the loads)
+    a[i] = inv ? (i == jc ? 1.0 : 0.0) : a[i];
+  }
+  double own = 0.0;                                    // the lane's pivot (a dropped column: zero)
+  auto keeps = [&](double piv, int k) { const double l = lane_value(least, k); return piv > l && l > 0.0; };
+  double piv = lane_value(a[0], 0), r = __builtin_amdgcn_rcp(piv), e = fma(-piv, r, 1.0), t = fma(e, e, e);
+  bool keep = keeps(piv, 0);
+  r = keep ? fma(r, t, r) : 0.0;                       // (the estimate has 24 bits or more: cubed, all 53)
+  own = j == 0 && keep ? piv : own;
+#pragma unroll
+  for (int k = 0; k + 1 < BB; ++k) {
+    const double s = a[k], w = s * r;                  // (a dropped column changes nothing)
+    a[k + 1] = fma(-lane_value(s, k + 1), w, a[k + 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    piv = lane_value(a[k + 1], k + 1);
+    r = __builtin_amdgcn_rcp(piv);
+    __builtin_amdgcn_sched_barrier(0);
+    const int left = BB - (k + 2), per = (left + 3) / 4;
+#pragma unroll
+    for (int part = 0; part < 4; ++part) {
+      double b[(BB + 3) / 4];
+#pragma unroll
+      for (int u = 0; u < per; ++u)
+        if (part * per + u < left) b[u] = lane_value(s, k + 2 + part * per + u);
+      __builtin_amdgcn_sched_barrier(0);
+      if (part == 0) e = fma(-piv, r, 1.0);
+      if (part == 1) t = fma(e, e, e);
+      if (part == 2) r = fma(r, t, r);
+      if (part == 3) {
+        keep = keeps(piv, k + 1);
+        r = keep ? r : 0.0;
+        own = j == k + 1 && keep ? piv : own;
+      }
+#pragma unroll
+      for (int u = 0; u < per; ++u)
+        if (part * per + u < left) a[k + 2 + part * per + u] = fma(-b[u], w, a[k + 2 + part * per + u]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  const double root = own > 0.0 ? rsqrt(own) : 0.0;
+  if (inv && j < BB) {
+#pragma unroll
+    for (int i = 0; i < BB; ++i) {
+      const double v = a[i] * lane_value(root, i);
+      Tm[j * BB + i] = v;
+      Tf[j * BB + i] = (float)v;
+    }
+  }
+}
+
+// ---- P[chunk][o][:] = sum over the chunk's contraction entries q of |Z[.]| * X'[q, :],   X' = X T  (SCALED) or X
+// SCALED: T (in Tf) is there.  Else, with nparts > 0, workgroup 0 of the launch works it out beside the others' products, from
+// the parts of X^T X that the launch before left, and the launch that adds up the partial sums applies it to them:
+// |Z| (X T) = (|Z| X) T.
 // COLS: outputs are the columns of Z (|Z|^T X, X has a row per row of Z); else its rows (|Z| X).
-// Grid: (output strips of 64, contraction chunks of 256).  A wave owns the strip and 64 contraction entries, works out
+// Grid: output strips of 64, times contraction chunks of 256.  A wave owns the strip and 64 contraction entries, works out
 // its 64 rows of X' and contracts a 64 x 64 piece of Z in four rounds of 16 entries: four 16-byte loads per lane, a
 // round ahead, then 4 steps of v_mfma_f32_16x16x4_f32 (fp32 operands and sums) per 16 outputs and 16 columns of X'.
 // The four waves meet in LDS in wave order.
@@ -62,28 +200,40 @@ __global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict_
 // sums, which only partly overlap.  (All of a wave's sixteen loads in flight: no change; X as single elements in
 // operand order: 8 us more.)  Lanes that own columns and fused multiply-adds took 24 us per product of 4096 x 2656 and b = 24, and a transposed
 // copy of Z for |Z| X another 20 us per call; now 18 to 20 us.
-template <int BB, bool COLS>
+template <int BB, bool COLS, bool SCALED>
 __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
-                                                              const float* __restrict__ X, const float* __restrict__ Tm,
+                                                              const float* __restrict__ X, const float* __restrict__ Gp,
+                                                              int nparts, double* __restrict__ Tm, float* __restrict__ Tf,
                                                               float* __restrict__ P) {
   constexpr int NT = (BB + 15) / 16;                   // 16-column tiles of X' (the last may be partly past BB)
   constexpr int RS = BB + 1;                           // floats per output in the waves' sums
   constexpr int kXs = 4 * (64 * BB + 16), kRed = 4 * kOut * RS;
   __shared__ __attribute__((aligned(16))) float buf[kXs > kRed ? kXs : kRed];
-  __shared__ __attribute__((aligned(16))) float tms[BB * BB];
+  int unit = blockIdx.x;
+  if constexpr (!SCALED) {
+    if (nparts > 0 && unit-- == 0) {
+      constexpr int kEntries = BB * BB;
+      static_assert((gram_groups<BB, kThreads>() + 1) * kEntries * 8 <= sizeof(buf), "they take the products' LDS");
+      double (&G)[BB][BB] = *reinterpret_cast<double (*)[BB][BB]>(buf);
+      gather_gram<BB, kThreads, false>(Gp, nparts, reinterpret_cast<double*>(buf) + kEntries, G);
+      if (threadIdx.x < 64) cholesky_inverse<BB>(G, Tm, Tf);
+      return;
+    }
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int nout = COLS ? cols : rows, nin = COLS ? rows : cols;
-  const int o0 = blockIdx.x * kOut, q0 = blockIdx.y * kChunk;
+  const int strips = (nout + kOut - 1) / kOut, chunk = unit / strips;
+  const int o0 = (unit - chunk * strips) * kOut, q0 = chunk * kChunk;
   const int qw = q0 + wave * 64;
-  // ---- the wave's 64 rows of X, coalesced, and Tm (requested before Z: a load waits for all before it)
+  // ---- the wave's 64 rows of X, coalesced, and T (requested before Z: a load waits for all before it)
   constexpr int KS = BB / 4;                           // steps of four columns of X
   const MDBF_GLOBAL floatx4* xg = (const MDBF_GLOBAL floatx4*)X;
   floatx4 xr[KS], tr = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int i = 0; i < KS; ++i) xr[i] = xg[min((int64_t)qw * KS + lane + 64 * i, (int64_t)nin * KS - 1)];
-  if (Tm && tid < BB * BB / 4) tr = ((const MDBF_GLOBAL floatx4*)Tm)[tid];
+  if (SCALED && tid < BB * BB / 4) tr = ((const MDBF_GLOBAL floatx4*)Tf)[tid];
   // ---- Z.  COLS: load i of round j covers row qw + 16 j + 4 i + g and columns o0 + 4 n .. + 3: step i contracts its
   // four rows, output tile v holds columns o0 + 4 m + v.  Rows: load i covers row o0 + 16 i + n and columns
   // qw + 16 j + 4 g .. + 3: step v contracts columns qw + 16 j + 4 g' + v, output tile i holds rows o0 + 16 i + m.
@@ -115,9 +265,10 @@ __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __res
     reinterpret_cast<floatx4*>(xs)[lane + 64 * i] = ok ? xr[i] : floatx4{0.f, 0.f, 0.f, 0.f};
   }
   if (lane < 16) xs[64 * BB + lane] = 0.f;             // (read by the partial last tile, never used)
-  if (tid < BB * BB / 4) reinterpret_cast<floatx4*>(tms)[tid] = tr;
-  __syncthreads();
-  if (Tm) {
+  if constexpr (SCALED) {
+    __shared__ __attribute__((aligned(16))) float tms[BB * BB];
+    if (tid < BB * BB / 4) reinterpret_cast<floatx4*>(tms)[tid] = tr;
+    __syncthreads();
     float tb[KS][NT];
 #pragma unroll
     for (int k = 0; k < KS; ++k)
@@ -138,8 +289,8 @@ __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __res
           if (n + 16 * u < BB) xs[(16 * t + 4 * g + i) * BB + n + 16 * u] = d[i];
       }
     }
-    __syncthreads();
   }
+  __syncthreads();
 
   floatx4 acc[4][NT];
 #pragma unroll
@@ -177,7 +328,7 @@ __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __res
         if (n + 16 * u < BB) buf[(wave * kOut + o) * RS + n + 16 * u] = acc[t][u][i];
       }
   __syncthreads();
-  float* out = P + ((size_t)blockIdx.y * nout + o0) * BB;
+  float* out = P + ((size_t)chunk * nout + o0) * BB;
   const int valid = min(kOut, nout - o0) * BB;
 #pragma unroll 1
   for (int e = tid; e < valid; e += kThreads) {
@@ -187,129 +338,97 @@ __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __res
   }
 }
 
-// G = sum of the workgroups' parts, in fp64, in a fixed order: a thread adds two neighbouring entries of every
-// kGroups-th part, sixteen loads in flight, then the groups are added in order.
-// COHERENT: the parts were written by other workgroups of the same launch, with device-scope stores
-template <int BB, int THREADS, bool COHERENT>
-__device__ void gather_gram(const float* __restrict__ Gp, int nparts, double (&G)[BB][BB]) {
-  constexpr int kPairs = BB * BB / 2, kGroups = THREADS / kPairs;
-  static_assert(kGroups >= 1, "a thread per pair");
-  __shared__ double sums[kGroups][BB * BB];
-  const int grp = threadIdx.x / kPairs, pr = threadIdx.x - grp * kPairs;
-  if (grp < kGroups) {
-    double s0 = 0.0, s1 = 0.0;
-    for (int w0 = grp; w0 < nparts; w0 += 16 * kGroups) {
-      uint64_t v[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const MDBF_GLOBAL uint64_t* src =
-            (const MDBF_GLOBAL uint64_t*)Gp + (size_t)min(w0 + u * kGroups, nparts - 1) * kPairs + pr;
-        v[u] = COHERENT ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
-      }
-#pragma unroll
-      for (int u = 0; u < 16; ++u)
-        if (w0 + u * kGroups < nparts) {
-          const uint32_t lo = (uint32_t)v[u], hi = (uint32_t)(v[u] >> 32);
-          s0 += (double)__builtin_bit_cast(float, lo);
-          s1 += (double)__builtin_bit_cast(float, hi);
-        }
-    }
-    sums[grp][2 * pr] = s0;
-    sums[grp][2 * pr + 1] = s1;
-  }
-  __syncthreads();
-  for (int p = threadIdx.x; p < BB * BB; p += THREADS) {
-    double sum = sums[0][p];
-#pragma unroll
-    for (int w = 1; w < kGroups; ++w) sum += sums[w][p];
-    G[p / BB][p % BB] = sum;
-  }
-  __syncthreads();
-}
-
-// a double held by lane `src` (a compile-time or wave-uniform index), in every lane
-__device__ __forceinline__ double lane_value(double v, int src) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
-// ---- Cholesky-QR: G = R^T R (R upper triangular), Tm = R^(-1): Y Tm has orthonormal columns.
-// One wave; lane j < 32 holds column j of the matrix in registers (right-looking: after step k the trailing columns
-// hold the Schur complement), lane 32 + j column j of the identity, which the same steps turn into column j of
-// L^(-1), L = R^T, i.e. row j of R^(-1).  Row k is passed round by lane reads: no LDS traffic and no barrier inside
-// the b steps, and no substitution after them.
-// A column that the earlier ones span (|Z| of lower rank than the block is wide: a member of the format is) has
-// a pivot at the level of the Gram matrix's rounding, 1e-6 of its diagonal entry (fp32 partial sums): such a
-// column is dropped (its column of Tm is zero, and stays zero through the products that follow).
-template <int BB>
-__device__ __forceinline__ void cholesky_inverse(const double (&G)[BB][BB], double* __restrict__ Tm, float* __restrict__ Tf) {
-  const int j = (int)threadIdx.x & 31;
-  const bool inv = (threadIdx.x & 32) != 0;
-  const int jc = min(j, BB - 1);                       // lanes past the last column shadow it and store nothing
-  double a[BB];
-#pragma unroll
-  for (int i = 0; i < BB; ++i) a[i] = inv ? (i == jc ? 1.0 : 0.0) : G[i][jc];
-#pragma unroll
-  for (int k = 0; k < BB; ++k) {
-    const double piv = lane_value(a[k], k);            // the Schur complement's diagonal entry
-    const double g0 = G[k][k];
-    const bool drop = !(piv > 1e-6 * g0) || !(g0 > 0.0);
-    const double rd = drop ? 1.0 : rsqrt(piv);
-    // lanes j > k: R[k][j] (a dropped column: zeros); lanes 32 + j: entry k of the solution, zero where it was dropped
-    const double x = drop && !inv ? 0.0 : a[k] * rd;
-#pragma unroll
-    for (int i = k + 1; i < BB; ++i) a[i] -= lane_value(x, i) * x;     // (columns <= k are not read again)
-    a[k] = drop ? 0.0 : x;
-  }
-  if (inv && j < BB) {
-#pragma unroll
-    for (int i = 0; i < BB; ++i) {
-      Tm[j * BB + i] = a[i];
-      Tf[j * BB + i] = (float)a[i];
-    }
-  }
-}
-
-// ---- Y = sum over chunks of P (in chunk order), and this workgroup's part of Y^T Y.  Tm (or null): the last
-// workgroup to finish (a counter, which it sets back to zero; nobody waits) adds the parts up and leaves
-// Tm = R^(-1) of the Cholesky factorisation (Tf: the same in fp32).  In launches of their own the sums took 7 us and
-// the factorisation 17; together 15, most of it the chain of b pivots in fp64.
+// ---- Y = sum over chunks of P (in chunk order), times T where it is given (all in fp64), and this workgroup's part of
+// Y^T Y.  Tm (or null): the last workgroup to finish (a counter, which it sets back to zero; nobody waits) adds the parts up
+// and leaves Tm = R^(-1) of the Cholesky factorisation (Tf: the same in fp32).  T may be Tm: every workgroup has read it then.
+// In launches of their own the sums took 7 us and the factorisation 17; together 15, most of it the chain of b pivots in fp64,
+// which the products of later passes work out for themselves: 6 us without it.
 template <int BB>
 __global__ __launch_bounds__(kSmallThreads) void reduce_gram_kernel(const float* __restrict__ P, int nchunks, int n,
                                                                     float* __restrict__ Y, float* __restrict__ Gp,
-                                                                    double* __restrict__ Tm, float* __restrict__ Tf,
+                                                                    const double* T, double* Tm, float* Tf,
                                                                     uint32_t* __restrict__ counter) {
-  __shared__ float ys[kGramRows * BB];
+  constexpr int NT = (BB + 15) / 16;                   // 16-column tiles (the last may be partly past BB)
+  constexpr int RS = BB + 1;                           // entries per row in LDS
+  constexpr int kGroups = gram_groups<BB, kSmallThreads>();
+  __shared__ float ys[kGramRows * RS];
+  __shared__ double yd[kGramRows * RS], ts[BB * BB];
   __shared__ double G[BB][BB];
+  __shared__ double sums[kGroups * BB * BB];
   __shared__ uint32_t is_last;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane & 15, g = lane >> 4;
   const int row0 = blockIdx.x * kGramRows;
   const int nrow = min(kGramRows, n - row0);
   const size_t plane = (size_t)n * BB;
-  for (int idx = tid; idx < kGramRows * BB; idx += blockDim.x) {
-    float y = 0.f;
-    if (idx < nrow * BB) {
-      const size_t e = (size_t)row0 * BB + idx;
-      for (int c0 = 0; c0 < nchunks; c0 += 8) {        // eight loads in flight, added in chunk order
-        float v[8];
+  if (T)
+    for (int p = tid; p < BB * BB; p += kSmallThreads) ts[p] = T[p];
+  static_assert(kGramRows * BB / 2 <= kSmallThreads && BB % 2 == 0, "a thread per pair");
+  if (tid < kGramRows * BB / 2) {                      // two entries, sixteen chunks in flight, added in their order
+    const int idx = 2 * tid, r = idx / BB, j = idx - r * BB;
+    const size_t e = (size_t)row0 * BB + idx;
+    double y[2] = {0.0, 0.0};
+    if (r < nrow) {
+      for (int c0 = 0; c0 < nchunks; c0 += 16) {
+        floatx2 v[16];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = P[(size_t)min(c0 + u, nchunks - 1) * plane + e];
+        for (int u = 0; u < 16; ++u) v[u] = *(const MDBF_GLOBAL floatx2*)((const MDBF_GLOBAL float*)P + (size_t)min(c0 + u, nchunks - 1) * plane + e);
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (c0 + u < nchunks) y += v[u];
+        for (int u = 0; u < 16; ++u)
+          if (c0 + u < nchunks) {
+            y[0] += (double)v[u].x;
+            y[1] += (double)v[u].y;
+          }
       }
-      Y[e] = y;
+      if (!T) *(MDBF_GLOBAL floatx2*)((MDBF_GLOBAL float*)Y + e) = floatx2{(float)y[0], (float)y[1]};
     }
-    ys[idx] = y;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (T) yd[r * RS + j + i] = y[i];
+      else ys[r * RS + j + i] = (float)y[i];
+    }
   }
   __syncthreads();
-  for (int p = tid; p < BB * BB; p += blockDim.x) {
-    const int i = p / BB, j = p - i * BB;
-    float g = 0.f;
-    for (int r = 0; r < kGramRows; ++r) g = fmaf(ys[r * BB + i], ys[r * BB + j], g);
-    __hip_atomic_store((MDBF_GLOBAL float*)Gp + (size_t)blockIdx.x * BB * BB + p, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // Both small products on the matrix cores in fp64: lane (m, g) of an operand holds entry 4 k + g of row (column) m, of the
+  // result rows 4 i + g of column m.
+  if (T) {
+    if (wave < 4 * NT) {                               // 16 rows, 16 columns
+      const int t = wave & 3, col = 16 * (wave >> 2) + m;
+      doublex4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int k = 0; k < BB / 4; ++k)
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(yd[(16 * t + m) * RS + 4 * k + g], ts[(4 * k + g) * BB + min(col, BB - 1)], d, 0, 0, 0);
+      if (col < BB) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int r = 16 * t + 4 * i + g;
+          ys[r * RS + col] = (float)d[i];
+          if (r < nrow) ((MDBF_GLOBAL float*)Y)[(size_t)(row0 + r) * BB + col] = (float)d[i];
+        }
+      }
+    }
+    __syncthreads();
+  }
+  static_assert(4 * NT * NT <= kSmallThreads / 64 && kGroups >= 4, "a wave per tile and quarter of the rows");
+  if (wave < 4 * NT * NT) {
+    const int q = wave & 3, ci = 16 * ((wave >> 2) % NT) + m, cj = 16 * ((wave >> 2) / NT) + m;
+    doublex4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kGramRows / 16; ++k) {
+      const float* row = ys + (kGramRows / 4 * q + 4 * k + g) * RS;
+      d = __builtin_amdgcn_mfma_f64_16x16x4f64((double)row[min(ci, BB - 1)], (double)row[min(cj, BB - 1)], d, 0, 0, 0);
+    }
+    if (cj < BB) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (ci - m + 4 * i + g < BB) sums[q * (BB * BB) + (ci - m + 4 * i + g) * BB + cj] = d[i];
+    }
+  }
+  __syncthreads();
+  for (int p = tid; p < BB * BB; p += kSmallThreads) {
+    const float part = (float)((sums[p] + sums[BB * BB + p]) + (sums[2 * BB * BB + p] + sums[3 * BB * BB + p]));
+    __hip_atomic_store((MDBF_GLOBAL float*)Gp + (size_t)blockIdx.x * BB * BB + p, part, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (!Tm) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's entries are in memory
@@ -321,7 +440,7 @@ __global__ __launch_bounds__(kSmallThreads) void reduce_gram_kernel(const float*
   __syncthreads();
   if (!is_last) return;
   if (tid == 0) __hip_atomic_store((MDBF_GLOBAL uint32_t*)counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  gather_gram<BB, kSmallThreads, true>(Gp, gridDim.x, G);
+  gather_gram<BB, kSmallThreads, true>(Gp, gridDim.x, sums, G);
   if (tid >= 64) return;                               // (no barrier below)
   cholesky_inverse<BB>(G, Tm, Tf);
 }
@@ -347,7 +466,8 @@ __global__ __launch_bounds__(kRitzThreads) void ritz_kernel(const float* __restr
   __shared__ int pp[H], qq[H];
   __shared__ int order[BB];
   const int t = threadIdx.x;
-  gather_gram<BB, kRitzThreads, false>(Gp, nparts, aa[0]);
+  __shared__ double sums[gram_groups<BB, kRitzThreads>() * BB * BB];
+  gather_gram<BB, kRitzThreads, false>(Gp, nparts, sums, aa[0]);
   for (int p = t; p < BB * BB; p += kRitzThreads) w[p / BB][p % BB] = (p / BB == p % BB) ? 1.0 : 0.0;
   __syncthreads();
   static_assert(BB % 2 == 0, "pairs");
@@ -486,40 +606,55 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
   const int rows_per_wg = kThreads >> sh;
   hipLaunchKernelGGL(sign_kernel, dim3((rows + rows_per_wg - 1) / rows_per_wg, (cols + (4 << sh) - 1) / (4 << sh)), blk, 0, s,
                      Z, rows, cols, ld, sh, S, ctr);
-  // Y = Yin's sums (nchunks of them), its Gram parts and (Tout) the inverse of its Cholesky factor
-  auto reduce = [&](const float* Yin, int nchunks, int n, float* Y, double* Tout) {
+  // Y = Yin's sums (nchunks of them), times T, its Gram parts and (Tout) the inverse of its Cholesky factor
+  auto reduce = [&](const float* Yin, int nchunks, int n, float* Y, const double* T, double* Tout) {
     const int nparts = (n + kGramRows - 1) / kGramRows;
-    hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(nparts), dim3(kSmallThreads), 0, s, Yin, nchunks, n, Y, Gp, Tout, Tf, ctr);
+    hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(nparts), dim3(kSmallThreads), 0, s, Yin, nchunks, n, Y, Gp, T, Tout, Tf, ctr);
     return nparts;
   };
-  auto product = [&](auto cols_side, int nout, int nin, const float* X, const float* Tx) {
+  auto product = [&](auto cols_side, auto is_scaled, int nout, int nin, const float* X, int nparts) {
     const int nchunks = (nin + kChunk - 1) / kChunk;
-    hipLaunchKernelGGL((abs_mul_kernel<BB, decltype(cols_side)::value>), dim3((nout + kOut - 1) / kOut, nchunks), blk, 0, s,
-                       Z, rows, cols, ld, X, Tx, P);
+    const int64_t units = (int64_t)((nout + kOut - 1) / kOut) * nchunks + (nparts > 0 ? 1 : 0);
+    hipLaunchKernelGGL((abs_mul_kernel<BB, decltype(cols_side)::value, decltype(is_scaled)::value>), dim3((unsigned)units), blk,
+                       0, s, Z, rows, cols, ld, X, Gp, nparts, Tm, Tf, P);
     return nchunks;
   };
-  auto rows_product = [&](const float* X, const float* Tx, double* Tout) {      // Yb = |Z| (X Tx)
-    return reduce(P, product(std::false_type(), rows, cols, X, Tx), rows, Yb, Tout);
-  };
-  auto cols_product = [&](const float* X, const float* Tx, double* Tout) {      // Yc = |Z|^T (X Tx)
-    return reduce(P, product(std::true_type(), cols, rows, X, Tx), cols, Yc, Tout);
+  // Step 2 i of the iteration is B = |Z| V of pass i, step 2 i + 1 V = |Z|^T B.  X is not orthonormal: T = R^(-1) of X^T X = R^T R
+  // is applied to it in front of the product (T from the launch before), or behind it (T from beside it, from the Gram parts):
+  // 9 us less of waiting, a product without the 1.6 us of X T.  Behind the product, T also takes out what the leading
+  // columns have in common with the others after |Z| has magnified it: with a leading mode sigma_1 / sigma_j = 1 / rho times
+  // larger, at an angle theta_i to the first column after i passes, the rounding of those columns grows by at most
+  // min(1 / rho, rho^(2 i - 1) tan theta_0) <= (tan theta_0)^(1 / 2 i): 7 after one pass from a random start (tan theta_0 = 50), 2.7 after
+  // two, while 38 would be lost at the start of a Gaussian matrix.  So the first two passes apply it in front.
+  // (Long blocks, of many Gram parts, always: four waves would be too long adding them up.)
+  constexpr int kStepsBehind = 4, kMostParts = 256;
+  const int row_parts = (rows + kGramRows - 1) / kGramRows, col_parts = (cols + kGramRows - 1) / kGramRows;
+  const bool can = row_parts <= kMostParts && col_parts <= kMostParts;
+  auto behind = [&](int step) { return can && step >= kStepsBehind; };
+  auto step_product = [&](auto cols_side, int step, const float* X, bool last) {
+    constexpr bool kCols = decltype(cols_side)::value;
+    const int nout = kCols ? cols : rows, nin = kCols ? rows : cols;
+    int nchunks;
+    if (step == 0 || behind(step))
+      nchunks = product(cols_side, std::false_type(), nout, nin, X, step == 0 ? 0 : kCols ? row_parts : col_parts);
+    else
+      nchunks = product(cols_side, std::true_type(), nout, nin, X, 0);
+    return reduce(P, nchunks, nout, kCols ? Yc : Yb, behind(step) ? Tm : nullptr, last || !behind(step + 1) ? Tm : nullptr);
   };
   const float* X = X0;
-  const float* Tx = nullptr;
   for (int it = 0; it < iters; ++it) {
-    rows_product(X, Tx, Tm);                           // B = |Z| V
-    cols_product(Yb, Tf, Tm);                          // V = |Z|^T B
+    step_product(std::false_type(), 2 * it, X, false);
+    step_product(std::true_type(), 2 * it + 1, Yb, it + 1 == iters);
     X = Yc;
-    Tx = Tf;
   }
   // an orthonormal V: Cholesky-QR twice (iters == 0: on the start block itself)
   const int grid_apply = 1024;
-  if (iters == 0) reduce(X0, 1, cols, Yc, Tm);
+  if (iters == 0) reduce(X0, 1, cols, Yc, nullptr, Tm);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);
-  reduce(V1, 1, cols, Yc, Tm);                                                                    // (Yc = copy of V1)
+  reduce(V1, 1, cols, Yc, nullptr, Tm);                                                              // (Yc = copy of V1)
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);        // V1 = V, orthonormal
   // Rayleigh-Ritz on B = |Z| V
-  const int npb = rows_product(V1, nullptr, nullptr);
+  const int npb = reduce(P, product(std::false_type(), std::false_type(), rows, cols, V1, 0), rows, Yb, nullptr, nullptr);
   hipLaunchKernelGGL(ritz_kernel<BB>, dim3(1), dim3(kRitzThreads), 0, s, Gp, npb, l, MA, MQ, sigma);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yb, rows, MA, l, A);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, V1, cols, MQ, l, Q);

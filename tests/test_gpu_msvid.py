@@ -63,6 +63,25 @@ def test_mask_is_exact_and_error_is_the_spectral_tail(gpu, shape, l):
     np.testing.assert_allclose(Q.T @ Q, np.diag(sg[:l].astype(np.float64)), atol=2e-4 * sg[0])
 
 
+@pytest.mark.parametrize("rows,cols,l,iters", [(65, 40, 4, 3), (1025, 130, 16, 3), (191, 700, 8, 4), (24, 2049, 16, 5),
+                                               (16384, 32, 8, 3), (16385, 33, 16, 3), (70, 16500, 1, 3)])
+def test_later_passes_normalise_behind_the_product(gpu, rows, cols, l, iters):
+    """From the third pass on the inverse Cholesky factor is worked out beside the product and applied to its sums, for up to
+    256 row groups of 64 (16384 and 16385 rows, 16500 columns: the two sides of that line); blocks of both widths.  Against the
+    same iteration in fp64: Ritz values and envelope are those of the same subspace, whatever basis is taken on the way."""
+    Z = _f32(np.random.default_rng(rows + cols).standard_normal((rows, cols)))
+    S, A, Q, sg = _run(gpu, Z, l, iters=iters)
+    M, V = np.abs(Z), synth.normal_block(cols, 16 if l <= 8 else 24, 1).astype(np.float64)
+    for _ in range(iters):
+        V = M.T @ np.linalg.qr(M @ V)[0]
+    V = np.linalg.qr(V)[0]
+    U, sig, Wt = np.linalg.svd(M @ V, full_matrices=False)
+    best = (U[:, :l] * sig[:l]) @ (V @ Wt[:l].T).T
+    # fp32 products of 2 iters steps, each 2^-24 of the block per entry, added up at random signs (2e-7 measured at most)
+    assert np.abs(sg - sig).max() <= 2e-6 * sig[0]
+    assert np.linalg.norm(A @ Q.T - best) <= 5e-6 * np.linalg.norm(best)
+
+
 @pytest.mark.parametrize("l", [1, 3, 8, 16])
 def test_members_of_the_format_are_fixed_points(gpu, l):
     """Z = S o (A0 Q0^T) with a non-negative envelope of rank l: |Z| has rank l, so MSVID_l returns Z itself
