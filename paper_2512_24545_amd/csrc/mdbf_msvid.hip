@@ -447,115 +447,136 @@ __global__ __launch_bounds__(kSmallThreads) void reduce_gram_kernel(const float*
 
 // ---- Rayleigh-Ritz: G = B^T B = W L W^T by cyclic Jacobi in fp64; Ritz values sigma_i = sqrt(L_i), descending.
 // MA = W_l Sigma_l^(-1/2) (A = B MA), MQ = W_l Sigma_l^(1/2) (Q = V MQ); both BB x BB row-major, columns >= l zero.
-// Cyclic Jacobi with the round-robin ordering: a step rotates BB / 2 disjoint index pairs at once (player BB - 1
-// stays, the others move round a circle), BB - 1 steps visit every pair once.  BB / 2 lanes work out the rotations
-// of a step, then a thread applies them to the 2 x 2 block of a row pair and a column pair (rows and columns in one
-// go, into the other of two copies) or to two entries of a row of W: two barriers a step.  What bounds it is the
-// chain of a step (a reciprocal root, a reciprocal and another root in fp64 between trips to LDS), some 160 steps.
-// Rows after columns, with full square roots and divisions, and a last sweep to see that nothing rotates any more:
-// 172 us, now 91 us.  (Every thread working out its own rotations saves a barrier and costs more: 116 us.)
-constexpr int kRitzThreads = 576;
+// Cyclic Jacobi with the round-robin ordering: a step rotates the BB / 2 index pairs (2 i, 2 i + 1) at once and moves rows
+// and columns on as it writes them (one stays, the others move round a circle), so that the next pairs lie in the same places: BB - 1
+// steps bring every two together once, and everything back.  A lane works out the rotation of one column pair and applies it
+// to the 2 x 2 block of four rows (with the row pair's, from another lane; rows and columns in one go, into the other of two
+// copies) or to two entries of a row of W: one barrier a step, and no more trips to LDS than the entries themselves.
+// What bounds it is a step's chain of instructions (8 cycles each for a lone wave of a SIMD), BB - 1 steps in six or seven sweeps.
+// The angle comes from fp32 arithmetic (the next sweep takes out what it leaves, 1e-7 of an entry), its cosine and sine from fp64:
+// a rotation to working precision whatever the angle is.  Entries below 1e-13 of their diagonal ones' mean are left: the results
+// are rounded to fp32.
+// Moving indices instead of rows, angles in fp64 by one wave and two barriers a step 91 us (every thread for itself 116; every
+// wave for itself in fp32 102), seven sweeps; now 64, six.
+constexpr int ritz_block_waves(int BB) { return (BB / 2 + 3) / 4; }   // a row pair, or a row of W, per sixteen lanes
 template <int BB>
-__global__ __launch_bounds__(kRitzThreads) void ritz_kernel(const float* __restrict__ Gp, int nparts, int l,
+constexpr int ritz_threads() { return 64 * (ritz_block_waves(BB) + (BB + 3) / 4); }
+template <int BB>
+__global__ __launch_bounds__(ritz_threads<BB>()) void ritz_kernel(const float* __restrict__ Gp, int nparts, int l,
                                                   double* __restrict__ MA, double* __restrict__ MQ,
                                                   float* __restrict__ sigma) {
-  constexpr int H = BB / 2;
-  __shared__ double aa[2][BB][BB];
-  __shared__ double w[BB][BB];
-  __shared__ double cc[H], ss[H];
-  __shared__ int pp[H], qq[H];
+  constexpr int H = BB / 2, kThr = ritz_threads<BB>(), RS = BB + 2;   // (rows of 16-byte pairs, spread over the banks)
+  __shared__ double g0[BB][BB];
+  __shared__ __attribute__((aligned(16))) double lds[4 * BB * RS];    // the matrix, W, and their other copies
   __shared__ int order[BB];
-  const int t = threadIdx.x;
-  __shared__ double sums[gram_groups<BB, kRitzThreads>() * BB * BB];
-  gather_gram<BB, kRitzThreads, false>(Gp, nparts, sums, aa[0]);
-  for (int p = t; p < BB * BB; p += kRitzThreads) w[p / BB][p % BB] = (p / BB == p % BB) ? 1.0 : 0.0;
+  __shared__ double sums[gram_groups<BB, kThr>() * BB * BB];
+  const int t = threadIdx.x, lane = t & 63;
+  gather_gram<BB, kThr, false>(Gp, nparts, sums, g0);
+  // the largest diagonal entry to [0.5, 1), by a power of two, for the fp32 angles
+  double most = 0.0;
+  for (int i = 0; i < BB; ++i) most = fmax(most, g0[i][i]);
+  int ex = 0;
+  if (most > 0.0 && most < __builtin_huge_val()) (void)frexp(most, &ex);
+  for (int p = t; p < BB * BB; p += kThr) {
+    const int i = p / BB, j = p - i * BB;
+    // (row and column i, and BB - 1 - i, at places 2 i and 2 i + 1)
+    const int pi = (i & 1) ? BB - 1 - (i >> 1) : i >> 1, pj = (j & 1) ? BB - 1 - (j >> 1) : j >> 1;
+    lds[i * RS + j] = ldexp(g0[pi][pj], -ex);
+    lds[(BB + i) * RS + j] = i == pj ? 1.0 : 0.0;
+  }
+  static_assert(BB % 2 == 0 && H >= 3 && H <= 64, "pairs");
+  // where a row (column) goes after a step
+  auto moved = [](int x) {
+    return x == 1 ? 1 : x == 0 ? 3 : x == BB - 1 ? BB - 2 : (x & 1) ? x + 2 : x - 2;
+  };
+  static_assert(H <= 16 && BB % 4 == 0, "a lane per column pair");
+  constexpr int kBlockWaves = ritz_block_waves(BB);
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const bool on_a = wave < kBlockWaves;                // (uniform)
+  const int cp = min(lane & 15, H - 1), sub = lane >> 4;              // (lanes past the last pair store nothing)
+  const int rp = on_a ? 4 * wave + sub : 0, wrow = on_a ? 0 : 4 * (wave - kBlockWaves) + sub;
+  const bool live = (lane & 15) < H && rp < H;
+  const int rpc = min(rp, H - 1);
+  const int row = on_a ? 2 * rpc : BB + wrow;          // the block's rows (of W: one) and columns
+  const int from0 = row * RS + 2 * cp, from1 = from0 + (on_a ? RS : 0);
+  const int to_row0 = on_a ? moved(2 * rpc) : BB + wrow, to_row1 = on_a ? moved(2 * rpc + 1) : BB + wrow;
+  const int to_col0 = moved(2 * cp), to_col1 = moved(2 * cp + 1);
+  const int to00 = to_row0 * RS + to_col0, to01 = to_row0 * RS + to_col1, to10 = to_row1 * RS + to_col0, to11 = to_row1 * RS + to_col1;
+  const int diag = 2 * cp * RS + 2 * cp;
+  auto cosine = [](float tf) {                         // (the estimate has 22 bits: cubed, all 53)
+    const double tt = (double)tf, x = fma(tt, tt, 1.0), c0 = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.f));
+    const double e = fma(-x * c0, c0, 1.0);
+    return fma(c0 * e, fma(e, 0.375, 0.5), c0);
+  };
+  int cur = 0;                                         // the copy that is read: 0 or its distance
   __syncthreads();
-  static_assert(BB % 2 == 0, "pairs");
-  static_assert(BB * BB <= kRitzThreads && H * H + BB * H <= kRitzThreads, "a thread per entry, per block, per pair of entries of W");
-  const bool on_a = t < H * H, on_w = !on_a && t < H * H + BB * H;
-  const int wi = t - H * H;
-  const int rp = on_a ? t / H : 0, cp = on_a ? t - rp * H : on_w ? wi % H : 0, wrow = on_w ? wi / H : 0;
-  // an off-diagonal entry that still has to go
-  auto big = [](double apq, double app, double aqq) { return fabs(apq) > 1e-150 && apq * apq > 1e-32 * fabs(app * aqq); };
-  int cur = 0;
   for (int sweep = 0; sweep < 12; ++sweep) {
-    {
-      const int p = t / BB, q = t - p * BB;
-      const double (&a)[BB][BB] = aa[cur];
-      if (!__syncthreads_or(t < BB * BB && p < q && big(a[p][q], a[p][p], a[q][q]) ? 1 : 0)) break;   // diagonal to working precision
+    bool any = false;                                  // an off-diagonal entry that still has to go
+    for (int e = t; e < BB * BB; e += kThr) {
+      const int p = e / BB, q = e - p * BB;
+      const double apq = lds[cur + p * RS + q], app = lds[cur + p * RS + p], aqq = lds[cur + q * RS + q];
+      any = any || (p < q && fabs(apq) > 1e-30 && apq * apq > 1e-26 * fabs(app * aqq));
     }
+    if (!__syncthreads_or(any ? 1 : 0)) break;
+#pragma unroll 1
     for (int step = 0; step < BB - 1; ++step) {
-      const double (&a)[BB][BB] = aa[cur];
-      if (t < H) {
-        int p = t == 0 ? step : (step + t) % (BB - 1);
-        int q = t == 0 ? BB - 1 : (step - t + (BB - 1)) % (BB - 1);
-        if (p > q) { const int tmp = p; p = q; q = tmp; }
-        // (the angle only has to be good enough to converge; c and sn are a rotation to working precision whatever
-        // tt is)
-        const double apq = a[p][q], app = a[p][p], aqq = a[q][q];
-        const bool turn = big(apq, app, aqq);
-        const double d = 0.5 * (aqq - app), x = turn ? d * d + apq * apq : 1.0;
-        double h = __builtin_amdgcn_rsq(x);
-        h = x * (h * (1.5 - 0.5 * x * h * h));                            // sqrt(d^2 + apq^2)
-        const double den = fabs(d) + h;
-        double r = __builtin_amdgcn_rcp(den);
-        r = r * (2.0 - den * r);
-        const double tt = turn ? (d >= 0.0 ? apq : -apq) * r : 0.0;         // the smaller of the two rotations
-        const double c = rsqrt(1.0 + tt * tt);
-        pp[t] = p;
-        qq[t] = q;
-        cc[t] = c;
-        ss[t] = tt * c;
-      }
-      __syncthreads();
-      if (on_a || on_w) {
-        const int p2 = pp[cp], q2 = qq[cp];
-        const double c2 = cc[cp], s2 = ss[cp];
-        if (on_a) {
-          const int p1 = pp[rp], q1 = qq[rp];
-          const double c1 = cc[rp], s1 = ss[rp];
-          const double app = a[p1][p2], apq = a[p1][q2], aqp = a[q1][p2], aqq = a[q1][q2];
-          const double bpp = c2 * app - s2 * apq, bpq = s2 * app + c2 * apq;     // columns
-          const double bqp = c2 * aqp - s2 * aqq, bqq = s2 * aqp + c2 * aqq;
-          double (&o)[BB][BB] = aa[cur ^ 1];
-          o[p1][p2] = c1 * bpp - s1 * bqp;                                       // rows
-          o[p1][q2] = c1 * bpq - s1 * bqq;
-          o[q1][p2] = s1 * bpp + c1 * bqp;
-          o[q1][q2] = s1 * bpq + c1 * bqq;
-        } else {
-          const double wp = w[wrow][p2], wq = w[wrow][q2];
-          w[wrow][p2] = c2 * wp - s2 * wq;
-          w[wrow][q2] = s2 * wp + c2 * wq;
+      const double* a = lds + cur;
+      double* out = lds + (2 * BB * RS - cur);
+      const double2 top = *reinterpret_cast<const double2*>(a + diag);
+      const double aqq = a[diag + RS + 1];
+      const double2 b0 = *reinterpret_cast<const double2*>(a + from0);
+      double2 b1 = {0.0, 0.0};
+      if (on_a) b1 = *reinterpret_cast<const double2*>(a + from1);
+      const float h = (float)(0.5 * (aqq - top.x)), o = (float)top.y;
+      float tf = o * __builtin_amdgcn_rcpf(fabsf(h) + __builtin_amdgcn_sqrtf(fmaf(h, h, o * o)));
+      tf = o == 0.f ? 0.f : fminf(fmaxf(tf, -1.f), 1.f);                  // the smaller of the two rotations
+      tf = h >= 0.f ? tf : -tf;
+      if (on_a) {
+        const float tr = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * rpc, __builtin_bit_cast(int, tf)));
+        const double c2 = cosine(tf), s2 = (double)tf * c2, c1 = cosine(tr), s1 = (double)tr * c1;
+        const double bpp = c2 * b0.x - s2 * b0.y, bpq = s2 * b0.x + c2 * b0.y;     // columns
+        const double bqp = c2 * b1.x - s2 * b1.y, bqq = s2 * b1.x + c2 * b1.y;
+        if (live) {
+          out[to00] = c1 * bpp - s1 * bqp;                                         // rows
+          out[to01] = c1 * bpq - s1 * bqq;
+          out[to10] = s1 * bpp + c1 * bqp;
+          out[to11] = s1 * bpq + c1 * bqq;
+        }
+      } else {
+        const double c2 = cosine(tf), s2 = (double)tf * c2;
+        if (live) {
+          out[to00] = c2 * b0.x - s2 * b0.y;
+          out[to01] = s2 * b0.x + c2 * b0.y;
         }
       }
       __syncthreads();
-      cur ^= 1;
+      cur = 2 * BB * RS - cur;
     }
   }
-  const double (&a)[BB][BB] = aa[cur];
+  auto eigen = [&](int i) { return ldexp(lds[cur + i * RS + i], ex); };
   if (t < BB) {            // eigenvalues in descending order, ties by index
     // (a NaN, from a NaN or infinity in Z, ranks below everything: `order` is a permutation whatever the entries are)
     const double none = -__builtin_huge_val();
-    const double own = a[t][t] == a[t][t] ? a[t][t] : none;
+    const double at = eigen(t), mine = at == at ? at : none;
     int rank = 0;
     for (int i = 0; i < BB; ++i) {
-      const double e = a[i][i] == a[i][i] ? a[i][i] : none;
-      rank += (e > own || (e == own && i < t)) ? 1 : 0;
+      const double ai = eigen(i), e = ai == ai ? ai : none;
+      rank += (e > mine || (e == mine && i < t)) ? 1 : 0;
     }
     order[rank] = t;
   }
   __syncthreads();
-  if (t < BB) sigma[t] = (float)sqrt(fmax(a[order[t]][order[t]], 0.0));
+  if (t < BB) sigma[t] = (float)sqrt(fmax(eigen(order[t]), 0.0));
   for (int p = t; p < BB * BB; p += blockDim.x) {
     const int i = p / BB, j = p - i * BB;
     double ma = 0.0, mq = 0.0;
     if (j < l) {
-      const double sg = sqrt(fmax(a[order[j]][order[j]], 0.0));
-      const double sg_max = sqrt(fmax(a[order[0]][order[0]], 0.0));
+      const double sg = sqrt(fmax(eigen(order[j]), 0.0));
+      const double sg_max = sqrt(fmax(eigen(order[0]), 0.0));
       if (sg > 1e-7 * sg_max) {    // a mode at the level of fp32 rounding of the largest is a null mode of |Z|
         const double rs = sqrt(sg);
-        mq = w[i][order[j]] * rs;
-        ma = w[i][order[j]] / rs;
+        mq = lds[cur + (BB + i) * RS + order[j]] * rs;
+        ma = lds[cur + (BB + i) * RS + order[j]] / rs;
       }
     }
     MA[p] = ma;
@@ -655,7 +676,7 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);        // V1 = V, orthonormal
   // Rayleigh-Ritz on B = |Z| V
   const int npb = reduce(P, product(std::false_type(), std::false_type(), rows, cols, V1, 0), rows, Yb, nullptr, nullptr);
-  hipLaunchKernelGGL(ritz_kernel<BB>, dim3(1), dim3(kRitzThreads), 0, s, Gp, npb, l, MA, MQ, sigma);
+  hipLaunchKernelGGL(ritz_kernel<BB>, dim3(1), dim3(ritz_threads<BB>()), 0, s, Gp, npb, l, MA, MQ, sigma);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yb, rows, MA, l, A);
   hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, V1, cols, MQ, l, Q);
   return (int)hipGetLastError();
