@@ -345,6 +345,7 @@ int mdbf_forward(const mdbf_desc_t* desc, const void* SA_packed_dev, const void*
   make_stages(desc, SA_packed_dev, SB_packed_dev, env, X_dev, ldx, Y_dev, ldy, T, workspace_dev, sp);
   hipStream_t s = (hipStream_t)stream;
   if (wants_one(desc, T) && workspace_bytes >= layer_ws_bytes(desc, T) && stage_is_one(sp[0]) && stage_is_one(sp[1])) {
+    if (stage_is_pair(sp)) return hip_fail(launch_stage_pair(sp, s));
     // the second factor's workgroups add up the first factor's partial sums as they load them; its own, where it has few rows
     // and a long contraction, take a third launch
     const int64_t ld[2] = {(int64_t)align_up((size_t)desc->k, 64), (int64_t)align_up((size_t)desc->m, 64)};

@@ -144,6 +144,25 @@ struct EinBlock {
   uint32_t v[kLoads][ENV == MDBF_F32 ? kPer : 4];
 };
 
+// Rows of exactly four fp32 modes come a whole column of set 4 j + g per lane (VEC, below): a lane's entry t of the j-th such
+// vector is mode t of column m of set 4 j + g, and has to be mode g of set 4 j + t.  (As one mode per lane and load, sixteen bytes
+// apart, 128 loads of a compute unit took 2.6 us longer.)
+__device__ __forceinline__ void transpose_modes(uint32_t (&v)[8][1]) {
+#pragma unroll
+  for (int j = 0; j < 8; j += 4) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    // halves of the wave, then neighbouring sixteens: row r, group g of a 4 x 4 exchange places
+    const u32x2 a = __builtin_amdgcn_permlane32_swap(v[j][0], v[j + 2][0], false, false);
+    const u32x2 b = __builtin_amdgcn_permlane32_swap(v[j + 1][0], v[j + 3][0], false, false);
+    const u32x2 c = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+    const u32x2 d = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+    v[j][0] = c.x;
+    v[j + 1][0] = c.y;
+    v[j + 2][0] = d.x;
+    v[j + 3][0] = d.y;
+  }
+}
+
 // where the lane's modes of load i of block q begin
 template <int ENV, int M>
 __device__ __forceinline__ uint32_t ein_first(int K, uint32_t l, int q, int i, int lane) {
@@ -158,6 +177,17 @@ __device__ __forceinline__ uint32_t ein_first(int K, uint32_t l, int q, int i, i
 template <int ENV, int M, bool VEC>
 __device__ __forceinline__ void load_ein(const StageProb& p, int q, int lane, EinBlock<ENV, M>& e) {
   typedef EinBlock<ENV, M> EB;
+  if constexpr (ENV == MDBF_F32 && M == 4 && VEC) {
+    const int m = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = q * kBlockCols + 64 * j + 32 * (g >> 1) + 4 * (g & 1) + 8 * (m >> 2) + (m & 3);
+      const u32x4 v = at<u32x4>(p.Ein, (uint32_t)min(col, p.K - 1));
+#pragma unroll
+      for (int t = 0; t < 4; ++t) e.v[4 * j + t][0] = v[t];
+    }
+    return;
+  }
   const uint32_t l = VEC ? (uint32_t)M : (uint32_t)p.l;
   const uint32_t count = (uint32_t)p.K * l;
   constexpr int kWords = sizeof(e.v[0]) / 4;
@@ -242,7 +272,7 @@ struct EoutRow {
 };
 
 template <int ENV, int M, bool VEC>
-__device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row, int g) {
+__device__ __forceinline__ EoutRow<ENV, M> load_eout_bits(const StageProb& p, int row, int g) {
   EoutRow<ENV, M> o;
   constexpr int kN = EinBlock<ENV, M>::kPer;
   const uint32_t l = VEC ? (uint32_t)M : (uint32_t)p.l;
@@ -268,7 +298,13 @@ __device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row
       for (int t = 0; t < 4; ++t) o.v[t] = b[2 * t] | (b[2 * t + 1] << 16);
     }
   }
+  return o;
+}
+
+template <int ENV, int M>
+__device__ __forceinline__ void scale_eout(EoutRow<ENV, M>& o) {
   if constexpr (ENV != MDBF_F16) {
+    constexpr int kN = EinBlock<ENV, M>::kPer;
     // The products of two envelope entries of these types can leave the range of fp32 where entry times activation
     // does not: the row's largest entry goes below 1 / M, so that a sum of M products with entries of any size stays in
     // range (the smallest, 2^-126, keep 19 of their bits with M = 16); the power of two comes back with the result.
@@ -293,6 +329,12 @@ __device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row
         o.v[t] = (__builtin_bit_cast(uint32_t, v[2 * t]) >> 16) | (__builtin_bit_cast(uint32_t, v[2 * t + 1]) & 0xFFFF0000u);
     }
   }
+}
+
+template <int ENV, int M, bool VEC>
+__device__ __forceinline__ EoutRow<ENV, M> load_eout(const StageProb& p, int row, int g) {
+  EoutRow<ENV, M> o = load_eout_bits<ENV, M, VEC>(p, row, g);
+  scale_eout<ENV, M>(o);
   return o;
 }
 
@@ -310,6 +352,56 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One 16 x 128 piece: acc += its rows' sums over block q, the signs in `sw`, the activations in LDS at `buf`.
+template <int ENV, int M, bool VEC>
+__device__ __forceinline__ void contract_block(const StageProb& p, int q, int lane, EinBlock<ENV, M>& ein, uint32_t sw,
+                                               const EoutRow<ENV, M>& eo, const float* buf, float (&acc)[2]) {
+  typedef EinBlock<ENV, M> EB;
+  const int g = lane >> 4;
+  if constexpr (ENV == MDBF_F32 && M == 4 && VEC) transpose_modes(ein.v);
+  // (the block's last row may be read past the factor's end: fewer than sixteen elements lie behind its first)
+  if (!VEC && (int64_t)(p.K - (q + 1) * kBlockCols + 1) * p.l < 16) ein_tail<ENV, M>(p, q, lane, ein);
+  // the packed word keeps the signs of columns 2 t and 2 t + 1 of step f at bits c and c + 16, c = 8 (f / 2) + 4 (f % 2) + t:
+  // they are taken from the top of two registers, which double from entry to entry (a left shift by a constant takes the
+  // vector ALUs four cycles, an addition less)
+  uint32_t odd = sw, even = sw << 16;
+  auto flip = [](float v, uint32_t& signs) __attribute__((always_inline)) {
+    const uint32_t out = __builtin_bit_cast(uint32_t, v) ^ (signs & 0x80000000u);
+    asm("v_add_u32 %0, %0, %0" : "+v"(signs));
+    return __builtin_bit_cast(float, out);
+  };
+#pragma unroll
+  for (int f = 3; f >= 0; --f) {
+    const floatx4 xa = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g);
+    const floatx4 xb = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g + 4);
+    floatx4 d[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if constexpr (ENV == MDBF_F32) {
+        d[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < EB::kPer; ++s)
+          d[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, ein.v[2 * f + h][s]),
+                                                      __builtin_bit_cast(float, eo.v[s]), d[h], 0, 0, 0);
+      } else {
+        const bool on = M == 8 ? g == 2 * (f & 1) + h : (g >> 1) == h;
+        const uint32_t (&x)[4] = ein.v[M == 8 ? f >> 1 : f];
+        d[h] = rebuild16<ENV>(u32x4{x[0], x[1], x[2], x[3]},
+                              u32x4{on ? eo.v[0] : 0u, on ? eo.v[1] : 0u, on ? eo.v[2] : 0u, on ? eo.v[3] : 0u});
+      }
+    }
+#pragma unroll
+    for (int t = 3; t >= 0; --t) {
+      const floatx4 e = d[t >> 1], x = t < 2 ? xa : xb;
+      acc[0] = fmaf(flip(e[2 * (t & 1)], even), x[2 * (t & 1)], acc[0]);
+      acc[1] = fmaf(flip(e[2 * (t & 1) + 1], odd), x[2 * (t & 1) + 1], acc[1]);
+    }
+    // (a step at a time: without this the products of a block are all made first, in 64 registers)
+    asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 template <int ENV, int M, bool VEC, bool PARTS, bool BATCH>
@@ -381,50 +473,6 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
   };
   float acc[2] = {0.f, 0.f};
   EoutRow<ENV, M> eo;
-  auto contract = [&](int q, Block& b, const float* buf) __attribute__((always_inline)) {
-    // (the block's last row may be read past the factor's end: fewer than sixteen elements lie behind its first)
-    if (!VEC && (int64_t)(p.K - (q + 1) * kBlockCols + 1) * p.l < 16) ein_tail<ENV, M>(p, q, lane, b.ein);
-    // the packed word keeps the signs of columns 2 t and 2 t + 1 of step f at bits c and c + 16, c = 8 (f / 2) + 4 (f % 2) + t:
-    // they are taken from the top of two registers, which double from entry to entry (a left shift by a constant takes the
-    // vector ALUs four cycles, an addition less)
-    uint32_t odd = b.sw, even = b.sw << 16;
-    auto flip = [](float v, uint32_t& signs) __attribute__((always_inline)) {
-      const uint32_t out = __builtin_bit_cast(uint32_t, v) ^ (signs & 0x80000000u);
-      asm("v_add_u32 %0, %0, %0" : "+v"(signs));
-      return __builtin_bit_cast(float, out);
-    };
-#pragma unroll
-    for (int f = 3; f >= 0; --f) {
-      const floatx4 xa = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g);
-      const floatx4 xb = *reinterpret_cast<const floatx4*>(buf + 32 * f + 8 * g + 4);
-      floatx4 d[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if constexpr (ENV == MDBF_F32) {
-          d[h] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int s = 0; s < EB::kPer; ++s)
-            d[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, b.ein.v[2 * f + h][s]),
-                                                        __builtin_bit_cast(float, eo.v[s]), d[h], 0, 0, 0);
-        } else {
-          const bool on = M == 8 ? g == 2 * (f & 1) + h : (g >> 1) == h;
-          const uint32_t (&x)[4] = b.ein.v[M == 8 ? f >> 1 : f];
-          d[h] = rebuild16<ENV>(u32x4{x[0], x[1], x[2], x[3]},
-                                u32x4{on ? eo.v[0] : 0u, on ? eo.v[1] : 0u, on ? eo.v[2] : 0u, on ? eo.v[3] : 0u});
-        }
-      }
-#pragma unroll
-      for (int t = 3; t >= 0; --t) {
-        const floatx4 e = d[t >> 1], x = t < 2 ? xa : xb;
-        acc[0] = fmaf(flip(e[2 * (t & 1)], even), x[2 * (t & 1)], acc[0]);
-        acc[1] = fmaf(flip(e[2 * (t & 1) + 1], odd), x[2 * (t & 1) + 1], acc[1]);
-      }
-      // (a step at a time: without this the products of a block are all made first, in 64 registers)
-      asm volatile("" : "+v"(acc[0]), "+v"(acc[1]));
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
   eo.e = 0;
   if (q_lo < q_hi) {
     Block b0, b1;
@@ -434,12 +482,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
     int q = q_lo;
     for (;;) {
       if (q + nwaves < q_hi) fetch(q + nwaves, b1);
-      contract(q, b0, xs);
+      contract_block<ENV, M, VEC>(p, q, lane, b0.ein, b0.sw, eo, xs, acc);
       q += nwaves;
       if (q >= q_hi) break;
       park(q, b1, xs + kBlockCols);
       if (q + nwaves < q_hi) fetch(q + nwaves, b0);
-      contract(q, b1, xs + kBlockCols);
+      contract_block<ENV, M, VEC>(p, q, lane, b1.ein, b1.sw, eo, xs + kBlockCols, acc);
       q += nwaves;
       if (q >= q_hi) break;
       park(q, b0, xs);
@@ -463,6 +511,121 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
       else ((MDBF_GLOBAL float*)a.part_out)[split * a.part_out_ld + row] = sum;
     }
   }
+}
+
+// ---- Both factors of a small layer in one launch.  Every workgroup works out all of z = V x for itself, in LDS, piece (16 x 128)
+// by piece, and then row tiles of its own of U z.  What bounds a call of two launches on such a layer is the launches: 2.7 us each
+// on the host.  On the device the second one saved pays for the pieces as long as they are few: pair_pieces.
+// us per call, two launches -> one, from a graph and one after the other: 256 x 256, k = 128 (16 pieces), l = 4 in fp32
+// 5.5 -> 4.7 and 10.1 -> 7.0; l = 16 in fp16 4.7 -> 4.1 and 10.2 -> 7.2; 300 x 384, k = 128 (24) 4.8 -> 4.9 and 10.2 -> 7.2.
+constexpr int kPairPieces = 24;
+constexpr int kPairWaves = 8;       // (sixteen, a piece each: no faster, and the element-wise rows spill)
+
+struct PairArgs {
+  StageProb p, u;
+};
+
+template <int ENV, int M, bool VEC>
+__global__ __launch_bounds__(64 * kPairWaves) void stage_pair_kernel(PairArgs a) {
+  // the pieces' sums (of the first factor, then of the waves), z, the waves' activations
+  __shared__ float red[kPairPieces * kTileRows];
+  __shared__ __attribute__((aligned(16))) float z[(kPairPieces * kTileRows + kBlockCols - 1) / kBlockCols * kBlockCols];
+  __shared__ __attribute__((aligned(16))) float xs[kPairWaves][kBlockCols];
+  const StageProb &p = a.p, &u = a.u;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, g = lane >> 4;
+  struct Piece {
+    EinBlock<ENV, M> ein;
+    EoutRow<ENV, M> eo;
+    uint32_t sw, x[2];
+  };
+  auto fetch = [&](const StageProb& s, int tile, int q, Piece& b) __attribute__((always_inline)) {
+    load_ein<ENV, M, VEC>(s, q, lane, b.ein);
+    b.sw = ((const MDBF_GLOBAL uint32_t*)s.S)[word_offset(tile, q, lane, s.KB, s.ntiles)];
+    b.eo = load_eout_bits<ENV, M, VEC>(s, min(tile * kTileRows + r16, s.rows - 1), g);
+  };
+  // a piece's sums, a row on each of the first sixteen lanes
+  auto contract = [&](const StageProb& s, int q, Piece& b, const float* x, float* out) __attribute__((always_inline)) {
+    float acc[2] = {0.f, 0.f};
+    scale_eout<ENV, M>(b.eo);
+    contract_block<ENV, M, VEC>(s, q, lane, b.ein, b.sw, b.eo, x, acc);
+    float v = acc[0] + acc[1];
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if constexpr (ENV != MDBF_F16) v = ldexpf(v, b.eo.e);
+    if (lane < kTileRows) out[lane] = v;
+  };
+  // ---- the first factor: piece i is block i % KB of tile i / KB
+  const int pieces = p.ntiles * p.KB;
+  const uint32_t xshift = p.vin_dt == MDBF_F32 ? 2u : 1u;
+  auto fetch1 = [&](int i, Piece& b) __attribute__((always_inline)) {
+    const int q = i % p.KB;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)                                        // (the aligned word that holds it)
+      b.x[h] = at<uint32_t>(p.vin, ((uint32_t)min(q * kBlockCols + lane + 64 * h, p.K - 1) << xshift) >> 2);
+    fetch(p, i / p.KB, q, b);
+  };
+  Piece now, next;
+  if (wave < pieces) fetch1(wave, now);
+#pragma unroll 1
+  for (int i = wave; i < pieces; i += kPairWaves) {
+    if (i + kPairWaves < pieces) fetch1(i + kPairWaves, next);
+    const int q = i % p.KB;
+    wave_lds_order();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int col = q * kBlockCols + lane + 64 * h;
+      const uint32_t half = (min(col, p.K - 1) & 1) ? now.x[h] >> 16 : now.x[h] & 0xFFFFu;
+      const float xh = (float)__builtin_bit_cast(_Float16, (uint16_t)half);
+      const float x = p.vin_dt == MDBF_F32 ? __builtin_bit_cast(float, now.x[h]) : p.vin_dt == MDBF_F16 ? xh : __builtin_bit_cast(float, half << 16);
+      xs[wave][lane + 64 * h] = col < p.K ? x : 0.f;
+    }
+    wave_lds_order();
+    contract(p, q, now, xs[wave], red + i * kTileRows);
+    now = next;
+  }
+  // ---- the second one: the waves' slots of a tile each, a block on each of a slot's waves (there are at most three)
+  const int slots = kPairWaves / u.KB, slot = wave / u.KB, q2 = wave - slot * u.KB;
+  const int tile = (int)blockIdx.x + (int)gridDim.x * slot;
+  const bool live = slot < slots && tile < u.ntiles;                   // (uniform in a wave)
+  if (live) fetch(u, tile, q2, now);
+  __syncthreads();
+  for (int r = tid; r < u.KB * kBlockCols; r += 64 * kPairWaves) {     // (zeros past the last row)
+    float sum = 0.f;
+    if (r < p.rows) {
+      const float* part = red + (r >> 4) * p.KB * kTileRows + (r & 15);
+      sum = part[0];
+      for (int q = 1; q < p.KB; ++q) sum += part[q * kTileRows];
+    }
+    z[r] = sum;
+  }
+  __syncthreads();
+  if (live) contract(u, q2, now, z + q2 * kBlockCols, red + wave * kTileRows);
+  __syncthreads();
+  if (live && q2 == 0 && lane < kTileRows) {
+    float sum = red[wave * kTileRows + lane];
+    for (int q = 1; q < u.KB; ++q) sum += red[(wave + q) * kTileRows + lane];
+    const int row = tile * kTileRows + lane;
+    if (row < u.rows) emit_result(u.out, row, u.out_dt, sum, u.flags);
+  }
+}
+
+template <int ENV, int M>
+static int launch_pair_em(const PairArgs& a, int grid, hipStream_t s) {
+  if (ENV != MDBF_BF16 && a.p.l == M)
+    hipLaunchKernelGGL((stage_pair_kernel<ENV, M, ENV != MDBF_BF16>), dim3((unsigned)grid), dim3(64 * kPairWaves), 0, s, a);
+  else
+    hipLaunchKernelGGL((stage_pair_kernel<ENV, M, false>), dim3((unsigned)grid), dim3(64 * kPairWaves), 0, s, a);
+  return (int)hipGetLastError();
+}
+template <int ENV>
+static int launch_pair_e(const PairArgs& a, int grid, hipStream_t s) {
+  if constexpr (ENV == MDBF_F32) {
+    if (a.p.l <= 4) return launch_pair_em<ENV, 4>(a, grid, s);
+  }
+  if (a.p.l <= 8) return launch_pair_em<ENV, 8>(a, grid, s);
+  return launch_pair_em<ENV, 16>(a, grid, s);
 }
 
 template <int ENV, int M, bool VEC>
@@ -549,6 +712,34 @@ bool stage_is_one(const StageProb& p) {
   const int64_t row = (int64_t)p.l * dtype_size(p.env_dt), most = (int64_t)1 << 32;
   return p.K < (1 << 30) && p.rows < (1 << 30) && p.K * row < most && p.rows * row < most &&
          (p.T == 1 || p.vin_ld < ((int64_t)1 << 30) / p.T);
+}
+
+// Pieces of the first factor that one launch may go through in every workgroup: as many as cost no more than the launch does on
+// the device (the host saves its 2.7 us in any case).  us per call from a graph, two launches and one: rank 16 and 8 in fp16,
+// 24 pieces, 4.9 and 4.9, 5.35 and 5.37 (688 row tiles); fp32 rank 4, 20, 5.6 and 5.3, 24, 5.7 and 5.9; rank 8, 12, 5.5 and 5.1, 16,
+// 5.5 and 5.8; other rows, loaded entry by entry or of 16 fp32 modes, 8: 5.7 and 4.8, with 10 to 16 5.8 and 6.5, 5.5 and 6.1.
+// And one round of workgroups: 688 row tiles on 344 of them (k = 384) 5.4 and 7.5.
+static int pair_pieces(const StageProb& p) {
+  if (p.env_dt == MDBF_F16 && (p.l == 16 || p.l == 8)) return one::kPairPieces;
+  if (p.env_dt == MDBF_F32 && p.l == 4) return 20;
+  return p.env_dt == MDBF_F32 && p.l == 8 ? 12 : 8;
+}
+// a workgroup for each row tile up to 256 of them, then one for as many as its waves take at once
+static int pair_grid(const StageProb& u) {
+  const int slots = one::kPairWaves / u.KB;
+  return std::max(std::min(u.ntiles, 256), (u.ntiles + slots - 1) / slots);
+}
+
+bool stage_is_pair(const StageProb sp[2]) {
+  return (int64_t)sp[0].ntiles * sp[0].KB <= pair_pieces(sp[0]) && pair_grid(sp[1]) <= 256 && stage_is_one(sp[0]) && stage_is_one(sp[1]);
+}
+
+int launch_stage_pair(const StageProb sp[2], hipStream_t s) {
+  const one::PairArgs a = {sp[0], sp[1]};
+  const int grid = pair_grid(sp[1]);
+  if (sp[0].env_dt == MDBF_F16) return one::launch_pair_e<MDBF_F16>(a, grid, s);
+  if (sp[0].env_dt == MDBF_BF16) return one::launch_pair_e<MDBF_BF16>(a, grid, s);
+  return one::launch_pair_e<MDBF_F32>(a, grid, s);
 }
 
 int one_item_tiles() { return one::kOneItemTiles; }

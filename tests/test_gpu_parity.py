@@ -990,6 +990,35 @@ def test_small_plans_of_rank_16_with_an_infinite_envelope_entry(gpu, k):
     assert torch.equal(torch.cat((got[:5], got[6:])), torch.cat((clean[:5], clean[6:])))
 
 
+PAIR_EDGES = [
+    # m, n, k, l, env, x: as many pieces of the first factor (16 x 128) as one launch takes of each kind of rows, and more; one,
+    # two and three blocks of the second one, its last row tile on a second slot; sizes that are no multiples of anything
+    (256, 256, 128, 4, "f32", "f32"), (33, 640, 64, 4, "f32", "bf16"), (33, 641, 64, 4, "f32", "f32"), (47, 383, 61, 8, "f32", "f16"),
+    (300, 384, 128, 16, "f16", "f16"), (300, 385, 128, 16, "f16", "f16"), (520, 127, 384, 16, "f16", "f32"), (4099, 101, 383, 8, "f16", "bf16"),
+    (8190, 101, 383, 8, "f16", "f16"), (50, 255, 63, 3, "f16", "f16"), (50, 129, 64, 16, "bf16", "bf16"), (17, 1000, 15, 11, "f32", "f32"),
+    (1, 1, 1, 1, "f16", "f16"), (4, 4, 4, 4, "f32", "f32"), (19, 5, 130, 4, "f32", "f32"), (70, 1030, 520, 4, "f32", "f32"),
+]
+
+
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", PAIR_EDGES)
+def test_small_one_token_calls(gpu, m, n, k, l, env_dtype, x_dtype):
+    """Both factors in one launch, z in LDS, and layers just too large for it: the gate of the fp32 path; a second call adds;
+    an infinity in one row of the last envelope stays in that row's output; the scratch array's entry point has the same bits."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    X = synth.make_activations(n, 1, seed=9 + m, x_dtype=x_dtype)
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, x_dtype)
+    got = mb.mdbf_forward(_between_nans(torch, dl), Xd, y_dtype="f32")
+    assert orc.max_rel_error(got.cpu().numpy(), ref) <= 2e-5
+    assert torch.equal(mb.mdbf_forward(dl, Xd, y_dtype="f32", Y=got.clone(), accumulate=True), got + got)
+    out = torch.zeros((1, m), dtype=torch.float32, device="cuda:0")
+    assert torch.equal(mb.mdbf_forward_static(dl, Xd, out), got)
+    dl.A[m - 1, l - 1] = float("inf")
+    again = mb.mdbf_forward(dl, Xd, y_dtype="f32")
+    assert not torch.isfinite(again[0, m - 1]) and torch.equal(again[0, :m - 1], got[0, :m - 1])
+
+
 ONE_PLANS = [
     # specs (m, n, k, l), envelopes, activations, tokens: ranks of every class and mixed ones, odd row pitches, contractions of
     # one block and of more than one per wave, row tiles that do not fill the last item
