@@ -146,9 +146,9 @@ def _stream_ptr(stream=None):
     """The stream's handle; None: the current stream of the current device.  (Its handle is asked for directly: the
     Stream object around it takes 2.7 us to make, a quarter of the host time of a call of two launches.)"""
     if stream is not None:
-        return C.c_void_p(stream.cuda_stream)
-    torch = _torch()
-    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        return stream.cuda_stream
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _torch_dtype(name):
@@ -226,8 +226,10 @@ class DeviceLayer:
         return DeviceLayer(self.m, self.n, self.k, l_to, self.SA_packed, self.SB_packed, *env)
 
     def desc(self, x_dtype, y_dtype, precise=False, block_scaled=False, accumulate=False, fp16_staged=False):
-        flags = ((MDBF_FLAG_PRECISE if precise else 0) | (MDBF_FLAG_BLOCK_SCALED if block_scaled else 0) |
-                 (MDBF_FLAG_ACCUMULATE if accumulate else 0) | (MDBF_FLAG_FP16_STAGED if fp16_staged else 0))
+        flags = 0
+        if precise or block_scaled or accumulate or fp16_staged:
+            flags = ((MDBF_FLAG_PRECISE if precise else 0) | (MDBF_FLAG_BLOCK_SCALED if block_scaled else 0) |
+                     (MDBF_FLAG_ACCUMULATE if accumulate else 0) | (MDBF_FLAG_FP16_STAGED if fp16_staged else 0))
         return Desc(self.m, self.n, self.k, self.l, DTYPE_CODE[x_dtype], DTYPE_CODE[self.env_dtype],
                     DTYPE_CODE[y_dtype], flags)
 
@@ -244,19 +246,22 @@ def mdbf_workspace_bytes(desc, T):
 def mdbf_forward(layer, X, y_dtype="f32", precise=False, Y=None, workspace=None, stream=None, block_scaled=False,
                  accumulate=False, fp16_staged=False):
     """Y[b,:] = What X[b,:].  X: CUDA tensor (T, n) of f16/bf16/f32; returns Y (T, m) of y_dtype."""
+    # (a call of one or two launches takes the host as long as the device or longer: attributes are asked for once)
     torch = _torch()
-    assert X.is_cuda and X.dim() == 2 and X.shape[1] == layer.n and X.stride(1) == 1
-    T = X.shape[0]
-    d = layer.desc(_dtype_name(X), y_dtype, precise, block_scaled, accumulate, fp16_staged)
+    assert X.is_cuda and X.dim() == 2
+    T, n = X.shape
+    ldx, sx = X.stride()
+    assert n == layer.n and sx == 1
+    d = layer.desc(_DTYPE_NAME[X.dtype], y_dtype, precise, block_scaled, accumulate, fp16_staged)
     assert not (accumulate and Y is None), "accumulate needs the Y to add to"
     if Y is None:
         Y = torch.empty((T, layer.m), dtype=_torch_dtype(y_dtype), device=X.device)
     if workspace is None:
         workspace = torch.empty(mdbf_workspace_bytes(d, T), dtype=torch.uint8, device=X.device)
-    env = layer.env()
-    _check(lib().mdbf_forward(C.byref(d), layer.SA_packed.data_ptr(), layer.SB_packed.data_ptr(), C.byref(env),
-                              X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), T, workspace.data_ptr(),
-                              workspace.numel(), _stream_ptr(stream)), "mdbf_forward")
+    status = (_lib or lib()).mdbf_forward(d, layer.SA_packed.data_ptr(), layer.SB_packed.data_ptr(), layer.env(), X.data_ptr(), ldx,
+                                          Y.data_ptr(), Y.stride(0), T, workspace.data_ptr(), workspace.numel(), _stream_ptr(stream))
+    if status:
+        _check(status, "mdbf_forward")
     return Y
 
 
