@@ -36,6 +36,18 @@ constexpr int kSmallThreads = 1024;   // the b x b kernels (a thread per matrix 
                                       // (few workgroups: many loads in flight in each)
 constexpr int kGramRows = 64;         // rows per workgroup of the reduce + Gram kernel
 
+// the signs of the first `count` (at most four) entries
+__device__ __forceinline__ void store_signs(floatx4 v, MDBF_GLOBAL int8_t* out, int count) {
+  if (count == 4) {
+    *(MDBF_GLOBAL u32_any*)out = (v.x < 0.f ? 0xFFu : 1u) | (v.y < 0.f ? 0xFF00u : 0x100u) |
+                                 (v.z < 0.f ? 0xFF0000u : 0x10000u) | (v.w < 0.f ? 0xFF000000u : 0x1000000u);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (e < count) out[e] = v[e] < 0.f ? (int8_t)-1 : (int8_t)1;
+  }
+}
+
 // ---- S = sign(Z) as int8 (+1 / -1, sign(0) = +1: Sec. 2, Notation), four entries per thread, 2^sh threads per row
 // (a workgroup takes several rows of a narrow matrix: with one each 10^6 x 24 took 0.5 ms); clears the counter of
 // reduce_gram_kernel's launches
@@ -47,13 +59,13 @@ __global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict_
   if (row >= rows || c >= cols) return;
   const MDBF_GLOBAL float* z = (const MDBF_GLOBAL float*)Z + row * ld + c;
   MDBF_GLOBAL int8_t* out = (MDBF_GLOBAL int8_t*)S + row * cols + c;
+  floatx4 v = {0.f, 0.f, 0.f, 0.f};
   if (c + 4 <= cols) {
-    const floatx4 v = *(const MDBF_GLOBAL floatx4_any*)z;
-    *(MDBF_GLOBAL u32_any*)out = (v.x < 0.f ? 0xFFu : 1u) | (v.y < 0.f ? 0xFF00u : 0x100u) |
-                                 (v.z < 0.f ? 0xFF0000u : 0x10000u) | (v.w < 0.f ? 0xFF000000u : 0x1000000u);
+    v = *(const MDBF_GLOBAL floatx4_any*)z;
   } else {
-    for (int e = 0; c + e < cols; ++e) out[e] = z[e] < 0.f ? (int8_t)-1 : (int8_t)1;
+    for (int e = 0; c + e < cols; ++e) v[e] = z[e];
   }
+  store_signs(v, out, min(4, cols - c));
 }
 
 // G = sum of the workgroups' parts, in fp64, in a fixed order: a thread adds four neighbouring entries of every
@@ -204,7 +216,8 @@ template <int BB, bool COLS, bool SCALED>
 __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
                                                               const float* __restrict__ X, const float* __restrict__ Gp,
                                                               int nparts, double* __restrict__ Tm, float* __restrict__ Tf,
-                                                              float* __restrict__ P) {
+                                                              float* __restrict__ P, int8_t* __restrict__ S,
+                                                              uint32_t* __restrict__ counter) {
   constexpr int NT = (BB + 15) / 16;                   // 16-column tiles of X' (the last may be partly past BB)
   constexpr int RS = BB + 1;                           // floats per output in the waves' sums
   constexpr int kXs = 4 * (64 * BB + 16), kRed = 4 * kOut * RS;
@@ -220,6 +233,7 @@ __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __res
       return;
     }
   }
+  if (!COLS && counter && blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
@@ -302,6 +316,13 @@ __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __res
 #pragma unroll
     for (int i = 0; i < 4; ++i) z[i] = zn[i];
     if (j < 3) load(j + 1, zn);
+    if (COLS && SCALED && S) {                         // (uniform) the signs of what is here anyway
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = qw + 16 * j + 4 * i + g, c = o0 + 4 * n;
+        if (r < rows) store_signs(z[i], (MDBF_GLOBAL int8_t*)S + (int64_t)r * cols + c, min(4, cols - c));
+      }
+    }
     const float* xw = xs + (16 * j + (COLS ? g : 4 * g)) * BB + n;
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
@@ -584,22 +605,28 @@ __global__ __launch_bounds__(ritz_threads<BB>()) void ritz_kernel(const float* _
   }
 }
 
-// ---- Out (n x lo) = Y (n x BB) . Mm (BB x BB, its first lo columns), fp64 accumulation
+// ---- out (n x lo) = Y (n x BB) . m (BB x BB, its first lo columns), fp64 accumulation; blockIdx.y = 1: the second one
+struct Applied {
+  const float* Y;
+  const double* m;
+  float* out;
+  int n, lo;
+};
 template <int BB>
-__global__ __launch_bounds__(kThreads) void apply_kernel(const float* __restrict__ Y, int n, const double* __restrict__ Mm,
-                                                         int lo, float* __restrict__ Out) {
+__global__ __launch_bounds__(kThreads) void apply_kernel(Applied first, Applied second) {
   __shared__ double ms[BB * BB];
-  for (int p = threadIdx.x; p < BB * BB; p += kThreads) ms[p] = Mm[p];
+  const Applied a = blockIdx.y ? second : first;
+  for (int p = threadIdx.x; p < BB * BB; p += kThreads) ms[p] = a.m[p];
   __syncthreads();
-  const size_t total = (size_t)n * lo;
+  const size_t total = (size_t)a.n * a.lo;
   for (size_t e = (size_t)blockIdx.x * kThreads + threadIdx.x; e < total; e += (size_t)gridDim.x * kThreads) {
-    const size_t r = e / lo;
-    const int j = (int)(e - r * lo);
-    const float* yr = Y + r * BB;
+    const size_t r = e / a.lo;
+    const int j = (int)(e - r * a.lo);
+    const float* yr = a.Y + r * BB;
     double s = 0.0;
 #pragma unroll
     for (int i = 0; i < BB; ++i) s += (double)yr[i] * ms[i * BB + j];
-    Out[e] = (float)s;
+    a.out[e] = (float)s;
   }
 }
 
@@ -622,22 +649,25 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
   double* MQ = (double*)(ws + L.mq);
   uint32_t* ctr = (uint32_t*)(ws + L.ctr);
   const dim3 blk(kThreads);
-  int sh = 0;
-  while ((4 << sh) < cols && (1 << sh) < kThreads) ++sh;
-  const int rows_per_wg = kThreads >> sh;
-  hipLaunchKernelGGL(sign_kernel, dim3((rows + rows_per_wg - 1) / rows_per_wg, (cols + (4 << sh) - 1) / (4 << sh)), blk, 0, s,
-                     Z, rows, cols, ld, sh, S, ctr);
+  // (with passes, the first product along the columns writes the signs, and the first one of all clears the counter)
+  if (iters == 0) {
+    int sh = 0;
+    while ((4 << sh) < cols && (1 << sh) < kThreads) ++sh;
+    const int rows_per_wg = kThreads >> sh;
+    hipLaunchKernelGGL(sign_kernel, dim3((rows + rows_per_wg - 1) / rows_per_wg, (cols + (4 << sh) - 1) / (4 << sh)), blk, 0, s,
+                       Z, rows, cols, ld, sh, S, ctr);
+  }
   // Y = Yin's sums (nchunks of them), times T, its Gram parts and (Tout) the inverse of its Cholesky factor
   auto reduce = [&](const float* Yin, int nchunks, int n, float* Y, const double* T, double* Tout) {
     const int nparts = (n + kGramRows - 1) / kGramRows;
     hipLaunchKernelGGL(reduce_gram_kernel<BB>, dim3(nparts), dim3(kSmallThreads), 0, s, Yin, nchunks, n, Y, Gp, T, Tout, Tf, ctr);
     return nparts;
   };
-  auto product = [&](auto cols_side, auto is_scaled, int nout, int nin, const float* X, int nparts) {
+  auto product = [&](auto cols_side, auto is_scaled, int nout, int nin, const float* X, int nparts, int step) {
     const int nchunks = (nin + kChunk - 1) / kChunk;
     const int64_t units = (int64_t)((nout + kOut - 1) / kOut) * nchunks + (nparts > 0 ? 1 : 0);
     hipLaunchKernelGGL((abs_mul_kernel<BB, decltype(cols_side)::value, decltype(is_scaled)::value>), dim3((unsigned)units), blk,
-                       0, s, Z, rows, cols, ld, X, Gp, nparts, Tm, Tf, P);
+                       0, s, Z, rows, cols, ld, X, Gp, nparts, Tm, Tf, P, step == 1 ? S : nullptr, step == 0 ? ctr : nullptr);
     return nchunks;
   };
   // Step 2 i of the iteration is B = |Z| V of pass i, step 2 i + 1 V = |Z|^T B.  X is not orthonormal: T = R^(-1) of X^T X = R^T R
@@ -657,9 +687,9 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
     const int nout = kCols ? cols : rows, nin = kCols ? rows : cols;
     int nchunks;
     if (step == 0 || behind(step))
-      nchunks = product(cols_side, std::false_type(), nout, nin, X, step == 0 ? 0 : kCols ? row_parts : col_parts);
+      nchunks = product(cols_side, std::false_type(), nout, nin, X, step == 0 ? 0 : kCols ? row_parts : col_parts, step);
     else
-      nchunks = product(cols_side, std::true_type(), nout, nin, X, 0);
+      nchunks = product(cols_side, std::true_type(), nout, nin, X, 0, step);
     return reduce(P, nchunks, nout, kCols ? Yc : Yb, behind(step) ? Tm : nullptr, last || !behind(step + 1) ? Tm : nullptr);
   };
   const float* X = X0;
@@ -671,14 +701,14 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
   // an orthonormal V: Cholesky-QR twice (iters == 0: on the start block itself)
   const int grid_apply = 1024;
   if (iters == 0) reduce(X0, 1, cols, Yc, nullptr, Tm);
-  hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);
-  reduce(V1, 1, cols, Yc, nullptr, Tm);                                                              // (Yc = copy of V1)
-  hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yc, cols, Tm, BB, V1);        // V1 = V, orthonormal
+  reduce(Yc, 1, cols, V1, Tm, Tm);
+  const Applied v = {V1, Tm, Yc, cols, BB}, none = {V1, Tm, Yc, 0, BB};
+  hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, v, none);                     // Yc = V, orthonormal
   // Rayleigh-Ritz on B = |Z| V
-  const int npb = reduce(P, product(std::false_type(), std::false_type(), rows, cols, V1, 0), rows, Yb, nullptr, nullptr);
+  const int npb = reduce(P, product(std::false_type(), std::false_type(), rows, cols, Yc, 0, -1), rows, Yb, nullptr, nullptr);
   hipLaunchKernelGGL(ritz_kernel<BB>, dim3(1), dim3(ritz_threads<BB>()), 0, s, Gp, npb, l, MA, MQ, sigma);
-  hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, Yb, rows, MA, l, A);
-  hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply), blk, 0, s, V1, cols, MQ, l, Q);
+  const Applied a = {Yb, MA, A, rows, l}, q = {Yc, MQ, Q, cols, l};
+  hipLaunchKernelGGL(apply_kernel<BB>, dim3(grid_apply, 2), blk, 0, s, a, q);
   return (int)hipGetLastError();
 }
 

@@ -71,6 +71,7 @@ def test_later_passes_normalise_behind_the_product(gpu, rows, cols, l, iters):
     same iteration in fp64: Ritz values and envelope are those of the same subspace, whatever basis is taken on the way."""
     Z = _f32(np.random.default_rng(rows + cols).standard_normal((rows, cols)))
     S, A, Q, sg = _run(gpu, Z, l, iters=iters)
+    np.testing.assert_array_equal(S, qz.sign_pm1(Z))
     M, V = np.abs(Z), synth.normal_block(cols, 16 if l <= 8 else 24, 1).astype(np.float64)
     for _ in range(iters):
         V = M.T @ np.linalg.qr(M @ V)[0]
