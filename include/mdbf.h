@@ -140,7 +140,7 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
  *   workspace_dev / workspace_bytes  caller-owned scratch, >= mdbf_workspace_bytes()
  * Default arithmetic: fp32 accumulation on the matrix cores; z kept in fp32 with one token.  A single one-token call
  * rebuilds the factors S_A o (A Q^T), S_B o (G B^T) piece by piece in fp32 and applies them to the unrounded activations
- * in fp32, in two launches (three where the second factor has few rows and a long contraction): what remains is the
+ * in fp32, in two launches (one for small layers, three where the second factor has few rows and a long contraction): what remains is the
  * rounding of fp32 sums, added in a fixed order, so repeated calls return the same bits.  Plans with one to three tokens do the same if their layers are of other ranks than 16, of mixed ones or
  * not of fp16 envelopes, unless they are large and the block-scaled variant serves them.  The other plans quantise the
  * l-way scaled activations (b^(s) o x and q^(t) o z) once --

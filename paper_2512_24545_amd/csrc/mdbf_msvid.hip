@@ -50,7 +50,8 @@ __device__ __forceinline__ void store_signs(floatx4 v, MDBF_GLOBAL int8_t* out, 
 
 // ---- S = sign(Z) as int8 (+1 / -1, sign(0) = +1: Sec. 2, Notation), four entries per thread, 2^sh threads per row
 // (a workgroup takes several rows of a narrow matrix: with one each 10^6 x 24 took 0.5 ms); clears the counter of
-// reduce_gram_kernel's launches
+// reduce_gram_kernel's launches.  For calls without passes: in others the first product along the columns, which has the
+// entries in registers, writes the signs (9.4 us for a pass of its own over 4096 x 2656, 2 us more for that product)
 __global__ __launch_bounds__(kThreads) void sign_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld, int sh,
                                                         int8_t* __restrict__ S, uint32_t* __restrict__ counter) {
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *counter = 0u;
@@ -211,7 +212,7 @@ __device__ __forceinline__ void cholesky_inverse(const double (&G)[BB][BB], doub
 // What bounds it: 9 us for one read of Z beside 6 us of matrix-core work and 9 us of launch, staging and partial
 // sums, which only partly overlap.  (All of a wave's sixteen loads in flight: no change; X as single elements in
 // operand order: 8 us more.)  Lanes that own columns and fused multiply-adds took 24 us per product of 4096 x 2656 and b = 24, and a transposed
-// copy of Z for |Z| X another 20 us per call; now 18 to 20 us.
+// copy of Z for |Z| X another 20 us per call; now 17 to 20 us SCALED, 15.5 to 18.5 us not.
 template <int BB, bool COLS, bool SCALED>
 __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
                                                               const float* __restrict__ X, const float* __restrict__ Gp,

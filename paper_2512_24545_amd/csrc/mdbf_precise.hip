@@ -92,7 +92,7 @@ int launch_stage_precise(const StageProb* probs_dev, const WorkItem* items_dev, 
 // idle for long (one_geom_summed).
 // Against building block-scaled records of the scaled activations in every workgroup and adding partial sums of both
 // factors in memory, per call of one layer again and again from a graph: 4096 x 4096, k = 2656, l = 16 13.1 -> 8.4 us (10.6
-// with layers that come from memory); 256 x 256, k = 128, l = 4 in fp32 9.7 -> 5.5; 11008 x 4096, k = 4096, l = 16 20.1 ->
+// with layers that come from memory); 256 x 256, k = 128, l = 4 in fp32 9.7 -> 5.5 (in one launch 4.7, stage_pair_kernel); 11008 x 4096, k = 4096, l = 16 20.1 ->
 // 12.8; two calls of 4096 x 4096, k = 1601, l = 1 25.9 -> 17.9; 3000 x 5000, k = 1777, l = 16 in fp32 19.6 -> 13.5; an empty
 // pair of launches is 3 us.  Errors against 64 bits 6e-6 .. 2e-4 -> 2e-7.  Not faster: 1024 x 4096, k = 11008 (second factor
 // of 64 row tiles), bf16 rank 16 37.8 -> 40.2, fp32 rank 5 24.5 -> 25.9.
