@@ -401,6 +401,21 @@ def test_a_token_of_a_short_call_does_not_depend_on_its_length(gpu, m, n, k, l, 
             assert torch.equal(mb.mdbf_forward(dl, X[:T], y_dtype="f32"), full[:T]), T
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", [(300, 649, 1515, 12, "f32", "f32"), (530, 1027, 300, 3, "bf16", "bf16"), (65, 7, 130, 16, "f16", "f16")])
+def test_short_calls_of_any_number_of_slabs(gpu, m, n, k, l, env_dtype, x_dtype):
+    """17 to 64 tokens in two, three and four slabs of sixteen, the last one full and with a single token: the bits of 64
+    tokens, which meet the oracle at the fp16 gate; rows apart by one element more than they have."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n, env_dtype=env_dtype, env_kind="unit", signed_env=True)
+    dl, X = mb.DeviceLayer.from_host(L), synth.make_activations(n, 64, seed=5, x_dtype=x_dtype)
+    wide = torch.full((64, n + 1), float("nan"), dtype=_to_dev(torch, X[:1], x_dtype).dtype, device="cuda:0")
+    wide[:, :n] = _to_dev(torch, X, x_dtype)
+    full = mb.mdbf_forward(dl, wide[:, :n], y_dtype="f32")
+    assert orc.max_rel_error(full.cpu().numpy(), orc.forward_factored(*_oracle_args(L), X)) <= TOL
+    for T in (17, 32, 33, 48, 49):
+        assert torch.equal(mb.mdbf_forward(dl, wide[:T, :n], y_dtype="f32"), full[:T]), T
+
+
 @pytest.mark.parametrize("m,n,k,l,env_dtype,x_dtype", [
     (5000, 3001, 2003, 3, "bf16", "bf16"), (2064, 1032, 2056, 16, "f16", "f16"), (300, 649, 1515, 12, "f32", "f32")])
 def test_a_longer_calls_workspace_serves_the_shorter_ones_alike(gpu, m, n, k, l, env_dtype, x_dtype):
