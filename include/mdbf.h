@@ -136,7 +136,8 @@ int mdbf_workspace_bytes(const mdbf_desc_t* desc, int T, size_t* bytes_out);
 /* Y[b,:] = What X[b,:] for b < T.
  *   SA_packed_dev  packed SA (m x k),  SB_packed_dev  packed SB (k x n)
  *   X_dev  T x n row-major, leading dimension ldx >= n (elements of x_dtype)
- *   Y_dev  T x m row-major, leading dimension ldy >= m (elements of y_dtype); overwritten
+ *   Y_dev  T x m row-major, leading dimension ldy >= m (elements of y_dtype); overwritten.  It may overlap X in any way
+ *          (a call in place: all of X is read before anything of Y is stored), and nothing else that the call reads
  *   workspace_dev / workspace_bytes  caller-owned scratch, >= mdbf_workspace_bytes()
  * Default arithmetic: fp32 accumulation on the matrix cores; z kept in fp32 with one token.  A single one-token call
  * rebuilds the factors S_A o (A Q^T), S_B o (G B^T) piece by piece in fp32 and applies them to the unrounded activations

@@ -197,7 +197,7 @@ bool stage_is_one(const StageProb& p);       // its operands are addressable wit
 // part_out: g.nsplit vectors part_out_ld apart (unused when g.nsplit == 1: the result goes to p->out).
 int launch_stage_one(const StageProb* p, const OneGeom& g, const float* part_in, int nsplit_in, int64_t part_in_ld,
                      float* part_out, int64_t part_out_ld, hipStream_t s);
-// both factors in one launch, for small first ones
+// both factors in one launch, for small first ones; not where X and Y overlap
 bool stage_is_pair(const StageProb sp[2]);
 int launch_stage_pair(const StageProb sp[2], hipStream_t s);
 // The same for the work items of a plan with few tokens (at most one_item_tiles() row tiles each), their envelopes all of

@@ -730,8 +730,16 @@ static int pair_grid(const StageProb& u) {
   return std::max(std::min(u.ntiles, 256), (u.ntiles + slots - 1) / slots);
 }
 
+// Do the bytes of the (one token's) activations and of the result meet?  In the one launch workgroups store their rows of Y while
+// others still read X; the two launches read all of X before they store anything of Y, so calls in place are theirs.
+static bool in_place(const StageProb sp[2]) {
+  const uintptr_t x = (uintptr_t)sp[0].vin, y = (uintptr_t)sp[1].out;
+  return x < y + (uintptr_t)sp[1].rows * dtype_size(sp[1].out_dt) && y < x + (uintptr_t)sp[0].K * dtype_size(sp[0].vin_dt);
+}
+
 bool stage_is_pair(const StageProb sp[2]) {
-  return (int64_t)sp[0].ntiles * sp[0].KB <= pair_pieces(sp[0]) && pair_grid(sp[1]) <= 256 && stage_is_one(sp[0]) && stage_is_one(sp[1]);
+  return (int64_t)sp[0].ntiles * sp[0].KB <= pair_pieces(sp[0]) && pair_grid(sp[1]) <= 256 && stage_is_one(sp[0]) && stage_is_one(sp[1]) &&
+         !in_place(sp);
 }
 
 int launch_stage_pair(const StageProb sp[2], hipStream_t s) {

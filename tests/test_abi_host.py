@@ -483,3 +483,27 @@ def test_static_scratch_call_checks_its_limit_on_the_host():
     assert call(d, 0) == -1 and call(d, 1, None) == -1 and call(d, 1, FAKE + 4) == -2
     bad = mb.Desc(4096, 4096, 2656, 17, mb.MDBF_F16, mb.MDBF_F16, mb.MDBF_F32, 0)
     assert call(bad, 1) == -1
+
+
+@pytest.mark.parametrize("x_dt,y_dt", [(mb.MDBF_F32, mb.MDBF_F32), (mb.MDBF_F16, mb.MDBF_F32), (mb.MDBF_F32, mb.MDBF_F16), (mb.MDBF_BF16, mb.MDBF_BF16)])
+@pytest.mark.parametrize("m,n", [(256, 256), (256, 128), (100, 256)])
+def test_one_launch_serves_no_call_in_place(m, n, x_dt, y_dt):
+    """Small one-token calls work in one launch, whose workgroups store rows of Y while others read X: only where the bytes of
+    the two do not meet (equal, Y inside X and X inside Y, an element in common at either end; adjacent ones do not)."""
+    serves = mb.lib()._ZN4mdbf13stage_is_pairEPKNS_9StageProbE
+    serves.restype, serves.argtypes = C.c_bool, [C.POINTER(_StageProb)]
+    size = {mb.MDBF_F16: 2, mb.MDBF_BF16: 2, mb.MDBF_F32: 4}
+    X, k, x_bytes, y_bytes = 1 << 20, 128, n * size[x_dt], m * size[y_dt]
+
+    def one_launch(Y):
+        sp = (_StageProb * 2)()
+        sp[0].vin, sp[0].rows, sp[0].K, sp[0].vin_dt, sp[0].out_dt = X, k, n, x_dt, mb.MDBF_F32
+        sp[1].out, sp[1].rows, sp[1].K, sp[1].vin_dt, sp[1].out_dt = Y, m, k, mb.MDBF_F32, y_dt
+        for s in sp:
+            s.l, s.T, s.env_dt, s.KB, s.ntiles = 16, 1, mb.MDBF_F16, (s.K + 127) // 128, (s.rows + 15) // 16
+        return serves(sp)
+
+    for Y in (X, X + 16, X - 16, X + x_bytes - size[x_dt], X - y_bytes + size[y_dt]):
+        assert not one_launch(Y), Y - X
+    for Y in (X + x_bytes, X - y_bytes, X + (1 << 16), X - (1 << 16)):
+        assert one_launch(Y), Y - X

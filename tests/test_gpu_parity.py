@@ -1034,6 +1034,35 @@ def test_small_one_token_calls(gpu, m, n, k, l, env_dtype, x_dtype):
     assert not torch.isfinite(again[0, m - 1]) and torch.equal(again[0, :m - 1], got[0, :m - 1])
 
 
+@pytest.mark.parametrize("m,n,k,l,env_dtype,dtype", [(256, 256, 128, 4, "f32", "f32"), (256, 256, 128, 16, "f16", "f16"), (300, 384, 100, 8, "f16", "bf16"),
+                                                     (4096, 127, 60, 16, "f16", "f32"), (4096, 4096, 300, 16, "f16", "f16")])
+def test_one_token_calls_in_place(gpu, m, n, k, l, env_dtype, dtype):
+    """Y over X: the same memory, and 16 bytes behind its start; overwritten, and added to itself.  Both places have the same bits,
+    those of two launches, which meet the oracle at the gate of the fp32 path and the rounding of a 16-bit Y (2^-11, 2^-8; of the
+    product and of the sum where it is added)."""
+    torch, mb = gpu
+    L = synth.make_layer(m, n, k, l, seed=m + n + k + l, env_dtype=env_dtype, env_kind="llama", signed_env=True)
+    X = synth.make_activations(n, 1, seed=3, x_dtype=dtype)
+    ref = orc.forward_factored(*_oracle_args(L), X)
+    dl, Xd = mb.DeviceLayer.from_host(L), _to_dev(torch, X, dtype)
+    unit = {"f32": 0.0, "f16": 2.0 ** -11, "bf16": 2.0 ** -8}[dtype]
+    shift = 16 // Xd.element_size()
+
+    def in_place(offset, accumulate):
+        buf = torch.zeros(offset + max(m, n), dtype=Xd.dtype, device="cuda:0")
+        buf[:n] = Xd[0]
+        before = buf[offset:offset + m].float().cpu().numpy().astype(np.float64)
+        Y = buf[offset:offset + m].unsqueeze(0)
+        mb.mdbf_forward(dl, buf[:n].unsqueeze(0), y_dtype=dtype, Y=Y, accumulate=accumulate)
+        return Y, before if accumulate else 0.0
+
+    for accumulate in (False, True):
+        for offset in (0, shift):
+            Y, before = in_place(offset, accumulate)
+            assert orc.max_rel_error(Y.float().cpu().numpy(), ref + before) <= 2e-5 + (2 if accumulate else 1) * unit, (offset, accumulate)
+    assert torch.equal(in_place(0, False)[0], in_place(shift, False)[0])
+
+
 ONE_PLANS = [
     # specs (m, n, k, l), envelopes, activations, tokens: ranks of every class and mixed ones, odd row pitches, contractions of
     # one block and of more than one per wave, row tiles that do not fill the last item
