@@ -518,11 +518,12 @@ __global__ __launch_bounds__(kSmallThreads) void reduce_gram_kernel(const float*
 // to the 2 x 2 block of four rows (with the row pair's, from another lane; rows and columns in one go, into the other of two
 // copies) or to two entries of a row of W: one barrier a step, and no more trips to LDS than the entries themselves.
 // What bounds it is a step's chain of instructions (8 cycles each for a lone wave of a SIMD), BB - 1 steps in six or seven sweeps.
-// The angle comes from fp32 arithmetic (the next sweep takes out what it leaves, 1e-7 of an entry), its cosine and sine from fp64:
-// a rotation to working precision whatever the angle is.  Entries below 1e-13 of their diagonal ones' mean are left: the results
-// are rounded to fp32.
+// The angle comes from fp32 arithmetic, on numbers scaled for it (the next sweep takes out what it leaves, 1e-7 of an entry), its
+// cosine and sine from fp64: a rotation to working precision whatever the angle is.  Sweeps end where no entry is above 1e-16 of its
+// diagonal ones' mean, in the mean of its two copies: they differ by roundings of that size, and tests of one with rotations by the other
+// go on for ever.  As many sweeps as with angles in fp64.
 // Moving indices instead of rows, angles in fp64 by one wave and two barriers a step 91 us (every thread for itself 116; every
-// wave for itself in fp32 102), seven sweeps; now 64, six.
+// wave for itself in fp32 102); now 68.  (Six sweeps, to 1e-13, 64 us: modes 2^-52 of the largest were left as they were.)
 constexpr int ritz_block_waves(int BB) { return (BB / 2 + 3) / 4; }   // a row pair, or a row of W, per sixteen lanes
 template <int BB>
 constexpr int ritz_threads() { return 64 * (ritz_block_waves(BB) + (BB + 3) / 4); }
@@ -537,7 +538,7 @@ __global__ __launch_bounds__(ritz_threads<BB>()) void ritz_kernel(const float* _
   __shared__ double sums[gram_groups<BB, kThr>() * BB * BB];
   const int t = threadIdx.x, lane = t & 63;
   gather_gram<BB, kThr, false>(Gp, nparts, sums, g0);
-  // the largest diagonal entry to [0.5, 1), by a power of two, for the fp32 angles
+  // the largest diagonal entry to [0.5, 1), by a power of two
   double most = 0.0;
   for (int i = 0; i < BB; ++i) most = fmax(most, g0[i][i]);
   int ex = 0;
@@ -579,8 +580,8 @@ __global__ __launch_bounds__(ritz_threads<BB>()) void ritz_kernel(const float* _
     bool any = false;                                  // an off-diagonal entry that still has to go
     for (int e = t; e < BB * BB; e += kThr) {
       const int p = e / BB, q = e - p * BB;
-      const double apq = lds[cur + p * RS + q], app = lds[cur + p * RS + p], aqq = lds[cur + q * RS + q];
-      any = any || (p < q && fabs(apq) > 1e-30 && apq * apq > 1e-26 * fabs(app * aqq));
+      const double apq = 0.5 * (lds[cur + p * RS + q] + lds[cur + q * RS + p]), app = lds[cur + p * RS + p], aqq = lds[cur + q * RS + q];
+      any = any || (p < q && fabs(apq) > 1e-150 && apq * apq > 1e-32 * fabs(app * aqq));
     }
     if (!__syncthreads_or(any ? 1 : 0)) break;
 #pragma unroll 1
@@ -588,14 +589,18 @@ __global__ __launch_bounds__(ritz_threads<BB>()) void ritz_kernel(const float* _
       const double* a = lds + cur;
       double* out = lds + (2 * BB * RS - cur);
       const double2 top = *reinterpret_cast<const double2*>(a + diag);
-      const double aqq = a[diag + RS + 1];
+      const double2 bottom = *reinterpret_cast<const double2*>(a + diag + RS);
       const double2 b0 = *reinterpret_cast<const double2*>(a + from0);
       double2 b1 = {0.0, 0.0};
       if (on_a) b1 = *reinterpret_cast<const double2*>(a + from1);
-      const float h = (float)(0.5 * (aqq - top.x)), o = (float)top.y;
-      float tf = o * __builtin_amdgcn_rcpf(fabsf(h) + __builtin_amdgcn_sqrtf(fmaf(h, h, o * o)));
-      tf = o == 0.f ? 0.f : fminf(fmaxf(tf, -1.f), 1.f);                  // the smaller of the two rotations
-      tf = h >= 0.f ? tf : -tf;
+      // the tangent of the smaller of the two rotations, o / (|h| + (h^2 + o^2)^(1/2)) with the sign of h, of both by the larger one's
+      // power of two (a branch around that where it is not needed: 7 us more per call)
+      const double h = bottom.y - top.x, o = top.y + bottom.x;
+      const int larger = __builtin_amdgcn_frexp_exp(fmax(fabs(h), fabs(o)));
+      const float hf = (float)ldexp(h, -larger), of = (float)ldexp(o, -larger);
+      float tf = of * __builtin_amdgcn_rcpf(fabsf(hf) + __builtin_amdgcn_sqrtf(fmaf(hf, hf, of * of)));
+      tf = of == 0.f ? 0.f : fminf(fmaxf(tf, -1.f), 1.f);
+      tf = hf >= 0.f ? tf : -tf;
       if (on_a) {
         const float tr = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * rpc, __builtin_bit_cast(int, tf)));
         const double c2 = cosine(tf), s2 = (double)tf * c2, c1 = cosine(tr), s1 = (double)tr * c1;

@@ -198,6 +198,29 @@ def test_non_finite_input_gives_the_same_defined_result_every_time(gpu, bad, l, 
             np.testing.assert_array_equal(x.numpy(), y.numpy())         # (NaNs at the same places count as equal)
 
 
+@pytest.mark.parametrize("iters", [2, 4])
+@pytest.mark.parametrize("l", [4, 16])
+def test_modes_far_below_the_largest_are_told_apart(gpu, l, iters):
+    """Two blocks, one 2^-52 of the other, and a start block whose columns lie in one of them each: the Gram matrix has two blocks as
+    well, one 2^-104 of the other, and the Ritz step diagonalises both.  All b Ritz values against the same iteration in fp64."""
+    torch, mb = gpu
+    rng = np.random.default_rng(l)
+    b = mb.mdbf_msvid_block(l)
+    rows, cols, r0, c0, b0 = 300, 200, 170, 110, b // 2
+    Z, X0 = np.zeros((rows, cols)), np.zeros((cols, b))
+    Z[:r0, :c0], Z[r0:, c0:] = rng.standard_normal((r0, c0)), rng.standard_normal((rows - r0, cols - c0)) * 2.0 ** -52
+    X0[:c0, :b0], X0[c0:, b0:] = rng.standard_normal((c0, b0)), rng.standard_normal((cols - c0, b - b0))
+    Z, X0 = Z.astype(np.float32), X0.astype(np.float32)
+    want = []
+    for z, V in ((Z[:r0, :c0], X0[:c0, :b0]), (Z[r0:, c0:], X0[c0:, b0:])):
+        M, V = np.abs(z.astype(np.float64)), V.astype(np.float64)
+        for _ in range(iters):
+            V = M.T @ np.linalg.qr(M @ V)[0]
+        want.append(np.linalg.svd(M @ np.linalg.qr(V)[0], compute_uv=False))
+    sg = mb.mdbf_msvid(torch.from_numpy(Z).cuda(), l, torch.from_numpy(X0).cuda(), iters=iters)[3]
+    np.testing.assert_allclose(sg.cpu().numpy().astype(np.float64), np.concatenate(want), rtol=1e-5)     # (fp32 products)
+
+
 def test_error_falls_with_l_and_with_the_number_of_passes(gpu):
     """Monotone in l (nested feasible sets, Sec. 4.2) and non-increasing in the number of passes."""
     Z = _f32(np.random.default_rng(40).standard_normal((256, 160)))
