@@ -408,9 +408,8 @@ def main():
             e1.record()
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1) / reps
-            # Z is read once per product (2 per pass + 1 for the Rayleigh-Ritz step) and once, with the int8 mask
-            # written, at the start
-            nbytes = (2 * iters + 1 + 1) * rows * cols * 4 + rows * cols
+            # Z is read once per product (2 per pass + 1 for the Rayleigh-Ritz step), one of which writes the int8 mask
+            nbytes = (2 * iters + 1) * rows * cols * 4 + rows * cols
             Zs = synth.normal_block(512, 384, 5).astype(np.float64)
             S, A, Q, sg = mb.mdbf_msvid(torch.from_numpy(Zs.astype(np.float32)).cuda(), l,
                                         torch.from_numpy(synth.normal_block(384, b, 6)).cuda(), iters=iters)
