@@ -1012,6 +1012,10 @@ PAIR_EDGES = [
     (300, 384, 128, 16, "f16", "f16"), (300, 385, 128, 16, "f16", "f16"), (520, 127, 384, 16, "f16", "f32"), (4099, 101, 383, 8, "f16", "bf16"),
     (8190, 101, 383, 8, "f16", "f16"), (50, 255, 63, 3, "f16", "f16"), (50, 129, 64, 16, "bf16", "bf16"), (17, 1000, 15, 11, "f32", "f32"),
     (1, 1, 1, 1, "f16", "f16"), (4, 4, 4, 4, "f32", "f32"), (19, 5, 130, 4, "f32", "f32"), (70, 1030, 520, 4, "f32", "f32"),
+    # more than 256 row tiles of one and two blocks on the slots of 256 workgroups (two, three and all eight of them, three of four),
+    # and of three blocks past what 256 workgroups take (8192 rows: the two sides of that line)
+    (4113, 130, 128, 16, "f16", "f16"), (11008, 130, 100, 8, "f16", "f16"), (32767, 65, 90, 4, "f32", "f32"), (8200, 101, 250, 16, "f16", "f16"),
+    (8192, 101, 383, 8, "f16", "f16"), (8200, 101, 383, 8, "f16", "f16"),
 ]
 
 
