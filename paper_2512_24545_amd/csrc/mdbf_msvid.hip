@@ -255,7 +255,7 @@ __device__ __forceinline__ void cholesky_inverse(const double (&G)[BB][BB], bool
 // What bounds it: 9 us for one read of Z beside 6 us of matrix-core work and 9 us of launch, staging and partial
 // sums, which only partly overlap.  (All of a wave's sixteen loads in flight: no change; X as single elements in
 // operand order: 8 us more.)  Lanes that own columns and fused multiply-adds took 24 us per product of 4096 x 2656 and b = 24, and a transposed
-// copy of Z for |Z| X another 20 us per call; now 17 to 20 us SCALED, 15.5 to 18.5 us not.
+// copy of Z for |Z| X another 20 us per call; now 18 to 20 us SCALED, 16 to 19 us not.
 template <int BB, bool COLS, bool SCALED>
 __global__ __launch_bounds__(kThreads, 4) void abs_mul_kernel(const float* __restrict__ Z, int rows, int cols, int64_t ld,
                                                               const float* __restrict__ X, const float* __restrict__ Gp,

@@ -146,7 +146,8 @@ struct EinBlock {
 
 // Rows of exactly four fp32 modes come a whole column of set 4 j + g per lane (VEC, below): a lane's entry t of the j-th such
 // vector is mode t of column m of set 4 j + g, and has to be mode g of set 4 j + t.  (As one mode per lane and load, sixteen bytes
-// apart, 128 loads of a compute unit took 2.6 us longer.)
+// apart: stage_pair_kernel on 256 x 256, k = 128 7.5 us per call from a graph instead of 4.7, two launches on 4096 x 4096, k = 512 8.0
+// instead of 6.1.)
 __device__ __forceinline__ void transpose_modes(uint32_t (&v)[8][1]) {
 #pragma unroll
   for (int j = 0; j < 8; j += 4) {
@@ -516,8 +517,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void stage_one_kernel(OneArgs a) {
 // ---- Both factors of a small layer in one launch.  Every workgroup works out all of z = V x for itself, in LDS, piece (16 x 128)
 // by piece, and then row tiles of its own of U z.  What bounds a call of two launches on such a layer is the launches: 2.7 us each
 // on the host.  On the device the second one saved pays for the pieces as long as they are few: pair_pieces.
-// us per call, two launches -> one, from a graph and one after the other: 256 x 256, k = 128 (16 pieces), l = 4 in fp32
-// 5.5 -> 4.7 and 10.1 -> 7.0; l = 16 in fp16 4.7 -> 4.1 and 10.2 -> 7.2; 300 x 384, k = 128 (24) 4.8 -> 4.9 and 10.2 -> 7.2.
+// us per call, two launches -> one, from a graph, from one of four branches, and one after the other on a stream: 256 x 256, k = 128 (16
+// pieces), l = 4 in fp32 5.5 -> 4.8, 7.6 -> 4.1 and 8.8 -> 6.1; l = 16 in fp16 4.8 -> 4.1, 6.5 -> 4.0 and 8.7 -> 6.1; 300 x 384, k = 128 (24)
+// 4.9 -> 5.0, 6.6 -> 4.0 and 9.1 -> 6.4; 8190 x 101, k = 383 (24 in each of 256 workgroups) 6.1 -> 5.7, 6.5 -> 4.2 and 9.0 -> 6.4.  A single
+// call on operands that come from memory takes what two launches take.
 constexpr int kPairPieces = 24;
 constexpr int kPairWaves = 8;       // (sixteen, a piece each: no faster, and the element-wise rows spill)
 
@@ -714,10 +717,12 @@ bool stage_is_one(const StageProb& p) {
          (p.T == 1 || p.vin_ld < ((int64_t)1 << 30) / p.T);
 }
 
-// Pieces of the first factor that one launch may go through in every workgroup: as many as cost no more than the launch does on
-// the device (the host saves its 2.7 us in any case).  us per call from a graph, two launches and one: rank 16 and 8 in fp16,
-// 24 pieces, 4.9 and 4.9, 5.35 and 5.37 (688 row tiles); fp32 rank 4, 20, 5.6 and 5.3, 24, 5.7 and 5.9; rank 8, 12, 5.5 and 5.1, 16,
-// 5.5 and 5.8; other rows, loaded entry by entry or of 16 fp32 modes, 8: 5.7 and 4.8, with 10 to 16 5.8 and 6.5, 5.5 and 6.1.
+// Pieces of the first factor that one launch may go through in every workgroup: as many as cost about what the launch does on
+// the device (the host saves its 2.7 us in any case, and calls beside each other a third of their time).  us per call from a graph of
+// different layers one behind the other, two launches and one: rank 16 and 8 in fp16, 16 to 20 pieces 4.8 to 6.0 and 4.1 to 5.4, 21 to 24 (three
+// rounds of the eight waves) 4.9 and 5.0 to 5.2, 5.9 and 5.8 (8190 rows): the 2 to 6 % that a graph of nothing else loses there are a
+// tenth of what streams and branches gain; fp32 rank 4, 20, 5.7 to 7.3 and 5.4 to 6.6, 24, 5.7 and 5.9; rank 8, 12, 5.6 to 7.0 and 5.2 to 6.0, 16,
+// 5.5 and 5.8; other rows, loaded entry by entry or of 16 fp32 modes, 8: 5.4 to 6.9 and 4.4 to 5.6, with 10 to 16 5.8 and 6.5, 5.5 and 6.1.
 // And one round of workgroups: 688 row tiles on 344 of them (k = 384) 5.4 and 7.5.
 static int pair_pieces(const StageProb& p) {
   if (p.env_dt == MDBF_F16 && (p.l == 16 || p.l == 8)) return one::kPairPieces;
