@@ -268,7 +268,7 @@ int mdbf_stream_read(const void* src_dev, size_t bytes, uint32_t* sink_dev, int 
  * falls geometrically with iters at the rate of the gap between |Z|'s singular values l and b + 1.
  *   Z_dev      rows x cols, row-major fp32, leading dimension ld >= cols
  *   S_dev      rows x cols int8 (+1 / -1), row-major, ld = cols: the input mdbf_pack takes
- *   A_dev, Q_dev   rows x l and cols x l fp32, row-major;  sigma_dev  b Ritz values (fp32, descending; the first l
+ *   A_dev, Q_dev   rows x l and cols x l fp32, row-major (a column of A and that of Q: up to a sign they share);  sigma_dev  b Ritz values (fp32, descending; the first l
  *              are the singular values of A Q^T)
  *   workspace_dev  caller-owned, >= mdbf_msvid_workspace_bytes (partial sums of the products and the iteration's blocks;
  *              the size has room for a copy of Z too, which is not made any more)

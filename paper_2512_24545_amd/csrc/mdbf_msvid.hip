@@ -161,7 +161,7 @@ __device__ __forceinline__ float longest_from_here(float v) {
 // What bounds it: instructions of one wave, 8 cycles each (two lane reads and a multiply-add per entry of the trailing
 // columns).  The next pivot's entry goes first, so that its reciprocal is worked out between the others' updates:
 // 12600 -> 8200 cycles for b = 24 against a root per step and a zero or one per row behind a branch.
-constexpr float kTooShort = 64.f;
+constexpr float kTooShort = 16.f;
 template <int BB>
 __device__ __forceinline__ void cholesky_inverse(const double (&G)[BB][BB], bool by_length, double* Tm, float* Tf) {
   const int j = (int)threadIdx.x & 31;
@@ -729,8 +729,9 @@ static int run(const float* Z, int rows, int cols, int64_t ld, int l, int iters,
   // the second on columns in a bad order are sorted: the first one is then the one with the most of that mode, not the one that the caller
   // put there.  (In the caller's order a first column orthogonal to a mode a hundred times the others cost A Q^T a factor of 25 to 65
   // against R^(-1) in front, 1e-5 of it.  Sorted, over start blocks with one, four or half of the columns orthogonal to the leading modes,
-  // lengths from 1e6 to 1e-6 and centred columns, on six kinds of spectra: 0.44 to 1.0 of the errors in front in the mean of a kind, 1.33 at
-  // most; 3 us more per call of 8 passes.)
+  // lengths from 1e6 to 1e-6 and centred columns, on six kinds of spectra: 0.44 to 1.0 of the errors in front in the mean of a kind, 1.6 at
+  // most; over first columns with 1e-7 to 1 of the leading mode 1.33 at most, 2.2 where only columns eight times too short are
+  // sorted instead of four times; 3 us more per call of 8 passes.)
   // (Long blocks, of many Gram parts, always: four waves would be too long adding them up.)
   constexpr int kStepsInOrder = 2, kStepsBehind = 4, kMostParts = 256;
   const int row_parts = (rows + kGramRows - 1) / kGramRows, col_parts = (cols + kGramRows - 1) / kGramRows;
