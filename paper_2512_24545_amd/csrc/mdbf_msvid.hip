@@ -149,8 +149,8 @@ __device__ __forceinline__ float longest_from_here(float v) {
 // by_length: where a column is shorter than one after it by kTooShort (of the squares) the columns of Y are taken in the order of their
 // lengths, longest first (R is triangular in that order, and so do the columns of Y Tm stand).  After a product with |Z| that is the
 // order of what they hold of its largest modes, and as each step sorts what the columns in front left, the modes come to stand in
-// their order whatever the start block's is (what that is for: run(), below).  The columns of a random start stay where they are:
-// their lengths within the bulk of a spectrum differ by less.
+// their order whatever the start block's is (what that is for: run(), below).  The columns of a random start nearly always
+// stay where they are (99 of 100 starts of 500 x 500 to 4096 x 2656): their lengths within the bulk of a spectrum differ by less.
 // One wave; lane j < 32 holds column j of the matrix in registers (right-looking: after step k the trailing columns
 // hold the Schur complement), lane 32 + j column j of the identity, which the same steps turn into column j of
 // L^(-1), L D L^T = G, and the roots of the pivots at the end into row j of R^(-1).  Row k is passed round by lane reads: no
